@@ -16,14 +16,26 @@
 //   commit   : after batch k has trained: victims of k+1 move from their cache lines to
 //              the staging area, the new rows move in; late rows are copied HBM to HBM from
 //              where the map pointed.  Also writes batch k's overflow copies back.
-// Host rows are reached through the pinned mapping, 16 lanes per row, 16 bytes per lane.
+// Host rows are reached through the pinned mapping, 16 bytes per lane, 4 to 16 lanes per row (TBE_BY_ROW_LANES).
 #include <hip/hip_fp16.h>
 #include "tbe_internal.h"
 
 namespace tbe {
 
 typedef unsigned long long u64;
-constexpr int kMoveLanes = 16;
+// Runs CALL with `L` = the lanes that move a row, 16 bytes each: as many as the widest row of the model has pieces, 16
+// at most.  Rows of at most 128 bytes used to leave half of their 16 lanes idle, and a wavefront had four of them under
+// way instead of eight: swapping 241 k rows of 128 bytes with host memory 0.97 -> 0.93 ms (33 GB/s per direction; a
+// kernel that does nothing else reaches 36.5 whatever the order of the rows: each is a request of its own on the link),
+// their commit 0.050 -> 0.038 ms.  Wider rows keep a lane per piece: 256-byte rows by 8 lanes, two pieces each, have
+// twice the bytes under way and take 6.2 instead of 5.2 ms per transfer of the benchmark workload; 128 to 512-byte
+// rows mixed, by 8 lanes: 14.8 instead of 14.2 ms for four steps.
+#define TBE_BY_ROW_LANES(STRIDE, CALL)                       \
+  do {                                                       \
+    if ((STRIDE) <= 64) { constexpr int L = 4; CALL; }       \
+    else if ((STRIDE) <= 128) { constexpr int L = 8; CALL; } \
+    else { constexpr int L = 16; CALL; }                     \
+  } while (0)
 constexpr int kLinkBlocks = 192;   // workgroups of the smaller kernels that write to the host link
 constexpr int kLinkThreads = 1024;
 
@@ -72,27 +84,31 @@ __device__ inline uint4 init_chunk(u64 table_key, uint32_t row, int dtype, uint3
 
 // Has row `row` of table m a value yet?  If not, it gets one now: lane 0 of the group marks the
 // row and tells the others what the mark was before.
+template <int L>
 __device__ inline bool needs_init(const TableMeta &m, uint32_t row, int lig) {
   const uint32_t bit = 1u << (row & 31);
   uint32_t before = 0;
   if (lig == 0) before = atomicOr(m.init_bits + (row >> 5), bit);
-  before = __shfl(before, 0, kMoveLanes);
+  before = __shfl(before, 0, L);
   return (before & bit) == 0;
 }
 
 typedef uint32_t mv_u32x4 __attribute__((ext_vector_type(4)));
 // A row on its way to host memory: non-temporal stores (the transfer of the benchmark workload
 // 5.52 -> 5.36 ms; non-temporal loads from host memory change nothing).
+template <int L>
 __device__ inline void copy_row_to_host(char *dst, const char *src, uint32_t bytes, int lig) {
-  for (uint32_t c = lig * 16; c < bytes; c += kMoveLanes * 16) {
+  for (uint32_t c = lig * 16; c < bytes; c += L * 16) {
     const mv_u32x4 v = *(const mv_u32x4 *)(src + c);
     __builtin_nontemporal_store(v, (mv_u32x4 *)(dst + c));
   }
 }
+template <int L>
 __device__ inline void copy_row(char *dst, const char *src, uint32_t bytes, int lig) {
-  for (uint32_t c = lig * 16; c < bytes; c += kMoveLanes * 16) *(uint4 *)(dst + c) = *(const uint4 *)(src + c);
+  for (uint32_t c = lig * 16; c < bytes; c += L * 16) *(uint4 *)(dst + c) = *(const uint4 *)(src + c);
 }
 
+template <int L>
 __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, const BatchCounters *cnt,
                                                        char *const *__restrict__ ins_src,
                                                        const int32_t *__restrict__ ins_tab,
@@ -123,9 +139,9 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
   // the first passes (slot i + n) instead of forming a tail of passes that only write: the link's two
   // directions stay busy together to the end.
   const int n = max((n_wb + 1) / 2, max(n_ins, n_byp));
-  const int group = (bid * blockDim.x + threadIdx.x) / kMoveLanes;
-  const int lig = threadIdx.x % kMoveLanes;
-  const int n_groups = n_blocks * blockDim.x / kMoveLanes;
+  const int group = (bid * blockDim.x + threadIdx.x) / L;
+  const int lig = threadIdx.x % L;
+  const int n_groups = n_blocks * blockDim.x / L;
   u64 in_b = 0, out_b = 0;
   const int wpar = st.wb_n[1] & 1;
   // emulated slower tier: rows of this pass that the group moved to or from the backing tier proper
@@ -141,7 +157,7 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
     }
     if (dst) {
       const uint32_t wrb = st.wb_rb[w];
-      copy_row_to_host(dst, st.out[wpar] + (size_t)w * st.stride, wrb, lig);
+      copy_row_to_host<L>(dst, st.out[wpar] + (size_t)w * st.stride, wrb, lig);
       if (lig == 0) out_b += wrb;
       slow_rows += in_backing(dst);
     }
@@ -154,7 +170,7 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
       }
       if (dst2) {
         const uint32_t wrb = st.wb_rb[w];
-        copy_row_to_host(dst2, (wpar ? out2_odd : out2_even) + (size_t)w * st.stride, wrb, lig);
+        copy_row_to_host<L>(dst2, (wpar ? out2_odd : out2_even) + (size_t)w * st.stride, wrb, lig);
         if (lig == 0) out_b += wrb;
         slow_rows += in_backing(dst2);
       }
@@ -173,13 +189,13 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
         if (di_tm) {  // deferred initialisation: a row read for the first time gets its value here
           const TableMeta &m = di_tm[t];
           const uint32_t row = row_of_key(m, ins_key[i]);
-          made_up = needs_init(m, row, lig);
+          made_up = needs_init<L>(m, row, lig);
           if (made_up) {
             const u64 tk = init_table_key(di_seed, t);
             const uint32_t esz = m.dtype == 0 ? 4u : 2u;
 #pragma unroll
             for (int q = 0; q < 4; q++) {
-              const uint32_t c = lig * 16 + q * kMoveLanes * 16;
+              const uint32_t c = lig * 16 + q * L * 16;
               if (c < rb) fresh[q] = init_chunk(tk, row, m.dtype, c / esz, di_std);
             }
           }
@@ -189,7 +205,7 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
           slow_rows += in_backing(src);
 #pragma unroll
           for (int q = 0; q < 4; q++) {
-            const uint32_t c = lig * 16 + q * kMoveLanes * 16;
+            const uint32_t c = lig * 16 + q * L * 16;
             if (c < rb) fresh[q] = *(const uint4 *)(src + c);
           }
         }
@@ -201,7 +217,7 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
       const char *src = l2v_src[i];  // line still holds it (the victim is written there by the next transfer)
       if (src) {
         const uint32_t vrb = rb_of_table[ins_tab[i]];
-        copy_row(((k & 1) ? out2_odd : out2_even) + (size_t)i * st.stride, src, vrb, lig);
+        copy_row<L>(((k & 1) ? out2_odd : out2_even) + (size_t)i * st.stride, src, vrb, lig);
         if (lig == 0) in_b += vrb;
       }
     }
@@ -209,7 +225,7 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
       char *dst = st.in + (size_t)i * st.stride;
 #pragma unroll
       for (int q = 0; q < 4; q++) {
-        const uint32_t c = lig * 16 + q * kMoveLanes * 16;
+        const uint32_t c = lig * 16 + q * L * 16;
         if (c < rb) *(uint4 *)(dst + c) = fresh[q];
       }
       if (lig == 0 && !made_up) in_b += rb;
@@ -221,16 +237,16 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
       if (di_tm) {
         const TableMeta &m = di_tm[t];
         const uint32_t row = row_of_key(m, byp_key[i]);
-        fresh_row = needs_init(m, row, lig);
+        fresh_row = needs_init<L>(m, row, lig);
         if (fresh_row) {
           const u64 tk = init_table_key(di_seed, t);
           const uint32_t esz = m.dtype == 0 ? 4u : 2u;
-          for (uint32_t c = lig * 16; c < brb; c += kMoveLanes * 16)
+          for (uint32_t c = lig * 16; c < brb; c += L * 16)
             *(uint4 *)(ovf + (size_t)i * st.stride + c) = init_chunk(tk, row, m.dtype, c / esz, di_std);
         }
       }
       if (!fresh_row) {
-        copy_row(ovf + (size_t)i * st.stride, byp_src[i], brb, lig);
+        copy_row<L>(ovf + (size_t)i * st.stride, byp_src[i], brb, lig);
         if (lig == 0) in_b += brb;
         slow_rows += in_backing(byp_src[i]);
       }
@@ -272,13 +288,13 @@ hipError_t launch_transfer(const BatchBuf *b, const Staging &st, const Level2 &l
   // (with the overflow copies riding along, later: 40 CUs 5.81 ms per step, 48: 5.67, 56: 5.70, 64: 5.93, 72: 6.03)
   // The link needs about 750 waves; given CUs of their own (48 of 256) they leave the other
   // streams' kernels at 1.3 to 2 times their stand-alone time instead of 2.5 to 5 times.
-  hipLaunchKernelGGL(transfer_kernel, dim3(kLinkCus), dim3(kLinkThreads), 0, s, st, b ? b->cnt : nullptr,
+  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((transfer_kernel<L>), dim3(kLinkCus), dim3(kLinkThreads), 0, s, st, b ? b->cnt : nullptr,
                      b ? b->ins_src : nullptr, b ? b->ins_tab : nullptr, rb_of_table,
                      b ? b->ins_where : nullptr, b ? b->byp_src : nullptr, b ? b->byp_tab : nullptr,
                      b ? b->byp_where : nullptr, b ? b->ovf : nullptr, (b && l2.on) ? b->l2v_src : nullptr,
                      l2.on ? l2.wb2_dst : nullptr, l2.out2[0], l2.out2[1], k, b ? di.tm : nullptr, di.seed, di.std,
                      b ? b->ins_key : nullptr, b ? b->byp_key : nullptr, bytes_h2d, bytes_d2h, l2.lines_lo, l2.lines_hi,
-                     th.pauses);
+                     th.pauses));
   hipLaunchKernelGGL(clear_wb_kernel, dim3(1), dim3(64), 0, s, st.wb_n);
   return hipGetLastError();
 }
@@ -413,6 +429,7 @@ hipError_t launch_unmark_bypassed(const BatchBuf &b, int buf, const Staging &st,
   return hipGetLastError();
 }
 
+template <int L>
 __global__ __launch_bounds__(256) void fixup_kernel(const TableMeta *__restrict__ tm, const BatchCounters *cnt,
                                                     const int32_t *__restrict__ ins_tab,
                                                     const uint32_t *__restrict__ ins_where,
@@ -424,9 +441,9 @@ __global__ __launch_bounds__(256) void fixup_kernel(const TableMeta *__restrict_
                                                     const uint32_t *__restrict__ rb_of_table, u64 *n_copied) {
   if (cnt->err) return;
   const int n_ins = cnt->n_ins, n_byp = cnt->n_byp;
-  const int group = (blockIdx.x * blockDim.x + threadIdx.x) / kMoveLanes;
-  const int lig = threadIdx.x % kMoveLanes;
-  const int n_groups = gridDim.x * blockDim.x / kMoveLanes;
+  const int group = (blockIdx.x * blockDim.x + threadIdx.x) / L;
+  const int lig = threadIdx.x % L;
+  const int n_groups = gridDim.x * blockDim.x / L;
   unsigned int copied = 0;
   for (int i = group; i < n_ins + n_byp; i += n_groups) {
     const bool ins = i < n_ins;
@@ -437,12 +454,12 @@ __global__ __launch_bounds__(256) void fixup_kernel(const TableMeta *__restrict_
     if (ins) {
       const TableMeta &m = tm[ins_tab[i]];
       const int slot = ins_slot[i];
-      copy_row(m.lines + (size_t)(slot - m.slot_base) * m.row_bytes, src, m.row_bytes, lig);
+      copy_row<L>(m.lines + (size_t)(slot - m.slot_base) * m.row_bytes, src, m.row_bytes, lig);
       // the row's accumulator was updated among those of all rows while it trained as a bypassed row
       if (lig == 0) m.slot_m[slot - m.slot_base] = m.dev_m[row_of_key(m, ins_key[i])];
     } else {
       const int j = i - n_ins;
-      copy_row(ovf + (size_t)j * stride, src, rb_of_table[byp_tab[j]], lig);
+      copy_row<L>(ovf + (size_t)j * stride, src, rb_of_table[byp_tab[j]], lig);
     }
   }
   for (int d = 32; d >= 1; d >>= 1) copied += __shfl_xor(copied, d);
@@ -452,8 +469,8 @@ __global__ __launch_bounds__(256) void fixup_kernel(const TableMeta *__restrict_
 hipError_t launch_fixup(const TableMeta *tm, const BatchBuf &b, const OverflowCopies &oc, const Staging &st,
                         const uint32_t *rb_of_table, u64 *n_copied, hipStream_t s) {
   if (b.n == 0) return hipSuccess;
-  hipLaunchKernelGGL(fixup_kernel, dim3(1024), dim3(256), 0, s, tm, b.cnt, b.ins_tab, b.ins_where, b.ins_slot, b.ins_key,
-                     b.byp_tab, b.byp_where, b.ovf, oc, st.stride, rb_of_table, n_copied);
+  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((fixup_kernel<L>), dim3(1024), dim3(256), 0, s, tm, b.cnt, b.ins_tab, b.ins_where, b.ins_slot, b.ins_key,
+                     b.byp_tab, b.byp_where, b.ovf, oc, st.stride, rb_of_table, n_copied));
   return hipGetLastError();
 }
 
@@ -463,7 +480,7 @@ hipError_t launch_fixup(const TableMeta *tm, const BatchBuf &b, const OverflowCo
 // parked behind this batch's victims for the next transfer to write them (kPrevPark): the link's
 // write direction then carries them beside that transfer's fetches, which costs the transfer a
 // hundredth of its time, instead of alone between two transfers.
-template <bool DEEP>
+template <bool DEEP, int L>
 __global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict__ tm, Staging st,
                                                      const BatchCounters *cnt, const int32_t *__restrict__ ins_tab,
                                                      const uint32_t *__restrict__ ins_where,
@@ -485,9 +502,9 @@ __global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict
                                // is on the critical path of every step and keeps its code as it was)
   const uint32_t M = (uint32_t)st.max_inserts;  // map codes kWhereParked | (M + i): rows staged in out2
   const int n_prev = (prev_cnt && prev_cnt->err == 0) ? prev_cnt->n_byp : 0;
-  const int group = (blockIdx.x * blockDim.x + threadIdx.x) / kMoveLanes;
-  const int lig = threadIdx.x % kMoveLanes;
-  const int n_groups = gridDim.x * blockDim.x / kMoveLanes;
+  const int group = (blockIdx.x * blockDim.x + threadIdx.x) / L;
+  const int lig = threadIdx.x % L;
+  const int n_groups = gridDim.x * blockDim.x / L;
   if (cnt->err) {
     // This batch is refused (bad offsets or an index out of range) and does nothing, and no batch follows it
     // (the error sticks).  The batch before it has trained on its overflow copies, though: they go home now,
@@ -496,7 +513,7 @@ __global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict
       u64 b = 0;
       for (int j = group; j < n_prev; j += n_groups) {
         const uint32_t rb = rb_of_table[prev_byp_tab[j]];
-        copy_row_to_host(prev_byp_src[j], prev_ovf + (size_t)j * st.stride, rb, lig);
+        copy_row_to_host<L>(prev_byp_src[j], prev_ovf + (size_t)j * st.stride, rb, lig);
         if (lig == 0) b += rb;
       }
       for (int d = 32; d >= 1; d >>= 1) b += __shfl_xor(b, d);
@@ -514,14 +531,14 @@ __global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict
   if (wb_prev == kPrevWrite)
     for (int j = group; j < n_prev; j += n_groups) {
       const uint32_t rb = rb_of_table[prev_byp_tab[j]];
-      copy_row_to_host(prev_byp_src[j], prev_ovf + (size_t)j * st.stride, rb, lig);
+      copy_row_to_host<L>(prev_byp_src[j], prev_ovf + (size_t)j * st.stride, rb, lig);
       if (lig == 0) out_b += rb;
     }
   if (wb_prev == kPrevPark)
     for (int j = group; j < n_prev; j += n_groups) {
       const uint32_t rb = rb_of_table[prev_byp_tab[j]];
       const size_t slot = (size_t)n_ins + (size_t)j;
-      copy_row(st.out[par] + slot * st.stride, prev_ovf + (size_t)j * st.stride, rb, lig);
+      copy_row<L>(st.out[par] + slot * st.stride, prev_ovf + (size_t)j * st.stride, rb, lig);
       if (lig == 0) {
         st.wb_dst[slot] = prev_byp_src[j];
         st.wb_rb[slot] = rb;
@@ -551,7 +568,7 @@ __global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict
       m_victim = *sm;
       m_fresh = m.dev_m[row_of_key(m, ins_key[i])];
     }
-    for (uint32_t c = lig * 16; c < rb; c += kMoveLanes * 16) {
+    for (uint32_t c = lig * 16; c < rb; c += L * 16) {
       // The staged row and the parked victim pass through once: read and written around the caches, so that
       // the forward that follows does not start behind half a gigabyte of dirty lines (commit 0.274 -> 0.253 ms,
       // the forward after it 0.198 -> 0.186 ms).  The line itself is about to be read: it is stored as usual.
@@ -574,12 +591,13 @@ __global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict
     const char *src = (code & kWhereOverflow) ? prev_ovf + (size_t)ix * st.stride
                       : (out2_prev && ix >= M) ? out2_prev + (size_t)(ix - M) * st.stride
                                               : st.out[ppar] + (size_t)ix * st.stride;
-    copy_row(ovf + (size_t)j * st.stride, src, rb_of_table[byp_tab[j]], lig);
+    copy_row<L>(ovf + (size_t)j * st.stride, src, rb_of_table[byp_tab[j]], lig);
   }
   for (int d = 32; d >= 1; d >>= 1) out_b += __shfl_xor(out_b, d);
   if ((threadIdx.x & 63) == 0 && out_b) atomicAdd(bytes_d2h, out_b);
 }
 
+template <int L>
 __global__ __launch_bounds__(256) void ovf_writeback_kernel(Staging st, const BatchCounters *cnt,
                                                             char *const *__restrict__ byp_src,
                                                             const int32_t *__restrict__ byp_tab,
@@ -587,13 +605,13 @@ __global__ __launch_bounds__(256) void ovf_writeback_kernel(Staging st, const Ba
                                                             const uint32_t *__restrict__ rb_of_table, u64 *bytes_d2h) {
   if (cnt->err) return;
   const int n_byp = cnt->n_byp;
-  const int group = (blockIdx.x * blockDim.x + threadIdx.x) / kMoveLanes;
-  const int lig = threadIdx.x % kMoveLanes;
-  const int n_groups = gridDim.x * blockDim.x / kMoveLanes;
+  const int group = (blockIdx.x * blockDim.x + threadIdx.x) / L;
+  const int lig = threadIdx.x % L;
+  const int n_groups = gridDim.x * blockDim.x / L;
   u64 out_b = 0;
   for (int j = group; j < n_byp; j += n_groups) {
     const uint32_t rb = rb_of_table[byp_tab[j]];
-    copy_row_to_host(byp_src[j], ovf + (size_t)j * st.stride, rb, lig);
+    copy_row_to_host<L>(byp_src[j], ovf + (size_t)j * st.stride, rb, lig);
     if (lig == 0) out_b += rb;
   }
   for (int d = 32; d >= 1; d >>= 1) out_b += __shfl_xor(out_b, d);
@@ -603,21 +621,22 @@ __global__ __launch_bounds__(256) void ovf_writeback_kernel(Staging st, const Ba
 // The overflow copies that batch b's commit parked behind its victims (those of the batch before
 // it), written to the backing tier ahead of their turn: they must be home before b's own, newer
 // copies of the same rows are written.  Their slots are emptied, so the next transfer passes them by.
+template <int L>
 __global__ __launch_bounds__(256) void parked_copies_writeback_kernel(Staging st, const BatchCounters *cnt,
                                                                       const BatchCounters *prev_cnt, u64 *bytes_d2h) {
   if (cnt->err || prev_cnt->err) return;
   const int base = cnt->n_ins, n = prev_cnt->n_byp;
   const char *out = st.out[st.wb_n[1] & 1];
-  const int group = (blockIdx.x * blockDim.x + threadIdx.x) / kMoveLanes;
-  const int lig = threadIdx.x % kMoveLanes;
-  const int n_groups = gridDim.x * blockDim.x / kMoveLanes;
+  const int group = (blockIdx.x * blockDim.x + threadIdx.x) / L;
+  const int lig = threadIdx.x % L;
+  const int n_groups = gridDim.x * blockDim.x / L;
   u64 out_b = 0;
   for (int j = group; j < n; j += n_groups) {
     const size_t slot = (size_t)base + (size_t)j;
     char *dst = st.wb_dst[slot];
     if (dst) {
       const uint32_t rb = st.wb_rb[slot];
-      copy_row_to_host(dst, out + slot * st.stride, rb, lig);
+      copy_row_to_host<L>(dst, out + slot * st.stride, rb, lig);
       if (lig == 0) out_b += rb;
     }
   }
@@ -631,32 +650,32 @@ __global__ __launch_bounds__(256) void parked_copies_writeback_kernel(Staging st
 hipError_t launch_ovf_writeback(const BatchBuf &b, const BatchBuf *parked_prev, const Staging &st,
                                 const uint32_t *rb_of_table, u64 *bytes_d2h, hipStream_t s) {
   if (parked_prev)
-    hipLaunchKernelGGL(parked_copies_writeback_kernel, dim3(kLinkBlocks), dim3(256), 0, s, st, b.cnt, parked_prev->cnt,
-                       bytes_d2h);
+    TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((parked_copies_writeback_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, st, b.cnt, parked_prev->cnt,
+                       bytes_d2h));
   if (b.n == 0) return hipGetLastError();
-  hipLaunchKernelGGL(ovf_writeback_kernel, dim3(kLinkBlocks), dim3(256), 0, s, st, b.cnt, b.byp_src, b.byp_tab, b.ovf,
-                     rb_of_table, bytes_d2h);
+  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((ovf_writeback_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, st, b.cnt, b.byp_src, b.byp_tab, b.ovf,
+                     rb_of_table, bytes_d2h));
   return hipGetLastError();
 }
 
 hipError_t launch_commit(const TableMeta *tm, const BatchBuf &b, const BatchBuf *prev, int prev_mode, const Staging &st,
                          const Level2 &l2, const uint32_t *rb_of_table, u64 *bytes_d2h, bool deep, hipStream_t s) {
-  auto kern = deep ? commit_kernel<true> : commit_kernel<false>;
-  hipLaunchKernelGGL(kern, dim3(4096), dim3(256), 0, s, tm, st, b.cnt, b.ins_tab, b.ins_where, b.ins_slot,
+  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((deep ? commit_kernel<true, L> : commit_kernel<false, L>), dim3(4096), dim3(256), 0, s, tm, st, b.cnt, b.ins_tab, b.ins_where, b.ins_slot,
                      b.ins_old, b.byp_tab, b.byp_where, b.ovf, prev ? prev->cnt : nullptr,
                      prev ? prev->byp_src : nullptr, prev ? prev->byp_tab : nullptr, prev ? prev->ovf : nullptr,
                      prev ? prev_mode : kPrevKeep, b.k, l2.on ? b.ins_dst : nullptr, l2.on ? b.l2v_src : nullptr,
                      l2.on ? b.l2v_dst : nullptr, l2.on ? l2.wb2_dst : nullptr, l2.out2[(b.k & 1) ^ 1], rb_of_table,
-                     b.ins_key, bytes_d2h);
+                     b.ins_key, bytes_d2h));
   return hipGetLastError();
 }
 
 // flush: every valid line goes to the backing tier, its accumulator to those of all rows (which the host code copies)
+template <int L>
 __global__ __launch_bounds__(256) void flush_kernel(const TableMeta *__restrict__ tm, int T, int64_t total_slots,
                                                     const int32_t *__restrict__ tags, u64 *bytes_d2h) {
-  const int64_t group = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kMoveLanes;
-  const int lig = threadIdx.x % kMoveLanes;
-  const int64_t n_groups = (int64_t)gridDim.x * blockDim.x / kMoveLanes;
+  const int64_t group = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / L;
+  const int lig = threadIdx.x % L;
+  const int64_t n_groups = (int64_t)gridDim.x * blockDim.x / L;
   u64 out_b = 0;
   for (int64_t slot = group; slot < total_slots; slot += n_groups) {
     const int32_t row = tags[slot];
@@ -667,7 +686,7 @@ __global__ __launch_bounds__(256) void flush_kernel(const TableMeta *__restrict_
       if ((int64_t)tm[mid].slot_base <= slot) lo = mid; else hi = mid - 1;
     }
     const TableMeta &m = tm[lo];
-    copy_row_to_host(m.host_w + (size_t)row * m.row_bytes, m.lines + (size_t)(slot - m.slot_base) * m.row_bytes, m.row_bytes, lig);
+    copy_row_to_host<L>(m.host_w + (size_t)row * m.row_bytes, m.lines + (size_t)(slot - m.slot_base) * m.row_bytes, m.row_bytes, lig);
     if (lig == 0) {
       out_b += m.row_bytes;
       m.dev_m[row] = m.slot_m[slot - m.slot_base];  // the caller copies dev_m to the host; the line stays valid
@@ -679,12 +698,13 @@ __global__ __launch_bounds__(256) void flush_kernel(const TableMeta *__restrict_
 
 // flush of the second level: every valid line goes to its row in the lower tier (host to
 // host through the GPU); the levels are exclusive, so no row is written twice
+template <int L>
 __global__ __launch_bounds__(256) void flush2_kernel(const TableMeta *__restrict__ tm, int T, int64_t total_slots2,
                                                      const int32_t *__restrict__ tags2, u64 *bytes_h2d,
                                                      u64 *bytes_d2h) {
-  const int64_t group = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kMoveLanes;
-  const int lig = threadIdx.x % kMoveLanes;
-  const int64_t n_groups = (int64_t)gridDim.x * blockDim.x / kMoveLanes;
+  const int64_t group = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / L;
+  const int lig = threadIdx.x % L;
+  const int64_t n_groups = (int64_t)gridDim.x * blockDim.x / L;
   u64 b = 0;
   for (int64_t slot = group; slot < total_slots2; slot += n_groups) {
     const int32_t row = tags2[slot];
@@ -695,7 +715,7 @@ __global__ __launch_bounds__(256) void flush2_kernel(const TableMeta *__restrict
       if ((int64_t)tm[mid].slot2_base <= slot) lo = mid; else hi = mid - 1;
     }
     const TableMeta &m = tm[lo];
-    copy_row(m.host_w + (size_t)row * m.row_bytes, m.lines2 + (size_t)(slot - m.slot2_base) * m.row_bytes, m.row_bytes, lig);
+    copy_row<L>(m.host_w + (size_t)row * m.row_bytes, m.lines2 + (size_t)(slot - m.slot2_base) * m.row_bytes, m.row_bytes, lig);
     if (lig == 0) b += m.row_bytes;
   }
   for (int d = 32; d >= 1; d >>= 1) b += __shfl_xor(b, d);
@@ -708,10 +728,10 @@ __global__ __launch_bounds__(256) void flush2_kernel(const TableMeta *__restrict
 hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const Level2 &l2, u64 *bytes_h2d,
                         u64 *bytes_d2h, hipStream_t s) {
   if (g.total_slots)
-    hipLaunchKernelGGL(flush_kernel, dim3(1024), dim3(256), 0, s, tm, g.T, g.total_slots, tags, bytes_d2h);
+    TBE_BY_ROW_LANES(g.ovf_stride, hipLaunchKernelGGL((flush_kernel<L>), dim3(1024), dim3(256), 0, s, tm, g.T, g.total_slots, tags, bytes_d2h));
   if (l2.on && l2.total_slots2)
-    hipLaunchKernelGGL(flush2_kernel, dim3(kLinkBlocks), dim3(256), 0, s, tm, g.T, l2.total_slots2, l2.tags2, bytes_h2d,
-                       bytes_d2h);
+    TBE_BY_ROW_LANES(g.ovf_stride, hipLaunchKernelGGL((flush2_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, tm, g.T, l2.total_slots2, l2.tags2, bytes_h2d,
+                       bytes_d2h));
   return hipGetLastError();
 }
 
