@@ -250,6 +250,7 @@ int alloc_batchbuf(tbe_ctx *h, BatchBuf &b, int64_t n) {
   HIP_TRY(h, h->mem.get(&b.byp_key, 4 * N));
   HIP_TRY(h, h->mem.get(&b.byp_src, 8 * N));
   HIP_TRY(h, h->mem.get(&b.byp_where, 4 * N));
+  HIP_TRY(h, h->mem.get(&b.byp_taken, N));
   HIP_TRY(h, h->mem.get(&b.ovf, N * (size_t)h->g.ovf_stride));
   HIP_TRY(h, h->mem.get(&b.mid_idx, 4 * (N / 2 + 1)));
   HIP_TRY(h, h->mem.get(&b.heavy, 4 * (N / 32 + 1)));  // rows: N / 65 at most; extra parts: N / kHeavySplit at most
@@ -919,6 +920,12 @@ int tbe_flush(tbe_handle h) {
     // brings the backing tier up to the last batch that trained.
     (void)collect_device_errors(h);
     if (!h->sticky) return fail(h, TBE_EORDER, "flush: a batch is still in flight");
+    // The batch in front of the refused one may have been committed without training: rows it bypassed and took over
+    // from the copies of the batch before it have their value in its own copies alone, which go home here.  (In the
+    // pipeline several batches deep every batch's copies go home after its own backward.)
+    const int undone = h->deep ? -1 : h->current >= 0 ? h->current : (h->n_pend > 0 && h->pend[0] != h->deferred) ? h->pend[0] : -1;
+    if (undone >= 0)
+      HIP_TRY(h, launch_ovf_writeback(h->buf[undone], nullptr, h->st, h->d_rb, h->d_bytes + 1, h->cs));
     h->n_pend = 0;
     h->current = -1;
     h->deferred = -1;

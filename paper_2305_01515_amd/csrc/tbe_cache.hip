@@ -483,6 +483,7 @@ struct StatusOp {
   int32_t *byp_tab;
   uint32_t *byp_key;
   char **byp_src;
+  uint8_t *byp_taken;
   int32_t *loc_u;
   // second level (all null without one)
   const int32_t *src2, *dst2, *evict2;
@@ -561,6 +562,7 @@ struct StatusOp {
       byp_tab[j] = t;
       byp_key[j] = key;
       byp_src[j] = m.host_w + (size_t)m.row_of(key) * m.row_bytes;
+      byp_taken[j] = 0;
       if (src2 && src2[u] >= 0)  // lives in the second level: used in place
         byp_src[j] = m.lines2 + (size_t)(src2[u] - m.slot2_base) * m.row_bytes;
       loc_u[u] = -2 - (int32_t)j;  // the row is served from the j-th overflow slot
@@ -950,7 +952,7 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
                      l2.on ? b.src2 : nullptr, l2.on ? b.dst2 : nullptr, l2.on ? b.evict2 : nullptr, b.cnt);
   StatusOp st{tm, g.T, b.status, b.run_off, b.old_tag, b.uniq_key, b.uniq_tab, b.ins_idx, b.ins_tab, b.ins_slot,
               b.ins_old, b.ins_key, b.ins_src,
-              b.byp_idx, b.byp_tab, b.byp_key, b.byp_src, b.loc_u,
+              b.byp_idx, b.byp_tab, b.byp_key, b.byp_src, b.byp_taken, b.loc_u,
               l2.on ? b.src2 : nullptr, l2.on ? b.dst2 : nullptr, l2.on ? b.evict2 : nullptr,
               l2.on ? b.ins_dst : nullptr, l2.on ? b.l2v_src : nullptr, l2.on ? b.l2v_dst : nullptr,
               l2.on ? b.l2v_key : nullptr, ss.tally, 0u, 0ull, nullptr};

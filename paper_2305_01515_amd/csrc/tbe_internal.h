@@ -156,6 +156,8 @@ struct BatchBuf {
   uint32_t *byp_key;    // [N]   its sort key
   char **byp_src;       // [N]   its row in the backing tier
   uint32_t *byp_where;  // [N]   as ins_where
+  uint8_t *byp_taken;   // [N]   1 = the next batch wants the row too and takes it over from the overflow copy in HBM, so
+                        //       that copy need not go home: a newer one does, or the row's cache line
   char *ovf;            // [N * stride] HBM copies of the bypassed rows while their batch trains
   int32_t *mid_idx;     // [N/2 + 1] rows with 2..kLongRun lookups, in the order of the distinct rows (table order)
   int32_t *heavy;       // [N/32 + 1] rows with more lookups, same order, one entry per part of a row (heavy_parts)

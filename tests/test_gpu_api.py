@@ -389,6 +389,54 @@ def test_bad_batch_prefetched_ahead_does_not_lose_the_last_good_batch():
     o.close()
 
 
+@pytest.mark.parametrize("forwarded", [True, False])
+@pytest.mark.parametrize("dtype", [synth.FP32, synth.FP16])
+def test_rows_bypassed_twice_in_a_row_reach_the_backing_tier(forwarded, dtype):
+    """A row that two batches in a row bypass is handed from copy to copy in HBM and only the newest copy goes home.
+    Here every batch is the same one, so all bypassed rows are handed on; then a refused batch ends the run while the
+    batch in front of it, which holds the newest copies, has not trained: the flush must still bring home what the last
+    trained batch left."""
+    from oracle import Oracle
+    from paper_2305_01515_amd.tbe import TbeError
+    from parity_util import compare_backing
+    cfg = little(dtype=dtype, slots=(8, 0))
+    g, Wp, Mp = make(cfg)
+    Wn = [w.numpy().copy() for w in Wp]
+    Mn = [m.numpy().copy() for m in Mp]
+    o = Oracle(Wn, Mn, [t.cache_slots for t in cfg.tables], cfg.ways)
+    idx, off = synth.BatchStream(cfg).next()
+    good = (idx.cuda(), off.cuda())
+    bad_idx = idx.clone()
+    bad_idx[-1] = cfg.tables[1].rows
+    bad = (bad_idx.cuda(), off.cuda())
+    before = g.stats()["d2h_bytes"]
+    g.prefetch(*good)
+    for s in range(3):
+        g.prefetch(*good)
+        g.forward(*good)
+        go = synth.grad_out(cfg, s + 1)
+        g.backward_update(go.cuda(), cfg.lr, cfg.eps)
+        o.prefetch(idx.numpy(), off.numpy())
+        o.forward()
+        o.backward_update(go.numpy(), cfg.lr, cfg.eps)
+    st = o.stats()[0]
+    assert st["bypasses"] > 0 and st["evictions"] == 0
+    assert g.stats()["d2h_bytes"] == before  # no victim, and every bypassed row was handed on
+    if forwarded:
+        g.forward(*good)
+    g.prefetch(*bad)
+    with pytest.raises(TbeError) as e:
+        g.stats()
+    assert e.value.code == -2
+    with pytest.raises(TbeError) as e:
+        g.flush()
+    assert e.value.code == -2
+    o.flush()
+    compare_backing(cfg, Wn, Mn, Wp, Mp, "after the refused batch")
+    g.close()
+    o.close()
+
+
 def test_probe_grouping_takes_1_to_2_pow_30():
     """tbe_set_probe_grouping: a tuning value, refused outside its range"""
     from paper_2305_01515_amd.tbe import TbeError
