@@ -95,9 +95,9 @@ struct tbe_ctx {
   char *lines = nullptr;
   BatchBuf buf[kMaxBatchBufs]{};
   int nbuf = kBatchBufs;        // batch buffers in use
+  DeepBuf *d_deep = nullptr;    // deep pipeline: the batch buffers, for the look-up of rows whose backing-tier copy is stale
   int deep = 0;                 // 0: the one-deep pipeline; D >= 2: batches are fetched into the cache up to D ahead
   hipEvent_t ev_home[kMaxBatchBufs] = {};   // deep pipeline: the write-back of the buffer's bypassed rows
-  bool home_pending[kMaxBatchBufs] = {};    // ... has been enqueued and the rows' marks are still in the map
   bool home_recorded[kMaxBatchBufs] = {};
   SortScratch ss{};
   Staging st{};
@@ -188,7 +188,7 @@ int next_pow2(int v) { int p = 1; while (p < v) p <<= 1; return p; }
 __global__ void stream_pin_kernel() {}
 
 // Running totals of a batch's counters: tot (hits, evictions, lookups that hit), t64 ([0] distinct
-// rows, [1] inserts, [2] bypasses) and, with a second level, l2 (its four counters).
+// rows, [1] inserts, [2] bypasses, [3] late rows) and, with a second level, l2 (its four counters).
 // Also completes the batch's own counters: evictions and lookups that hit from the per-wavefront sums of the
 // status pass (tens of thousands of them at the benchmark's batch: a single wavefront took 27 us to add them up),
 // hits as what is left of the distinct rows.  One workgroup of kTotalsThreads.
@@ -197,15 +197,15 @@ __global__ __launch_bounds__(kTotalsThreads) void add_totals_kernel(BatchCounter
                                                                     unsigned long long *t64, unsigned long long *l2,
                                                                     const unsigned long long *tally, int tally_waves) {
   if (c->err != 0) return;
-  __shared__ unsigned long long s_e[kTotalsThreads / 64], s_l[kTotalsThreads / 64];
-  unsigned long long e = 0, l = 0;
-  for (int w = threadIdx.x; w < tally_waves; w += kTotalsThreads) { e += tally[2 * w]; l += tally[2 * w + 1]; }
-  for (int d = 32; d >= 1; d >>= 1) { e += __shfl_xor(e, d); l += __shfl_xor(l, d); }
-  if ((threadIdx.x & 63) == 0) { s_e[threadIdx.x >> 6] = e; s_l[threadIdx.x >> 6] = l; }
+  __shared__ unsigned long long s_e[kTotalsThreads / 64], s_l[kTotalsThreads / 64], s_t[kTotalsThreads / 64];
+  unsigned long long e = 0, l = 0, late = 0;
+  for (int w = threadIdx.x; w < tally_waves; w += kTotalsThreads) { e += tally[3 * w]; l += tally[3 * w + 1]; late += tally[3 * w + 2]; }
+  for (int d = 32; d >= 1; d >>= 1) { e += __shfl_xor(e, d); l += __shfl_xor(l, d); late += __shfl_xor(late, d); }
+  if ((threadIdx.x & 63) == 0) { s_e[threadIdx.x >> 6] = e; s_l[threadIdx.x >> 6] = l; s_t[threadIdx.x >> 6] = late; }
   __syncthreads();
   if (threadIdx.x != 0) return;
-  e = l = 0;
-  for (int w = 0; w < kTotalsThreads / 64; w++) { e += s_e[w]; l += s_l[w]; }
+  e = l = late = 0;
+  for (int w = 0; w < kTotalsThreads / 64; w++) { e += s_e[w]; l += s_l[w]; late += s_t[w]; }
   c->hits = (unsigned long long)(c->n_uniq - c->n_ins - c->n_byp);
   c->evictions = e;
   c->hit_lookups = l;
@@ -215,6 +215,7 @@ __global__ __launch_bounds__(kTotalsThreads) void add_totals_kernel(BatchCounter
   t64[0] += (unsigned long long)c->n_uniq;
   t64[1] += (unsigned long long)c->n_ins;
   t64[2] += (unsigned long long)c->n_byp;
+  t64[3] += late;
   if (l2) {
     l2[0] += (unsigned long long)c->l2_hits;
     l2[1] += (unsigned long long)c->l2_demotions;
@@ -243,6 +244,7 @@ int alloc_batchbuf(tbe_ctx *h, BatchBuf &b, int64_t n) {
   HIP_TRY(h, h->mem.get(&b.ins_slot, 4 * N));
   HIP_TRY(h, h->mem.get(&b.ins_old, 4 * N));
   HIP_TRY(h, h->mem.get(&b.ins_key, 4 * N));
+  HIP_TRY(h, h->mem.get(&b.vic_key, 4 * N));
   HIP_TRY(h, h->mem.get(&b.ins_src, 8 * N));
   HIP_TRY(h, h->mem.get(&b.ins_where, 4 * N));
   HIP_TRY(h, h->mem.get(&b.byp_idx, 4 * N));
@@ -304,6 +306,35 @@ int enqueue_commit(tbe_ctx *h, int bi, bool wb_prev) {
   return TBE_OK;
 }
 
+// What batch `b` (buffer bi) finds of the rows whose backing-tier copy is stale.
+StaleRows stale_rows(const tbe_ctx *h, const BatchBuf &b, int bi) {
+  StaleRows r{};
+  r.where = h->st.where;
+  r.max_inserts = (uint32_t)h->st.max_inserts;
+  r.own_code = kWhereOverflow | (h->deep ? (uint32_t)bi << kWhereBufShift : 0u);
+  r.wb_skip = h->st.wb_skip[(b.k - 1) & 1];
+  if (h->prev_buf < 0) return r;
+  const BatchBuf &prev = h->buf[h->prev_buf];
+  r.prev_cnt = prev.cnt;
+  r.prev_vic_key = prev.vic_key;
+  r.prev_byp_key = prev.byp_key;
+  r.prev_byp_taken = prev.byp_taken;
+  if (h->l2.on) {
+    r.prev_l2v_src = prev.l2v_src;
+    r.prev_l2v_key = prev.l2v_key;
+  }
+  if (prev.parks_prev && prev.prev_bi >= 0) {
+    r.pp_cnt = h->buf[prev.prev_bi].cnt;
+    r.pp_byp_key = h->buf[prev.prev_bi].byp_key;
+  }
+  if (h->deep) {
+    r.deep = h->d_deep;
+    for (int i = 0; i < h->n_pend; i++) r.live |= 1u << h->pend[i];
+    if (h->current >= 0) r.live |= 1u << h->current;
+  }
+  return r;
+}
+
 // Pipeline several batches deep (Section 5.7): the batch is fetched into the cache as soon as it is decided on.
 // The ways of the batches that may still wait for their training are locked (ts >= k - D), so its victims and
 // the lines it fills are used by none of them and nothing waits for a backward -- except the rows whose current
@@ -333,20 +364,11 @@ int do_prefetch_deep(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offs
   }
   {
     StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
-    // batches whose bypassed rows are on their way home in front of this batch's transfer: their marks go
-    // (before this buffer's lists are overwritten, should it be one of them)
-    for (int x = 0; x < h->nbuf; x++)
-      if (h->home_pending[x]) {
-        HIP_TRY(h, launch_unmark_bypassed(h->buf[x], x, h->st, h->as));
-        h->home_pending[x] = false;
-      }
     HIP_TRY(h, launch_keygen(h->d_tm, h->g, b, h->ss.keys[0], h->ss.vals[0], h->as));
     int res = 0;
     HIP_TRY(h, launch_sort(h->g, h->ss, n, &res, h->as));
     HIP_TRY(h, launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq,
-                                  h->policy == TBE_POLICY_LFU, h->l2, h->deep, h->as));
-    const BatchBuf *prev = h->prev_buf >= 0 ? &h->buf[h->prev_buf] : nullptr;
-    HIP_TRY(h, launch_classify_mark_deep(h->d_tm, prev, b, bi, h->st, h->d_bytes + 5, h->as));
+                                  h->policy == TBE_POLICY_LFU, h->l2, h->deep, stale_rows(h, b, bi), h->as));
     hipLaunchKernelGGL(add_totals_kernel, dim3(1), dim3(kTotalsThreads), 0, h->as, b.cnt, h->d_total, h->d_bytes + 2,
                        (unsigned long long *)nullptr, h->ss.tally, n > 0 ? h->ss.tally_waves : 0);
     HIP_TRY(h, hipGetLastError());
@@ -412,13 +434,7 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
     int res = 0;
     HIP_TRY(h, launch_sort(h->g, h->ss, n, &res, h->as));
     HIP_TRY(h, launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq,
-                                  h->policy == TBE_POLICY_LFU, h->l2, 0, h->as));
-    // which of the rows to insert have a backing-tier copy that is still being written
-    // (by the write-back of the previous batch's victims or by its backward), then move
-    // the marks on from the previous batch to this one
-    const BatchBuf *prev = h->prev_buf >= 0 ? &h->buf[h->prev_buf] : nullptr;
-    const BatchBuf *pp = (prev && prev->parks_prev && prev->prev_bi >= 0) ? &h->buf[prev->prev_bi] : nullptr;
-    HIP_TRY(h, launch_classify_mark(h->d_tm, pp, prev, b, h->st, h->l2, h->d_bytes + 5, h->as));
+                                  h->policy == TBE_POLICY_LFU, h->l2, 0, stale_rows(h, b, bi), h->as));
     hipLaunchKernelGGL(add_totals_kernel, dim3(1), dim3(kTotalsThreads), 0, h->as, b.cnt, h->d_total, h->d_bytes + 2,
                        h->l2.on ? h->d_l2tot : nullptr, h->ss.tally, n > 0 ? h->ss.tally_waves : 0);
     HIP_TRY(h, hipGetLastError());
@@ -690,7 +706,7 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   }
   CREATE_TRY(h->mem.get(&h->ss.hist, 4 * (512 * 1024 + 512)));  // sort: counts per digit value (<= 512) and block (<= 1024), digit totals
   CREATE_TRY(h->mem.get(&h->ss.blk, 8 * (8192 + 1)));
-  CREATE_TRY(h->mem.get(&h->ss.tally, 8 * 2 * 8192));
+  CREATE_TRY(h->mem.get(&h->ss.tally, 8 * 3 * 8192));
   CREATE_TRY(h->mem.get(&h->ss.wl, 4 * 4 * (size_t)kWorklistBlocks));
   CREATE_TRY(h->mem.get(&h->d_total, sizeof(BatchCounters)));
   CREATE_TRY(hipMemset(h->d_total, 0, sizeof(BatchCounters)));
@@ -750,6 +766,10 @@ int tbe_set_prefetch_depth(tbe_handle h, int32_t depth) {
     h->nbuf = i + 1;
   }
   for (int i = 0; i < want; i++) HIP_TRY(h, hipEventCreateWithFlags(&h->ev_home[i], hipEventDisableTiming));
+  std::vector<DeepBuf> bufs(kMaxBatchBufs);
+  for (int i = 0; i < want; i++) bufs[i] = DeepBuf{h->buf[i].cnt, h->buf[i].byp_key};
+  HIP_TRY(h, h->mem.get(&h->d_deep, sizeof(DeepBuf) * kMaxBatchBufs));
+  HIP_TRY(h, hipMemcpy(h->d_deep, bufs.data(), sizeof(DeepBuf) * kMaxBatchBufs, hipMemcpyHostToDevice));
   HIP_TRY(h, hipDeviceSynchronize());
   h->deep = depth;
   return TBE_OK;
@@ -879,10 +899,9 @@ static int backward_update_with(tbe_ctx *h, const float *d_grad_out, float lr, f
     const BatchBuf &b = h->buf[bi];
     const BatchBuf *parked_prev = (b.parks_prev && b.prev_bi >= 0) ? &h->buf[b.prev_bi] : nullptr;
     HIP_TRY(h, launch_ovf_writeback(b, parked_prev, h->st, h->d_rb, h->d_bytes + 1, h->ls));
-    if (h->deep) {  // the marks of these rows go with the next prefetch; the buffer is free once they are home
+    if (h->deep) {  // the buffer is free once they are home
       HIP_TRY(h, hipEventRecord(h->ev_home[bi], h->ls));
       h->home_recorded[bi] = true;
-      h->home_pending[bi] = true;
     }
   }
   return pump_queue(h);
@@ -931,21 +950,10 @@ int tbe_flush(tbe_handle h) {
     h->deferred = -1;
     h->queued.clear();
   }
-  for (int x = 0; x < h->nbuf; x++)  // deep pipeline: bypassed rows that went home after their backward
-    if (h->home_pending[x]) {
-      HIP_TRY(h, launch_unmark_bypassed(h->buf[x], x, h->st, h->cs));
-      h->home_pending[x] = false;
-    }
   HIP_TRY(h, launch_transfer(nullptr, h->st, h->l2, h->di, h->throttle, 0, h->d_rb, h->d_bytes, h->d_bytes + 1, h->cs));  // parked victims first
-  if (h->prev_buf >= 0) {
-    // Every copy in the backing tier is current now, so the next batch must find no row marked
-    // "still on its way".  Left in place, such a mark would make that batch ask the transfer to skip
-    // a write-back that has already happened, and the request would hit a later batch's victim.
-    const BatchBuf &last = h->buf[h->prev_buf];
-    HIP_TRY(h, launch_unmark(h->d_tm, last, (last.parks_prev && last.prev_bi >= 0) ? &h->buf[last.prev_bi] : nullptr, h->st,
-                             h->l2, h->cs));
-    h->prev_buf = -1;
-  }
+  // Every copy in the backing tier is current now: the next batch must not take any row for one on its way (it would
+  // make the transfer skip a write-back that has already happened, and the request would hit a later batch's victim).
+  h->prev_buf = -1;
   HIP_TRY(h, launch_flush(h->d_tm, h->g, h->tags, h->l2, h->d_bytes, h->d_bytes + 1, h->cs));  // also slot accumulators -> dev_m
   for (const TableMeta &m : h->tm) {
     HIP_TRY(h, hipMemcpyAsync(m.host_m, m.dev_m, 4 * (size_t)m.rows, hipMemcpyDeviceToHost, h->cs));

@@ -463,7 +463,12 @@ __global__ __launch_bounds__(256) void heavy_starts_kernel(const TableMeta *__re
   }
 }
 
-// ---- pass 3 over the distinct rows after the probe: insert and bypass lists, counters ----
+// ---- pass 3 over the distinct rows after the probe: insert and bypass lists, counters, and for every missed row
+// whether its backing-tier copy is stale and where its value is instead.  The map that says so is read and written here,
+// by the lane that handles the row; its entries are checked against the lists of the batches whose copies are on their
+// way instead of being taken out again.  (With a pass of its own over the missed rows for the look-up and up to three
+// for entering and taking out entries, four launches more: small configuration, six steps 1276 -> 1198 us; 16 x 500k
+// resident rows, four steps 2773 -> 2731 us.)
 struct StatusOp {
   static constexpr int kItems = 1;
   const TableMeta *tm;
@@ -478,22 +483,26 @@ struct StatusOp {
   int32_t *ins_slot;
   int32_t *ins_old;
   uint32_t *ins_key;
+  uint32_t *vic_key;
   char **ins_src;
+  uint32_t *ins_where;
   int32_t *byp_idx;
   int32_t *byp_tab;
   uint32_t *byp_key;
   char **byp_src;
+  uint32_t *byp_where;
   uint8_t *byp_taken;
+  StaleRows stale;
   int32_t *loc_u;
   // second level (all null without one)
   const int32_t *src2, *dst2, *evict2;
   char **ins_dst, **l2v_src, **l2v_dst;
   uint32_t *l2v_key;
   // per-thread tallies (the emit kernel keeps one Op copy per thread in registers); every wavefront leaves
-  // its sums in `tally` (two words each), which the kernel that keeps the running totals adds up -- thousands
+  // its sums in `tally` (three words each), which the kernel that keeps the running totals adds up -- thousands
   // of atomic additions to one counter from all over the chip would take longer than the pass itself
   u64 *tally;
-  mutable unsigned int evs;
+  mutable unsigned int evs, late;
   mutable u64 hit_lookups;
   mutable const TableLut *lut;  // null: the model has too many tables for it
   __device__ bool prepare(TableLut &l) const {
@@ -524,6 +533,42 @@ struct StatusOp {
     const TableMeta &m = tm[t];
     return TabView{m.key_base, m.sets, m.rows_per_set, m.row_bytes, m.host_w, m.lines2, m.slot2_base};
   }
+  // Where the value of the missed row with this key is: 0 = in the backing tier, else the kWhere* code of an HBM copy
+  // that is newer (the row is "late").  Says so to whoever would send that copy home.
+  __device__ uint32_t current_place(uint32_t key) const {
+    const uint32_t code = stale.where[key];
+    if (code == 0u || !stale.prev_cnt) return 0u;
+    if (code & kWhereOverflow) {
+      if (stale.deep) {
+        const uint32_t buf = (code >> kWhereBufShift) & (kMaxBatchBufs - 1), j = code & kWhereBufIndex;
+        if (!(stale.live >> buf & 1u)) return 0u;
+        const DeepBuf d = stale.deep[buf];
+        return (int)j < d.cnt->n_byp && d.byp_key[j] == key ? code : 0u;
+      }
+      const int j = (int)(code & kWhereIndex);
+      if (j < stale.prev_cnt->n_byp && stale.prev_byp_key[j] == key) {
+        stale.prev_byp_taken[j] = 1;  // that copy need not go home: this batch's does, or the row's cache line
+        return code;
+      }
+      if (stale.pp_cnt && j < stale.pp_cnt->n_byp && stale.pp_byp_key[j] == key) {
+        const uint32_t slot = (uint32_t)(stale.prev_cnt->n_ins + j);
+        stale.wb_skip[slot] = 1;
+        return kWhereParked | slot;
+      }
+      return 0u;
+    }
+    // a victim the batch before parked and this batch wants back skips the trip to the host
+    const uint32_t i = code & kWhereIndex;
+    const uint32_t n = (uint32_t)stale.prev_cnt->n_ins;
+    bool there = i < n && stale.prev_vic_key[i] == key;
+    if (stale.prev_l2v_src && i >= stale.max_inserts) {
+      const uint32_t v = i - stale.max_inserts;
+      there = v < n && stale.prev_l2v_src[v] && stale.prev_l2v_key[v] == key;
+    }
+    if (!there) return 0u;
+    stale.wb_skip[i] = 1;
+    return code;
+  }
   __device__ u64 flag(int u, int) const {
     const uint8_t s = status[u];
     return s == ST_INSERT ? 1ull : s == ST_BYPASS ? (1ull << 32) : 0ull;
@@ -541,6 +586,9 @@ struct StatusOp {
       ins_slot[i] = loc_u[u];
       ins_old[i] = old;
       ins_key[i] = key;
+      const uint32_t place = current_place(key);
+      ins_where[i] = place;
+      late += place != 0u;
       ins_src[i] = m.host_w + (size_t)row * m.row_bytes;
       if (src2) {  // second level: the row may come from there, the victim may go there
         const int32_t s2 = src2[u], d2 = dst2[u], e2 = evict2[u];
@@ -551,8 +599,17 @@ struct StatusOp {
         l2v_src[i] = e2 >= 0 ? dst : nullptr;  // the line the victim takes still holds the row it pushes out
         l2v_dst[i] = e2 >= 0 ? m.host_w + (size_t)e2 * m.row_bytes : nullptr;
         l2v_key[i] = e2 >= 0 ? m.key_of((uint32_t)e2) : 0u;
+        if (e2 >= 0) stale.where[l2v_key[i]] = kWhereParked | (stale.max_inserts + i);  // staged behind the victims
       }
-      if (old >= 0) evs++;
+      // The victim's entry in the map.  No row of this batch is a victim of it, and no two of its rows have the same
+      // victim, so every entry is read or written by one lane.
+      uint32_t vk = key;
+      if (old >= 0) {
+        evs++;
+        vk = m.key_of((uint32_t)old);
+        stale.where[vk] = kWhereParked | i;
+      }
+      vic_key[i] = vk;
     } else if (f) {
       const uint32_t j = (uint32_t)(pre >> 32);
       const uint32_t key = uniq_key[u];
@@ -562,6 +619,10 @@ struct StatusOp {
       byp_tab[j] = t;
       byp_key[j] = key;
       byp_src[j] = m.host_w + (size_t)m.row_of(key) * m.row_bytes;
+      const uint32_t place = current_place(key);
+      byp_where[j] = place;
+      late += place != 0u;
+      stale.where[key] = stale.own_code | j;
       byp_taken[j] = 0;
       if (src2 && src2[u] >= 0)  // lives in the second level: used in place
         byp_src[j] = m.lines2 + (size_t)(src2[u] - m.slot2_base) * m.row_bytes;
@@ -572,14 +633,17 @@ struct StatusOp {
   }
   __device__ void thread_done(BatchCounters *, int lane) const {
     u64 e = evs, l = hit_lookups;
+    unsigned int lt = late;
     for (int d = 32; d >= 1; d >>= 1) {
       e += __shfl_xor(e, d);
       l += __shfl_xor(l, d);
+      lt += __shfl_xor(lt, d);
     }
     if (lane == 0) {
       const int w = blockIdx.x * kScanWavesPerBlock + (threadIdx.x >> 6);
-      tally[2 * w] = e;
-      tally[2 * w + 1] = l;
+      tally[3 * w] = e;
+      tally[3 * w + 1] = l;
+      tally[3 * w + 2] = lt;
     }
   }
   __device__ void finish(BatchCounters *cnt, int, u64 total) const {
@@ -922,7 +986,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(int n, const uint32_t *__
 
 hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const BatchBuf &b, SortScratch &ss,
                               const uint32_t *sorted_keys, const uint32_t *sorted_pos, int32_t *tags, int32_t *ts,
-                              int32_t *freq, bool lfu, const Level2 &l2, int lock, hipStream_t s) {
+                              int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale, hipStream_t s) {
   const int n = (int)b.n;
   if (n == 0) return hipSuccess;
   DedupOp d{tm, g.T, sorted_keys, sorted_pos, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
@@ -951,11 +1015,11 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
                      tags, ts, freq, b.run_off, b.loc_u, b.status, b.old_tag, l2.tags2, l2.ts2, l2.factor,
                      l2.on ? b.src2 : nullptr, l2.on ? b.dst2 : nullptr, l2.on ? b.evict2 : nullptr, b.cnt);
   StatusOp st{tm, g.T, b.status, b.run_off, b.old_tag, b.uniq_key, b.uniq_tab, b.ins_idx, b.ins_tab, b.ins_slot,
-              b.ins_old, b.ins_key, b.ins_src,
-              b.byp_idx, b.byp_tab, b.byp_key, b.byp_src, b.byp_taken, b.loc_u,
+              b.ins_old, b.ins_key, b.vic_key, b.ins_src, b.ins_where,
+              b.byp_idx, b.byp_tab, b.byp_key, b.byp_src, b.byp_where, b.byp_taken, stale, b.loc_u,
               l2.on ? b.src2 : nullptr, l2.on ? b.dst2 : nullptr, l2.on ? b.evict2 : nullptr,
               l2.on ? b.ins_dst : nullptr, l2.on ? b.l2v_src : nullptr, l2.on ? b.l2v_dst : nullptr,
-              l2.on ? b.l2v_key : nullptr, ss.tally, 0u, 0ull, nullptr};
+              l2.on ? b.l2v_key : nullptr, ss.tally, 0u, 0u, 0ull, nullptr};
   ss.tally_waves = run_compaction(st, &b.cnt->n_uniq, 0, n, ss.blk, b.cnt, s) * kScanWavesPerBlock;
   hipLaunchKernelGGL(finalize_kernel, dim3(TBE_FINALIZE_BLOCKS), dim3(256), 0, s, n, sorted_pos, b.uid_sorted, b.loc_u, b.run_off,
                      b.loc, b.d_offsets, g.within_bits, b.cnt);

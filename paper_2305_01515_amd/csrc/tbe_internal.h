@@ -143,6 +143,7 @@ struct BatchBuf {
   int32_t *ins_slot;    // [N]   the global slot it takes
   int32_t *ins_old;     // [N]   the row evicted from that slot, -1 if it was free
   uint32_t *ins_key;    // [N]   its sort key
+  uint32_t *vic_key;    // [N]   the sort key of the row evicted from that slot (the inserted row's if the entry was free)
   char **ins_src;       // [N]   where its row is fetched from (lower tier or second-level line)
   char **ins_dst;       // [N]   second level only: where its victim goes (second-level line or lower tier)
   char **l2v_src;       // [N]   second level only: line of the row the victim pushes out of the second
@@ -186,8 +187,8 @@ struct SortScratch {
   uint32_t *hist;          // [256 * max sort blocks] block histograms, then [256] digit totals
   unsigned long long *blk; // [scan blocks + 1] block sums of the compaction passes
   int32_t *wl;             // [kWorklistBlocks * 4] per-workgroup counts of the backward work lists
-  unsigned long long *tally;  // [2 * wavefronts of a compaction pass] (evictions, lookups that hit) per wavefront of
-  int tally_waves;            //     the last batch's status pass, and how many wavefronts that pass had
+  unsigned long long *tally;  // [3 * wavefronts of a compaction pass] (evictions, lookups that hit, late rows) per wave-
+  int tally_waves;            //     front of the last batch's status pass, and how many wavefronts that pass had
 };
 
 // Staging between the cache and the host link (one instance; the prefetch stage is serial).
@@ -203,8 +204,10 @@ struct Staging {
   uint8_t *wb_skip[2]; // [max_inserts] by parity of the batch that parked the victim: 1 = the next batch
                        // takes the row straight back (from `out`), so it need not travel to the host
   int32_t *wb_n;       // [0] number of parked victim slots, [1] which `out` holds them (device)
-  uint32_t *where;     // [key span] per sort key: 0, or where the row's current value is while its
-                       // backing-tier copy is stale (kWhereOverflow | j, kWhereParked | i)
+  uint32_t *where;     // [key span] per sort key: where the row's value was the last time its backing-tier copy went
+                       // stale (kWhereOverflow | j: bypassed row j of that batch, kWhereParked | i: its i-th victim; 0:
+                       // never).  Entries are not taken out: one counts while the list it points into still belongs to
+                       // a batch whose copies are on their way and holds this key there (StaleRows)
   uint32_t stride;     // bytes per staged row (widest row)
   int64_t max_inserts;
   int64_t max_parked;  // room behind the victims for the overflow copies parked with them (0: they are never parked)
@@ -228,6 +231,30 @@ struct Level2 {
 // reads from or writes to the backing tier proper (not the second-level lines).  0 pauses = off.
 struct Throttle {
   int32_t pauses = 0;  // s_sleep instructions of the longest kind per backing-tier row
+};
+
+// Which backing-tier copies are stale when a batch is decided on, and where the rows' values are: the lists of the
+// batches whose copies are still in HBM, against which an entry of Staging::where is checked.  A row that is in one of
+// them has its newest entry there, because every batch enters its own rows and the lists of older batches run out first.
+struct DeepBuf {  // one batch buffer of the pipeline several batches deep
+  const BatchCounters *cnt;
+  const uint32_t *byp_key;
+};
+struct StaleRows {
+  uint32_t *where;
+  uint32_t max_inserts;            // codes kWhereParked | (max_inserts + i): rows pushed out of the second level
+  uint32_t own_code;               // kWhereOverflow, with the batch's buffer in the pipeline several batches deep
+  uint8_t *wb_skip;                // of the victims the batch before parked: 1 = this batch takes the row back
+  const BatchCounters *prev_cnt;   // the batch before (null: none since the start or the last flush): its victims, and
+  const uint32_t *prev_vic_key;    //   in the one-deep pipeline the rows it bypassed
+  const uint32_t *prev_byp_key;
+  uint8_t *prev_byp_taken;
+  char *const *prev_l2v_src;       // second level only: rows its victims pushed out of there
+  const uint32_t *prev_l2v_key;
+  const BatchCounters *pp_cnt;     // the batch before that one, when prev's commit parks the copies of its bypassed rows
+  const uint32_t *pp_byp_key;      //   behind prev's victims (else null)
+  const DeepBuf *deep;             // pipeline several batches deep: all batch buffers, and which of them hold a batch
+  uint32_t live;                   //   that has not trained yet
 };
 
 struct Geometry {
@@ -264,7 +291,7 @@ hipError_t launch_sort(const Geometry &g, SortScratch &ss, int64_t n, int *resul
 // lock: batches before the current one whose ways are locked like the current batch's own (0 in the one-deep pipeline)
 hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const BatchBuf &b, SortScratch &ss,
                               const uint32_t *sorted_keys, const uint32_t *sorted_pos, int32_t *tags, int32_t *ts,
-                              int32_t *freq, bool lfu, const Level2 &l2, int lock, hipStream_t s);
+                              int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale, hipStream_t s);
 // write back the staged victims and (b != null) fetch ahead the rows b's batch inserts
 // Deferred initialisation on read (Section 5.4.2): a row of the backing tier has no value until it is
 // first fetched; the fetch then makes it up instead of reading it.
@@ -277,11 +304,6 @@ struct DeferredInit {
 hipError_t launch_transfer(const BatchBuf *b, const Staging &st, const Level2 &l2, const DeferredInit &di,
                            const Throttle &th, int k, const uint32_t *rb_of_table,
                            unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
-// look up, for the rows cur inserts or bypasses, whether their backing-tier copy is stale
-// and where the current value is; then remove prev's entries from the map and enter cur's
-// pp: the batch before prev when prev's commit parked pp's overflow copies (their marks go now), else null
-hipError_t launch_classify_mark(const TableMeta *tm, const BatchBuf *pp, const BatchBuf *prev, const BatchBuf &cur,
-                                const Staging &st, const Level2 &l2, unsigned long long *n_late, hipStream_t s);
 // prev_mode: what becomes of prev's overflow copies: kPrevKeep (nothing), kPrevWrite (to the backing tier now),
 // kPrevPark (among this batch's parked victims: the next transfer writes them)
 constexpr int kPrevKeep = 0, kPrevWrite = 1, kPrevPark = 2;
@@ -295,14 +317,6 @@ hipError_t launch_commit(const TableMeta *tm, const BatchBuf &b, const BatchBuf 
 struct OverflowCopies {
   const char *of_buf[kMaxBatchBufs];
 };
-// which of cur's rows are late (as launch_classify_mark), then: prev's victims are home with cur's transfer, prev's
-// bypassed rows keep their marks (they go home after prev's backward: launch_unmark_bypassed), cur's rows are
-// entered -- its bypassed rows with the number of its buffer
-hipError_t launch_classify_mark_deep(const TableMeta *tm, const BatchBuf *prev, const BatchBuf &cur, int cur_buf,
-                                     const Staging &st, unsigned long long *n_late, hipStream_t s);
-// the marks of b's bypassed rows go, unless a later batch has entered the row again (the write-back that follows
-// b's backward is on the link stream in front of every later transfer)
-hipError_t launch_unmark_bypassed(const BatchBuf &b, int buf, const Staging &st, hipStream_t s);
 // before b's forward, on the compute stream (every earlier batch has trained): the rows of b whose current value
 // was an overflow copy of an earlier batch when b's commit ran are copied from there to where b uses them, and
 // the accumulators of those it inserted are taken over again
@@ -312,8 +326,6 @@ hipError_t launch_fixup(const TableMeta *tm, const BatchBuf &b, const OverflowCo
 // parked_prev: the batch whose overflow copies b's commit parked and no transfer has written yet (else null)
 hipError_t launch_ovf_writeback(const BatchBuf &b, const BatchBuf *parked_prev, const Staging &st,
                                 const uint32_t *rb_of_table, unsigned long long *bytes_d2h, hipStream_t s);
-hipError_t launch_unmark(const TableMeta *tm, const BatchBuf &last, const BatchBuf *parked_prev, const Staging &st,
-                         const Level2 &l2, hipStream_t s);
 hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const Level2 &l2,
                         unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
 hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,

@@ -299,140 +299,7 @@ hipError_t launch_transfer(const BatchBuf *b, const Staging &st, const Level2 &l
   return hipGetLastError();
 }
 
-// Enter (set) or remove (clear) in the map the rows whose backing-tier copy batch `b` leaves
-// stale for a while: the rows it evicted (parked victim i, written back by the next
-// transfer) and the rows it bypassed (overflow copy j, written back after its backward).
-// byp_mode: what the rows the batch bypassed get: kMarkClear, kMarkOverflow (overflow copy j of this
-// batch) or kMarkParked (the next batch's commit parks copy j behind its own n_ins victims:
-// kWhereParked | (next->n_ins + j)).  vic_mode: kMarkClear / kMarkOverflow (= set) for its victims, or
-// kMarkKeep to leave them alone.
-constexpr int kMarkClear = 0, kMarkOverflow = 1, kMarkParked = 2, kMarkKeep = 3;
-
-__global__ __launch_bounds__(256) void mark_kernel(const TableMeta *__restrict__ tm, const BatchCounters *cnt,
-                                                   const int32_t *__restrict__ ins_tab,
-                                                   const int32_t *__restrict__ ins_old,
-                                                   const uint32_t *__restrict__ byp_key,
-                                                   char *const *__restrict__ l2v_src,
-                                                   const uint32_t *__restrict__ l2v_key, uint32_t max_inserts,
-                                                   uint32_t *where, int vic_mode, int byp_mode,
-                                                   const BatchCounters *next_cnt, uint32_t overflow_code) {
-  if (cnt->err) return;
-  const int n_ins = vic_mode == kMarkKeep ? 0 : cnt->n_ins, n_byp = byp_mode == kMarkKeep ? 0 : cnt->n_byp;
-  const int set = vic_mode != kMarkClear;
-  const uint32_t park_base = (byp_mode == kMarkParked && next_cnt) ? (uint32_t)next_cnt->n_ins : 0u;
-  const int stride = gridDim.x * blockDim.x;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_ins + n_byp; i += stride) {
-    if (i < n_ins) {
-      const int32_t old = ins_old[i];
-      if (old >= 0) where[key_of_row(tm[ins_tab[i]], (uint32_t)old)] = set ? (kWhereParked | (uint32_t)i) : 0u;
-      // the row pushed out of the second level is staged like a victim, behind the victims
-      if (l2v_src && l2v_src[i]) where[l2v_key[i]] = set ? (kWhereParked | (max_inserts + (uint32_t)i)) : 0u;
-    } else {
-      const uint32_t j = (uint32_t)(i - n_ins);
-      where[byp_key[j]] = byp_mode == kMarkOverflow ? (overflow_code | j) : byp_mode == kMarkParked ? (kWhereParked | (park_base + j)) : 0u;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void classify_kernel(const BatchCounters *cnt, const uint32_t *__restrict__ ins_key,
-                                                       const uint32_t *__restrict__ byp_key,
-                                                       const uint32_t *__restrict__ where,
-                                                       uint32_t *__restrict__ ins_where,
-                                                       uint32_t *__restrict__ byp_where,
-                                                       uint8_t *__restrict__ prev_wb_skip,
-                                                       uint8_t *__restrict__ prev_byp_taken, u64 *n_late) {
-  if (cnt->err) return;
-  const int n_ins = cnt->n_ins, n_byp = cnt->n_byp;
-  unsigned int late = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_ins + n_byp; i += gridDim.x * blockDim.x) {
-    const uint32_t code = where[i < n_ins ? ins_key[i] : byp_key[i - n_ins]];
-    if (i < n_ins) ins_where[i] = code; else byp_where[i - n_ins] = code;
-    // a victim the batch before parked and this batch wants back skips the trip to the host
-    if (code & kWhereParked) prev_wb_skip[code & kWhereIndex] = 1;
-    // one of the batch before's overflow copies: this batch takes the row over from there (null in the pipeline several
-    // batches deep, whose codes name one of several buffers)
-    if ((code & kWhereOverflow) && prev_byp_taken) prev_byp_taken[code & kWhereIndex] = 1;
-    late += code != 0;
-  }
-  __shared__ unsigned int s_late[4];
-  for (int d = 32; d >= 1; d >>= 1) late += __shfl_xor(late, d);
-  if ((threadIdx.x & 63) == 0) s_late[threadIdx.x >> 6] = late;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    late = s_late[0] + s_late[1] + s_late[2] + s_late[3];
-    if (late) atomicAdd(n_late, (unsigned long long)late);
-  }
-}
-
-hipError_t launch_classify_mark(const TableMeta *tm, const BatchBuf *pp, const BatchBuf *prev, const BatchBuf &cur,
-                                const Staging &st, const Level2 &l2, u64 *n_late, hipStream_t s) {
-  const uint32_t M = (uint32_t)st.max_inserts;
-  hipLaunchKernelGGL(classify_kernel, dim3(512), dim3(256), 0, s, cur.cnt, cur.ins_key, cur.byp_key, st.where,
-                     cur.ins_where, cur.byp_where, st.wb_skip[(cur.k - 1) & 1], prev ? prev->byp_taken : nullptr, n_late);
-  // The marks move on in this order (a later one may overwrite an earlier one's entry, never the
-  // other way round): the overflow copies that prev's commit parked are home once the transfer of
-  // this batch is through; prev's victims likewise; prev's own overflow copies are either home
-  // already or will be parked by this batch's commit behind its victims; then this batch's rows.
-  if (pp)
-    hipLaunchKernelGGL(mark_kernel, dim3(512), dim3(256), 0, s, tm, pp->cnt, pp->ins_tab, pp->ins_old, pp->byp_key,
-                       (char *const *)nullptr, (const uint32_t *)nullptr, M, st.where, kMarkKeep, kMarkClear,
-                       (const BatchCounters *)nullptr, kWhereOverflow);
-  if (prev)
-    hipLaunchKernelGGL(mark_kernel, dim3(512), dim3(256), 0, s, tm, prev->cnt, prev->ins_tab, prev->ins_old, prev->byp_key,
-                       l2.on ? prev->l2v_src : nullptr, prev->l2v_key, M, st.where, kMarkClear,
-                       cur.parks_prev ? kMarkParked : kMarkClear, cur.cnt, kWhereOverflow);
-  hipLaunchKernelGGL(mark_kernel, dim3(512), dim3(256), 0, s, tm, cur.cnt, cur.ins_tab, cur.ins_old, cur.byp_key,
-                     l2.on ? cur.l2v_src : nullptr, cur.l2v_key, M, st.where, kMarkOverflow, kMarkOverflow,
-                     (const BatchCounters *)nullptr, kWhereOverflow);
-  return hipGetLastError();
-}
-
-// After a flush nothing is on its way to the backing tier any more: the marks of the last batch go,
-// and those of the overflow copies its commit parked (parked_prev: the batch they belonged to).
-hipError_t launch_unmark(const TableMeta *tm, const BatchBuf &last, const BatchBuf *parked_prev, const Staging &st,
-                         const Level2 &l2, hipStream_t s) {
-  if (parked_prev)
-    hipLaunchKernelGGL(mark_kernel, dim3(512), dim3(256), 0, s, tm, parked_prev->cnt, parked_prev->ins_tab,
-                       parked_prev->ins_old, parked_prev->byp_key, (char *const *)nullptr, (const uint32_t *)nullptr,
-                       (uint32_t)st.max_inserts, st.where, kMarkKeep, kMarkClear, (const BatchCounters *)nullptr, kWhereOverflow);
-  hipLaunchKernelGGL(mark_kernel, dim3(512), dim3(256), 0, s, tm, last.cnt, last.ins_tab, last.ins_old, last.byp_key,
-                     l2.on ? last.l2v_src : nullptr, last.l2v_key, (uint32_t)st.max_inserts, st.where, kMarkClear, kMarkClear,
-                     (const BatchCounters *)nullptr, kWhereOverflow);
-  return hipGetLastError();
-}
-
 // ---- pipeline several batches deep ----
-hipError_t launch_classify_mark_deep(const TableMeta *tm, const BatchBuf *prev, const BatchBuf &cur, int cur_buf,
-                                     const Staging &st, u64 *n_late, hipStream_t s) {
-  const uint32_t M = (uint32_t)st.max_inserts;
-  hipLaunchKernelGGL(classify_kernel, dim3(512), dim3(256), 0, s, cur.cnt, cur.ins_key, cur.byp_key, st.where,
-                     cur.ins_where, cur.byp_where, st.wb_skip[(cur.k - 1) & 1], (uint8_t *)nullptr, n_late);
-  if (prev)
-    hipLaunchKernelGGL(mark_kernel, dim3(512), dim3(256), 0, s, tm, prev->cnt, prev->ins_tab, prev->ins_old, prev->byp_key,
-                       (char *const *)nullptr, (const uint32_t *)nullptr, M, st.where, kMarkClear, kMarkKeep,
-                       (const BatchCounters *)nullptr, kWhereOverflow);
-  hipLaunchKernelGGL(mark_kernel, dim3(512), dim3(256), 0, s, tm, cur.cnt, cur.ins_tab, cur.ins_old, cur.byp_key,
-                     (char *const *)nullptr, (const uint32_t *)nullptr, M, st.where, kMarkOverflow, kMarkOverflow,
-                     (const BatchCounters *)nullptr, kWhereOverflow | ((uint32_t)cur_buf << kWhereBufShift));
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void unmark_bypassed_kernel(const BatchCounters *cnt, const uint32_t *__restrict__ byp_key,
-                                                              uint32_t *where, uint32_t overflow_code) {
-  if (cnt->err) return;
-  const int n_byp = cnt->n_byp;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n_byp; j += gridDim.x * blockDim.x) {
-    uint32_t *w = where + byp_key[j];
-    if (*w == (overflow_code | (uint32_t)j)) *w = 0u;  // a later batch's entry for the same row stays
-  }
-}
-
-hipError_t launch_unmark_bypassed(const BatchBuf &b, int buf, const Staging &st, hipStream_t s) {
-  hipLaunchKernelGGL(unmark_bypassed_kernel, dim3(512), dim3(256), 0, s, b.cnt, b.byp_key, st.where,
-                     kWhereOverflow | ((uint32_t)buf << kWhereBufShift));
-  return hipGetLastError();
-}
-
 template <int L>
 __global__ __launch_bounds__(256) void fixup_kernel(const TableMeta *__restrict__ tm, const BatchCounters *cnt,
                                                     const int32_t *__restrict__ ins_tab,
