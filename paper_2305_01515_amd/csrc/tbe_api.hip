@@ -233,7 +233,6 @@ int alloc_batchbuf(tbe_ctx *h, BatchBuf &b, int64_t n) {
   HIP_TRY(h, h->mem.get(&b.uid_sorted, 4 * N));
   HIP_TRY(h, h->mem.get(&b.uniq_key, 4 * N));
   HIP_TRY(h, h->mem.get(&b.run_off, 4 * (N + 1)));
-  HIP_TRY(h, h->mem.get(&b.uniq_sid, 4 * N));
   HIP_TRY(h, h->mem.get(&b.uniq_tab, 4 * N));
   HIP_TRY(h, h->mem.get(&b.loc_u, 4 * N));
   HIP_TRY(h, h->mem.get(&b.status, N));
@@ -260,8 +259,7 @@ int alloc_batchbuf(tbe_ctx *h, BatchBuf &b, int64_t n) {
   HIP_TRY(h, h->mem.get(&b.harrive, 4 * (N / 32 + 1)));
   HIP_TRY(h, hipMemset(b.harrive, 0, 4 * (N / 32 + 1)));
   HIP_TRY(h, h->mem.get(&b.hchunks, 16 * (N / 32 + (size_t)h->g.T + 1)));
-  HIP_TRY(h, h->mem.get(&b.hg_count, 4 * 2 * ((size_t)h->g.T + 1)));
-  HIP_TRY(h, hipMemset(b.hg_count, 0, 4 * 2 * ((size_t)h->g.T + 1)));
+  HIP_TRY(h, h->mem.get(&b.hfirst, 4 * ((size_t)h->g.T + 1)));
   HIP_TRY(h, h->mem.get(&b.hperm, 4 * (N / 32 + 1)));
   HIP_TRY(h, h->mem.get(&b.hstart, 4 * (h->huge_slots + 1)));
   HIP_TRY(h, h->mem.get(&b.cnt, sizeof(BatchCounters)));
@@ -705,9 +703,8 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
     h->static_partials = (float *)p;
   }
   CREATE_TRY(h->mem.get(&h->ss.hist, 4 * (512 * 1024 + 512)));  // sort: counts per digit value (<= 512) and block (<= 1024), digit totals
-  CREATE_TRY(h->mem.get(&h->ss.blk, 8 * (8192 + 1)));
+  CREATE_TRY(h->mem.get(&h->ss.blk, 16 * (8192 + 1)));
   CREATE_TRY(h->mem.get(&h->ss.tally, 8 * 3 * 8192));
-  CREATE_TRY(h->mem.get(&h->ss.wl, 4 * 4 * (size_t)kWorklistBlocks));
   CREATE_TRY(h->mem.get(&h->d_total, sizeof(BatchCounters)));
   CREATE_TRY(hipMemset(h->d_total, 0, sizeof(BatchCounters)));
   CREATE_TRY(h->mem.get(&h->d_bytes, 8 * 8));

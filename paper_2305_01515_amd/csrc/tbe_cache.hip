@@ -28,16 +28,44 @@ constexpr int kScanBlocks = TBE_SCAN_BLOCKS;     // workgroups at most (SortScra
 
 typedef unsigned long long u64;
 
-__device__ inline u64 wave_incl_scan(u64 v, int lane) {
+// What a pass scans: 2 N counters of 32 bits, two to a word (a pass's Op::V).
+template <int N>
+struct Counts {
+  u64 w[N];
+  __device__ Counts &operator+=(const Counts &o) {
+#pragma unroll
+    for (int i = 0; i < N; i++) w[i] += o.w[i];
+    return *this;
+  }
+  __device__ Counts operator-(const Counts &o) const {
+    Counts r{};
+#pragma unroll
+    for (int i = 0; i < N; i++) r.w[i] = w[i] - o.w[i];
+    return r;
+  }
+  __device__ uint32_t lo(int i) const { return (uint32_t)w[i]; }
+  __device__ uint32_t hi(int i) const { return (uint32_t)(w[i] >> 32); }
+};
+
+template <int N>
+__device__ inline Counts<N> wave_incl_scan(Counts<N> v, int lane) {
   for (int d = 1; d < 64; d <<= 1) {
-    u64 o = __shfl_up(v, d);
+    Counts<N> o{};
+#pragma unroll
+    for (int i = 0; i < N; i++) o.w[i] = __shfl_up(v.w[i], d);
     if (lane >= d) v += o;
   }
   return v;
 }
 
-__device__ inline u64 wave_total(u64 v) {
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+template <int N>
+__device__ inline Counts<N> wave_total(Counts<N> v) {
+  for (int d = 32; d >= 1; d >>= 1) {
+    Counts<N> o{};
+#pragma unroll
+    for (int i = 0; i < N; i++) o.w[i] = __shfl_xor(v.w[i], d);
+    v += o;
+  }
   return v;
 }
 
@@ -51,9 +79,11 @@ __device__ inline int scan_chunk(int n, int nblocks, int step) {
 // blk: [0, nblocks) sums per workgroup; [nblocks, nblocks * 5) sums per wavefront
 template <class Op>
 __global__ __launch_bounds__(kScanThreads) void compact_count_kernel(Op op, const int32_t *n_ptr, int n_fixed,
-                                                                     u64 *blk, const BatchCounters *cnt) {
-  __shared__ u64 wsum[kScanWavesPerBlock];
+                                                                     typename Op::V *blk, const BatchCounters *cnt) {
+  __shared__ typename Op::V wsum[kScanWavesPerBlock];
+  __shared__ typename Op::Lut s_lut;
   if (cnt->err) return;
+  if (op.prepare_count(s_lut)) __syncthreads();
   constexpr int kScanItems = Op::kItems, kScanStep = kWave * kScanItems;
   const int n = n_ptr ? *n_ptr : n_fixed;
   const int chunk = scan_chunk(n, gridDim.x, kScanStep);
@@ -61,7 +91,7 @@ __global__ __launch_bounds__(kScanThreads) void compact_count_kernel(Op op, cons
   const int w = blockIdx.x * kScanWavesPerBlock + wave;
   const int64_t base64 = (int64_t)w * chunk;
   const int base = (int)(base64 < n ? base64 : n), end = (int)(base64 + chunk < n ? base64 + chunk : n);
-  u64 s = 0;
+  typename Op::V s{};
   for (int i0 = base + lane * kScanItems; i0 < end; i0 += kScanStep) {
 #pragma unroll
     for (int q = 0; q < kScanItems; q++)
@@ -74,37 +104,47 @@ __global__ __launch_bounds__(kScanThreads) void compact_count_kernel(Op op, cons
   }
   __syncthreads();
   if (tid == 0) {
-    u64 t = 0;
+    typename Op::V t{};
     for (int k = 0; k < kScanWavesPerBlock; k++) t += wsum[k];
     blk[blockIdx.x] = t;
   }
 }
 
-// Per-table constants the emit passes need for every flagged element, copied to LDS by the workgroup (a
-// look-up in the table descriptions in memory is a chain of dependent loads per element otherwise).
+// Per-table constants the passes need for every flagged element, copied to LDS by the workgroup (a look-up in the table
+// descriptions in memory is a chain of dependent loads per element otherwise).
 #ifndef TBE_FINALIZE_BLOCKS
 #define TBE_FINALIZE_BLOCKS 512  // a multiple of 8
 #endif
 constexpr int kLutTables = 512;  // models with more tables read the descriptions from memory
+struct KeyLut {
+  uint32_t key_base[kLutTables], sets[kLutTables], rows_per_set[kLutTables], set_base[kLutTables];
+};
 struct TableLut {
-  uint32_t key_base[kLutTables], sets[kLutTables], rows_per_set[kLutTables], set_base[kLutTables], row_bytes[kLutTables];
+  uint32_t key_base[kLutTables], sets[kLutTables], rows_per_set[kLutTables], row_bytes[kLutTables];
   char *host_w[kLutTables];
   char *lines2[kLutTables];
   int32_t slot2_base[kLutTables];
 };
 
+__device__ inline void fill_lut(KeyLut &l, const TableMeta *tm, int T) {
+  for (int t = threadIdx.x; t < T && t < kLutTables; t += blockDim.x) {
+    l.key_base[t] = tm[t].key_base; l.sets[t] = tm[t].sets; l.rows_per_set[t] = tm[t].rows_per_set;
+    l.set_base[t] = tm[t].set_base;
+  }
+}
 __device__ inline void fill_lut(TableLut &l, const TableMeta *tm, int T) {
   for (int t = threadIdx.x; t < T && t < kLutTables; t += blockDim.x) {
     l.key_base[t] = tm[t].key_base; l.sets[t] = tm[t].sets; l.rows_per_set[t] = tm[t].rows_per_set;
-    l.set_base[t] = tm[t].set_base; l.row_bytes[t] = tm[t].row_bytes; l.host_w[t] = tm[t].host_w;
+    l.row_bytes[t] = tm[t].row_bytes; l.host_w[t] = tm[t].host_w;
     l.lines2[t] = tm[t].lines2; l.slot2_base[t] = tm[t].slot2_base;
   }
 }
 
 template <class Op>
 __global__ __launch_bounds__(kScanThreads) void compact_emit_kernel(Op op, const int32_t *n_ptr, int n_fixed,
-                                                                    const u64 *blk, BatchCounters *cnt) {
-  __shared__ TableLut s_lut;
+                                                                    const typename Op::V *blk, BatchCounters *cnt) {
+  typedef typename Op::V V;
+  __shared__ typename Op::Lut s_lut;
   if (cnt->err) return;
   if (op.prepare(s_lut)) __syncthreads();
   constexpr int kScanItems = Op::kItems, kScanStep = kWave * kScanItems;
@@ -115,31 +155,35 @@ __global__ __launch_bounds__(kScanThreads) void compact_emit_kernel(Op op, const
   const int64_t base64 = (int64_t)w * chunk;
   const int base = (int)(base64 < n ? base64 : n), end = (int)(base64 + chunk < n ? base64 + chunk : n);
   // flags before this wavefront: the workgroups before its own, then the waves before it in its own
-  u64 carry = 0;
+  V carry{};
   for (int b = lane; b < (int)blockIdx.x; b += kWave) carry += blk[b];
   if (lane < wave) carry += blk[gridDim.x + blockIdx.x * kScanWavesPerBlock + lane];
   carry = wave_total(carry);
-  u64 total = 0;
+  V total{};
   if (blockIdx.x == 0 && wave == 0) {
     for (int b = lane; b < (int)gridDim.x; b += kWave) total += blk[b];
     total = wave_total(total);
   }
   for (int i0 = base + lane * kScanItems; i0 - lane * kScanItems < end; i0 += kScanStep) {
-    u64 f[kScanItems];
-    u64 tsum = 0;
+    V f[kScanItems] = {};
+    V tsum{};
 #pragma unroll
     for (int q = 0; q < kScanItems; q++) {
-      f[q] = (i0 + q < end) ? op.flag(i0 + q, n) : 0;
+      if (i0 + q < end) f[q] = op.flag(i0 + q, n);
       tsum += f[q];
     }
-    const u64 incl = wave_incl_scan(tsum, lane);
-    u64 pre = carry + incl - tsum;
+    const V incl = wave_incl_scan(tsum, lane);
+    V pre = carry;
+    pre += incl - tsum;
 #pragma unroll
     for (int q = 0; q < kScanItems; q++) {
       if (i0 + q < end) op.emit(i0 + q, n, pre, f[q]);
       pre += f[q];
     }
-    carry += __shfl(incl, 63, 64);
+    V last{};
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(V) / sizeof(u64)); i++) last.w[i] = __shfl(incl.w[i], 63, 64);
+    carry += last;
   }
   op.thread_done(cnt, lane);
   if (blockIdx.x == 0 && tid == 0) op.finish(cnt, n, total);
@@ -147,8 +191,9 @@ __global__ __launch_bounds__(kScanThreads) void compact_emit_kernel(Op op, const
 
 // returns the number of workgroups of the two kernels
 template <class Op>
-static int run_compaction(Op op, const int32_t *n_ptr, int n_fixed, int n_bound, u64 *blk, BatchCounters *cnt,
+static int run_compaction(Op op, const int32_t *n_ptr, int n_fixed, int n_bound, u64 *words, BatchCounters *cnt,
                            hipStream_t s) {
+  typename Op::V *blk = (typename Op::V *)words;
   int nb = (n_bound + kScanThreads * Op::kItems - 1) / (kScanThreads * Op::kItems);
   if (nb > kScanBlocks) nb = kScanBlocks;
   if (nb < 1) nb = 1;
@@ -157,9 +202,18 @@ static int run_compaction(Op op, const int32_t *n_ptr, int n_fixed, int n_bound,
   return nb;
 }
 
-// ---- pass 1 over the N sorted lookups: distinct rows, run starts, set ids ----
+// n / d for any 32-bit n, with m = ceil(2^64 / d) (0 stands for d = 1): exact, because m d exceeds 2^64 by less than d
+__device__ inline uint32_t div_by(uint32_t n, u64 m) { return m ? (uint32_t)__umul64hi((u64)n, m) : n; }
+__device__ inline u64 div_magic(uint32_t d) { return d > 1 ? ~0ull / d + 1ull : 0ull; }
+
+// ---- pass 1 over the N sorted lookups: distinct rows, run starts, and the first row of every touched set ----
+// Set heads are found here as well, from the keys of neighbouring rows (they were a count and emit pass of their own over
+// the set ids of the distinct rows, written here for it).  Keys ascend along a lane's elements, so every lane keeps the
+// constants of the table it is in and moves on when a key passes the table's last; the set number is a multiplication.
 struct DedupOp {
   static constexpr int kItems = 2;
+  typedef Counts<1> V;  // lo: distinct rows, hi: touched sets
+  typedef KeyLut Lut;
   const TableMeta *tm;
   int T;
   const uint32_t *key;      // sorted
@@ -173,297 +227,199 @@ struct DedupOp {
   int32_t *sorted_bag;
   uint32_t *uniq_key;
   int32_t *run_off;
-  uint32_t *uniq_sid;
   int32_t *uniq_tab;
-  mutable const TableLut *lut;  // null: the model has too many tables for it
-  __device__ bool prepare(TableLut &l) const {
+  uint2 *touched;
+  // the table this lane's keys are in
+  mutable int t;
+  mutable uint32_t base, last, set_base;  // keys base .. last
+  mutable u64 magic;                      // of rows_per_set; sets == 0: not used
+  mutable bool cached;
+  mutable const KeyLut *lut;  // null: the model has too many tables for it
+  __device__ bool prepare(KeyLut &l) const {
     lut = T <= kLutTables ? &l : nullptr;
     if (lut) fill_lut(l, tm, T);
+    t = -1;
+    last = 0;
     return lut != nullptr;
   }
-  __device__ u64 flag(int i, int) const { return (i == 0 || key[i] != key[i - 1]) ? 1ull : 0ull; }
-  __device__ void emit(int i, int, u64 pre, u64 f) const {
-    const uint32_t u = (uint32_t)(pre & 0xFFFFFFFFull) + (uint32_t)f - 1u;
+  __device__ bool prepare_count(KeyLut &l) const { return prepare(l); }
+  __device__ void enter_table(uint32_t k) const {  // last table with key_base <= k
+    int lo = t < 0 ? 0 : t, hi = T - 1;
+    uint32_t sets, rps;
+    if (lut) {
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (lut->key_base[mid] <= k) lo = mid; else hi = mid - 1;
+      }
+      base = lut->key_base[lo]; sets = lut->sets[lo]; rps = lut->rows_per_set[lo]; set_base = lut->set_base[lo];
+      last = lo + 1 < T ? lut->key_base[lo + 1] - 1u : 0xFFFFFFFFu;
+    } else {
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (tm[mid].key_base <= k) lo = mid; else hi = mid - 1;
+      }
+      base = tm[lo].key_base; sets = tm[lo].sets; rps = tm[lo].rows_per_set; set_base = tm[lo].set_base;
+      last = lo + 1 < T ? tm[lo + 1].key_base - 1u : 0xFFFFFFFFu;
+    }
+    t = lo;
+    cached = sets != 0;
+    magic = div_magic(rps);
+  }
+  __device__ V flag(int i, int) const {
+    V f{};
+    const uint32_t k = key[i], before = i ? key[i - 1] : 0u;
+    if (i == 0 || k != before) {
+      if (t < 0 || k > last) enter_table(k);
+      // rows of a table without a cache are one set
+      const bool head = i == 0 || before < base || (cached && div_by(k - base, magic) != div_by(before - base, magic));
+      f.w[0] = head ? (1ull | 1ull << 32) : 1ull;
+    }
+    return f;
+  }
+  __device__ void emit(int i, int, const V &pre, const V &f) const {
+    const uint32_t u = pre.lo(0) + f.lo(0) - 1u;
     uid_sorted[i] = u;
     const uint32_t p = pos[i];
     const int32_t bag = cnt->packed ? (int32_t)(p >> within_bits) : bag_of_pos[p];
     sorted_bag[i] = bag;
     if (sorted_within)
       sorted_within[i] = cnt->packed ? (int32_t)(p & ((1u << within_bits) - 1u)) : (int32_t)((int64_t)p - offsets[bag]);
-    if (f) {
+    if (f.lo(0)) {
       const uint32_t k = key[i];
+      if (k < base || k > last) enter_table_of(k);  // (the lane's next element may lie in the next table)
       uniq_key[u] = k;
       run_off[u] = i;
-      if (lut) {
-        int lo = 0, hi = T - 1;  // table that owns the key: last t with key_base[t] <= k
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (lut->key_base[mid] <= k) lo = mid; else hi = mid - 1;
-        }
-        uniq_tab[u] = lo;
-        uniq_sid[u] = lut->sets[lo] ? lut->set_base[lo] + (k - lut->key_base[lo]) / lut->rows_per_set[lo] : kNoSet;
-      } else {
-        const int t = find_table(tm, T, k);
-        const TableMeta &m = tm[t];
-        uniq_tab[u] = t;
-        uniq_sid[u] = m.sets ? m.set_base + (k - m.key_base) / m.rows_per_set : kNoSet;
-      }
+      uniq_tab[u] = t;
+      if (f.hi(0)) touched[pre.hi(0)] = make_uint2(cached ? set_base + div_by(k - base, magic) : kNoSet, u);
     }
   }
+  __device__ void enter_table_of(uint32_t k) const {
+    t = -1;
+    enter_table(k);
+  }
   __device__ void thread_done(BatchCounters *, int) const {}
-  __device__ void finish(BatchCounters *cnt, int n, u64 total) const {
-    cnt->n_uniq = (int32_t)(total & 0xFFFFFFFFull);
-    run_off[total & 0xFFFFFFFFull] = n;
+  __device__ void finish(BatchCounters *cnt, int n, const V &total) const {
+    cnt->n_uniq = (int32_t)total.lo(0);
+    cnt->n_touched = (int32_t)total.hi(0);
+    run_off[total.lo(0)] = n;
   }
 };
 
-// ---- pass 2 over the distinct rows: first row of every touched set; long runs ----
-struct SetHeadOp {
-  static constexpr int kItems = 4;
-  const uint32_t *uniq_sid;
-  const int32_t *run_off;
-  uint2 *touched;
-  __device__ bool prepare(TableLut &) const { return false; }
-  __device__ u64 flag(int u, int) const { return (u == 0 || uniq_sid[u] != uniq_sid[u - 1]) ? 1ull : 0ull; }
-  __device__ void emit(int u, int, u64 pre, u64 f) const {
-    if (f) touched[pre & 0xFFFFFFFFull] = make_uint2(uniq_sid[u], (uint32_t)u);
-  }
-  __device__ void thread_done(BatchCounters *, int) const {}
-  __device__ void finish(BatchCounters *cnt, int, u64 total) const { cnt->n_touched = (int32_t)(total & 0xFFFFFFFFull); }
-};
-
-// Work lists of the backward by run length (see kLongRun), in the order of the distinct rows (= table
-// order: the backward kernels give each XCD a contiguous part of a list).  A workgroup takes a contiguous
-// chunk of the distinct rows; the count kernel leaves the two counts of every workgroup in `wl`, the
-// emit kernel adds up the counts of the workgroups before it and writes its rows out in order.  It also
-// counts the heavy rows of every table.
-__device__ inline void worklist_chunk(int n, int &w0, int &w1) {
-  const int wave = threadIdx.x >> 6;
-  const int per_wave = ((n + gridDim.x * 4 - 1) / (gridDim.x * 4) + 63) / 64 * 64;
-  w0 = (blockIdx.x * 4 + wave) * per_wave;
-  w1 = min(n, w0 + per_wave);
-}
-
-__device__ inline int wave_sum(int v) {
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
-}
-
-// counts of the wavefront's chunk: (rows with 2..kLongRun lookups, heavy-list entries of the rows with more)
-__device__ inline void worklist_tally(const int32_t *__restrict__ run_off, int w0, int w1, int (&c)[2]) {
-  const int lane = threadIdx.x & 63;
-  c[0] = c[1] = 0;
-  for (int u0 = w0; u0 < w1; u0 += 64) {
-    const int u = u0 + lane;
-    const int len = u < w1 ? run_off[u + 1] - run_off[u] : 0;
-    c[0] += __popcll(__ballot(len >= 2 && len <= kLongRun));
-    if (__ballot(len > kLongRun)) c[1] += wave_sum(len > kLongRun ? heavy_parts(len) : 0);
-  }
-}
-
-__global__ __launch_bounds__(256) void worklist_count_kernel(const int32_t *__restrict__ run_off, int32_t *wl,
-                                                             const BatchCounters *cnt) {
-  __shared__ int s_cnt[4][2];
-  if (cnt->err) return;
-  int w0, w1, c[2];
-  worklist_chunk(cnt->n_uniq, w0, w1);
-  worklist_tally(run_off, w0, w1, c);
-  if ((threadIdx.x & 63) == 0)
-    for (int k = 0; k < 2; k++) s_cnt[threadIdx.x >> 6][k] = c[k];
-  __syncthreads();
-  if (threadIdx.x < 2) wl[blockIdx.x * 2 + threadIdx.x] = s_cnt[0][threadIdx.x] + s_cnt[1][threadIdx.x] + s_cnt[2][threadIdx.x] + s_cnt[3][threadIdx.x];
-}
-
-__global__ __launch_bounds__(256) void worklist_emit_kernel(const int32_t *__restrict__ run_off,
-                                                            const int32_t *__restrict__ uniq_tab,
-                                                            const int32_t *__restrict__ wl, int32_t *mid_idx,
-                                                            int32_t *heavy, int32_t *heavy_sub,
-                                                            int32_t *heavy_per_table, BatchCounters *cnt) {
-  __shared__ int s_cnt[4][2];
-  __shared__ int s_before[4][2];
-  __shared__ int s_base[4][2];
-  // Heavy-list entries per table: gathered in LDS for the tables this workgroup's rows belong to (its rows are
-  // consecutive, so these are few) and added to the totals once per table -- thousands of atomic additions
-  // from all over the chip to a few dozen addresses took ten times as long as the rest of this kernel.
-  constexpr int kLocalTables = 256;
-  __shared__ int s_tab[kLocalTables];
-  __shared__ int s_tab0;
-  if (cnt->err) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t lt_mask = (1ull << lane) - 1ull;
-  int w0, w1, c[2];
-  worklist_chunk(cnt->n_uniq, w0, w1);
-  s_tab[threadIdx.x] = 0;
-  if (threadIdx.x == 0) {
-    int b0, b1;
-    worklist_chunk(cnt->n_uniq, b0, b1);  // wave 0: the workgroup's first row
-    s_tab0 = b0 < cnt->n_uniq ? uniq_tab[b0] : 0;
-  }
-  worklist_tally(run_off, w0, w1, c);
-  int before[2] = {0, 0};  // rows of each kind in the workgroups before this one
-  for (int b = threadIdx.x; b < (int)blockIdx.x; b += 256)
-    for (int k = 0; k < 2; k++) before[k] += wl[b * 2 + k];
-  for (int k = 0; k < 2; k++)
-    for (int d = 32; d >= 1; d >>= 1) before[k] += __shfl_xor(before[k], d, 64);
-  if (lane == 0)
-    for (int k = 0; k < 2; k++) { s_cnt[wave][k] = c[k]; s_before[wave][k] = before[k]; }
-  __syncthreads();
-  if (threadIdx.x < 2) {
-    const int k = threadIdx.x;
-    int base = s_before[0][k] + s_before[1][k] + s_before[2][k] + s_before[3][k];
-    for (int w = 0; w < 4; w++) { s_base[w][k] = base; base += s_cnt[w][k]; }
-    if (blockIdx.x == gridDim.x - 1) {  // the last workgroup knows the totals
-      if (k == 0) cnt->n_mid = base;
-      if (k == 1) cnt->n_heavy = base;
-    }
-  }
-  __syncthreads();
-  int o_mid = s_base[wave][0], o_heavy = s_base[wave][1];
-  for (int u0 = w0; u0 < w1; u0 += 64) {
-    const int u = u0 + lane;
-    const int len = u < w1 ? run_off[u + 1] - run_off[u] : 0;
-    const bool is_mid = len >= 2 && len <= kLongRun;
-    const bool is_heavy = len > kLongRun;
-    const uint64_t bm = __ballot(is_mid);
-    if (is_mid) mid_idx[o_mid + __popcll(bm & lt_mask)] = u;
-    o_mid += __popcll(bm);
-    if (__ballot(is_heavy)) {  // uniform: the entries of the wavefront's heavy rows, in row order
-      const int parts = is_heavy ? heavy_parts(len) : 0;
-      int incl = parts;
-      for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-      }
-      const int at = o_heavy + incl - parts;
-      for (int q = 0; q < parts; q++) {
-        heavy[at + q] = u;
-        heavy_sub[at + q] = q | (parts << 16);
-      }
-      if (is_heavy) {
-        const int t = uniq_tab[u], rel = t - s_tab0;
-        if (rel >= 0 && rel < kLocalTables) atomicAdd(&s_tab[rel], parts); else atomicAdd(&heavy_per_table[t], parts);
-      }
-      o_heavy += __shfl(incl, 63, 64);
-    }
-  }
-  __syncthreads();
-  if (s_tab[threadIdx.x]) atomicAdd(&heavy_per_table[s_tab0 + threadIdx.x], s_tab[threadIdx.x]);
-}
-
-// The heavy list is in table order.  Cut every table's part into chunks of the rows one workgroup of the
-// tile kernel takes (heavy_chunk_rows of the table's lanes per row), and fix the number of bag ranges of
-// this batch.  One workgroup; tables are taken 256 at a time.
-__global__ __launch_bounds__(256) void heavy_group_kernel(const TableMeta *__restrict__ tm, int T,
-                                                          const int32_t *__restrict__ heavy_per_table,
-                                                          int32_t *first_of_table, uint4 *hchunks,
-                                                          long long slot_capacity, int target_items,
-                                                          BatchCounters *cnt) {
-  __shared__ int s_rows[4], s_chunks[4];
-  __shared__ int s_carry[2];
+// The plan of the tile kernel, from the heavy list (in table order; first_of_table[t] = position of table t's first entry,
+// first_of_table[T] = their number), in one launch:
+//   - every workgroup adds up the chunks of all tables (a chunk: the rows one workgroup of the tile kernel takes,
+//     heavy_chunk_rows of the table's lanes per row) and so knows the batch's number of bag ranges;
+//   - workgroup t < T writes table t's chunks and orders its entries by lookups per entry, descending, in classes of powers
+//     of two (entries of a class keep their order, so the result is a function of the batch alone): the tile kernel deals
+//     the entries round its lane groups in this order, so the groups that share a wavefront -- which runs as long as its
+//     busiest group -- get rows of like length;
+//   - the others find, for every entry and bag range, the first sorted position of the entry's row whose bag lies in the
+//     range (the row's lookups are sorted by bag), a thread per (entry, range).
+// (As three kernels, the chunks by one workgroup and the order by one wavefront per table: 10 M rows of one table, 32 k
+// bags, beside the transfer kernel: 4 + 35 + 21 us; here 17 us.)
+constexpr int kPlanThreads = 512;
+constexpr int kPlanStartBlocks = 128;
+__global__ __launch_bounds__(kPlanThreads) void heavy_plan_kernel(const TableMeta *__restrict__ tm, int T, int B,
+                                                                  const int32_t *__restrict__ first_of_table,
+                                                                  const int32_t *__restrict__ heavy,
+                                                                  const int32_t *__restrict__ heavy_sub,
+                                                                  const int32_t *__restrict__ uniq_tab,
+                                                                  const int32_t *__restrict__ run_off,
+                                                                  const int32_t *__restrict__ sorted_bag,
+                                                                  uint4 *hchunks, int32_t *hperm, int32_t *hstart,
+                                                                  long long slot_capacity, int target_items,
+                                                                  BatchCounters *cnt) {
+  constexpr int kWaves = kPlanThreads / kWave, kClasses = 32;
+  __shared__ int s_all[kWaves], s_before[kWaves];
+  __shared__ int s_base[kWaves][kClasses];
   if (cnt->err) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) s_carry[0] = s_carry[1] = 0;
+  const int n_heavy = cnt->n_heavy;
+  int all = 0, before = 0;  // chunks of all tables, and of those before this workgroup's
+  for (int t = tid; t < T; t += kPlanThreads) {
+    const int per = heavy_chunk_rows(tm[t].lanes, tm[t].dtype);
+    const int chunks = (first_of_table[t + 1] - first_of_table[t] + per - 1) / per;
+    all += chunks;
+    if (t < (int)blockIdx.x) before += chunks;
+  }
+  for (int d = 32; d >= 1; d >>= 1) { all += __shfl_xor(all, d); before += __shfl_xor(before, d); }
+  if (lane == 0) { s_all[wave] = all; s_before[wave] = before; }
+  if (tid < kClasses)
+    for (int w = 0; w < kWaves; w++) s_base[w][tid] = 0;
   __syncthreads();
-  for (int t0 = 0; t0 < T; t0 += 256) {
-    const int t = t0 + tid;
-    const int rows = t < T ? heavy_per_table[t] : 0;
-    const int per = t < T ? heavy_chunk_rows(tm[t].lanes, tm[t].dtype) : 1;
-    const int chunks = (rows + per - 1) / per;
-    int ir = rows, ic = chunks;  // inclusive scans over the workgroup
-    for (int d = 1; d < 64; d <<= 1) {
-      const int a = __shfl_up(ir, d), b = __shfl_up(ic, d);
-      if (lane >= d) { ir += a; ic += b; }
+  all = before = 0;
+  for (int w = 0; w < kWaves; w++) { all += s_all[w]; before += s_before[w]; }
+  const int R = heavy_ranges(all, n_heavy, slot_capacity, target_items);
+  if (blockIdx.x == 0 && tid == 0) {
+    cnt->n_hchunks = all;
+    cnt->h_ranges = R;
+  }
+  if ((int)blockIdx.x >= T) {
+    const int n = n_heavy * R;
+    for (int x = ((int)blockIdx.x - T) * kPlanThreads + tid; x < n; x += ((int)gridDim.x - T) * kPlanThreads) {
+      const int h = x / R, range = x % R;
+      const int u = heavy[h];
+      const int t = uniq_tab[u];
+      const long long first_bag = (long long)t * B + heavy_range_first(B, R, range);
+      int lo = run_off[u], hi = run_off[u + 1];
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (sorted_bag[mid] < first_bag) lo = mid + 1; else hi = mid;
+      }
+      hstart[x] = lo;
     }
-    if (lane == 63) { s_rows[wave] = ir; s_chunks[wave] = ic; }
-    __syncthreads();
-    int row0 = s_carry[0] + ir - rows, chunk0 = s_carry[1] + ic - chunks;
-    for (int w = 0; w < wave; w++) { row0 += s_rows[w]; chunk0 += s_chunks[w]; }
-    if (t < T) first_of_table[t] = row0;
-    for (int c = 0; c < chunks; c++)
-      hchunks[chunk0 + c] = make_uint4((uint32_t)t, (uint32_t)(row0 + c * per), (uint32_t)min(per, rows - c * per), 0u);
-    __syncthreads();
-    if (tid == 255) { s_carry[0] = row0 + rows; s_carry[1] = chunk0 + chunks; }
-    __syncthreads();
+    return;
   }
-  if (tid == 0) {
-    cnt->n_hchunks = s_carry[1];
-    cnt->h_ranges = heavy_ranges(s_carry[1], cnt->n_heavy, slot_capacity, target_items);
-  }
-}
-
-// Order of a table's heavy-list entries for the tile kernel: by lookups per entry, descending, in classes of
-// powers of two (entries of a class keep their order, so the result is a function of the batch alone).  The
-// tile kernel deals the entries round its lane groups in this order, so the groups that share a wavefront --
-// which runs as long as its busiest group -- get rows of like length.  One wavefront per table.
-__global__ __launch_bounds__(64) void heavy_order_kernel(const int32_t *__restrict__ heavy_per_table,
-                                                         const int32_t *__restrict__ first_of_table,
-                                                         const int32_t *__restrict__ heavy,
-                                                         const int32_t *__restrict__ heavy_sub,
-                                                         const int32_t *__restrict__ run_off, int32_t *hperm,
-                                                         const BatchCounters *cnt) {
-  __shared__ int s_base[32];
-  if (cnt->err) return;
-  const int t = blockIdx.x, lane = threadIdx.x;
-  const int n = heavy_per_table[t], first = first_of_table[t];
+  const int t = blockIdx.x;
+  const int first = first_of_table[t], n = first_of_table[t + 1] - first;
   if (n == 0) return;
-  const uint64_t lt_mask = (1ull << lane) - 1ull;
+  const int per = heavy_chunk_rows(tm[t].lanes, tm[t].dtype);
+  for (int c = tid; c * per < n; c += kPlanThreads)
+    hchunks[before + c] = make_uint4((uint32_t)t, (uint32_t)(first + c * per), (uint32_t)min(per, n - c * per), 0u);
   auto klass = [&](int h) {  // 31 - floor(log2(lookups per entry)): longer entries first
     const int u = heavy[h];
     const int len = (run_off[u + 1] - run_off[u]) / (heavy_sub[h] >> 16);
     return __clz(len < 1 ? 1 : len);
   };
-  if (lane < 32) s_base[lane] = 0;
+  // every wavefront takes a contiguous part of the entries: its counts per class, then the part's positions in order
+  const int part = ((n + kWaves - 1) / kWaves + 63) / 64 * 64;
+  const int p0 = min(n, wave * part), p1 = min(n, p0 + part);
+  for (int i = p0 + lane; i < p1; i += kWave) atomicAdd(&s_base[wave][klass(first + i) & (kClasses - 1)], 1);
   __syncthreads();
-  for (int i0 = 0; i0 < n; i0 += 64)
-    if (i0 + lane < n) atomicAdd(&s_base[klass(first + i0 + lane)], 1);
+  if (tid < kClasses) {  // counts to first positions: classes in order, inside a class the wavefronts in order
+    int mine = 0;
+    for (int w = 0; w < kWaves; w++) mine += s_base[w][tid];
+    int incl = mine;
+    for (int d = 1; d < kClasses; d <<= 1) {
+      const int o = __shfl_up(incl, d, 64);
+      if (tid >= d) incl += o;
+    }
+    int at = incl - mine;
+    for (int w = 0; w < kWaves; w++) { const int c = s_base[w][tid]; s_base[w][tid] = at; at += c; }
+  }
   __syncthreads();
-  if (lane == 0) {
+  const uint64_t lt_mask = (1ull << lane) - 1ull;
+  for (int i0 = p0; i0 < p1; i0 += kWave) {
+    const bool valid = i0 + lane < p1;
+    const int k = valid ? klass(first + i0 + lane) & (kClasses - 1) : 0;
+    uint64_t peers = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < 5; bit++) {
+      const bool on = (k >> bit) & 1;
+      const uint64_t bal = __ballot(on);
+      peers &= on ? bal : ~bal;
+    }
+    const int below = __popcll(peers & lt_mask);
     int at = 0;
-    for (int k = 0; k < 32; k++) { const int c = s_base[k]; s_base[k] = at; at += c; }
-  }
-  __syncthreads();
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    const bool valid = i0 + lane < n;
-    const int k = valid ? klass(first + i0 + lane) : -1;
-    uint64_t todo = __ballot(valid);
-    while (todo) {  // one class at a time, its entries in order
-      const int kk = __shfl(k, __ffsll((unsigned long long)todo) - 1, 64);
-      const uint64_t same = __ballot(k == kk);
-      if (k == kk) hperm[first + s_base[kk] + __popcll(same & lt_mask)] = first + i0 + lane;
-      __syncthreads();
-      if (lane == 0) s_base[kk] += __popcll(same);
-      __syncthreads();
-      todo &= ~same;
-    }
+    if (valid && below == 0) at = atomicAdd(&s_base[wave][k], __popcll(peers));
+    at = __shfl(at, valid ? __ffsll((unsigned long long)peers) - 1 : lane);
+    if (valid) hperm[first + at + below] = first + i0 + lane;
   }
 }
 
-// For every entry of the heavy list and bag range: the first sorted position of the entry's row whose bag
-// lies in the range (the row's lookups are sorted by bag).  One thread per (entry, range).
-__global__ __launch_bounds__(256) void heavy_starts_kernel(const TableMeta *__restrict__ tm, int B,
-                                                           const int32_t *__restrict__ heavy,
-                                                           const int32_t *__restrict__ uniq_tab,
-                                                           const int32_t *__restrict__ run_off,
-                                                           const int32_t *__restrict__ sorted_bag, int32_t *hstart,
-                                                           const BatchCounters *cnt) {
-  if (cnt->err) return;
-  const int R = cnt->h_ranges;
-  const int n = cnt->n_heavy * R;
-  for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
-    const int h = x / R, range = x % R;
-    const int u = heavy[h];
-    const int t = uniq_tab[u];
-    const long long first_bag = (long long)t * B + heavy_range_first(B, R, range);
-    int lo = run_off[u], hi = run_off[u + 1];
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (sorted_bag[mid] < first_bag) lo = mid + 1; else hi = mid;
-    }
-    hstart[x] = lo;
-  }
-}
-
-// ---- pass 3 over the distinct rows after the probe: insert and bypass lists, counters, and for every missed row
+// ---- pass 2 over the distinct rows after the probe: insert and bypass lists, the work lists of the backward by run
+// length (see kLongRun; in the order of the distinct rows, i.e. in table order: the backward kernels give each XCD a
+// contiguous part of a list), counters, and for every missed row
 // whether its backing-tier copy is stale and where its value is instead.  The map that says so is read and written here,
 // by the lane that handles the row; its entries are checked against the lists of the batches whose copies are on their
 // way instead of being taken out again.  (With a pass of its own over the missed rows for the look-up and up to three
@@ -471,6 +427,8 @@ __global__ __launch_bounds__(256) void heavy_starts_kernel(const TableMeta *__re
 // resident rows, four steps 2773 -> 2731 us.)
 struct StatusOp {
   static constexpr int kItems = 1;
+  typedef Counts<2> V;  // lo and hi of word 0: inserts, bypasses; of word 1: rows with 2..kLongRun lookups, heavy-list entries
+  struct Lut : TableLut {};
   const TableMeta *tm;
   int T;
   const uint8_t *status;
@@ -494,6 +452,7 @@ struct StatusOp {
   uint8_t *byp_taken;
   StaleRows stale;
   int32_t *loc_u;
+  int32_t *mid_idx, *heavy, *heavy_sub, *first_of_table;
   // second level (all null without one)
   const int32_t *src2, *dst2, *evict2;
   char **ins_dst, **l2v_src, **l2v_dst;
@@ -505,6 +464,7 @@ struct StatusOp {
   mutable unsigned int evs, late;
   mutable u64 hit_lookups;
   mutable const TableLut *lut;  // null: the model has too many tables for it
+  __device__ bool prepare_count(TableLut &) const { return false; }
   __device__ bool prepare(TableLut &l) const {
     lut = T <= kLutTables ? &l : nullptr;
     if (lut) fill_lut(l, tm, T);
@@ -569,15 +529,26 @@ struct StatusOp {
     stale.wb_skip[i] = 1;
     return code;
   }
-  __device__ u64 flag(int u, int) const {
+  __device__ V flag(int u, int) const {
+    V f{};
     const uint8_t s = status[u];
-    return s == ST_INSERT ? 1ull : s == ST_BYPASS ? (1ull << 32) : 0ull;
+    const int len = run_off[u + 1] - run_off[u];
+    f.w[0] = s == ST_INSERT ? 1ull : s == ST_BYPASS ? (1ull << 32) : 0ull;
+    f.w[1] = len > kLongRun ? (u64)heavy_parts(len) << 32 : len >= 2 ? 1ull : 0ull;
+    return f;
   }
-  __device__ void emit(int u, int, u64 pre, u64 f) const {
-    if (f == 1ull) {
-      const uint32_t i = (uint32_t)(pre & 0xFFFFFFFFull);
+  __device__ void emit(int u, int, const V &pre, const V &f) const {
+    const int t = uniq_tab[u];
+    for (int x = u ? uniq_tab[u - 1] + 1 : 0; x <= t; x++) first_of_table[x] = (int32_t)pre.hi(1);
+    if (f.lo(1)) mid_idx[pre.lo(1)] = u;
+    const int parts = (int)f.hi(1);
+    for (int q = 0; q < parts; q++) {  // a hot row is entered in several parts
+      heavy[pre.hi(1) + q] = u;
+      heavy_sub[pre.hi(1) + q] = q | (parts << 16);
+    }
+    if (f.lo(0)) {
+      const uint32_t i = pre.lo(0);
       const uint32_t key = uniq_key[u];
-      const int t = uniq_tab[u];
       const TabView m = view(t);
       const uint32_t row = m.row_of(key);
       const int32_t old = old_tag[u];
@@ -610,10 +581,9 @@ struct StatusOp {
         stale.where[vk] = kWhereParked | i;
       }
       vic_key[i] = vk;
-    } else if (f) {
-      const uint32_t j = (uint32_t)(pre >> 32);
+    } else if (f.hi(0)) {
+      const uint32_t j = pre.hi(0);
       const uint32_t key = uniq_key[u];
-      const int t = uniq_tab[u];
       const TabView m = view(t);
       byp_idx[j] = u;
       byp_tab[j] = t;
@@ -646,9 +616,12 @@ struct StatusOp {
       tally[3 * w + 2] = lt;
     }
   }
-  __device__ void finish(BatchCounters *cnt, int, u64 total) const {
-    cnt->n_ins = (int32_t)(total & 0xFFFFFFFFull);
-    cnt->n_byp = (int32_t)(total >> 32);
+  __device__ void finish(BatchCounters *cnt, int n, const V &total) const {
+    cnt->n_ins = (int32_t)total.lo(0);
+    cnt->n_byp = (int32_t)total.hi(0);
+    cnt->n_mid = (int32_t)total.lo(1);
+    cnt->n_heavy = (int32_t)total.hi(1);
+    for (int x = n > 0 ? uniq_tab[n - 1] + 1 : 0; x <= T; x++) first_of_table[x] = (int32_t)total.hi(1);
   }
 };
 
@@ -990,22 +963,9 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
   const int n = (int)b.n;
   if (n == 0) return hipSuccess;
   DedupOp d{tm, g.T, sorted_keys, sorted_pos, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
-            b.maxp ? b.sorted_within : nullptr, b.uid_sorted, b.sorted_bag, b.uniq_key, b.run_off, b.uniq_sid,
-            b.uniq_tab, nullptr};
+            b.maxp ? b.sorted_within : nullptr, b.uid_sorted, b.sorted_bag, b.uniq_key, b.run_off,
+            b.uniq_tab, b.touched, -1, 0u, 0u, 0u, 0ull, false, nullptr};
   run_compaction(d, nullptr, n, n, ss.blk, b.cnt, s);
-  SetHeadOp h{b.uniq_sid, b.run_off, b.touched};
-  run_compaction(h, &b.cnt->n_uniq, 0, n, ss.blk, b.cnt, s);
-  hipLaunchKernelGGL(worklist_count_kernel, dim3(kWorklistBlocks), dim3(256), 0, s, b.run_off, ss.wl, b.cnt);
-  hipLaunchKernelGGL(worklist_emit_kernel, dim3(kWorklistBlocks), dim3(256), 0, s, b.run_off, b.uniq_tab, ss.wl, b.mid_idx,
-                     b.heavy, b.heavy_sub, b.hg_count, b.cnt);
-  if (!b.maxp) {  // the tile kernel's chunks and range starts (max pooling takes heavy rows a workgroup each)
-    hipLaunchKernelGGL(heavy_group_kernel, dim3(1), dim3(256), 0, s, tm, g.T, b.hg_count, b.hg_count + g.T + 1, b.hchunks,
-                       (long long)g.partial_slots, g.heavy_target, b.cnt);
-    hipLaunchKernelGGL(heavy_order_kernel, dim3(g.T), dim3(64), 0, s, b.hg_count, b.hg_count + g.T + 1, b.heavy,
-                       b.heavy_sub, b.run_off, b.hperm, b.cnt);
-    hipLaunchKernelGGL(heavy_starts_kernel, dim3(256), dim3(256), 0, s, tm, b.batch, b.heavy, b.uniq_tab, b.run_off,
-                       b.sorted_bag, b.hstart, b.cnt);
-  }
   int64_t max_touched = (int64_t)g.total_sets + g.T;
   if (max_touched > n) max_touched = n;
   const int probe_blocks = (int)(max_touched < 65536 ? max_touched : 65536);
@@ -1016,11 +976,15 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
                      l2.on ? b.src2 : nullptr, l2.on ? b.dst2 : nullptr, l2.on ? b.evict2 : nullptr, b.cnt);
   StatusOp st{tm, g.T, b.status, b.run_off, b.old_tag, b.uniq_key, b.uniq_tab, b.ins_idx, b.ins_tab, b.ins_slot,
               b.ins_old, b.ins_key, b.vic_key, b.ins_src, b.ins_where,
-              b.byp_idx, b.byp_tab, b.byp_key, b.byp_src, b.byp_where, b.byp_taken, stale, b.loc_u,
+              b.byp_idx, b.byp_tab, b.byp_key, b.byp_src, b.byp_where, b.byp_taken, stale, b.loc_u, b.mid_idx, b.heavy, b.heavy_sub, b.hfirst,
               l2.on ? b.src2 : nullptr, l2.on ? b.dst2 : nullptr, l2.on ? b.evict2 : nullptr,
               l2.on ? b.ins_dst : nullptr, l2.on ? b.l2v_src : nullptr, l2.on ? b.l2v_dst : nullptr,
               l2.on ? b.l2v_key : nullptr, ss.tally, 0u, 0u, 0ull, nullptr};
   ss.tally_waves = run_compaction(st, &b.cnt->n_uniq, 0, n, ss.blk, b.cnt, s) * kScanWavesPerBlock;
+  if (!b.maxp)  // the tile kernel's chunks and range starts (max pooling takes heavy rows a workgroup each)
+    hipLaunchKernelGGL(heavy_plan_kernel, dim3(g.T + kPlanStartBlocks), dim3(kPlanThreads), 0, s, tm, g.T, b.batch, b.hfirst,
+                       b.heavy, b.heavy_sub, b.uniq_tab, b.run_off, b.sorted_bag, b.hchunks, b.hperm, b.hstart,
+                       (long long)g.partial_slots, g.heavy_target, b.cnt);
   hipLaunchKernelGGL(finalize_kernel, dim3(TBE_FINALIZE_BLOCKS), dim3(256), 0, s, n, sorted_pos, b.uid_sorted, b.loc_u, b.run_off,
                      b.loc, b.d_offsets, g.within_bits, b.cnt);
   return hipGetLastError();

@@ -128,7 +128,6 @@ struct BatchBuf {
   // per distinct row (ascending key)
   uint32_t *uniq_key;   // [N]
   int32_t *run_off;     // [N+1] first sorted position of each distinct row; run_off[U] = N
-  uint32_t *uniq_sid;   // [N] global set id or kNoSet
   int32_t *uniq_tab;    // [N] table of the distinct row
   int32_t *loc_u;       // [N] global slot id, or -2-j for the j-th bypassed row
   uint8_t *status;      // [N] Status
@@ -165,7 +164,7 @@ struct BatchBuf {
   int32_t *heavy_sub;   // [N/32 + 1] per entry: part number | parts << 16
   int32_t *harrive;     // [N/32 + 1] per entry list position of a row's first part: parts whose sums are in (0 between batches)
   uint4 *hchunks;       // [N/kLongRun + T + 1] (table, first position in `heavy`, count, -)
-  int32_t *hg_count;    // [2 * (T + 1)] heavy-list entries per table, then the position of each table's first entry
+  int32_t *hfirst;      // [T + 1] position of each table's first entry in the heavy list; hfirst[T] = number of entries
   int32_t *hperm;       // [N/32 + 1] the heavy list's positions, every table's entries ordered by lookups per entry
                         //     (descending, by power of two): lane groups that share a wavefront get rows of like length
   int32_t *hstart;      // [heavy rows * h_ranges] first sorted position of a heavy row in each bag range
@@ -185,8 +184,7 @@ struct SortScratch {
   uint32_t *keys[2];
   uint32_t *vals[2];
   uint32_t *hist;          // [256 * max sort blocks] block histograms, then [256] digit totals
-  unsigned long long *blk; // [scan blocks + 1] block sums of the compaction passes
-  int32_t *wl;             // [kWorklistBlocks * 4] per-workgroup counts of the backward work lists
+  unsigned long long *blk; // [2 * (5 * scan blocks + 1)] sums per workgroup and per wavefront of the compaction passes
   unsigned long long *tally;  // [3 * wavefronts of a compaction pass] (evictions, lookups that hit, late rows) per wave-
   int tally_waves;            //     front of the last batch's status pass, and how many wavefronts that pass had
 };
@@ -378,7 +376,6 @@ __host__ __device__ inline int heavy_tile_bags(int lanes, int dtype) {
 // so a table's rows and its slice of the output gradient are cached in one L2 instead of
 // in all eight.  Only the placement changes; any mapping gives the same results.
 constexpr int kXcds = 8;
-constexpr int kWorklistBlocks = 1024;  // workgroups that build the backward work lists
 
 // position of linear workgroup `id` of `n` when every workgroup is one unit of work
 __device__ inline int xcd_block_position(int id, int n) {

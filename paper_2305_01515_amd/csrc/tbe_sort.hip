@@ -66,8 +66,7 @@ __global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict
   }
 }
 
-__global__ void reset_counters_kernel(BatchCounters *cnt, int within_bits, int32_t *heavy_per_table, int T) {
-  for (int t = threadIdx.x; t < T; t += blockDim.x) heavy_per_table[t] = 0;
+__global__ void reset_counters_kernel(BatchCounters *cnt, int within_bits) {
   if (threadIdx.x == 0) {
     cnt->n_uniq = cnt->n_touched = cnt->n_ins = cnt->n_byp = cnt->n_heavy = cnt->err = 0;
     cnt->n_mid = cnt->n_hchunks = 0;
@@ -80,7 +79,7 @@ __global__ void reset_counters_kernel(BatchCounters *cnt, int within_bits, int32
 
 hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf &b, uint32_t *keys, uint32_t *vals,
                          hipStream_t s) {
-  hipLaunchKernelGGL(reset_counters_kernel, dim3(1), dim3(64), 0, s, b.cnt, g.within_bits, b.hg_count, g.T);
+  hipLaunchKernelGGL(reset_counters_kernel, dim3(1), dim3(64), 0, s, b.cnt, g.within_bits);
   const int64_t nb = (int64_t)g.T * b.batch;
   if (g.within_bits > 0 && nb > 0)
     hipLaunchKernelGGL(baglen_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, nb, b.d_offsets, g.within_bits,

@@ -1,0 +1,43 @@
+"""The passes of the prefetch stage at the sizes where they can go wrong: lookups and distinct rows around the widths of a
+wavefront's step, tables whose rows, sets or heavy rows begin and end anywhere in a step, tables without a cache side by
+side, tables without a lookup, more tables than the passes keep constants of in LDS, and rows entered several times."""
+import pytest
+
+from paper_2305_01515_amd import synth
+from parity_util import run_parity
+
+pytestmark = pytest.mark.gpu
+T = synth.TableCfg
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 1023, 1025, 2047, 2048, 2049])
+def test_lookups_around_the_steps(n):
+    """one bag of n lookups (n distinct rows at the most), then the same in two tables of unlike size"""
+    tabs = [T(3 * n + 1, 8, synth.FP32, None, "fixed", n, cache_slots=8 * (1 + n // 11)),
+            T(2 * n + 5, 4, synth.FP32, 1.2, "fixed", n, cache_slots=0)]
+    for t in (tabs[:1], tabs):
+        run_parity(synth.WorkloadCfg("edge", t, batch=1, ways=8, steps=3, seed=n, init_std=0.05, lr=0.05), steps=3, order="early")
+
+
+@pytest.mark.parametrize("overlap", [True, False])
+def test_tables_without_cache_or_lookups_in_between(overlap):
+    tabs = [T(40, 8, synth.FP32, None, "fixed", 0, cache_slots=8), T(50, 8, synth.FP32, 1.0, "poisson", 5, 0, 30),
+            T(1, 8, synth.FP32, None, "fixed", 3), T(33, 8, synth.FP32, None, "fixed", 2, cache_slots=4),
+            T(700, 16, synth.FP32, 0.8, "poisson", 9, 0, 60, cache_slots=4 * 13), T(5, 4, synth.FP32, None, "fixed", 0)]
+    run_parity(synth.WorkloadCfg("gaps", tabs, batch=37, ways=4, steps=5, seed=3, init_std=0.05, lr=0.05), steps=5, order="early",
+               overlap=overlap)
+
+
+def test_more_tables_than_constants_fit_in_lds():
+    tabs = [T(5 + t % 13, 4, synth.FP32, None, "fixed", t % 4, cache_slots=4 * (t % 3)) for t in range(523)]
+    run_parity(synth.WorkloadCfg("many", tabs, batch=3, ways=4, steps=3, seed=5, init_std=0.05, lr=0.05), steps=3, order="early")
+
+
+@pytest.mark.parametrize("batch", [200, 4500])
+@pytest.mark.parametrize("pooling", ["sum", "mean", "max"])
+def test_heavy_rows_of_many_lengths(batch, pooling):
+    """rows with 65 to tens of thousands of lookups, entered once or several times, over several tables"""
+    tabs = [T(40, 16, synth.FP32, 1.3, "fixed", 8, cache_slots=64), T(900, 32, synth.FP32, None, "fixed", 1, cache_slots=64),
+            T(7, 16, synth.FP32, 1.0, "poisson", 4, 0, 20), T(2500, 32, synth.FP32, 1.1, "poisson", 12, 0, 90, cache_slots=320)]
+    run_parity(synth.WorkloadCfg("heavy", tabs, batch=batch, ways=16, steps=2, seed=9, init_std=0.05, lr=0.05), steps=2, order="early",
+               pooling=pooling)
