@@ -187,43 +187,6 @@ int next_pow2(int v) { int p = 1; while (p < v) p <<= 1; return p; }
 
 __global__ void stream_pin_kernel() {}
 
-// Running totals of a batch's counters: tot (hits, evictions, lookups that hit), t64 ([0] distinct
-// rows, [1] inserts, [2] bypasses, [3] late rows) and, with a second level, l2 (its four counters).
-// Also completes the batch's own counters: evictions and lookups that hit from the per-wavefront sums of the
-// status pass (tens of thousands of them at the benchmark's batch: a single wavefront took 27 us to add them up),
-// hits as what is left of the distinct rows.  One workgroup of kTotalsThreads.
-constexpr int kTotalsThreads = 256;
-__global__ __launch_bounds__(kTotalsThreads) void add_totals_kernel(BatchCounters *c, BatchCounters *tot,
-                                                                    unsigned long long *t64, unsigned long long *l2,
-                                                                    const unsigned long long *tally, int tally_waves) {
-  if (c->err != 0) return;
-  __shared__ unsigned long long s_e[kTotalsThreads / 64], s_l[kTotalsThreads / 64], s_t[kTotalsThreads / 64];
-  unsigned long long e = 0, l = 0, late = 0;
-  for (int w = threadIdx.x; w < tally_waves; w += kTotalsThreads) { e += tally[3 * w]; l += tally[3 * w + 1]; late += tally[3 * w + 2]; }
-  for (int d = 32; d >= 1; d >>= 1) { e += __shfl_xor(e, d); l += __shfl_xor(l, d); late += __shfl_xor(late, d); }
-  if ((threadIdx.x & 63) == 0) { s_e[threadIdx.x >> 6] = e; s_l[threadIdx.x >> 6] = l; s_t[threadIdx.x >> 6] = late; }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  e = l = late = 0;
-  for (int w = 0; w < kTotalsThreads / 64; w++) { e += s_e[w]; l += s_l[w]; late += s_t[w]; }
-  c->hits = (unsigned long long)(c->n_uniq - c->n_ins - c->n_byp);
-  c->evictions = e;
-  c->hit_lookups = l;
-  tot->hits += c->hits;
-  tot->evictions += c->evictions;
-  tot->hit_lookups += c->hit_lookups;
-  t64[0] += (unsigned long long)c->n_uniq;
-  t64[1] += (unsigned long long)c->n_ins;
-  t64[2] += (unsigned long long)c->n_byp;
-  t64[3] += late;
-  if (l2) {
-    l2[0] += (unsigned long long)c->l2_hits;
-    l2[1] += (unsigned long long)c->l2_demotions;
-    l2[2] += (unsigned long long)c->l2_evictions;
-    l2[3] += (unsigned long long)c->l2_bypasses;
-  }
-}
-
 int alloc_batchbuf(tbe_ctx *h, BatchBuf &b, int64_t n) {
   const size_t N = (size_t)std::max<int64_t>(n, 1);
   HIP_TRY(h, h->mem.get(&b.loc, 4 * N));
@@ -362,14 +325,12 @@ int do_prefetch_deep(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offs
   }
   {
     StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
-    HIP_TRY(h, launch_keygen(h->d_tm, h->g, b, h->ss.keys[0], h->ss.vals[0], h->as));
+    HIP_TRY(h, launch_keygen(h->d_tm, h->g, b, h->ss, h->as));
     int res = 0;
     HIP_TRY(h, launch_sort(h->g, h->ss, n, &res, h->as));
     HIP_TRY(h, launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq,
-                                  h->policy == TBE_POLICY_LFU, h->l2, h->deep, stale_rows(h, b, bi), h->as));
-    hipLaunchKernelGGL(add_totals_kernel, dim3(1), dim3(kTotalsThreads), 0, h->as, b.cnt, h->d_total, h->d_bytes + 2,
-                       (unsigned long long *)nullptr, h->ss.tally, n > 0 ? h->ss.tally_waves : 0);
-    HIP_TRY(h, hipGetLastError());
+                                  h->policy == TBE_POLICY_LFU, h->l2, h->deep, stale_rows(h, b, bi),
+                                  Totals{h->d_total, h->d_bytes + 2, nullptr}, h->as));
   }
   if (h->ls != h->as) {
     HIP_TRY(h, hipEventRecord(h->ev_probed[bi], h->as));
@@ -428,14 +389,12 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
   }
   {
     StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
-    HIP_TRY(h, launch_keygen(h->d_tm, h->g, b, h->ss.keys[0], h->ss.vals[0], h->as));
+    HIP_TRY(h, launch_keygen(h->d_tm, h->g, b, h->ss, h->as));
     int res = 0;
     HIP_TRY(h, launch_sort(h->g, h->ss, n, &res, h->as));
     HIP_TRY(h, launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq,
-                                  h->policy == TBE_POLICY_LFU, h->l2, 0, stale_rows(h, b, bi), h->as));
-    hipLaunchKernelGGL(add_totals_kernel, dim3(1), dim3(kTotalsThreads), 0, h->as, b.cnt, h->d_total, h->d_bytes + 2,
-                       h->l2.on ? h->d_l2tot : nullptr, h->ss.tally, n > 0 ? h->ss.tally_waves : 0);
-    HIP_TRY(h, hipGetLastError());
+                                  h->policy == TBE_POLICY_LFU, h->l2, 0, stale_rows(h, b, bi),
+                                  Totals{h->d_total, h->d_bytes + 2, h->l2.on ? h->d_l2tot : nullptr}, h->as));
   }
   if (h->ls != h->as) {
     HIP_TRY(h, hipEventRecord(h->ev_probed[bi], h->as));
@@ -705,6 +664,8 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   CREATE_TRY(h->mem.get(&h->ss.hist, 4 * (512 * 1024 + 512)));  // sort: counts per digit value (<= 512) and block (<= 1024), digit totals
   CREATE_TRY(h->mem.get(&h->ss.blk, 16 * (8192 + 1)));
   CREATE_TRY(h->mem.get(&h->ss.tally, 8 * 3 * 8192));
+  CREATE_TRY(h->mem.get(&h->ss.too_long, 16));
+  CREATE_TRY(hipMemset(h->ss.too_long, 0, 16));
   CREATE_TRY(h->mem.get(&h->d_total, sizeof(BatchCounters)));
   CREATE_TRY(hipMemset(h->d_total, 0, sizeof(BatchCounters)));
   CREATE_TRY(h->mem.get(&h->d_bytes, 8 * 8));

@@ -924,23 +924,64 @@ __global__ __launch_bounds__(kWave) void probe_kernel(const TableMeta *__restric
 // where the stores meet and leave as full lines; the streamed inputs are read around the cache.  (Workgroups
 // dealt round robin over the XCDs wrote every line from eight L2s, in eight partial pieces: 260 MB of write
 // traffic for 31 MB of words.)
-__global__ __launch_bounds__(256) void finalize_kernel(int n, const uint32_t *__restrict__ pos,
-                                                       const uint32_t *__restrict__ uid_sorted,
-                                                       const int32_t *__restrict__ loc_u,
-                                                       const int32_t *__restrict__ run_off, uint32_t *__restrict__ loc,
-                                                       const int64_t *__restrict__ offsets, int within_bits,
-                                                       const BatchCounters *cnt) {
+//
+// One workgroup more (the last) ends the stage: it completes the batch's counters -- evictions, lookups that hit and late
+// rows from the per-wavefront sums of the status pass, hits as what is left of the distinct rows -- and adds them to the
+// running totals.
+constexpr int kFinalThreads = 256;
+__device__ inline void add_totals(BatchCounters *c, const Totals &t, const u64 *__restrict__ tally, int tally_waves) {
+  __shared__ u64 s_e[kFinalThreads / 64], s_l[kFinalThreads / 64], s_t[kFinalThreads / 64];
+  u64 e = 0, l = 0, late = 0;
+  for (int w = threadIdx.x; w < tally_waves; w += kFinalThreads) { e += tally[3 * w]; l += tally[3 * w + 1]; late += tally[3 * w + 2]; }
+  for (int d = 32; d >= 1; d >>= 1) { e += __shfl_xor(e, d); l += __shfl_xor(l, d); late += __shfl_xor(late, d); }
+  if ((threadIdx.x & 63) == 0) { s_e[threadIdx.x >> 6] = e; s_l[threadIdx.x >> 6] = l; s_t[threadIdx.x >> 6] = late; }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  e = l = late = 0;
+  for (int w = 0; w < kFinalThreads / 64; w++) { e += s_e[w]; l += s_l[w]; late += s_t[w]; }
+  c->hits = (u64)(c->n_uniq - c->n_ins - c->n_byp);
+  c->evictions = e;
+  c->hit_lookups = l;
+  t.sum->hits += c->hits;
+  t.sum->evictions += e;
+  t.sum->hit_lookups += l;
+  t.n[0] += (u64)c->n_uniq;
+  t.n[1] += (u64)c->n_ins;
+  t.n[2] += (u64)c->n_byp;
+  t.n[3] += late;
+  if (t.l2) {
+    t.l2[0] += (u64)c->l2_hits;
+    t.l2[1] += (u64)c->l2_demotions;
+    t.l2[2] += (u64)c->l2_evictions;
+    t.l2[3] += (u64)c->l2_bypasses;
+  }
+}
+
+__global__ __launch_bounds__(kFinalThreads) void finalize_kernel(int n, const uint32_t *__restrict__ pos,
+                                                                 const uint32_t *__restrict__ uid_sorted,
+                                                                 const int32_t *__restrict__ loc_u,
+                                                                 const int32_t *__restrict__ run_off,
+                                                                 uint32_t *__restrict__ loc,
+                                                                 const int64_t *__restrict__ offsets, int within_bits,
+                                                                 Totals totals, const u64 *__restrict__ tally,
+                                                                 int tally_waves, uint32_t *too_long, BatchCounters *cnt) {
+  const bool last = blockIdx.x + 1 == gridDim.x;
+  if (last && threadIdx.x == 0) *too_long = 0u;  // as the next batch expects it, whatever became of this one
   if (cnt->err) return;
+  if (last) {
+    add_totals(cnt, totals, tally, tally_waves);
+    return;
+  }
   const bool packed = cnt->packed != 0;
   const uint32_t within_mask = (1u << within_bits) - 1u;
   constexpr int K = 4;  // lookups per thread and pass, a workgroup's width apart: their loads are in flight together
   int first, end, step;
-  xcd_span(n, 256 * K, first, end, step);
+  xcd_span_of(blockIdx.x, gridDim.x - 1, n, kFinalThreads * K, first, end, step);
   for (int i0 = first + threadIdx.x; i0 < end; i0 += step) {
     uint32_t u[K], p[K], w[K], at[K];
 #pragma unroll
     for (int q = 0; q < K; q++) {
-      const int i = i0 + q * 256;
+      const int i = i0 + q * kFinalThreads;
       u[q] = i < end ? __builtin_nontemporal_load(uid_sorted + i) : 0u;
       p[q] = i < end ? __builtin_nontemporal_load(pos + i) : 0u;  // the lookup's position: as is, or (bag, position inside it)
     }
@@ -953,15 +994,20 @@ __global__ __launch_bounds__(256) void finalize_kernel(int n, const uint32_t *__
     }
 #pragma unroll
     for (int q = 0; q < K; q++)
-      if (i0 + q * 256 < end) loc[at[q]] = w[q];
+      if (i0 + q * kFinalThreads < end) loc[at[q]] = w[q];
   }
 }
 
 hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const BatchBuf &b, SortScratch &ss,
                               const uint32_t *sorted_keys, const uint32_t *sorted_pos, int32_t *tags, int32_t *ts,
-                              int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale, hipStream_t s) {
+                              int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale,
+                              const Totals &totals, hipStream_t s) {
   const int n = (int)b.n;
-  if (n == 0) return hipSuccess;
+  if (n == 0) {  // nothing but the end of the stage
+    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kFinalThreads), 0, s, 0, sorted_pos, b.uid_sorted, b.loc_u, b.run_off,
+                       b.loc, b.d_offsets, g.within_bits, totals, ss.tally, 0, ss.too_long, b.cnt);
+    return hipGetLastError();
+  }
   DedupOp d{tm, g.T, sorted_keys, sorted_pos, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
             b.maxp ? b.sorted_within : nullptr, b.uid_sorted, b.sorted_bag, b.uniq_key, b.run_off,
             b.uniq_tab, b.touched, -1, 0u, 0u, 0u, 0ull, false, nullptr};
@@ -985,8 +1031,11 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
     hipLaunchKernelGGL(heavy_plan_kernel, dim3(g.T + kPlanStartBlocks), dim3(kPlanThreads), 0, s, tm, g.T, b.batch, b.hfirst,
                        b.heavy, b.heavy_sub, b.uniq_tab, b.run_off, b.sorted_bag, b.hchunks, b.hperm, b.hstart,
                        (long long)g.partial_slots, g.heavy_target, b.cnt);
-  hipLaunchKernelGGL(finalize_kernel, dim3(TBE_FINALIZE_BLOCKS), dim3(256), 0, s, n, sorted_pos, b.uid_sorted, b.loc_u, b.run_off,
-                     b.loc, b.d_offsets, g.within_bits, b.cnt);
+  // a multiple of the XCDs, no more than have a pass to do, and the one that ends the stage
+  int final_blocks = (n + 4 * kFinalThreads - 1) / (4 * kFinalThreads);
+  final_blocks = final_blocks > TBE_FINALIZE_BLOCKS ? TBE_FINALIZE_BLOCKS : (final_blocks + kXcds - 1) / kXcds * kXcds;
+  hipLaunchKernelGGL(finalize_kernel, dim3(final_blocks + 1), dim3(kFinalThreads), 0, s, n, sorted_pos, b.uid_sorted, b.loc_u,
+                     b.run_off, b.loc, b.d_offsets, g.within_bits, totals, ss.tally, ss.tally_waves, ss.too_long, b.cnt);
   return hipGetLastError();
 }
 

@@ -187,6 +187,7 @@ struct SortScratch {
   unsigned long long *blk; // [2 * (5 * scan blocks + 1)] sums per workgroup and per wavefront of the compaction passes
   unsigned long long *tally;  // [3 * wavefronts of a compaction pass] (evictions, lookups that hit, late rows) per wave-
   int tally_waves;            //     front of the last batch's status pass, and how many wavefronts that pass had
+  uint32_t *too_long;         // a bag of the batch does not fit the packed payload (0 between batches)
 };
 
 // Staging between the cache and the host link (one instance; the prefetch stage is serial).
@@ -201,7 +202,8 @@ struct Staging {
   uint32_t *wb_rb;     // [max_inserts] row bytes
   uint8_t *wb_skip[2]; // [max_inserts] by parity of the batch that parked the victim: 1 = the next batch
                        // takes the row straight back (from `out`), so it need not travel to the host
-  int32_t *wb_n;       // [0] number of parked victim slots, [1] which `out` holds them (device)
+  int32_t *wb_n;       // [0] number of parked victim slots, [1] which `out` holds them (device), [2] workgroups of the
+                       // transfer kernel that are done (0 between transfers)
   uint32_t *where;     // [key span] per sort key: where the row's value was the last time its backing-tier copy went
                        // stale (kWhereOverflow | j: bypassed row j of that batch, kWhereParked | i: its i-th victim; 0:
                        // never).  Entries are not taken out: one counts while the list it points into still belongs to
@@ -255,6 +257,13 @@ struct StaleRows {
   uint32_t live;                   //   that has not trained yet
 };
 
+// Running totals of the batches' counters: sum (hits, evictions, lookups that hit), n ([0] distinct rows, [1] inserts,
+// [2] bypasses, [3] late rows) and, with a second level, l2 (its four counters).
+struct Totals {
+  BatchCounters *sum;
+  unsigned long long *n, *l2;
+};
+
 struct Geometry {
   int32_t T, ways;
   int32_t sum_dim;
@@ -283,13 +292,14 @@ struct ClassInfo {
 
 // ---- launchers (each enqueues on `s` and returns the HIP status of the launch) ----
 
-hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf &b, uint32_t *keys, uint32_t *vals,
-                         hipStream_t s);
+// counters of the batch to zero, sort keys and payloads of its lookups into ss.keys[0] / ss.vals[0]
+hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf &b, const SortScratch &ss, hipStream_t s);
 hipError_t launch_sort(const Geometry &g, SortScratch &ss, int64_t n, int *result_buf, hipStream_t s);
 // lock: batches before the current one whose ways are locked like the current batch's own (0 in the one-deep pipeline)
 hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const BatchBuf &b, SortScratch &ss,
                               const uint32_t *sorted_keys, const uint32_t *sorted_pos, int32_t *tags, int32_t *ts,
-                              int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale, hipStream_t s);
+                              int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale,
+                              const Totals &totals, hipStream_t s);
 // write back the staged victims and (b != null) fetch ahead the rows b's batch inserts
 // Deferred initialisation on read (Section 5.4.2): a row of the backing tier has no value until it is
 // first fetched; the fetch then makes it up instead of reading it.

@@ -266,10 +266,9 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
     if (in_b) atomicAdd(bytes_h2d, in_b);
     if (out_b) atomicAdd(bytes_d2h, out_b);
   }
-}
-
-__global__ void clear_wb_kernel(int32_t *wb_n) {
-  if (threadIdx.x == 0) wb_n[0] = 0;
+  // The last workgroup through empties the list of parked victims (every other one has read its length long before).
+  __syncthreads();
+  if (threadIdx.x == 0 && atomicInc((unsigned int *)&st.wb_n[2], gridDim.x - 1) == gridDim.x - 1) st.wb_n[0] = 0;
 }
 
 hipError_t launch_transfer(const BatchBuf *b, const Staging &st, const Level2 &l2, const DeferredInit &di,
@@ -295,7 +294,6 @@ hipError_t launch_transfer(const BatchBuf *b, const Staging &st, const Level2 &l
                      l2.on ? l2.wb2_dst : nullptr, l2.out2[0], l2.out2[1], k, b ? di.tm : nullptr, di.seed, di.std,
                      b ? b->ins_key : nullptr, b ? b->byp_key : nullptr, bytes_h2d, bytes_d2h, l2.lines_lo, l2.lines_hi,
                      th.pauses));
-  hipLaunchKernelGGL(clear_wb_kernel, dim3(1), dim3(64), 0, s, st.wb_n);
   return hipGetLastError();
 }
 

@@ -10,12 +10,21 @@ namespace tbe {
 // --------------------------------------------------------------------------------------
 constexpr int kKeygenLanes = 8;
 
-// Does every bag fit the packed payload?  (cnt->packed starts at 1.)
-__global__ __launch_bounds__(256) void baglen_kernel(int64_t nb, const int64_t *__restrict__ offsets, int within_bits,
-                                                     BatchCounters *cnt) {
+// First kernel of the stage: the batch's counters start at zero (workgroup 0), and every bag is looked at: does it fit the
+// packed payload?  The answer is gathered in *too_long, which the stage's last kernel leaves at zero for the next batch, so
+// that no launch has to come before this one.
+__global__ __launch_bounds__(256) void begin_kernel(int64_t nb, const int64_t *__restrict__ offsets, int within_bits,
+                                                    uint32_t *too_long, BatchCounters *cnt) {
   const int64_t bag = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool too_long = bag < nb && offsets[bag + 1] - offsets[bag] > (1ll << within_bits);
-  if (__ballot(too_long) && (threadIdx.x & 63) == 0) atomicMin(&cnt->packed, 0);
+  if (bag == 0) {
+    cnt->n_uniq = cnt->n_touched = cnt->n_ins = cnt->n_byp = cnt->n_heavy = cnt->err = 0;
+    cnt->n_mid = cnt->n_hchunks = 0;
+    cnt->h_ranges = 1;
+    cnt->hits = cnt->evictions = cnt->hit_lookups = 0;
+    cnt->l2_hits = cnt->l2_demotions = cnt->l2_evictions = cnt->l2_bypasses = 0;
+  }
+  const bool is = within_bits > 0 && bag < nb && offsets[bag + 1] - offsets[bag] > (1ll << within_bits);
+  if (__ballot(is) && (threadIdx.x & 63) == 0) atomicOr(too_long, 1u);
 }
 
 __global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict__ tm, int T, int B, int64_t N,
@@ -23,8 +32,10 @@ __global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict
                                                      const int64_t *__restrict__ offsets, uint32_t *__restrict__ keys,
                                                      uint32_t *__restrict__ vals, int32_t *__restrict__ bag_of_pos,
                                                      float *__restrict__ inv_len, int within_bits,
-                                                     BatchCounters *cnt) {
+                                                     const uint32_t *__restrict__ too_long, BatchCounters *cnt) {
   const int64_t nb = (int64_t)T * B;
+  const bool packed = within_bits > 0 && *too_long == 0u;
+  if (blockIdx.x == 0 && threadIdx.x == 0) cnt->packed = packed ? 1 : 0;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t bag = gid / kKeygenLanes;
   const int sub = (int)(gid % kKeygenLanes);
@@ -41,7 +52,6 @@ __global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict
   if (inv_len && sub == 0) inv_len[bag] = hi > lo ? 1.0f / (float)(hi - lo) : 0.0f;
   const int t = (int)(bag / B);
   const TableMeta m = tm[t];
-  const bool packed = cnt->packed != 0;
   // two indices per lane and step, both requested before either is used (the loop is bound by the latency
   // of these reads: a bag has a few dozen lookups, so a lane makes only a few steps)
   auto emit = [&](int64_t j, int64_t r) {
@@ -66,29 +76,16 @@ __global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict
   }
 }
 
-__global__ void reset_counters_kernel(BatchCounters *cnt, int within_bits) {
-  if (threadIdx.x == 0) {
-    cnt->n_uniq = cnt->n_touched = cnt->n_ins = cnt->n_byp = cnt->n_heavy = cnt->err = 0;
-    cnt->n_mid = cnt->n_hchunks = 0;
-    cnt->h_ranges = 1;
-    cnt->hits = cnt->evictions = cnt->hit_lookups = 0;
-    cnt->l2_hits = cnt->l2_demotions = cnt->l2_evictions = cnt->l2_bypasses = 0;
-    cnt->packed = within_bits > 0 ? 1 : 0;
-  }
-}
-
-hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf &b, uint32_t *keys, uint32_t *vals,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(reset_counters_kernel, dim3(1), dim3(64), 0, s, b.cnt, g.within_bits);
+hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf &b, const SortScratch &ss, hipStream_t s) {
   const int64_t nb = (int64_t)g.T * b.batch;
-  if (g.within_bits > 0 && nb > 0)
-    hipLaunchKernelGGL(baglen_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, nb, b.d_offsets, g.within_bits,
-                       b.cnt);
+  hipLaunchKernelGGL(begin_kernel, dim3((unsigned)(nb > 256 ? (nb + 255) / 256 : 1)), dim3(256), 0, s, nb, b.d_offsets,
+                     g.within_bits, ss.too_long, b.cnt);
   const int64_t threads = (int64_t)g.T * b.batch * kKeygenLanes;
   if (threads > 0) {
     const int64_t blocks = (threads + 255) / 256;
     hipLaunchKernelGGL(keygen_kernel, dim3((unsigned)blocks), dim3(256), 0, s, tm, g.T, b.batch, b.n, b.d_indices,
-                       b.d_offsets, keys, vals, b.bag_of_pos, b.mean ? b.inv_len : nullptr, g.within_bits, b.cnt);
+                       b.d_offsets, ss.keys[0], ss.vals[0], b.bag_of_pos, b.mean ? b.inv_len : nullptr, g.within_bits,
+                       ss.too_long, b.cnt);
   }
   return hipGetLastError();
 }
