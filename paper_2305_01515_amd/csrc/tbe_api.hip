@@ -48,10 +48,27 @@ hipError_t static_scratch_of_current_device(void **out, int *device) {
 
 struct DevAlloc {  // everything hipMalloc'ed, freed together
   std::vector<void *> ptrs;
+  char *pool = nullptr;  // the rest of the block that small pieces are cut from (a small handle is sixty of them, and
+  size_t left = 0;       // an allocation of its own for each was most of the time of tbe_create)
   template <class P>
   hipError_t get(P **p, size_t bytes) {
+    constexpr size_t kBlock = 1 << 20, kSmall = 1 << 16;
     void *v = nullptr;
-    hipError_t e = hipMalloc(&v, bytes ? bytes : 16);
+    bytes = bytes ? (bytes + 255) & ~(size_t)255 : 256;
+    if (bytes <= kSmall) {
+      if (left < bytes) {
+        hipError_t e = hipMalloc(&v, kBlock);
+        if (e != hipSuccess) { *p = nullptr; return e; }
+        ptrs.push_back(v);
+        pool = (char *)v;
+        left = kBlock;
+      }
+      *p = (P *)pool;
+      pool += bytes;
+      left -= bytes;
+      return hipSuccess;
+    }
+    hipError_t e = hipMalloc(&v, bytes);
     if (e == hipSuccess) ptrs.push_back(v);
     *p = (P *)v;
     return e;
@@ -59,6 +76,8 @@ struct DevAlloc {  // everything hipMalloc'ed, freed together
   void release() {
     for (void *p : ptrs) (void)hipFree(p);
     ptrs.clear();
+    pool = nullptr;
+    left = 0;
   }
 };
 
@@ -327,7 +346,7 @@ int do_prefetch_deep(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offs
     StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
     HIP_TRY(h, launch_keygen(h->d_tm, h->g, b, h->ss, h->as));
     int res = 0;
-    HIP_TRY(h, launch_sort(h->g, h->ss, n, &res, h->as));
+    HIP_TRY(h, launch_sort(h->g, b, h->ss, &res, h->as));
     HIP_TRY(h, launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq,
                                   h->policy == TBE_POLICY_LFU, h->l2, h->deep, stale_rows(h, b, bi),
                                   Totals{h->d_total, h->d_bytes + 2, nullptr}, h->as));
@@ -391,7 +410,7 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
     StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
     HIP_TRY(h, launch_keygen(h->d_tm, h->g, b, h->ss, h->as));
     int res = 0;
-    HIP_TRY(h, launch_sort(h->g, h->ss, n, &res, h->as));
+    HIP_TRY(h, launch_sort(h->g, b, h->ss, &res, h->as));
     HIP_TRY(h, launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq,
                                   h->policy == TBE_POLICY_LFU, h->l2, 0, stale_rows(h, b, bi),
                                   Totals{h->d_total, h->d_bytes + 2, h->l2.on ? h->d_l2tot : nullptr}, h->as));
@@ -666,6 +685,9 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   CREATE_TRY(h->mem.get(&h->ss.tally, 8 * 3 * 8192));
   CREATE_TRY(h->mem.get(&h->ss.too_long, 16));
   CREATE_TRY(hipMemset(h->ss.too_long, 0, 16));
+  h->ss.ticket = h->ss.too_long + 1;
+  CREATE_TRY(h->mem.get(&h->ss.said, 4 * 256 * kMaxSortPasses * (size_t)(1 + kSmallSortBlocks)));
+  CREATE_TRY(h->mem.get(&h->ss.said_counts, 8 * 4 * (size_t)kSmallScanBlocks));
   CREATE_TRY(h->mem.get(&h->d_total, sizeof(BatchCounters)));
   CREATE_TRY(hipMemset(h->d_total, 0, sizeof(BatchCounters)));
   CREATE_TRY(h->mem.get(&h->d_bytes, 8 * 8));

@@ -17,6 +17,7 @@ namespace tbe {
 // --------------------------------------------------------------------------------------
 constexpr int kScanThreads = 256;
 constexpr int kScanWavesPerBlock = kScanThreads / kWave;
+static_assert(kSmallScanBlocks == kScanThreads, "a thread of the small batches' passes hears one workgroup");
 // Consecutive elements per lane and step: Op::kItems.  With several, the lanes of one store instruction write
 // compacted entries that lie apart (the entries of a lane's other elements fall between them), and the emit pass
 // that flags a third of its elements and writes seven arrays wrote 121 MB for 32 MB of lists (49 us; 38 MB and
@@ -140,6 +141,34 @@ __device__ inline void fill_lut(TableLut &l, const TableMeta *tm, int T) {
   }
 }
 
+// a wavefront's chunk [base, end), with `carry` flags before it
+template <class Op>
+__device__ inline void write_chunk(const Op &op, int base, int end, int n, int lane, typename Op::V carry) {
+  typedef typename Op::V V;
+  constexpr int kScanItems = Op::kItems, kScanStep = kWave * kScanItems;
+  for (int i0 = base + lane * kScanItems; i0 - lane * kScanItems < end; i0 += kScanStep) {
+    V f[kScanItems] = {};
+    V tsum{};
+#pragma unroll
+    for (int q = 0; q < kScanItems; q++) {
+      if (i0 + q < end) f[q] = op.flag(i0 + q, n);
+      tsum += f[q];
+    }
+    const V incl = wave_incl_scan(tsum, lane);
+    V pre = carry;
+    pre += incl - tsum;
+#pragma unroll
+    for (int q = 0; q < kScanItems; q++) {
+      if (i0 + q < end) op.emit(i0 + q, n, pre, f[q]);
+      pre += f[q];
+    }
+    V last{};
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(V) / sizeof(u64)); i++) last.w[i] = __shfl(incl.w[i], 63, 64);
+    carry += last;
+  }
+}
+
 template <class Op>
 __global__ __launch_bounds__(kScanThreads) void compact_emit_kernel(Op op, const int32_t *n_ptr, int n_fixed,
                                                                     const typename Op::V *blk, BatchCounters *cnt) {
@@ -164,35 +193,79 @@ __global__ __launch_bounds__(kScanThreads) void compact_emit_kernel(Op op, const
     for (int b = lane; b < (int)gridDim.x; b += kWave) total += blk[b];
     total = wave_total(total);
   }
-  for (int i0 = base + lane * kScanItems; i0 - lane * kScanItems < end; i0 += kScanStep) {
-    V f[kScanItems] = {};
-    V tsum{};
-#pragma unroll
-    for (int q = 0; q < kScanItems; q++) {
-      if (i0 + q < end) f[q] = op.flag(i0 + q, n);
-      tsum += f[q];
-    }
-    const V incl = wave_incl_scan(tsum, lane);
-    V pre = carry;
-    pre += incl - tsum;
-#pragma unroll
-    for (int q = 0; q < kScanItems; q++) {
-      if (i0 + q < end) op.emit(i0 + q, n, pre, f[q]);
-      pre += f[q];
-    }
-    V last{};
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(V) / sizeof(u64)); i++) last.w[i] = __shfl(incl.w[i], 63, 64);
-    carry += last;
-  }
-  op.thread_done(cnt, lane);
+  write_chunk(op, base, end, n, lane, carry);
+  op.thread_done(cnt, lane, blockIdx.x);
   if (blockIdx.x == 0 && tid == 0) op.finish(cnt, n, total);
 }
 
-// returns the number of workgroups of the two kernels
+// Small batches: the same in one kernel.  A workgroup counts its chunk, says its sums, adds up those of the workgroups
+// before it and writes; the last one knows the totals.
 template <class Op>
-static int run_compaction(Op op, const int32_t *n_ptr, int n_fixed, int n_bound, u64 *words, BatchCounters *cnt,
-                           hipStream_t s) {
+__global__ __launch_bounds__(kScanThreads) void compact_small_kernel(Op op, const int32_t *n_ptr, int n_fixed, u64 *said,
+                                                                     uint32_t *ticket, BatchCounters *cnt) {
+  typedef typename Op::V V;
+  constexpr int kWords = sizeof(V) / sizeof(u64);
+  __shared__ typename Op::Lut s_lut;
+  __shared__ V s_wave[kScanWavesPerBlock], s_before[kScanWavesPerBlock];
+  if (cnt->err) return;  // the same for all workgroups, and before their tickets
+  const int blk = take_ticket(ticket);
+  if (op.prepare(s_lut)) __syncthreads();
+  constexpr int kScanItems = Op::kItems, kScanStep = kWave * kScanItems;
+  const int n = n_ptr ? *n_ptr : n_fixed;
+  const int chunk = scan_chunk(n, gridDim.x, kScanStep);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t base64 = (int64_t)(blk * kScanWavesPerBlock + wave) * chunk;
+  const int base = (int)(base64 < n ? base64 : n), end = (int)(base64 + chunk < n ? base64 + chunk : n);
+  V mine{};
+  for (int i0 = base + lane * kScanItems; i0 < end; i0 += kScanStep) {
+#pragma unroll
+    for (int q = 0; q < kScanItems; q++)
+      if (i0 + q < end) mine += op.flag(i0 + q, n);
+  }
+  mine = wave_total(mine);
+  if (lane == 0) s_wave[wave] = mine;
+  __syncthreads();
+  V own{}, carry{};
+  for (int w = 0; w < kScanWavesPerBlock; w++) {
+    own += s_wave[w];
+    if (w < wave) carry += s_wave[w];
+  }
+  if (gridDim.x > 1) {
+    if (tid < kWords) say(said + tid * kSmallScanBlocks + blk, tid == 0 ? own.w[0] : own.w[kWords - 1]);
+    V before{};
+    if (tid < blk) {  // kSmallScanBlocks == kScanThreads: a workgroup before this one per thread
+      V v{};
+#pragma unroll
+      for (int i = 0; i < kWords; i++) v.w[i] = look(said + i * kSmallScanBlocks + tid);
+#pragma unroll
+      for (int i = 0; i < kWords; i++) before.w[i] = hear(said + i * kSmallScanBlocks + tid, v.w[i]);
+    }
+    before = wave_total(before);
+    if (lane == 0) s_before[wave] = before;
+    __syncthreads();
+    before = V{};
+    for (int w = 0; w < kScanWavesPerBlock; w++) before += s_before[w];
+    carry += before;
+    own += before;  // the last workgroup's is the total
+  }
+  op.rewind();
+  write_chunk(op, base, end, n, lane, carry);
+  op.thread_done(cnt, lane, blk);
+  if (blk == (int)gridDim.x - 1 && tid == 0) op.finish(cnt, n, own);
+}
+
+// small_pass: number of the pass among those of a small batch, -1 = not a small batch; returns the number of workgroups
+template <class Op>
+static int run_compaction(Op op, const int32_t *n_ptr, int n_fixed, int n_bound, const SortScratch &ss, int small_pass,
+                          BatchCounters *cnt, hipStream_t s) {
+  if (small_pass >= 0) {
+    int nb = (n_bound + kScanThreads * Op::kItems - 1) / (kScanThreads * Op::kItems);
+    if (nb > kSmallScanBlocks) nb = kSmallScanBlocks;
+    hipLaunchKernelGGL(compact_small_kernel<Op>, dim3(nb), dim3(kScanThreads), 0, s, op, n_ptr, n_fixed,
+                       ss.said_counts + 2 * small_pass * kSmallScanBlocks, ss.ticket, cnt);
+    return nb;
+  }
+  u64 *words = ss.blk;
   typename Op::V *blk = (typename Op::V *)words;
   int nb = (n_bound + kScanThreads * Op::kItems - 1) / (kScanThreads * Op::kItems);
   if (nb > kScanBlocks) nb = kScanBlocks;
@@ -297,7 +370,8 @@ struct DedupOp {
     t = -1;
     enter_table(k);
   }
-  __device__ void thread_done(BatchCounters *, int) const {}
+  __device__ void rewind() const { t = -1; }
+  __device__ void thread_done(BatchCounters *, int, int) const {}
   __device__ void finish(BatchCounters *cnt, int n, const V &total) const {
     cnt->n_uniq = (int32_t)total.lo(0);
     cnt->n_touched = (int32_t)total.hi(0);
@@ -601,7 +675,8 @@ struct StatusOp {
       hit_lookups += (u64)(run_off[u + 1] - run_off[u]);
     }
   }
-  __device__ void thread_done(BatchCounters *, int lane) const {
+  __device__ void rewind() const {}
+  __device__ void thread_done(BatchCounters *, int lane, int blk) const {
     u64 e = evs, l = hit_lookups;
     unsigned int lt = late;
     for (int d = 32; d >= 1; d >>= 1) {
@@ -610,7 +685,7 @@ struct StatusOp {
       lt += __shfl_xor(lt, d);
     }
     if (lane == 0) {
-      const int w = blockIdx.x * kScanWavesPerBlock + (threadIdx.x >> 6);
+      const int w = blk * kScanWavesPerBlock + (threadIdx.x >> 6);
       tally[3 * w] = e;
       tally[3 * w + 1] = l;
       tally[3 * w + 2] = lt;
@@ -1011,7 +1086,8 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
   DedupOp d{tm, g.T, sorted_keys, sorted_pos, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
             b.maxp ? b.sorted_within : nullptr, b.uid_sorted, b.sorted_bag, b.uniq_key, b.run_off,
             b.uniq_tab, b.touched, -1, 0u, 0u, 0u, 0ull, false, nullptr};
-  run_compaction(d, nullptr, n, n, ss.blk, b.cnt, s);
+  const bool small = small_batch(g, n, b.batch);
+  run_compaction(d, nullptr, n, n, ss, small ? 0 : -1, b.cnt, s);
   int64_t max_touched = (int64_t)g.total_sets + g.T;
   if (max_touched > n) max_touched = n;
   const int probe_blocks = (int)(max_touched < 65536 ? max_touched : 65536);
@@ -1026,7 +1102,7 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
               l2.on ? b.src2 : nullptr, l2.on ? b.dst2 : nullptr, l2.on ? b.evict2 : nullptr,
               l2.on ? b.ins_dst : nullptr, l2.on ? b.l2v_src : nullptr, l2.on ? b.l2v_dst : nullptr,
               l2.on ? b.l2v_key : nullptr, ss.tally, 0u, 0u, 0ull, nullptr};
-  ss.tally_waves = run_compaction(st, &b.cnt->n_uniq, 0, n, ss.blk, b.cnt, s) * kScanWavesPerBlock;
+  ss.tally_waves = run_compaction(st, &b.cnt->n_uniq, 0, n, ss, small ? 1 : -1, b.cnt, s) * kScanWavesPerBlock;
   if (!b.maxp)  // the tile kernel's chunks and range starts (max pooling takes heavy rows a workgroup each)
     hipLaunchKernelGGL(heavy_plan_kernel, dim3(g.T + kPlanStartBlocks), dim3(kPlanThreads), 0, s, tm, g.T, b.batch, b.hfirst,
                        b.heavy, b.heavy_sub, b.uniq_tab, b.run_off, b.sorted_bag, b.hchunks, b.hperm, b.hstart,

@@ -188,6 +188,10 @@ struct SortScratch {
   unsigned long long *tally;  // [3 * wavefronts of a compaction pass] (evictions, lookups that hit, late rows) per wave-
   int tally_waves;            //     front of the last batch's status pass, and how many wavefronts that pass had
   uint32_t *too_long;         // a bag of the batch does not fit the packed payload (0 between batches)
+  // small batches (small_batch): what the workgroups of a kernel tell each other
+  uint32_t *ticket;           // workgroups of the running kernel that have begun (0 between kernels)
+  uint32_t *said;             // [kMaxSortPasses][256] digit totals, then [kMaxSortPasses][workgroups][256] digit counts
+  unsigned long long *said_counts;  // [2 passes][2 words][kSmallScanBlocks] counts of the compaction passes
 };
 
 // Staging between the cache and the host link (one instance; the prefetch stage is serial).
@@ -290,11 +294,55 @@ struct ClassInfo {
   const int32_t *table_class;              // device: class of every table
 };
 
+// Batches of few lookups are bound by launches, not by bytes: every pass of the prefetch stage over them is one kernel,
+// whose workgroups tell each other their counts through memory, instead of a kernel that counts and one that writes (and
+// one that scans in between, for the sort).  A workgroup takes the next ticket when it begins and waits only for the counts
+// of workgroups with earlier tickets, which have begun and say their counts before they wait for anything: every wait ends
+// whatever else runs on the GPU.  The words are cleared by the stage's first kernel.
+// The line lies where both ways cost the same on this chip: with a kernel a pass, four tables of 41 k lookups take 845
+// instead of 1054 us for six steps, 262 k lookups 1080 instead of 1113 us for five, 327 k 2660 instead of 2740; beyond half
+// a million the sums over the workgroups before one's own (128 x 256 words a pass) take as long as the launches they
+// spare.  The digit totals cost the key generation an addition to memory per digit value and workgroup of 32 bags: not
+// with more than 65536 bags.
+constexpr int64_t kSmallLookups = 524288, kSmallBags = 65536;
+constexpr int kMaxSortPasses = 4;
+constexpr int kSmallSortThreads = 512;
+constexpr int kSmallSortBlocks = 128;  // a workgroup's tile is 4 or 8 keys per thread
+constexpr int kSmallScanBlocks = 256;
+static_assert(kSmallLookups <= kSmallSortBlocks * kSmallSortThreads * 8, "the sort's workgroups must hold the batch");
+inline bool small_batch(const Geometry &g, int64_t n, int32_t batch) {
+  return n > 0 && n <= kSmallLookups && (int64_t)g.T * batch <= kSmallBags;
+}
+inline int small_sort_items(int64_t n) { return n <= 131072 ? 4 : 8; }
+inline int small_sort_blocks(int64_t n) {
+  const int tile = kSmallSortThreads * small_sort_items(n);
+  return (int)((n + tile - 1) / tile);
+}
+
+// Digits of the radix sort: pass p sorts by (key >> shift[p]) & mask[p].
+struct DigitPlan {
+  int passes;
+  int shift[kMaxSortPasses];
+  uint32_t mask[kMaxSortPasses];
+};
+inline DigitPlan digit_plan(int key_bits, int passes) {
+  DigitPlan d{};
+  d.passes = passes;
+  int shift = 0;
+  for (int p = 0; p < passes; p++) {
+    const int w = (key_bits - shift + (passes - p) - 1) / (passes - p);  // balanced digit widths, the wider ones first
+    d.shift[p] = shift;
+    d.mask[p] = (1u << w) - 1u;
+    shift += w;
+  }
+  return d;
+}
+
 // ---- launchers (each enqueues on `s` and returns the HIP status of the launch) ----
 
 // counters of the batch to zero, sort keys and payloads of its lookups into ss.keys[0] / ss.vals[0]
 hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf &b, const SortScratch &ss, hipStream_t s);
-hipError_t launch_sort(const Geometry &g, SortScratch &ss, int64_t n, int *result_buf, hipStream_t s);
+hipError_t launch_sort(const Geometry &g, const BatchBuf &b, SortScratch &ss, int *result_buf, hipStream_t s);
 // lock: batches before the current one whose ways are locked like the current batch's own (0 in the one-deep pipeline)
 hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const BatchBuf &b, SortScratch &ss,
                               const uint32_t *sorted_keys, const uint32_t *sorted_pos, int32_t *tags, int32_t *ts,
@@ -410,6 +458,36 @@ __device__ inline void xcd_span_of(int id, int nblocks, int n, int per_block, in
   end = (int)((int64_t)n * (x + 1) / kXcds);
   first = lo + (id / kXcds) * per_block;
   step = nb * per_block;
+}
+
+// ---- words through which the workgroups of one kernel tell each other their counts ----
+// A word carries its own "said" bit, so that a reader needs nothing but the word: written and read by atomics at the scope
+// of the whole GPU, which pass the XCDs' own L2s by.
+__device__ inline void say(uint32_t *p, uint32_t v) {
+  __hip_atomic_store(p, v | 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void say(unsigned long long *p, unsigned long long v) {
+  __hip_atomic_store(p, v | 1ull << 63, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class W>
+__device__ inline W look(const W *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class W>
+__device__ inline W hear(const W *p, W v) {  // v: what a first look found
+  constexpr W kSaid = (W)1 << (sizeof(W) * 8 - 1);
+  while (!(v & kSaid)) {
+    __builtin_amdgcn_s_sleep(1);
+    v = look(p);
+  }
+  return v & ~kSaid;
+}
+// The workgroup's number by the order in which workgroups began; the counter is back at zero when all have.
+__device__ inline int take_ticket(uint32_t *ticket) {
+  __shared__ int s_ticket;
+  if (threadIdx.x == 0) s_ticket = gridDim.x == 1 ? 0 : (int)atomicInc(ticket, gridDim.x - 1);
+  __syncthreads();
+  return s_ticket;
 }
 
 // table that owns sort key `key`: last t with key_base[t] <= key

@@ -19,6 +19,22 @@ def test_lookups_around_the_steps(n):
         run_parity(synth.WorkloadCfg("edge", t, batch=1, ways=8, steps=3, seed=n, init_std=0.05, lr=0.05), steps=3, order="early")
 
 
+@pytest.mark.parametrize("batch,pool", [(64, 64), (65, 63), (241, 17), (2047, 64), (2048, 64), (2049, 64), (4099, 63), (8191, 64),
+                                        (8192, 64), (8193, 64)])
+def test_lookups_around_the_lines_of_the_small_batches(batch, pool):
+    """the sort's tiles (2048 keys, from 131073 lookups on 4096) and the last batch size with a kernel a pass (524288)"""
+    tabs = [T(70001, 4, synth.FP32, 0.9, "fixed", pool - pool // 3, cache_slots=32 * 300),
+            T(1999, 4, synth.FP32, None, "fixed", pool // 3, cache_slots=320)]
+    run_parity(synth.WorkloadCfg("lines", tabs, batch=batch, ways=32, steps=2, seed=batch, init_std=0.05, lr=0.05), steps=2, order="early")
+
+
+def test_more_bags_than_a_small_batch_takes():
+    """few lookups in 65536 and 65544 bags: either side of the line"""
+    for batch in (8192, 8193):
+        tabs = [T(500, 4, synth.FP32, 1.0, "poisson", 0.5, 0, 20, cache_slots=64) for _ in range(8)]
+        run_parity(synth.WorkloadCfg("bags", tabs, batch=batch, ways=8, steps=3, seed=4, init_std=0.05, lr=0.05), steps=3, order="early")
+
+
 @pytest.mark.parametrize("overlap", [True, False])
 def test_tables_without_cache_or_lookups_in_between(overlap):
     tabs = [T(40, 8, synth.FP32, None, "fixed", 0, cache_slots=8), T(50, 8, synth.FP32, 1.0, "poisson", 5, 0, 30),
