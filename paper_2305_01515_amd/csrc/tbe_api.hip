@@ -544,6 +544,8 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   h->g.total_sets = (uint32_t)sets;
   h->g.total_slots = (int64_t)sets * ways;
   h->g.ovf_stride = 16;
+  h->g.win_stride = 1;
+  for (const TableMeta &m : h->tm) h->g.win_stride = std::max(h->g.win_stride, m.lanes);
   for (const TableMeta &m : h->tm) h->g.ovf_stride = std::max(h->g.ovf_stride, m.row_bytes);
   h->g.key_bits = 1;
   while (h->g.key_bits < 32 && (1ull << h->g.key_bits) < key) h->g.key_bits++;
@@ -737,8 +739,8 @@ int tbe_set_prefetch_depth(tbe_handle h, int32_t depth) {
     int rc = alloc_batchbuf(h, h->buf[i], h->max_lookups);
     if (rc) return rc;
     if (h->pooling == TBE_POOL_MAX) {
-      HIP_TRY(h, h->mem.get(&h->buf[i].argpos, 4 * (size_t)h->max_batch * (size_t)h->g.sum_dim));
-      HIP_TRY(h, h->mem.get(&h->buf[i].sorted_within, 4 * (size_t)std::max<int64_t>(h->max_lookups, 1)));
+      HIP_TRY(h, h->mem.get(&h->buf[i].wins, (size_t)h->g.win_stride * (size_t)std::max<int64_t>(h->max_lookups, 1)));
+      HIP_TRY(h, h->mem.get(&h->buf[i].sorted_pos, 4 * (size_t)std::max<int64_t>(h->max_lookups, 1)));
     }
     HIP_TRY(h, hipEventCreateWithFlags(&h->ev_ready[i], hipEventDisableTiming));
     HIP_TRY(h, hipEventCreateWithFlags(&h->ev_trained[i], hipEventDisableTiming));
@@ -1106,10 +1108,10 @@ int tbe_set_pooling(tbe_handle h, int32_t pooling) {
   if (pooling != TBE_POOL_SUM && pooling != TBE_POOL_MEAN && pooling != TBE_POOL_MAX)
     return fail(h, TBE_EINVAL, "set_pooling: unknown pooling mode");
   if (h->k != 0) return fail(h, TBE_EORDER, "set_pooling: batches have been prefetched already");
-  if (pooling == TBE_POOL_MAX && !h->buf[0].argpos) {  // who supplied each maximum, and the lookups' positions in their bags
+  if (pooling == TBE_POOL_MAX && !h->buf[0].wins) {  // the maxima every lookup supplied, and the lookups' positions by sorted order
     for (int i = 0; i < h->nbuf; i++) {
-      HIP_TRY(h, h->mem.get(&h->buf[i].argpos, 4 * (size_t)h->max_batch * (size_t)h->g.sum_dim));
-      HIP_TRY(h, h->mem.get(&h->buf[i].sorted_within, 4 * (size_t)std::max<int64_t>(h->max_lookups, 1)));
+      HIP_TRY(h, h->mem.get(&h->buf[i].wins, (size_t)h->g.win_stride * (size_t)std::max<int64_t>(h->max_lookups, 1)));
+      HIP_TRY(h, h->mem.get(&h->buf[i].sorted_pos, 4 * (size_t)std::max<int64_t>(h->max_lookups, 1)));
     }
   }
   h->pooling = pooling;
@@ -1122,7 +1124,7 @@ int tbe_export_argmax(tbe_handle h, int32_t *d_argmax) {
   if (h->pooling != TBE_POOL_MAX) return fail(h, TBE_EORDER, "export_argmax: the pooling mode is not max");
   if (h->current < 0) return fail(h, TBE_EORDER, "export_argmax: no forwarded batch waits for its update");
   const BatchBuf &b = h->buf[h->current];
-  HIP_TRY(h, hipMemcpyAsync(d_argmax, b.argpos, 4 * (size_t)b.batch * (size_t)h->g.sum_dim, hipMemcpyDeviceToDevice, h->cs));
+  HIP_TRY(h, launch_argmax_classes(h->d_tm, h->ci, h->g, b, d_argmax, h->cs));
   return TBE_OK;
 }
 

@@ -295,7 +295,7 @@ struct DedupOp {
   const BatchCounters *cnt;  // cnt->packed: the payload carries the bag
   int within_bits;
   const int64_t *offsets;
-  int32_t *sorted_within;    // max pooling only (else null): position of the lookup inside its bag
+  uint32_t *sorted_pos;      // max pooling only (else null): position of the lookup in input order
   uint32_t *uid_sorted;
   int32_t *sorted_bag;
   uint32_t *uniq_key;
@@ -355,8 +355,7 @@ struct DedupOp {
     const uint32_t p = pos[i];
     const int32_t bag = cnt->packed ? (int32_t)(p >> within_bits) : bag_of_pos[p];
     sorted_bag[i] = bag;
-    if (sorted_within)
-      sorted_within[i] = cnt->packed ? (int32_t)(p & ((1u << within_bits) - 1u)) : (int32_t)((int64_t)p - offsets[bag]);
+    if (sorted_pos) sorted_pos[i] = cnt->packed ? (uint32_t)offsets[bag] + (p & ((1u << within_bits) - 1u)) : p;
     if (f.lo(0)) {
       const uint32_t k = key[i];
       if (k < base || k > last) enter_table_of(k);  // (the lane's next element may lie in the next table)
@@ -1084,7 +1083,7 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
     return hipGetLastError();
   }
   DedupOp d{tm, g.T, sorted_keys, sorted_pos, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
-            b.maxp ? b.sorted_within : nullptr, b.uid_sorted, b.sorted_bag, b.uniq_key, b.run_off,
+            b.maxp ? b.sorted_pos : nullptr, b.uid_sorted, b.sorted_bag, b.uniq_key, b.run_off,
             b.uniq_tab, b.touched, -1, 0u, 0u, 0u, 0ull, false, nullptr};
   const bool small = small_batch(g, n, b.batch);
   run_compaction(d, nullptr, n, n, ss, small ? 0 : -1, b.cnt, s);

@@ -180,16 +180,16 @@ __global__ __launch_bounds__(256) void forward_kernel(const TableMeta *__restric
 }
 
 // Max pooling (Section 2.1.1): element d of the pooled vector is the largest element d among the
-// bag's rows; `argpos` records, per pooled element, the position inside the bag of the lookup
-// that supplied it -- the first one when several tie (lookups are visited in bag order), -1 for
-// an empty bag, whose pooled vector is zero.  The backward sends the gradient there.
+// bag's rows, supplied by one lookup -- the first one when several tie (lookups are visited in bag order); the
+// pooled vector of an empty bag is zero.  The backward sends the element's gradient there, so every lookup gets a
+// record of the elements it supplied, a bit each (`wins`): a byte per lane of the row.
 template <int DT, int G>
 __global__ __launch_bounds__(256) void forward_max_kernel(const TableMeta *__restrict__ tm,
                                                           const int32_t *__restrict__ class_tables, int B, int sum_dim,
                                                           const int64_t *__restrict__ offsets,
                                                           const uint32_t *__restrict__ loc,
                                                           const char *__restrict__ ovf, uint32_t ovf_stride,
-                                                          float *__restrict__ out, int32_t *__restrict__ argpos,
+                                                          float *__restrict__ out, uint8_t *__restrict__ wins, int win_stride,
                                                           const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
   constexpr int R = G < 4 ? G : 4;
@@ -237,13 +237,45 @@ __global__ __launch_bounds__(256) void forward_max_kernel(const TableMeta *__res
   }
   if (active) {
     float *o = out + (size_t)b * sum_dim + m.col + lig * EPL;
-    int32_t *a = argpos + (size_t)b * sum_dim + m.col + lig * EPL;
 #pragma unroll
-    for (int e = 0; e < EPL; e += 4) {
-      *(float4 *)(o + e) = make_float4(best[e], best[e + 1], best[e + 2], best[e + 3]);
-      *(int4 *)(a + e) = make_int4(who[e], who[e + 1], who[e + 2], who[e + 3]);
+    for (int e = 0; e < EPL; e += 4) *(float4 *)(o + e) = make_float4(best[e], best[e + 1], best[e + 2], best[e + 3]);
+    uint8_t *w = wins + (size_t)lo * win_stride + lig;
+    const int len = (int)(hi - lo);
+    for (int p = 0; p < len; p++) {
+      uint32_t bits = 0;
+#pragma unroll
+      for (int e = 0; e < EPL; e++) bits |= (who[e] == p ? 1u : 0u) << e;
+      w[(size_t)p * win_stride] = (uint8_t)bits;
     }
   }
+}
+
+// The positions inside their bags of the lookups that supplied the maxima, from the lookups' records.
+template <int DT, int G>
+__global__ __launch_bounds__(256) void argmax_kernel(const TableMeta *__restrict__ tm, const int32_t *__restrict__ class_tables,
+                                                     int B, int sum_dim, const int64_t *__restrict__ offsets,
+                                                     const uint8_t *__restrict__ wins, int win_stride,
+                                                     int32_t *__restrict__ argmax, const BatchCounters *cnt) {
+  constexpr int EPL = Elems<DT>::n;
+  if (cnt->err) return;
+  const int t = class_tables[blockIdx.y];
+  const TableMeta &m = tm[t];
+  const int b = blockIdx.x * (256 / G) + threadIdx.x / G;
+  const int lig = threadIdx.x % G;
+  if (b >= B || lig * EPL >= m.dim) return;
+  const int64_t lo = offsets[(int64_t)t * B + b], hi = offsets[(int64_t)t * B + b + 1];
+  int who[EPL];
+#pragma unroll
+  for (int e = 0; e < EPL; e++) who[e] = -1;
+  for (int64_t j = lo; j < hi; j++) {
+    const uint32_t bits = wins[(size_t)j * win_stride + lig];
+#pragma unroll
+    for (int e = 0; e < EPL; e++)
+      if (bits >> e & 1u) who[e] = (int)(j - lo);
+  }
+  int32_t *a = argmax + (size_t)b * sum_dim + m.col + lig * EPL;
+#pragma unroll
+  for (int e = 0; e < EPL; e++) a[e] = who[e];
 }
 
 // --------------------------------------------------------------------------------------
@@ -322,26 +354,86 @@ __device__ inline RowRef locate(const TableMeta &m, uint32_t key, int slot, char
 // lanes: the bag ids are read G at a time (coalesced) and handed round by shuffles, four
 // gradient rows are in flight per lane.  `stride_chunks` > 1 lets several groups share a
 // range chunk-wise (group `first_chunk` of `stride_chunks`).  Summation order is fixed.
-// MODE: kSum, kMean (every gradient row weighs 1 / lookups of its bag, from inv_len) or kMax (a
-// lookup receives element d of its bag's gradient only if it supplied the maximum: argbase points
-// at the row's columns of the recorded positions, sorted_within gives the lookup's own position).
+// MODE: kSum, kMean (every gradient row weighs 1 / lookups of its bag, from inv_len) or kMax (a lookup receives element d
+// of its bag's gradient only if it supplied the maximum: Wins has its record).
 constexpr int kSum = 0, kMean = 1, kMax = 2;
+
+struct Wins {
+  const uint8_t *rec;          // the lookups' records, input order
+  int stride;
+  const uint32_t *sorted_pos;  // position of the i-th lookup in sorted order
+};
+
+// Max pooling: a lookup of a bag of L lookups supplies one element in L.  Its record, a byte per lane, says which, and a lane
+// reads only the 16-byte pieces of the gradient that hold one of its own.  (With who supplied each element recorded per
+// pooled element, four bytes each, a lookup read as many bytes of that as of gradients, and all of both: 1 KB instead of
+// about 160 bytes at 128 elements and 25 lookups.)
+template <int DT, int Q>
+struct MaxTaken {
+  float4 v[Q][Elems<DT>::n / 4];
+};
+template <int DT, int Q>
+__device__ inline void max_request(MaxTaken<DT, Q> &t, const float *const (&p)[Q], const uint32_t (&w)[Q]) {
+#pragma unroll
+  for (int x = 0; x < Q; x++)
+#pragma unroll
+    for (int e = 0; e < Elems<DT>::n / 4; e++)
+      t.v[x][e] = (w[x] >> (4 * e) & 15u) ? *(const float4 *)(p[x] + 4 * e) : make_float4(0.f, 0.f, 0.f, 0.f);
+}
+template <int DT, int Q>
+__device__ inline void max_add(float (&g)[Elems<DT>::n], const MaxTaken<DT, Q> &t, const uint32_t (&w)[Q]) {
+#pragma unroll
+  for (int x = 0; x < Q; x++)
+#pragma unroll
+    for (int e = 0; e < Elems<DT>::n / 4; e++) {
+      const uint32_t bits = w[x] >> (4 * e);
+      g[4 * e] += bits & 1u ? t.v[x][e].x : 0.f;
+      g[4 * e + 1] += bits & 2u ? t.v[x][e].y : 0.f;
+      g[4 * e + 2] += bits & 4u ? t.v[x][e].z : 0.f;
+      g[4 * e + 3] += bits & 8u ? t.v[x][e].w : 0.f;
+    }
+}
+
+template <int DT, int G>
+__device__ inline void reduce_max_grads(float (&g)[Elems<DT>::n], const float *gbase, const int32_t *sorted_bag, int bag0,
+                                        int sum_dim, int i0, int i1, int first_chunk, int stride_chunks, int lig,
+                                        bool active, const Wins &wins) {
+  for (int base = i0 + first_chunk * G; base < i1; base += stride_chunks * G) {
+    const int nq = (i1 - base) < G ? (i1 - base) : G;
+    const int my_bag = lig < nq ? sorted_bag[base + lig] - bag0 : 0;
+    const uint32_t my_pos = lig < nq ? wins.sorted_pos[base + lig] : 0u;
+    for (int q = 0; q < nq; q += 4) {
+      uint32_t w[4];
+      const float *p[4];
+#pragma unroll
+      for (int x = 0; x < 4; x++) {
+        const uint32_t pos = (uint32_t)__shfl((int)my_pos, (q + x) & (G - 1), G);
+        p[x] = gbase + (size_t)__shfl(my_bag, (q + x) & (G - 1), G) * sum_dim;
+        w[x] = (active && q + x < nq) ? wins.rec[(size_t)pos * wins.stride + lig] : 0u;
+      }
+      MaxTaken<DT, 4> t;
+      max_request(t, p, w);
+      max_add(g, t, w);
+    }
+  }
+}
 
 template <int DT, int G, int MODE>
 __device__ inline void reduce_grads(float (&g)[Elems<DT>::n], const float *gbase, const int32_t *sorted_bag, int bag0,
                                     int sum_dim, int i0, int i1, int first_chunk, int stride_chunks, int lig,
-                                    bool active, const float *inv_len, const int32_t *argbase,
-                                    const int32_t *sorted_within) {
+                                    bool active, const float *inv_len, const Wins &wins) {
   constexpr int EPL = Elems<DT>::n;
   constexpr bool MEAN = MODE == kMean;
+  if constexpr (MODE == kMax) {
+    reduce_max_grads<DT, G>(g, gbase, sorted_bag, bag0, sum_dim, i0, i1, first_chunk, stride_chunks, lig, active, wins);
+    return;
+  }
   for (int base = i0 + first_chunk * G; base < i1; base += stride_chunks * G) {
     const int nq = (i1 - base) < G ? (i1 - base) : G;
     const int my_gbag = lig < nq ? sorted_bag[base + lig] : bag0;
     const int my_bag = my_gbag - bag0;
     float my_w = 0.f;  // mean pooling: the weight 1/L of the lookup's bag
     if (MEAN) my_w = lig < nq ? inv_len[my_gbag] : 0.f;
-    int my_within = -2;  // max pooling: the lookup's position inside its bag
-    if (MODE == kMax) my_within = lig < nq ? sorted_within[base + lig] : -2;
     for (int q = 0; q < nq; q += 4) {
       float4 v[4][EPL / 4];
       float w[4];
@@ -349,23 +441,10 @@ __device__ inline void reduce_grads(float (&g)[Elems<DT>::n], const float *gbase
       for (int x = 0; x < 4; x++) {
         const int bq = __shfl(my_bag, (q + x) & (G - 1), G);
         if (MEAN) w[x] = __shfl(my_w, (q + x) & (G - 1), G);
-        int within = 0;
-        if (MODE == kMax) within = __shfl(my_within, (q + x) & (G - 1), G);
         const float *p = gbase + (size_t)bq * sum_dim;
         const bool ok = active && (q + x < nq);
 #pragma unroll
         for (int e = 0; e < EPL / 4; e++) v[x][e] = ok ? *(const float4 *)(p + 4 * e) : make_float4(0.f, 0.f, 0.f, 0.f);
-        if (MODE == kMax && ok) {
-          const int32_t *a = argbase + (size_t)bq * sum_dim;
-#pragma unroll
-          for (int e = 0; e < EPL / 4; e++) {
-            const int4 who = *(const int4 *)(a + 4 * e);
-            if (who.x != within) v[x][e].x = 0.f;
-            if (who.y != within) v[x][e].y = 0.f;
-            if (who.z != within) v[x][e].z = 0.f;
-            if (who.w != within) v[x][e].w = 0.f;
-          }
-        }
       }
 #pragma unroll
       for (int x = 0; x < 4; x++)
@@ -486,7 +565,7 @@ __global__ __launch_bounds__(256) void backward_single_kernel(const TableMeta *_
 // The same for max pooling: the row receives the elements of the bag's gradient whose maximum
 // its lookup supplied (recorded by the forward), so the masked gradient and its sum of squares
 // differ from row to row.  Rows with exactly one lookup in the batch, bag by bag, the bag's
-// gradient slice and the recorded positions of its elements in registers.
+// gradient slice in registers.
 template <int DT, int G>
 __global__ __launch_bounds__(256) void backward_single_max_kernel(const TableMeta *__restrict__ tm,
                                                               const int32_t *__restrict__ class_tables, int B,
@@ -495,7 +574,7 @@ __global__ __launch_bounds__(256) void backward_single_max_kernel(const TableMet
                                                               const uint32_t *__restrict__ loc,
                                                               const float *__restrict__ grad_out, float lr, float eps,
                                                               char *__restrict__ ovf, uint32_t ovf_stride,
-                                                              const int32_t *__restrict__ argpos,
+                                                              const uint8_t *__restrict__ wins, int win_stride,
                                                               const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
   if (cnt->err) return;
@@ -516,17 +595,6 @@ __global__ __launch_bounds__(256) void backward_single_max_kernel(const TableMet
 #pragma unroll
   for (int e = 0; e < EPL; e++) g[e] = 0.f;
   if (active) load_grad<DT>(g, grad_out + (size_t)b * sum_dim + m.col + lig * EPL);
-  int aw[EPL];  // who supplied the maximum of this lane's elements
-#pragma unroll
-  for (int e = 0; e < EPL; e++) aw[e] = -1;
-  if (active) {
-    const int32_t *a = argpos + (size_t)b * sum_dim + m.col + lig * EPL;
-#pragma unroll
-    for (int e = 0; e < EPL; e += 4) {
-      const int4 w4 = *(const int4 *)(a + e);
-      aw[e] = w4.x; aw[e + 1] = w4.y; aw[e + 2] = w4.z; aw[e + 3] = w4.w;
-    }
-  }
   const float inv_dim = 1.0f / (float)m.dim;
   for (int64_t j0 = lo; j0 < hi; j0 += G) {
     const int nq = (int)((hi - j0) < G ? (hi - j0) : G);
@@ -538,7 +606,7 @@ __global__ __launch_bounds__(256) void backward_single_max_kernel(const TableMet
       float *mp[4];
       float m_old[4];
       uint4 raw[4];
-      int within[4];
+      uint32_t win[4];
       int n = 0;
 #pragma unroll
       for (int x = 0; x < 4; x++) {
@@ -555,7 +623,7 @@ __global__ __launch_bounds__(256) void backward_single_max_kernel(const TableMet
             mp[x] = slot_m + ((int)ix - slot_base);
           }
           m_old[x] = *mp[x];
-          within[x] = (int)(j0 - lo) + q;
+          win[x] = active ? wins[(size_t)(j0 + q) * win_stride + lig] : 0u;
           if (active) raw[x] = load_once(w[x]);
           n = x + 1;
         }
@@ -567,7 +635,7 @@ __global__ __launch_bounds__(256) void backward_single_max_kernel(const TableMet
           float sq = 0.f;
 #pragma unroll
           for (int e = 0; e < EPL; e++) {
-            gm[e] = aw[e] == within[x] ? g[e] : 0.f;
+            gm[e] = win[x] >> e & 1u ? g[e] : 0.f;
             sq += gm[e] * gm[e];
           }
           for (int d = G / 2; d >= 1; d >>= 1) sq += __shfl_xor(sq, d, G);
@@ -594,9 +662,7 @@ __global__ __launch_bounds__(256) void backward_short_kernel(const TableMeta *__
                                                              char *__restrict__ ovf, uint32_t ovf_stride,
                                                              const int32_t *__restrict__ table_class,
                                                              const float *__restrict__ inv_len,
-                                                             const int32_t *__restrict__ argpos,
-                                                             const int32_t *__restrict__ sorted_within,
-                                                             const BatchCounters *cnt) {
+                                                             Wins wins, const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
   if (cnt->err) return;
   const int n_mid = cnt->n_mid;
@@ -614,12 +680,12 @@ __global__ __launch_bounds__(256) void backward_short_kernel(const TableMeta *__
 #pragma unroll
     for (int e = 0; e < EPL; e++) g[e] = 0.f;
     reduce_grads<DT, G, MODE>(g, grad_out + m.col + lig * EPL, sorted_bag, t * B, sum_dim, i0, i1, 0, 1, lig, active, inv_len,
-                              MODE == kMax ? argpos + m.col + lig * EPL : nullptr, sorted_within);
+                              wins);
     update_row<DT, G>(m, uniq_key[u], loc_u[u], ovf, ovf_stride, g, lr, eps, lig, active);
   }
 }
 
-// Max pooling, and rows narrower than 4 lanes: rows with more than kLongRun lookups, one workgroup per row, its 256/G groups take
+// Rows narrower than 4 lanes, and under max pooling narrower than 8: rows with more than kLongRun lookups, one workgroup per row, its 256/G groups take
 // chunks of G lookups round robin; the partial sums are added in group order through LDS.  (The
 // gradient a lookup receives is masked by who supplied each maximum, so the bags' gradient rows cannot
 // be shared between rows the way the tile kernel below shares them.)
@@ -636,9 +702,7 @@ __global__ __launch_bounds__(256) void backward_long_kernel(const TableMeta *__r
                                                             char *__restrict__ ovf, uint32_t ovf_stride,
                                                             const int32_t *__restrict__ table_class,
                                                             const float *__restrict__ inv_len,
-                                                            const int32_t *__restrict__ argpos,
-                                                            const int32_t *__restrict__ sorted_within,
-                                                            const BatchCounters *cnt) {
+                                                            Wins wins, const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
   constexpr int NG = 256 / G;
   __shared__ float part[NG][G * EPL + 1];
@@ -658,8 +722,7 @@ __global__ __launch_bounds__(256) void backward_long_kernel(const TableMeta *__r
 #pragma unroll
     for (int e = 0; e < EPL; e++) g[e] = 0.f;
     reduce_grads<DT, G, MODE>(g, grad_out + m.col + lig * EPL, sorted_bag, t * B, sum_dim, run_off[u], run_off[u + 1], grp,
-                              NG, lig, active, inv_len, MODE == kMax ? argpos + m.col + lig * EPL : nullptr,
-                              sorted_within);
+                              NG, lig, active, inv_len, wins);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < EPL; e++) part[grp][lig * EPL + e] = g[e];
@@ -670,6 +733,118 @@ __global__ __launch_bounds__(256) void backward_long_kernel(const TableMeta *__r
         float s = 0.f;
         for (int q = 0; q < NG; q++) s += part[q][lig * EPL + e];
         g[e] = s;
+      }
+      update_row<DT, G>(m, uniq_key[u], loc_u[u], ovf, ovf_stride, g, lr, eps, lig, active);
+    }
+  }
+}
+
+// Max pooling, rows with more than kLongRun lookups, rows of at least 8 lanes: one workgroup of 1024 threads per row.  The
+// sum is made of the same 256 / G chains as above, chain c adding the chunks c, c + 256 / G, ... of G lookups in lookup
+// order (so its rounding is that of the kernel above, bit for bit), but a chain has a wavefront instead of a lane group:
+// its 64 / G groups request Q lookups each at the same time, the records a step ahead, and the running sum is handed from
+// group to group.  A chain's length is what bounds this kernel: the hottest of 500 k rows has 12 k of a table's 100 k
+// lookups, 48 chunks a chain, each of which took a lane group four rounds of dependent reads.  8 tables of 500 k rows of
+// 128 elements, 818 k lookups: 0.28 -> 0.13 ms (0.29 ms with the row's elements spread over all 64 lanes: three times as many load instructions).
+template <int DT, int G>
+__global__ __launch_bounds__(1024) void backward_long_max_kernel(const TableMeta *__restrict__ tm, int cls, int B, int sum_dim,
+                                                                 const int32_t *__restrict__ heavy,
+                                                                 const int32_t *__restrict__ heavy_sub,
+                                                                 const uint32_t *__restrict__ uniq_key,
+                                                                 const int32_t *__restrict__ uniq_tab,
+                                                                 const int32_t *__restrict__ run_off,
+                                                                 const int32_t *__restrict__ loc_u,
+                                                                 const int32_t *__restrict__ sorted_bag,
+                                                                 const float *__restrict__ grad_out, float lr, float eps,
+                                                                 char *__restrict__ ovf, uint32_t ovf_stride,
+                                                                 const int32_t *__restrict__ table_class, Wins wins,
+                                                                 const BatchCounters *cnt) {
+  static_assert(G >= 8, "a chunk of G lookups has at least a lookup for each of a wavefront's groups");
+  constexpr int EPL = Elems<DT>::n;
+  constexpr int NG = 256 / G;                         // chains
+  constexpr int GU = kWave / G;                       // groups of a wavefront
+  constexpr int Q = G / GU < 4 ? G / GU : 4;          // lookups a group requests at a time
+  constexpr int STEP = GU * Q;                        // ... and the wavefront; G is a multiple of it
+  __shared__ float part[NG][G * EPL + 1];
+  if (cnt->err) return;
+  const int n_heavy = cnt->n_heavy;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lig = lane % G, grp = lane / G;
+  int first, end, step;
+  xcd_span(n_heavy, 1, first, end, step);  // the list is in table order
+  for (int it = first; it < end; it += step) {
+    if (heavy_sub[it] & 0xFFFF) continue;  // a hot row has several entries: it is taken whole at its first
+    const int u = heavy[it];
+    const int t = uniq_tab[u];
+    if (table_class[t] != cls) continue;  // uniform over the block
+    const TableMeta &m = tm[t];
+    const bool active = lig * EPL < m.dim;
+    const float *gbase = grad_out + m.col + lig * EPL;
+    const int i0 = run_off[u], i1 = run_off[u + 1];
+    const int bag0 = t * B;
+    __syncthreads();  // the row before is no longer read
+    for (int c = wave; c < NG; c += 16) {
+      float g[EPL];
+#pragma unroll
+      for (int e = 0; e < EPL; e++) g[e] = 0.f;
+      // The wavefront's steps are numbered: step s covers the lookups of chunk c + s / (G / STEP) * NG from (s % (G / STEP))
+      // * STEP on; this lane's group has Q of them.
+      auto first_of = [&](int s) { return i0 + (c + s / (G / STEP) * NG) * G + s % (G / STEP) * STEP + grp * Q; };
+      // (a chunk's lookups end where the next chain's begin, so a step never reaches past its own chunk)
+      auto places = [&](int s, int (&bag)[Q], uint32_t (&pos)[Q]) {
+        const int at = first_of(s);
+#pragma unroll
+        for (int x = 0; x < Q; x++) {
+          bag[x] = at + x < i1 ? sorted_bag[at + x] - bag0 : -1;
+          pos[x] = at + x < i1 ? wins.sorted_pos[at + x] : 0u;
+        }
+      };
+      auto records = [&](const int (&bag)[Q], const uint32_t (&pos)[Q], uint32_t (&w)[Q]) {
+#pragma unroll
+        for (int x = 0; x < Q; x++) w[x] = (bag[x] >= 0 && active) ? wins.rec[(size_t)pos[x] * wins.stride + lig] : 0u;
+      };
+      const int chunks = (i1 - i0 + G - 1) / G;
+      const int n_steps = chunks > c ? ((chunks - c + NG - 1) / NG) * (G / STEP) : 0;
+      // in flight: the gradients of step s, the records of step s + 1, the places of step s + 2 (past the last step: past
+      // the row's end or, for the chain's neighbours, looked at and never added)
+      uint32_t w[Q], w1[Q], pos1[Q], pos2[Q];
+      int bag[Q], bag1[Q], bag2[Q];
+      if (n_steps > 0) {
+        places(0, bag, pos1);
+        records(bag, pos1, w);
+        places(1, bag1, pos1);
+      }
+      for (int s = 0; s < n_steps; s++) {
+        const float *p[Q];
+#pragma unroll
+        for (int x = 0; x < Q; x++) p[x] = gbase + (size_t)(bag[x] < 0 ? 0 : bag[x]) * sum_dim;
+        MaxTaken<DT, Q> taken;
+        max_request(taken, p, w);
+        records(bag1, pos1, w1);
+        places(s + 2, bag2, pos2);
+        for (int j = 0; j < GU; j++) {  // every group adds its own lookups, the sum of group j is the one that counts
+          float sum[EPL];
+#pragma unroll
+          for (int e = 0; e < EPL; e++) sum[e] = g[e];
+          max_add(sum, taken, w);
+#pragma unroll
+          for (int e = 0; e < EPL; e++) g[e] = __shfl(sum[e], j * G + lig, kWave);
+        }
+#pragma unroll
+        for (int x = 0; x < Q; x++) { w[x] = w1[x]; bag[x] = bag1[x]; bag1[x] = bag2[x]; pos1[x] = pos2[x]; }
+      }
+      if (grp == 0)
+#pragma unroll
+        for (int e = 0; e < EPL; e++) part[c][lig * EPL + e] = g[e];
+    }
+    __syncthreads();
+    if (threadIdx.x < G) {
+      float g[EPL];
+#pragma unroll
+      for (int e = 0; e < EPL; e++) {
+        float sum = 0.f;
+        for (int q = 0; q < NG; q++) sum += part[q][lig * EPL + e];
+        g[e] = sum;
       }
       update_row<DT, G>(m, uniq_key[u], loc_u[u], ovf, ovf_stride, g, lr, eps, lig, active);
     }
@@ -1038,7 +1213,7 @@ static void fwd_one(const TableMeta *tm, const int32_t *tables, int count, const
   dim3 grid((b.batch + bags_per_block - 1) / bags_per_block, count);
   if (b.maxp)
     hipLaunchKernelGGL((forward_max_kernel<DT, G>), grid, dim3(256), 0, s, tm, tables, b.batch, g.sum_dim, b.d_offsets,
-                       b.loc, b.ovf, g.ovf_stride, out, b.argpos, b.cnt);
+                       b.loc, b.ovf, g.ovf_stride, out, b.wins, g.win_stride, b.cnt);
   else
     hipLaunchKernelGGL((forward_kernel<DT, G>), grid, dim3(256), 0, s, tm, tables, b.batch, g.sum_dim, b.d_offsets,
                        b.loc, b.ovf, g.ovf_stride, b.mean ? b.inv_len : nullptr, out, b.cnt);
@@ -1056,12 +1231,17 @@ static void bwd_one(int which, const TableMeta *tm, int cls, const int32_t *tabl
       hipLaunchKernelGGL((backward_heavy_kernel<DT, G>), dim3(1024), dim3(kHeavyThreads), 0, s, tm, cls, b.batch, g.sum_dim,
                          b.hchunks, b.heavy, b.heavy_sub, b.hperm, b.hstart, b.run_off, b.sorted_bag, grad_out, partials, g.partial_stride,
                          table_class, b.mean ? b.inv_len : nullptr, b.cnt);
+  } else if (which == kBwdHeavy && b.maxp && G >= 8) {
+    if constexpr (G >= 8)
+      hipLaunchKernelGGL((backward_long_max_kernel<DT, G>), dim3(4096), dim3(1024), 0, s, tm, cls, b.batch, g.sum_dim, b.heavy,
+                         b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off, b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf,
+                         g.ovf_stride, table_class, Wins{b.wins, g.win_stride, b.sorted_pos}, b.cnt);
   } else if (which == kBwdHeavy) {
     auto kern = b.maxp ? backward_long_kernel<DT, G, kMax>
                 : b.mean ? backward_long_kernel<DT, G, kMean> : backward_long_kernel<DT, G, kSum>;
     hipLaunchKernelGGL(kern, dim3(8192), dim3(256), 0, s, tm, cls, b.batch, g.sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab,
                        b.run_off, b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf, g.ovf_stride, table_class,
-                       b.mean ? b.inv_len : nullptr, b.argpos, b.sorted_within, b.cnt);
+                       b.mean ? b.inv_len : nullptr, Wins{b.wins, g.win_stride, b.sorted_pos}, b.cnt);
   } else if (which == kBwdCombine) {
     if (tiled)
       hipLaunchKernelGGL((backward_combine_kernel<DT, G>), dim3(2048), dim3(256), 0, s, tm, cls, b.heavy, b.heavy_sub, b.harrive,
@@ -1072,7 +1252,7 @@ static void bwd_one(int which, const TableMeta *tm, int cls, const int32_t *tabl
                 : b.mean ? backward_short_kernel<DT, G, kMean> : backward_short_kernel<DT, G, kSum>;
     hipLaunchKernelGGL(kern, dim3(4096), dim3(256), 0, s, tm, cls, b.batch, g.sum_dim, b.mid_idx, b.uniq_key, b.uniq_tab,
                        b.run_off, b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf, g.ovf_stride, table_class,
-                       b.mean ? b.inv_len : nullptr, b.argpos, b.sorted_within, b.cnt);
+                       b.mean ? b.inv_len : nullptr, Wins{b.wins, g.win_stride, b.sorted_pos}, b.cnt);
   }
 }
 
@@ -1083,7 +1263,7 @@ static void bwd_single_one(const TableMeta *tm, const int32_t *tables, int count
   dim3 grid((b.batch + bags_per_block - 1) / bags_per_block, count);
   if (b.maxp)
     hipLaunchKernelGGL((backward_single_max_kernel<DT, G>), grid, dim3(256), 0, s, tm, tables, b.batch, g.sum_dim,
-                       b.byp_key, b.d_offsets, b.loc, grad_out, lr, eps, b.ovf, g.ovf_stride, b.argpos, b.cnt);
+                       b.byp_key, b.d_offsets, b.loc, grad_out, lr, eps, b.ovf, g.ovf_stride, b.wins, g.win_stride, b.cnt);
   else
     hipLaunchKernelGGL((backward_single_kernel<DT, G>), grid, dim3(256), 0, s, tm, tables, b.batch, g.sum_dim, b.byp_key,
                        b.d_offsets, b.loc, grad_out, lr, eps, b.ovf, g.ovf_stride, b.mean ? b.inv_len : nullptr, b.cnt);
@@ -1119,6 +1299,22 @@ hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, cons
   if (b.batch == 0) return hipSuccess;
   for (int c = 0; c < ci.n_classes; c++)
     TBE_DISPATCH(ci.cls_dtype[c], ci.cls_lanes[c], (fwd_one<d, l>(tm, ci.cls_tables[c], ci.cls_count[c], g, b, out, s)));
+  return hipGetLastError();
+}
+
+template <int DT, int G>
+static void argmax_one(const TableMeta *tm, const int32_t *tables, int count, const Geometry &g, const BatchBuf &b,
+                       int32_t *argmax, hipStream_t s) {
+  const int bags_per_block = 256 / G;
+  hipLaunchKernelGGL((argmax_kernel<DT, G>), dim3((b.batch + bags_per_block - 1) / bags_per_block, count), dim3(256), 0, s, tm,
+                     tables, b.batch, g.sum_dim, b.d_offsets, b.wins, g.win_stride, argmax, b.cnt);
+}
+
+hipError_t launch_argmax_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
+                                 int32_t *argmax, hipStream_t s) {
+  if (b.batch == 0) return hipSuccess;
+  for (int c = 0; c < ci.n_classes; c++)
+    TBE_DISPATCH(ci.cls_dtype[c], ci.cls_lanes[c], (argmax_one<d, l>(tm, ci.cls_tables[c], ci.cls_count[c], g, b, argmax, s)));
   return hipGetLastError();
 }
 

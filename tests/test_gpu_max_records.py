@@ -1,0 +1,20 @@
+"""Max pooling: the lookups' records of the maxima they supplied, and the kernel that gives a row's chains of lookups a
+wavefront each: every number of lanes per row, rows with 65 to thousands of lookups (one chunk a chain to many, ragged
+ends), and the exported positions, which the parity driver compares element by element."""
+import pytest
+
+from paper_2305_01515_amd import synth
+from parity_util import run_parity
+
+pytestmark = pytest.mark.gpu
+T = synth.TableCfg
+
+
+@pytest.mark.parametrize("dim,dtype", [(4, synth.FP32), (8, synth.FP32), (16, synth.FP32), (20, synth.FP32), (32, synth.FP32),
+                                       (64, synth.FP32), (100, synth.FP32), (256, synth.FP32), (8, synth.FP16), (64, synth.FP16),
+                                       (128, synth.FP16), (200, synth.FP16), (512, synth.FP16)])
+def test_rows_of_every_width_and_length(dim, dtype):
+    tabs = [T(900, dim, dtype, 1.3, "poisson", 9, 0, 60, cache_slots=16 * 9), T(3, 16, dtype, None, "fixed", 2, cache_slots=16),
+            T(1, dim, dtype, None, "fixed", 1)]
+    run_parity(synth.WorkloadCfg("rec", tabs, batch=523, ways=16, steps=3, seed=dim, init_std=0.05, lr=0.05), steps=3,
+               order="early", pooling="max")
