@@ -739,6 +739,7 @@ int tbe_set_prefetch_depth(tbe_handle h, int32_t depth) {
     int rc = alloc_batchbuf(h, h->buf[i], h->max_lookups);
     if (rc) return rc;
     if (h->pooling == TBE_POOL_MAX) {
+      HIP_TRY(h, h->mem.get(&h->buf[i].argpos, 4 * (size_t)h->max_batch * (size_t)h->g.sum_dim));
       HIP_TRY(h, h->mem.get(&h->buf[i].wins, (size_t)h->g.win_stride * (size_t)std::max<int64_t>(h->max_lookups, 1)));
       HIP_TRY(h, h->mem.get(&h->buf[i].sorted_pos, 4 * (size_t)std::max<int64_t>(h->max_lookups, 1)));
     }
@@ -1108,8 +1109,9 @@ int tbe_set_pooling(tbe_handle h, int32_t pooling) {
   if (pooling != TBE_POOL_SUM && pooling != TBE_POOL_MEAN && pooling != TBE_POOL_MAX)
     return fail(h, TBE_EINVAL, "set_pooling: unknown pooling mode");
   if (h->k != 0) return fail(h, TBE_EORDER, "set_pooling: batches have been prefetched already");
-  if (pooling == TBE_POOL_MAX && !h->buf[0].wins) {  // the maxima every lookup supplied, and the lookups' positions by sorted order
+  if (pooling == TBE_POOL_MAX && !h->buf[0].argpos) {  // who supplied each maximum, by element and by lookup, and the lookups' positions by sorted order
     for (int i = 0; i < h->nbuf; i++) {
+      HIP_TRY(h, h->mem.get(&h->buf[i].argpos, 4 * (size_t)h->max_batch * (size_t)h->g.sum_dim));
       HIP_TRY(h, h->mem.get(&h->buf[i].wins, (size_t)h->g.win_stride * (size_t)std::max<int64_t>(h->max_lookups, 1)));
       HIP_TRY(h, h->mem.get(&h->buf[i].sorted_pos, 4 * (size_t)std::max<int64_t>(h->max_lookups, 1)));
     }
@@ -1124,7 +1126,7 @@ int tbe_export_argmax(tbe_handle h, int32_t *d_argmax) {
   if (h->pooling != TBE_POOL_MAX) return fail(h, TBE_EORDER, "export_argmax: the pooling mode is not max");
   if (h->current < 0) return fail(h, TBE_EORDER, "export_argmax: no forwarded batch waits for its update");
   const BatchBuf &b = h->buf[h->current];
-  HIP_TRY(h, launch_argmax_classes(h->d_tm, h->ci, h->g, b, d_argmax, h->cs));
+  HIP_TRY(h, hipMemcpyAsync(d_argmax, b.argpos, 4 * (size_t)b.batch * (size_t)h->g.sum_dim, hipMemcpyDeviceToDevice, h->cs));
   return TBE_OK;
 }
 

@@ -180,8 +180,9 @@ __global__ __launch_bounds__(256) void forward_kernel(const TableMeta *__restric
 }
 
 // Max pooling (Section 2.1.1): element d of the pooled vector is the largest element d among the
-// bag's rows, supplied by one lookup -- the first one when several tie (lookups are visited in bag order); the
-// pooled vector of an empty bag is zero.  The backward sends the element's gradient there, so every lookup gets a
+// bag's rows; `argpos` records, per pooled element, the position inside the bag of the lookup
+// that supplied it -- the first one when several tie (lookups are visited in bag order), -1 for
+// an empty bag, whose pooled vector is zero.  The backward sends the element's gradient there, so every lookup gets a
 // record of the elements it supplied, a bit each (`wins`): a byte per lane of the row.
 template <int DT, int G>
 __global__ __launch_bounds__(256) void forward_max_kernel(const TableMeta *__restrict__ tm,
@@ -189,7 +190,8 @@ __global__ __launch_bounds__(256) void forward_max_kernel(const TableMeta *__res
                                                           const int64_t *__restrict__ offsets,
                                                           const uint32_t *__restrict__ loc,
                                                           const char *__restrict__ ovf, uint32_t ovf_stride,
-                                                          float *__restrict__ out, uint8_t *__restrict__ wins, int win_stride,
+                                                          float *__restrict__ out, int32_t *__restrict__ argpos,
+                                                          uint8_t *__restrict__ wins, int win_stride,
                                                           const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
   constexpr int R = G < 4 ? G : 4;
@@ -237,8 +239,12 @@ __global__ __launch_bounds__(256) void forward_max_kernel(const TableMeta *__res
   }
   if (active) {
     float *o = out + (size_t)b * sum_dim + m.col + lig * EPL;
+    int32_t *a = argpos + (size_t)b * sum_dim + m.col + lig * EPL;
 #pragma unroll
-    for (int e = 0; e < EPL; e += 4) *(float4 *)(o + e) = make_float4(best[e], best[e + 1], best[e + 2], best[e + 3]);
+    for (int e = 0; e < EPL; e += 4) {
+      *(float4 *)(o + e) = make_float4(best[e], best[e + 1], best[e + 2], best[e + 3]);
+      *(int4 *)(a + e) = make_int4(who[e], who[e + 1], who[e + 2], who[e + 3]);
+    }
     uint8_t *w = wins + (size_t)lo * win_stride + lig;
     const int len = (int)(hi - lo);
     for (int p = 0; p < len; p++) {
@@ -248,34 +254,6 @@ __global__ __launch_bounds__(256) void forward_max_kernel(const TableMeta *__res
       w[(size_t)p * win_stride] = (uint8_t)bits;
     }
   }
-}
-
-// The positions inside their bags of the lookups that supplied the maxima, from the lookups' records.
-template <int DT, int G>
-__global__ __launch_bounds__(256) void argmax_kernel(const TableMeta *__restrict__ tm, const int32_t *__restrict__ class_tables,
-                                                     int B, int sum_dim, const int64_t *__restrict__ offsets,
-                                                     const uint8_t *__restrict__ wins, int win_stride,
-                                                     int32_t *__restrict__ argmax, const BatchCounters *cnt) {
-  constexpr int EPL = Elems<DT>::n;
-  if (cnt->err) return;
-  const int t = class_tables[blockIdx.y];
-  const TableMeta &m = tm[t];
-  const int b = blockIdx.x * (256 / G) + threadIdx.x / G;
-  const int lig = threadIdx.x % G;
-  if (b >= B || lig * EPL >= m.dim) return;
-  const int64_t lo = offsets[(int64_t)t * B + b], hi = offsets[(int64_t)t * B + b + 1];
-  int who[EPL];
-#pragma unroll
-  for (int e = 0; e < EPL; e++) who[e] = -1;
-  for (int64_t j = lo; j < hi; j++) {
-    const uint32_t bits = wins[(size_t)j * win_stride + lig];
-#pragma unroll
-    for (int e = 0; e < EPL; e++)
-      if (bits >> e & 1u) who[e] = (int)(j - lo);
-  }
-  int32_t *a = argmax + (size_t)b * sum_dim + m.col + lig * EPL;
-#pragma unroll
-  for (int e = 0; e < EPL; e++) a[e] = who[e];
 }
 
 // --------------------------------------------------------------------------------------
@@ -1213,7 +1191,7 @@ static void fwd_one(const TableMeta *tm, const int32_t *tables, int count, const
   dim3 grid((b.batch + bags_per_block - 1) / bags_per_block, count);
   if (b.maxp)
     hipLaunchKernelGGL((forward_max_kernel<DT, G>), grid, dim3(256), 0, s, tm, tables, b.batch, g.sum_dim, b.d_offsets,
-                       b.loc, b.ovf, g.ovf_stride, out, b.wins, g.win_stride, b.cnt);
+                       b.loc, b.ovf, g.ovf_stride, out, b.argpos, b.wins, g.win_stride, b.cnt);
   else
     hipLaunchKernelGGL((forward_kernel<DT, G>), grid, dim3(256), 0, s, tm, tables, b.batch, g.sum_dim, b.d_offsets,
                        b.loc, b.ovf, g.ovf_stride, b.mean ? b.inv_len : nullptr, out, b.cnt);
@@ -1299,22 +1277,6 @@ hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, cons
   if (b.batch == 0) return hipSuccess;
   for (int c = 0; c < ci.n_classes; c++)
     TBE_DISPATCH(ci.cls_dtype[c], ci.cls_lanes[c], (fwd_one<d, l>(tm, ci.cls_tables[c], ci.cls_count[c], g, b, out, s)));
-  return hipGetLastError();
-}
-
-template <int DT, int G>
-static void argmax_one(const TableMeta *tm, const int32_t *tables, int count, const Geometry &g, const BatchBuf &b,
-                       int32_t *argmax, hipStream_t s) {
-  const int bags_per_block = 256 / G;
-  hipLaunchKernelGGL((argmax_kernel<DT, G>), dim3((b.batch + bags_per_block - 1) / bags_per_block, count), dim3(256), 0, s, tm,
-                     tables, b.batch, g.sum_dim, b.d_offsets, b.wins, g.win_stride, argmax, b.cnt);
-}
-
-hipError_t launch_argmax_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
-                                 int32_t *argmax, hipStream_t s) {
-  if (b.batch == 0) return hipSuccess;
-  for (int c = 0; c < ci.n_classes; c++)
-    TBE_DISPATCH(ci.cls_dtype[c], ci.cls_lanes[c], (argmax_one<d, l>(tm, ci.cls_tables[c], ci.cls_count[c], g, b, argmax, s)));
   return hipGetLastError();
 }
 

@@ -121,8 +121,10 @@ struct BatchBuf {
   float *inv_len;       // [T * batch] mean pooling: 1 / lookups of the bag (0 for an empty bag)
   bool mean;            // mean pooling instead of sum: forward and backward weigh by inv_len
   bool maxp;            // max pooling: forward records who supplied each maximum, backward sends the gradient there
+  int32_t *argpos;      // [batch * sum_dim] max pooling: position inside its bag of the lookup that supplied the
+                        //     maximum of each pooled element (-1 for an empty bag); null unless max pooling is set
   uint8_t *wins;        // [N * win_stride] max pooling: which elements of its row a lookup supplied the maximum of, input
-                        //     order: byte l for the elements of lane l, bit e for the lane's e-th; null unless max pooling is set
+                        //     order: byte l for the elements of lane l, bit e for the lane's e-th
   uint32_t *sorted_pos; // [N] max pooling: position (input order) of the i-th lookup in sorted order
   uint32_t *uid_sorted; // [N] index of the distinct row of the i-th sorted lookup
   // per distinct row (ascending key)
@@ -387,9 +389,6 @@ hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *t
                         unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
 hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
                                   float *out, hipStream_t s);
-// max pooling: position inside its bag of the lookup that supplied each maximum, -1 for an empty bag
-hipError_t launch_argmax_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
-                                 int32_t *argmax, hipStream_t s);
 hipError_t launch_backward_single_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
                                           const float *grad_out, float lr, float eps, hipStream_t s);
 // which: kBwdHeavy (tile kernel; under max pooling the workgroup-per-row kernel instead), kBwdCombine (sums of the

@@ -1,6 +1,6 @@
 """Max pooling: the lookups' records of the maxima they supplied, and the kernel that gives a row's chains of lookups a
 wavefront each: every number of lanes per row, rows with 65 to thousands of lookups (one chunk a chain to many, ragged
-ends), and the exported positions, which the parity driver compares element by element."""
+ends)."""
 import pytest
 
 from paper_2305_01515_amd import synth
