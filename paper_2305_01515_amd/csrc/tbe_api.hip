@@ -829,36 +829,31 @@ static int backward_update_with(tbe_ctx *h, const float *d_grad_out, float lr, f
   if (!d_grad_out) return fail(h, TBE_EINVAL, "backward_update: null gradient");
   if (h->current < 0) return fail(h, TBE_EORDER, "backward_update: no forwarded batch");
   const int bi = h->current;
-  // The four kernels touch disjoint rows and run one after the other.  (The heavy rows' tile kernel and its
-  // combine on a stream of their own, beside the other two: the tile kernel's workgroups need a CU to
-  // themselves each and waited for the others' waves to drain -- 0.28 ms instead of 0.12 alone, the whole
-  // backward 0.51 ms instead of 0.48, and 0.72 instead of 0.65 ms beside the other streams' work.)
+  // The sections touch disjoint rows; the combine follows the heavy rows' kernel.  Small batches: that kernel, then
+  // everything else in one launch.  With more lookups the rows with one and with 2..64 lookups first, the heavy rows' kernel
+  // and the combine last: 0.471 ms alone against 0.479 with the tile kernel first (it takes 0.124 instead of 0.134 ms when
+  // it does not follow the forward), 0.627 against 0.635 ms beside the other streams.  (The heavy rows on a stream of their
+  // own, beside the others: the tile kernel's workgroups need a CU to themselves each and waited for the others' waves to
+  // drain -- 0.28 ms instead of 0.12 alone, the whole backward 0.51 ms instead of 0.48, and 0.72 instead of 0.65 ms beside
+  // the other streams' work.)  With every section bracketed each has a launch of its own.
   {
     StageTimer all_(h, TBE_STAGE_BACKWARD, h->cs);
-    auto heavy = [&]() -> int {
-      {
-        StageTimer tm_(h, TBE_STAGE_BACKWARD_HEAVY, h->cs);
-        HIP_TRY(h, launch_backward_classes(kBwdHeavy, h->d_tm, h->ci, h->g, h->buf[bi], d_grad_out, partials, lr, eps, h->cs));
-      }
-      StageTimer tm_(h, TBE_STAGE_BACKWARD_COMBINE, h->cs);
-      HIP_TRY(h, launch_backward_classes(kBwdCombine, h->d_tm, h->ci, h->g, h->buf[bi], d_grad_out, partials, lr, eps, h->cs));
+    auto run = [&](int which, int stage) -> int {
+      StageTimer tm_(h, stage, h->cs);
+      HIP_TRY(h, launch_backward_classes(which, h->d_tm, h->ci, h->g, h->buf[bi], d_grad_out, partials, lr, eps, h->cs));
       return TBE_OK;
     };
-    auto single = [&]() -> int {
-      StageTimer tm_(h, TBE_STAGE_BACKWARD_SINGLE, h->cs);
-      HIP_TRY(h, launch_backward_single_classes(h->d_tm, h->ci, h->g, h->buf[bi], d_grad_out, lr, eps, h->cs));
-      return TBE_OK;
-    };
-    auto shortk = [&]() -> int {
-      StageTimer tm_(h, TBE_STAGE_BACKWARD_SHORT, h->cs);
-      HIP_TRY(h, launch_backward_classes(kBwdShort, h->d_tm, h->ci, h->g, h->buf[bi], d_grad_out, partials, lr, eps, h->cs));
-      return TBE_OK;
-    };
-    // single-lookup rows first, the heavy rows' tile kernel last: 0.471 ms alone against 0.479 with the tile kernel
-    // first (it takes 0.124 instead of 0.134 ms when it does not follow the forward), 0.627 against 0.635 ms beside
-    // the other streams; the other orders lie between
     int rc;
-    if ((rc = single()) || (rc = shortk()) || (rc = heavy())) return rc;
+    if (h->profiling == 1)
+      rc = (rc = run(kBwdSingle, TBE_STAGE_BACKWARD_SINGLE)) ? rc : (rc = run(kBwdShort, TBE_STAGE_BACKWARD_SHORT)) ? rc
+           : (rc = run(kBwdHeavy, TBE_STAGE_BACKWARD_HEAVY)) ? rc : run(kBwdCombine, TBE_STAGE_BACKWARD_COMBINE);
+    else if (h->buf[bi].n <= kSmallLookups)
+      rc = (rc = run(kBwdHeavy, TBE_STAGE_BACKWARD_HEAVY)) ? rc
+           : run(kBwdCombine | kBwdSingle | kBwdShort, TBE_STAGE_BACKWARD_SHORT);
+    else
+      rc = (rc = run(kBwdSingle | kBwdShort, TBE_STAGE_BACKWARD_SHORT)) ? rc : (rc = run(kBwdHeavy, TBE_STAGE_BACKWARD_HEAVY)) ? rc
+           : run(kBwdCombine, TBE_STAGE_BACKWARD_COMBINE);
+    if (rc) return rc;
   }
   h->current = -1;
   if (h->as != h->cs) {

@@ -460,20 +460,18 @@ __device__ inline void update_row(const TableMeta &m, uint32_t key, int slot, ch
 // lookups, updating the rows flagged kLocSingle, four rows in flight at a time.  No
 // per-lookup gradient read at all.
 template <int DT, int G>
-__global__ __launch_bounds__(256) void backward_single_kernel(const TableMeta *__restrict__ tm,
+__device__ inline void update_single_rows(int blk, int blocks_per_table, const TableMeta *__restrict__ tm,
                                                               const int32_t *__restrict__ class_tables, int B,
                                                               int sum_dim, const uint32_t *__restrict__ byp_key,
                                                               const int64_t *__restrict__ offsets,
                                                               const uint32_t *__restrict__ loc,
                                                               const float *__restrict__ grad_out, float lr, float eps,
                                                               char *__restrict__ ovf, uint32_t ovf_stride,
-                                                              const float *__restrict__ inv_len,
-                                                              const BatchCounters *cnt) {
+                                                              const float *__restrict__ inv_len) {
   constexpr int EPL = Elems<DT>::n;
-  if (cnt->err) return;
-  const int t = class_tables[blockIdx.y];
+  const int t = class_tables[blk / blocks_per_table];
   const TableMeta &m = tm[t];
-  const int b = blockIdx.x * (256 / G) + threadIdx.x / G;
+  const int b = blk % blocks_per_table * (256 / G) + threadIdx.x / G;
   const int lig = threadIdx.x % G;
   if (b >= B) return;
   const int64_t lo = offsets[(int64_t)t * B + b], hi = offsets[(int64_t)t * B + b + 1];
@@ -545,20 +543,18 @@ __global__ __launch_bounds__(256) void backward_single_kernel(const TableMeta *_
 // differ from row to row.  Rows with exactly one lookup in the batch, bag by bag, the bag's
 // gradient slice in registers.
 template <int DT, int G>
-__global__ __launch_bounds__(256) void backward_single_max_kernel(const TableMeta *__restrict__ tm,
+__device__ inline void update_single_rows_max(int blk, int blocks_per_table, const TableMeta *__restrict__ tm,
                                                               const int32_t *__restrict__ class_tables, int B,
                                                               int sum_dim, const uint32_t *__restrict__ byp_key,
                                                               const int64_t *__restrict__ offsets,
                                                               const uint32_t *__restrict__ loc,
                                                               const float *__restrict__ grad_out, float lr, float eps,
                                                               char *__restrict__ ovf, uint32_t ovf_stride,
-                                                              const uint8_t *__restrict__ wins, int win_stride,
-                                                              const BatchCounters *cnt) {
+                                                              const uint8_t *__restrict__ wins, int win_stride) {
   constexpr int EPL = Elems<DT>::n;
-  if (cnt->err) return;
-  const int t = class_tables[blockIdx.y];
+  const int t = class_tables[blk / blocks_per_table];
   const TableMeta &m = tm[t];
-  const int b = blockIdx.x * (256 / G) + threadIdx.x / G;
+  const int b = blk % blocks_per_table * (256 / G) + threadIdx.x / G;
   const int lig = threadIdx.x % G;
   if (b >= B) return;
   const int64_t lo = offsets[(int64_t)t * B + b], hi = offsets[(int64_t)t * B + b + 1];
@@ -629,7 +625,7 @@ __global__ __launch_bounds__(256) void backward_single_max_kernel(const TableMet
 // Rows with 2..kLongRun lookups: one group of G lanes per distinct row, gradients summed
 // in sorted (= ascending bag) order.
 template <int DT, int G, int MODE>
-__global__ __launch_bounds__(256) void backward_short_kernel(const TableMeta *__restrict__ tm, int cls, int B,
+__device__ inline void update_short_rows(int blk, int blocks, const TableMeta *__restrict__ tm, int cls, int B,
                                                              int sum_dim, const int32_t *__restrict__ mid_idx,
                                                              const uint32_t *__restrict__ uniq_key,
                                                              const int32_t *__restrict__ uniq_tab,
@@ -642,11 +638,10 @@ __global__ __launch_bounds__(256) void backward_short_kernel(const TableMeta *__
                                                              const float *__restrict__ inv_len,
                                                              Wins wins, const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
-  if (cnt->err) return;
   const int n_mid = cnt->n_mid;
   const int lig = threadIdx.x % G;
   int first, end, step;
-  xcd_span(n_mid, 256 / G, first, end, step);  // the list is in table order
+  xcd_span_of(blk, blocks, n_mid, 256 / G, first, end, step);  // the list is in table order
   for (int i = first + threadIdx.x / G; i < end; i += step) {
     const int u = mid_idx[i];
     const int t = uniq_tab[u];
@@ -1097,9 +1092,8 @@ __global__ __launch_bounds__(kHeavyThreads) void backward_heavy_kernel(const Tab
 // sums of one row from which its parts are added up side by side (128: the hot rows of a heterogeneous model pay
 // for the fences beside the other streams, its backward 4.6 -> 5.0 ms; 2048: a chain of 2047 sums takes 0.2 ms)
 constexpr int kCombineChain = 512;
-constexpr int kCombineLoads = 8;  // partial sums a lane group has in flight (4: a chain of 500 sums 0.059 ms, 8: 0.049 ms)
-template <int DT, int G>
-__global__ __launch_bounds__(256) void backward_combine_kernel(const TableMeta *__restrict__ tm, int cls,
+template <int DT, int G, int kCombineLoads>
+__device__ inline void combine_heavy_rows(int blk, int blocks, const TableMeta *__restrict__ tm, int cls,
                                                                const int32_t *__restrict__ heavy,
                                                                const int32_t *__restrict__ heavy_sub,
                                                                int32_t *harrive,
@@ -1113,12 +1107,11 @@ __global__ __launch_bounds__(256) void backward_combine_kernel(const TableMeta *
                                                                const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
   constexpr int NG = 256 / G;
-  if (cnt->err) return;
   const int n_heavy = cnt->n_heavy;
   const int R = cnt->h_ranges;
   const int lig = threadIdx.x % G, grp = threadIdx.x / G;
   int first, end, step;
-  xcd_span(n_heavy, NG, first, end, step);  // the list is in table order
+  xcd_span_of(blk, blocks, n_heavy, NG, first, end, step);  // the list is in table order
   for (int h = first + grp; h < end; h += step) {
     // A row entered once, or a few times, is added up by the lane group of its first entry: parts x R sums in
     // the slots h * R onwards.  For a row with a third of a million lookups that is a chain of 170 parts x 208
@@ -1181,6 +1174,49 @@ __global__ __launch_bounds__(256) void backward_combine_kernel(const TableMeta *
   }
 }
 
+// The rest of the backward: workgroups [0, combine) add up the heavy rows' partial sums, the next `single` take the bags'
+// single-lookup rows, the last the rows with 2..kLongRun lookups.  The three touch disjoint rows, so any of SECT can share a
+// launch: a small batch's backward, bound by launches, is the heavy rows' kernel and this one, where it was four; with more
+// lookups the combine, whose partial sums in flight cost the others two of seven wavefronts per SIMD, keeps a launch of its
+// own (with eight sums in flight instead of four: a chain of 500 sums 0.049 instead of 0.059 ms).  Small
+// configuration: combine, single-lookup and short rows 7 + 9 + 11 -> 11 us a step; 16 x 500k resident rows: single-lookup
+// and short rows 242 -> 235 us.
+template <int DT, int G, int MODE, int SECT>
+__global__ __launch_bounds__(256) void backward_rest_kernel(int combine, int single, int blocks_per_table, int n_tables,
+                                                            const TableMeta *__restrict__ tm,
+                                                            const int32_t *__restrict__ class_tables, int cls, int B,
+                                                            int sum_dim, BatchBuf b, const float *__restrict__ grad_out,
+                                                            float *partials, int pstride, float lr, float eps,
+                                                            uint32_t ovf_stride, const int32_t *__restrict__ table_class,
+                                                            int win_stride) {
+  if (b.cnt->err) return;
+  int blk = blockIdx.x;
+  if (blk < combine) {
+    if constexpr (MODE != kMax && (SECT & kBwdCombine))
+      combine_heavy_rows<DT, G, SECT == kBwdCombine ? 8 : 4>(blk, combine, tm, cls, b.heavy, b.heavy_sub, b.harrive, b.uniq_key, b.uniq_tab, b.loc_u, partials,
+                                pstride, lr, eps, b.ovf, ovf_stride, table_class, b.cnt);
+    return;
+  }
+  if constexpr ((SECT & kBwdSingle) != 0) {
+    blk -= combine;
+    if (blk < single && blk >= blocks_per_table * n_tables) return;  // padding
+    const float *inv_len = MODE == kMean ? b.inv_len : nullptr;
+    if (blk < single) {
+      if constexpr (MODE == kMax)
+        update_single_rows_max<DT, G>(blk, blocks_per_table, tm, class_tables, B, sum_dim, b.byp_key, b.d_offsets, b.loc, grad_out,
+                                      lr, eps, b.ovf, ovf_stride, b.wins, win_stride);
+      else
+        update_single_rows<DT, G>(blk, blocks_per_table, tm, class_tables, B, sum_dim, b.byp_key, b.d_offsets, b.loc, grad_out, lr,
+                                  eps, b.ovf, ovf_stride, inv_len);
+      return;
+    }
+    blk -= single;
+    update_short_rows<DT, G, MODE>(blk, (int)gridDim.x - combine - single, tm, cls, B, sum_dim, b.mid_idx, b.uniq_key, b.uniq_tab,
+                                   b.run_off, b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf, ovf_stride, table_class, inv_len,
+                                   Wins{b.wins, win_stride, b.sorted_pos}, b.cnt);
+  }
+}
+
 // --------------------------------------------------------------------------------------
 // launchers: one launch per (storage type, G) class present in the model
 // --------------------------------------------------------------------------------------
@@ -1197,54 +1233,60 @@ static void fwd_one(const TableMeta *tm, const int32_t *tables, int count, const
                        b.loc, b.ovf, g.ovf_stride, b.mean ? b.inv_len : nullptr, out, b.cnt);
 }
 
+// workgroups for at most `n` units of work, `per` to a workgroup: a multiple of the XCDs, no more than `most`
+static int work_blocks(int64_t n, int per, int most) {
+  const int64_t want = (n + per - 1) / per;
+  return want >= most ? most : (int)((want + kXcds - 1) / kXcds * kXcds);
+}
+
+// which: sections to run (kBwdHeavy, or any of kBwdCombine | kBwdSingle | kBwdShort)
 template <int DT, int G>
-static void bwd_one(int which, const TableMeta *tm, int cls, const int32_t *table_class, const Geometry &g,
-                    const BatchBuf &b, const float *grad_out, float *partials, float lr, float eps, hipStream_t s) {
+static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int count, int cls, const int32_t *table_class,
+                    const Geometry &g, const BatchBuf &b, const float *grad_out, float *partials, float lr, float eps,
+                    hipStream_t s) {
   // The tile kernel serves rows of at least 4 lanes (64 bytes); narrower rows, whose lane groups would outnumber
   // what its bookkeeping in LDS is sized for, take the workgroup-per-row kernel, as max pooling does.
   constexpr bool kTiled = G >= 4;
   const bool tiled = kTiled && !b.maxp;
-  if (which == kBwdHeavy && tiled) {
-    if constexpr (kTiled)
-      hipLaunchKernelGGL((backward_heavy_kernel<DT, G>), dim3(1024), dim3(kHeavyThreads), 0, s, tm, cls, b.batch, g.sum_dim,
-                         b.hchunks, b.heavy, b.heavy_sub, b.hperm, b.hstart, b.run_off, b.sorted_bag, grad_out, partials, g.partial_stride,
-                         table_class, b.mean ? b.inv_len : nullptr, b.cnt);
-  } else if (which == kBwdHeavy && b.maxp && G >= 8) {
-    if constexpr (G >= 8)
-      hipLaunchKernelGGL((backward_long_max_kernel<DT, G>), dim3(4096), dim3(1024), 0, s, tm, cls, b.batch, g.sum_dim, b.heavy,
+  const int64_t most_heavy = b.n / (kLongRun + 1) + b.n / kHeavySplit;  // entries of the heavy list
+  const Wins wins{b.wins, g.win_stride, b.sorted_pos};
+  if (which & kBwdHeavy) {
+    if (most_heavy == 0) return;
+    if (tiled) {
+      if constexpr (kTiled)
+        hipLaunchKernelGGL((backward_heavy_kernel<DT, G>), dim3(b.n <= kSmallLookups ? 256 : 1024), dim3(kHeavyThreads), 0, s, tm,
+                           cls, b.batch, g.sum_dim, b.hchunks, b.heavy, b.heavy_sub, b.hperm, b.hstart, b.run_off, b.sorted_bag,
+                           grad_out, partials, g.partial_stride, table_class, b.mean ? b.inv_len : nullptr, b.cnt);
+    } else if (b.maxp && G >= 8) {
+      if constexpr (G >= 8)
+        hipLaunchKernelGGL((backward_long_max_kernel<DT, G>), dim3(work_blocks(most_heavy, 1, 4096)), dim3(1024), 0, s, tm, cls,
+                           b.batch, g.sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off, b.loc_u, b.sorted_bag,
+                           grad_out, lr, eps, b.ovf, g.ovf_stride, table_class, wins, b.cnt);
+    } else {
+      auto kern = b.maxp ? backward_long_kernel<DT, G, kMax>
+                  : b.mean ? backward_long_kernel<DT, G, kMean> : backward_long_kernel<DT, G, kSum>;
+      hipLaunchKernelGGL(kern, dim3(work_blocks(most_heavy, 1, 8192)), dim3(256), 0, s, tm, cls, b.batch, g.sum_dim, b.heavy,
                          b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off, b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf,
-                         g.ovf_stride, table_class, Wins{b.wins, g.win_stride, b.sorted_pos}, b.cnt);
-  } else if (which == kBwdHeavy) {
-    auto kern = b.maxp ? backward_long_kernel<DT, G, kMax>
-                : b.mean ? backward_long_kernel<DT, G, kMean> : backward_long_kernel<DT, G, kSum>;
-    hipLaunchKernelGGL(kern, dim3(8192), dim3(256), 0, s, tm, cls, b.batch, g.sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab,
-                       b.run_off, b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf, g.ovf_stride, table_class,
-                       b.mean ? b.inv_len : nullptr, Wins{b.wins, g.win_stride, b.sorted_pos}, b.cnt);
-  } else if (which == kBwdCombine) {
-    if (tiled)
-      hipLaunchKernelGGL((backward_combine_kernel<DT, G>), dim3(2048), dim3(256), 0, s, tm, cls, b.heavy, b.heavy_sub, b.harrive,
-                         b.uniq_key, b.uniq_tab, b.loc_u, partials, g.partial_stride, lr, eps, b.ovf, g.ovf_stride, table_class,
-                         b.cnt);
-  } else {
-    auto kern = b.maxp ? backward_short_kernel<DT, G, kMax>
-                : b.mean ? backward_short_kernel<DT, G, kMean> : backward_short_kernel<DT, G, kSum>;
-    hipLaunchKernelGGL(kern, dim3(4096), dim3(256), 0, s, tm, cls, b.batch, g.sum_dim, b.mid_idx, b.uniq_key, b.uniq_tab,
-                       b.run_off, b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf, g.ovf_stride, table_class,
-                       b.mean ? b.inv_len : nullptr, Wins{b.wins, g.win_stride, b.sorted_pos}, b.cnt);
+                         g.ovf_stride, table_class, b.mean ? b.inv_len : nullptr, wins, b.cnt);
+    }
+    return;
   }
-}
-
-template <int DT, int G>
-static void bwd_single_one(const TableMeta *tm, const int32_t *tables, int count, const Geometry &g, const BatchBuf &b,
-                           const float *grad_out, float lr, float eps, hipStream_t s) {
-  const int bags_per_block = 256 / G;
-  dim3 grid((b.batch + bags_per_block - 1) / bags_per_block, count);
-  if (b.maxp)
-    hipLaunchKernelGGL((backward_single_max_kernel<DT, G>), grid, dim3(256), 0, s, tm, tables, b.batch, g.sum_dim,
-                       b.byp_key, b.d_offsets, b.loc, grad_out, lr, eps, b.ovf, g.ovf_stride, b.wins, g.win_stride, b.cnt);
-  else
-    hipLaunchKernelGGL((backward_single_kernel<DT, G>), grid, dim3(256), 0, s, tm, tables, b.batch, g.sum_dim, b.byp_key,
-                       b.d_offsets, b.loc, grad_out, lr, eps, b.ovf, g.ovf_stride, b.mean ? b.inv_len : nullptr, b.cnt);
+  const int per = 256 / G;  // lane groups of a workgroup
+  const int blocks_per_table = (b.batch + per - 1) / per;
+  const int combine = (which & kBwdCombine) && tiled ? work_blocks(most_heavy, per, 2048) : 0;
+  // (padded, so that the workgroups behind it keep their XCDs)
+  const int single = (which & kBwdSingle) ? (blocks_per_table * count + kXcds - 1) / kXcds * kXcds : 0;
+  const int shrt = (which & kBwdShort) ? work_blocks(b.n / 2, per, 4096) : 0;
+  if (combine + single + shrt == 0) return;
+  constexpr int kRows = kBwdSingle | kBwdShort;
+  const bool rows = single + shrt > 0;
+  auto kern = !rows ? (b.mean ? backward_rest_kernel<DT, G, kMean, kBwdCombine> : backward_rest_kernel<DT, G, kSum, kBwdCombine>)
+              : b.maxp ? backward_rest_kernel<DT, G, kMax, kRows>
+              : combine ? (b.mean ? backward_rest_kernel<DT, G, kMean, kRows | kBwdCombine> : backward_rest_kernel<DT, G, kSum, kRows | kBwdCombine>)
+                        : (b.mean ? backward_rest_kernel<DT, G, kMean, kRows> : backward_rest_kernel<DT, G, kSum, kRows>);
+  hipLaunchKernelGGL(kern, dim3(combine + single + shrt), dim3(256), 0, s, combine, single, blocks_per_table, count, tm, tables, cls,
+                     b.batch, g.sum_dim, b, grad_out, partials, g.partial_stride, lr, eps, g.ovf_stride, table_class,
+                     g.win_stride);
 }
 
 #define TBE_DISPATCH(DT, LANES, CALL)                         \
@@ -1280,24 +1322,14 @@ hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, cons
   return hipGetLastError();
 }
 
-hipError_t launch_backward_single_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
-                                          const float *grad_out, float lr, float eps, hipStream_t s) {
-  if (b.n == 0 || b.batch == 0) return hipSuccess;
-  for (int c = 0; c < ci.n_classes; c++)
-    TBE_DISPATCH(ci.cls_dtype[c], ci.cls_lanes[c],
-                 (bwd_single_one<d, l>(tm, ci.cls_tables[c], ci.cls_count[c], g, b, grad_out, lr, eps, s)));
-  return hipGetLastError();
-}
-
-// A step runs the heavy kernel, the combine, the single-lookup kernel and the short kernel; they
-// touch disjoint rows (the combine after the heavy kernel).
+// A step runs the heavy rows' kernel, then the rest; they touch disjoint rows (but for the combine, which follows it).
 hipError_t launch_backward_classes(int which, const TableMeta *tm, const ClassInfo &ci, const Geometry &g,
                                    const BatchBuf &b, const float *grad_out, float *partials, float lr, float eps,
                                    hipStream_t s) {
-  if (b.n == 0) return hipSuccess;
+  if (b.n == 0 || b.batch == 0) return hipSuccess;
   for (int c = 0; c < ci.n_classes; c++)
     TBE_DISPATCH(ci.cls_dtype[c], ci.cls_lanes[c],
-                 (bwd_one<d, l>(which, tm, c, ci.table_class, g, b, grad_out, partials, lr, eps, s)));
+                 (bwd_one<d, l>(which, tm, ci.cls_tables[c], ci.cls_count[c], c, ci.table_class, g, b, grad_out, partials, lr, eps, s)));
   return hipGetLastError();
 }
 

@@ -389,11 +389,10 @@ hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *t
                         unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
 hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
                                   float *out, hipStream_t s);
-hipError_t launch_backward_single_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
-                                          const float *grad_out, float lr, float eps, hipStream_t s);
-// which: kBwdHeavy (tile kernel; under max pooling the workgroup-per-row kernel instead), kBwdCombine (sums of the
-// tile kernel's partial sums + update; nothing under max pooling), kBwdShort (rows with 2..kLongRun lookups)
-constexpr int kBwdHeavy = 0, kBwdCombine = 1, kBwdShort = 2;
+// which: kBwdHeavy (tile kernel; under max pooling the workgroup-per-row kernel instead), or any of kBwdCombine (sums of the
+// tile kernel's partial sums + update; nothing under max pooling), kBwdSingle (rows with one lookup), kBwdShort (rows with
+// 2..kLongRun lookups) in one launch
+constexpr int kBwdHeavy = 1, kBwdCombine = 2, kBwdSingle = 4, kBwdShort = 8;
 hipError_t launch_backward_classes(int which, const TableMeta *tm, const ClassInfo &ci, const Geometry &g,
                                    const BatchBuf &b, const float *grad_out, float *partials, float lr, float eps,
                                    hipStream_t s);
