@@ -379,7 +379,7 @@ struct DedupOp {
 };
 
 // The plan of the tile kernel, from the heavy list (in table order; first_of_table[t] = position of table t's first entry,
-// first_of_table[T] = their number), in one launch:
+// first_of_table[T] = their number), by workgroups of the stage's last kernel:
 //   - every workgroup adds up the chunks of all tables (a chunk: the rows one workgroup of the tile kernel takes,
 //     heavy_chunk_rows of the table's lanes per row) and so knows the batch's number of bag ranges;
 //   - workgroup t < T writes table t's chunks and orders its entries by lookups per entry, descending, in classes of powers
@@ -389,10 +389,9 @@ struct DedupOp {
 //   - the others find, for every entry and bag range, the first sorted position of the entry's row whose bag lies in the
 //     range (the row's lookups are sorted by bag), a thread per (entry, range).
 // (As three kernels, the chunks by one workgroup and the order by one wavefront per table: 10 M rows of one table, 32 k
-// bags, beside the transfer kernel: 4 + 35 + 21 us; here 17 us.)
-constexpr int kPlanThreads = 512;
-constexpr int kPlanStartBlocks = 128;
-__global__ __launch_bounds__(kPlanThreads) void heavy_plan_kernel(const TableMeta *__restrict__ tm, int T, int B,
+// bags, beside the transfer kernel: 4 + 35 + 21 us; as one kernel of workgroups of 512 threads 17 us.)
+constexpr int kPlanThreads = 256;
+__device__ inline void plan_heavy(int blk, int blocks, const TableMeta *__restrict__ tm, int T, int B,
                                                                   const int32_t *__restrict__ first_of_table,
                                                                   const int32_t *__restrict__ heavy,
                                                                   const int32_t *__restrict__ heavy_sub,
@@ -405,7 +404,6 @@ __global__ __launch_bounds__(kPlanThreads) void heavy_plan_kernel(const TableMet
   constexpr int kWaves = kPlanThreads / kWave, kClasses = 32;
   __shared__ int s_all[kWaves], s_before[kWaves];
   __shared__ int s_base[kWaves][kClasses];
-  if (cnt->err) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n_heavy = cnt->n_heavy;
   int all = 0, before = 0;  // chunks of all tables, and of those before this workgroup's
@@ -413,7 +411,7 @@ __global__ __launch_bounds__(kPlanThreads) void heavy_plan_kernel(const TableMet
     const int per = heavy_chunk_rows(tm[t].lanes, tm[t].dtype);
     const int chunks = (first_of_table[t + 1] - first_of_table[t] + per - 1) / per;
     all += chunks;
-    if (t < (int)blockIdx.x) before += chunks;
+    if (t < blk) before += chunks;
   }
   for (int d = 32; d >= 1; d >>= 1) { all += __shfl_xor(all, d); before += __shfl_xor(before, d); }
   if (lane == 0) { s_all[wave] = all; s_before[wave] = before; }
@@ -423,13 +421,13 @@ __global__ __launch_bounds__(kPlanThreads) void heavy_plan_kernel(const TableMet
   all = before = 0;
   for (int w = 0; w < kWaves; w++) { all += s_all[w]; before += s_before[w]; }
   const int R = heavy_ranges(all, n_heavy, slot_capacity, target_items);
-  if (blockIdx.x == 0 && tid == 0) {
+  if (blk == 0 && tid == 0) {
     cnt->n_hchunks = all;
     cnt->h_ranges = R;
   }
-  if ((int)blockIdx.x >= T) {
+  if (blk >= T) {
     const int n = n_heavy * R;
-    for (int x = ((int)blockIdx.x - T) * kPlanThreads + tid; x < n; x += ((int)gridDim.x - T) * kPlanThreads) {
+    for (int x = (blk - T) * kPlanThreads + tid; x < n; x += (blocks - T) * kPlanThreads) {
       const int h = x / R, range = x % R;
       const int u = heavy[h];
       const int t = uniq_tab[u];
@@ -443,7 +441,7 @@ __global__ __launch_bounds__(kPlanThreads) void heavy_plan_kernel(const TableMet
     }
     return;
   }
-  const int t = blockIdx.x;
+  const int t = blk;
   const int first = first_of_table[t], n = first_of_table[t + 1] - first;
   if (n == 0) return;
   const int per = heavy_chunk_rows(tm[t].lanes, tm[t].dtype);
@@ -999,7 +997,8 @@ __global__ __launch_bounds__(kWave) void probe_kernel(const TableMeta *__restric
 // dealt round robin over the XCDs wrote every line from eight L2s, in eight partial pieces: 260 MB of write
 // traffic for 31 MB of words.)
 //
-// One workgroup more (the last) ends the stage: it completes the batch's counters -- evictions, lookups that hit and late
+// The first workgroups plan the heavy rows (plan_heavy; `plan` of them, a multiple of the XCDs), which needs the same lists
+// and nothing of the location words.  One workgroup more (the last) ends the stage: it completes the batch's counters -- evictions, lookups that hit and late
 // rows from the per-wavefront sums of the status pass, hits as what is left of the distinct rows -- and adds them to the
 // running totals.
 constexpr int kFinalThreads = 256;
@@ -1031,6 +1030,17 @@ __device__ inline void add_totals(BatchCounters *c, const Totals &t, const u64 *
   }
 }
 
+struct PlanArgs {
+  const TableMeta *tm;
+  int T, B;
+  const int32_t *first_of_table, *heavy, *heavy_sub, *uniq_tab, *sorted_bag;
+  uint4 *hchunks;
+  int32_t *hperm, *hstart;
+  long long slot_capacity;
+  int target_items;
+};
+static_assert(kPlanThreads == kFinalThreads, "they share a kernel");
+
 __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(int n, const uint32_t *__restrict__ pos,
                                                                  const uint32_t *__restrict__ uid_sorted,
                                                                  const int32_t *__restrict__ loc_u,
@@ -1038,7 +1048,8 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(int n, const ui
                                                                  uint32_t *__restrict__ loc,
                                                                  const int64_t *__restrict__ offsets, int within_bits,
                                                                  Totals totals, const u64 *__restrict__ tally,
-                                                                 int tally_waves, uint32_t *too_long, BatchCounters *cnt) {
+                                                                 int tally_waves, uint32_t *too_long, int plan,
+                                                                 PlanArgs pa, BatchCounters *cnt) {
   const bool last = blockIdx.x + 1 == gridDim.x;
   if (last && threadIdx.x == 0) *too_long = 0u;  // as the next batch expects it, whatever became of this one
   if (cnt->err) return;
@@ -1046,11 +1057,16 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(int n, const ui
     add_totals(cnt, totals, tally, tally_waves);
     return;
   }
+  if ((int)blockIdx.x < plan) {
+    plan_heavy(blockIdx.x, plan, pa.tm, pa.T, pa.B, pa.first_of_table, pa.heavy, pa.heavy_sub, pa.uniq_tab, run_off, pa.sorted_bag,
+               pa.hchunks, pa.hperm, pa.hstart, pa.slot_capacity, pa.target_items, cnt);
+    return;
+  }
   const bool packed = cnt->packed != 0;
   const uint32_t within_mask = (1u << within_bits) - 1u;
   constexpr int K = 4;  // lookups per thread and pass, a workgroup's width apart: their loads are in flight together
   int first, end, step;
-  xcd_span_of(blockIdx.x, gridDim.x - 1, n, kFinalThreads * K, first, end, step);
+  xcd_span_of(blockIdx.x - plan, gridDim.x - 1 - plan, n, kFinalThreads * K, first, end, step);
   for (int i0 = first + threadIdx.x; i0 < end; i0 += step) {
     uint32_t u[K], p[K], w[K], at[K];
 #pragma unroll
@@ -1079,7 +1095,7 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
   const int n = (int)b.n;
   if (n == 0) {  // nothing but the end of the stage
     hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kFinalThreads), 0, s, 0, sorted_pos, b.uid_sorted, b.loc_u, b.run_off,
-                       b.loc, b.d_offsets, g.within_bits, totals, ss.tally, 0, ss.too_long, b.cnt);
+                       b.loc, b.d_offsets, g.within_bits, totals, ss.tally, 0, ss.too_long, 0, PlanArgs{}, b.cnt);
     return hipGetLastError();
   }
   DedupOp d{tm, g.T, sorted_keys, sorted_pos, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
@@ -1102,15 +1118,15 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
               l2.on ? b.ins_dst : nullptr, l2.on ? b.l2v_src : nullptr, l2.on ? b.l2v_dst : nullptr,
               l2.on ? b.l2v_key : nullptr, ss.tally, 0u, 0u, 0ull, nullptr};
   ss.tally_waves = run_compaction(st, &b.cnt->n_uniq, 0, n, ss, small ? 1 : -1, b.cnt, s) * kScanWavesPerBlock;
-  if (!b.maxp)  // the tile kernel's chunks and range starts (max pooling takes heavy rows a workgroup each)
-    hipLaunchKernelGGL(heavy_plan_kernel, dim3(g.T + kPlanStartBlocks), dim3(kPlanThreads), 0, s, tm, g.T, b.batch, b.hfirst,
-                       b.heavy, b.heavy_sub, b.uniq_tab, b.run_off, b.sorted_bag, b.hchunks, b.hperm, b.hstart,
-                       (long long)g.partial_slots, g.heavy_target, b.cnt);
+  const PlanArgs pa{tm, g.T, b.batch, b.hfirst, b.heavy, b.heavy_sub, b.uniq_tab, b.sorted_bag, b.hchunks, b.hperm, b.hstart,
+                    (long long)g.partial_slots, g.heavy_target};
+  // (max pooling takes heavy rows a workgroup each and needs no plan; 64 or 256 workgroups look for the ranges' starts)
+  const int plan = b.maxp ? 0 : (g.T + (small ? 64 : 256) + kXcds - 1) / kXcds * kXcds;
   // a multiple of the XCDs, no more than have a pass to do, and the one that ends the stage
   int final_blocks = (n + 4 * kFinalThreads - 1) / (4 * kFinalThreads);
   final_blocks = final_blocks > TBE_FINALIZE_BLOCKS ? TBE_FINALIZE_BLOCKS : (final_blocks + kXcds - 1) / kXcds * kXcds;
-  hipLaunchKernelGGL(finalize_kernel, dim3(final_blocks + 1), dim3(kFinalThreads), 0, s, n, sorted_pos, b.uid_sorted, b.loc_u,
-                     b.run_off, b.loc, b.d_offsets, g.within_bits, totals, ss.tally, ss.tally_waves, ss.too_long, b.cnt);
+  hipLaunchKernelGGL(finalize_kernel, dim3(plan + final_blocks + 1), dim3(kFinalThreads), 0, s, n, sorted_pos, b.uid_sorted, b.loc_u,
+                     b.run_off, b.loc, b.d_offsets, g.within_bits, totals, ss.tally, ss.tally_waves, ss.too_long, plan, pa, b.cnt);
   return hipGetLastError();
 }
 
