@@ -387,6 +387,9 @@ hipError_t launch_ovf_writeback(const BatchBuf &b, const BatchBuf *parked_prev, 
                                 const uint32_t *rb_of_table, unsigned long long *bytes_d2h, hipStream_t s);
 hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const Level2 &l2,
                         unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
+// after launch_flush: the accumulators of the tables of at most max_rows rows to their host arrays
+constexpr int64_t kFlushStateRows = 262144;  // a megabyte: what the copy engine moves in the time it takes to start
+hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, int64_t max_rows, hipStream_t s);
 hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
                                   float *out, hipStream_t s);
 // which: kBwdHeavy (tile kernel; under max pooling the workgroup-per-row kernel instead), or any of kBwdCombine (sums of the
