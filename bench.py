@@ -447,7 +447,8 @@ def main():
     main32 = (args.workload == "main" and T == 32 and args.policy == "lru" and args.pooling == "sum"
               and not args.second_level and not args.deferred_init)
     fwd_traffic = measured_traffic("forward_kernel") if main32 else None
-    bwd_traffic = {k: (measured_traffic(k + "_kernel") if fwd_traffic else None) for k in BWD}
+    # (the counter summary has one figure for the kernel that holds the sections single, short and combine)
+    bwd_traffic = {k: (measured_traffic(k + "_kernel") if fwd_traffic else None) for k in ("backward_rest", "backward_heavy")}
     hit_traffic = (fwd_traffic + sum(bwd_traffic.values())) if fwd_traffic and all(bwd_traffic.values()) else None
     fill_ms = ms["fill"]
     link_gbs = max(h2d, d2h) / (fill_ms * 1e-3) / 1e9 if fill_ms else 0.0

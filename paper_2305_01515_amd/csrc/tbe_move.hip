@@ -6,10 +6,10 @@
 // the computation of the batch before).
 //
 // For the batch being prefetched (k+1), with batch k possibly still training:
-//   classify : a row wanted by k+1 whose backing-tier copy is being written in this very
+//   (the list pass of k+1, in the prefetch stage: a row wanted by k+1 whose backing-tier copy is being written in this very
 //              window is "late".  A map over the sort keys says where its current value
 //              is: in batch k's overflow copies (k bypassed it and trains on that copy)
-//              or among the victims batch k parked (k evicted it).
+//              or among the victims batch k parked (k evicted it).)
 //   transfer : victims of batch k, parked in the staging area when k was committed, go to
 //              the backing tier; at the same time the rows batch k+1 inserts or bypasses
 //              are fetched into HBM, except the late ones.  Runs on the link stream.
