@@ -693,7 +693,11 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   CREATE_TRY(h->mem.get(&h->ss.too_long, 16));
   CREATE_TRY(hipMemset(h->ss.too_long, 0, 16));
   h->ss.ticket = h->ss.too_long + 1;
-  CREATE_TRY(h->mem.get(&h->ss.said, 4 * 256 * kMaxSortPasses * (size_t)(1 + kSmallSortBlocks)));
+  {  // (the larger tiles begin at 131073 lookups, so the batch with the most workgroups need not be the largest)
+    const int most = std::max(small_sort_blocks(std::min<int64_t>(max_lookups, 131072)),
+                              small_sort_blocks(std::min<int64_t>(max_lookups, kSmallLookups)));
+    CREATE_TRY(h->mem.get(&h->ss.said, 4 * 256 * kMaxSortPasses * (size_t)(1 + most)));
+  }
   CREATE_TRY(h->mem.get(&h->ss.said_counts, 8 * 4 * (size_t)kSmallScanBlocks));
   CREATE_TRY(h->mem.get(&h->d_total, sizeof(BatchCounters)));
   CREATE_TRY(hipMemset(h->d_total, 0, sizeof(BatchCounters)));
