@@ -148,7 +148,8 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
  * (With tbe_set_prefetch_depth(D), D >= 2: while no more than D batches are prefetched-or-forwarded
  * and not yet updated; the ways of those batches are locked instead, see there.)
  * Bad offsets / out-of-range indices are detected on the device: the batch then does
- * nothing and the error is reported by the next synchronising call (and by later calls).
+ * nothing, nor does any batch prefetched behind it (whether or not the caller knows yet), and the
+ * error is reported by the next synchronising call (and by later calls).
  */
 int tbe_prefetch(tbe_handle h, const int64_t *d_indices, const int64_t *d_offsets, int32_t batch,
                  int64_t num_lookups);

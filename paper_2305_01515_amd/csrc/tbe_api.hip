@@ -693,6 +693,7 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   CREATE_TRY(h->mem.get(&h->ss.too_long, 16));
   CREATE_TRY(hipMemset(h->ss.too_long, 0, 16));
   h->ss.ticket = h->ss.too_long + 1;
+  h->ss.refused = (int32_t *)h->ss.too_long + 2;
   {  // (the larger tiles begin at 131073 lookups, so the batch with the most workgroups need not be the largest)
     const int most = std::max(small_sort_blocks(std::min<int64_t>(max_lookups, 131072)),
                               small_sort_blocks(std::min<int64_t>(max_lookups, kSmallLookups)));

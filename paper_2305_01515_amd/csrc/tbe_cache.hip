@@ -1048,10 +1048,13 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(int n, const ui
                                                                  uint32_t *__restrict__ loc,
                                                                  const int64_t *__restrict__ offsets, int within_bits,
                                                                  Totals totals, const u64 *__restrict__ tally,
-                                                                 int tally_waves, uint32_t *too_long, int plan,
+                                                                 int tally_waves, uint32_t *too_long, int32_t *refused, int plan,
                                                                  PlanArgs pa, BatchCounters *cnt) {
   const bool last = blockIdx.x + 1 == gridDim.x;
-  if (last && threadIdx.x == 0) *too_long = 0u;  // as the next batch expects it, whatever became of this one
+  if (last && threadIdx.x == 0) {
+    *too_long = 0u;  // as the next batch expects it, whatever became of this one
+    if (cnt->err && *refused == 0) *refused = cnt->err;  // (read by the first two kernels of a stage alone, long done)
+  }
   if (cnt->err) return;
   if (last) {
     add_totals(cnt, totals, tally, tally_waves);
@@ -1095,7 +1098,7 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
   const int n = (int)b.n;
   if (n == 0) {  // nothing but the end of the stage
     hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kFinalThreads), 0, s, 0, sorted_pos, b.uid_sorted, b.loc_u, b.run_off,
-                       b.loc, b.d_offsets, g.within_bits, totals, ss.tally, 0, ss.too_long, 0, PlanArgs{}, b.cnt);
+                       b.loc, b.d_offsets, g.within_bits, totals, ss.tally, 0, ss.too_long, ss.refused, 0, PlanArgs{}, b.cnt);
     return hipGetLastError();
   }
   DedupOp d{tm, g.T, sorted_keys, sorted_pos, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
@@ -1126,7 +1129,7 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
   int final_blocks = (n + 4 * kFinalThreads - 1) / (4 * kFinalThreads);
   final_blocks = final_blocks > TBE_FINALIZE_BLOCKS ? TBE_FINALIZE_BLOCKS : (final_blocks + kXcds - 1) / kXcds * kXcds;
   hipLaunchKernelGGL(finalize_kernel, dim3(plan + final_blocks + 1), dim3(kFinalThreads), 0, s, n, sorted_pos, b.uid_sorted, b.loc_u,
-                     b.run_off, b.loc, b.d_offsets, g.within_bits, totals, ss.tally, ss.tally_waves, ss.too_long, plan, pa, b.cnt);
+                     b.run_off, b.loc, b.d_offsets, g.within_bits, totals, ss.tally, ss.tally_waves, ss.too_long, ss.refused, plan, pa, b.cnt);
   return hipGetLastError();
 }
 

@@ -190,6 +190,7 @@ struct SortScratch {
   unsigned long long *tally;  // [3 * wavefronts of a compaction pass] (evictions, lookups that hit, late rows) per wave-
   int tally_waves;            //     front of the last batch's status pass, and how many wavefronts that pass had
   uint32_t *too_long;         // a bag of the batch does not fit the packed payload (0 between batches)
+  int32_t *refused;           // error of the first batch that was refused (0: none): no batch behind it does anything
   // small batches (small_batch): what the workgroups of a kernel tell each other
   uint32_t *ticket;           // workgroups of the running kernel that have begun (0 between kernels)
   uint32_t *said;             // [kMaxSortPasses][256] digit totals, then [kMaxSortPasses][workgroups][256] digit counts

@@ -376,8 +376,8 @@ __global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict
   const int lig = threadIdx.x % L;
   const int n_groups = gridDim.x * blockDim.x / L;
   if (cnt->err) {
-    // This batch is refused (bad offsets or an index out of range) and does nothing, and no batch follows it
-    // (the error sticks).  The batch before it has trained on its overflow copies, though: they go home now,
+    // This batch is refused (bad offsets or an index out of range) and does nothing, and no batch behind it does
+    // anything (SortScratch::refused).  The batch before it has trained on its overflow copies, though: they go home now,
     // whatever was planned for them, so that a flush leaves the backing tier with that batch's updates.
     if (wb_prev != kPrevKeep) {
       u64 b = 0;

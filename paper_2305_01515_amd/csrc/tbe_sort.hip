@@ -13,16 +13,19 @@ constexpr int kKeygenLanes = 8;
 // First kernel of the stage: the batch's counters start at zero (workgroup 0), and every bag is looked at: does it fit the
 // packed payload?  The answer is gathered in *too_long, which the stage's last kernel leaves at zero for the next batch, so
 // that no launch has to come before this one.  It also clears the words in which the workgroups of a small batch's passes
-// tell each other their counts.
+// tell each other their counts.  Behind a batch that was refused every batch starts as refused, with that one's error (the
+// host learns of it only when it synchronises, and until then issues more): every later kernel of the batch then returns at
+// once, so tags, lines and copies stay as the last good batch left them, and a batch buffer that is used again still says so.
 __global__ __launch_bounds__(256) void begin_kernel(int64_t nb, const int64_t *__restrict__ offsets, int within_bits,
                                                     uint32_t *too_long, uint4 *said, int n_said, uint4 *said_counts,
-                                                    int n_said_counts, BatchCounters *cnt) {
+                                                    int n_said_counts, const int32_t *refused, BatchCounters *cnt) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   for (int64_t i = gid; i < n_said + n_said_counts; i += (int64_t)gridDim.x * blockDim.x)
     (i < n_said ? said + i : said_counts + (i - n_said))[0] = make_uint4(0u, 0u, 0u, 0u);
   const int64_t bag = gid;
   if (bag == 0) {
-    cnt->n_uniq = cnt->n_touched = cnt->n_ins = cnt->n_byp = cnt->n_heavy = cnt->err = 0;
+    cnt->n_uniq = cnt->n_touched = cnt->n_ins = cnt->n_byp = cnt->n_heavy = 0;
+    cnt->err = *refused;
     cnt->n_mid = cnt->n_hchunks = 0;
     cnt->h_ranges = 1;
     cnt->hits = cnt->evictions = cnt->hit_lookups = 0;
@@ -39,8 +42,10 @@ __global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict
                                                      const int64_t *__restrict__ offsets, uint32_t *__restrict__ keys,
                                                      uint32_t *__restrict__ vals, int32_t *__restrict__ bag_of_pos,
                                                      float *__restrict__ inv_len, int within_bits,
-                                                     const uint32_t *__restrict__ too_long, DigitPlan digits,
+                                                     const uint32_t *__restrict__ too_long,
+                                                     const int32_t *__restrict__ refused, DigitPlan digits,
                                                      uint32_t *digit_totals, BatchCounters *cnt) {
+  if (*refused) return;
   __shared__ uint32_t s_hist[HIST ? kMaxSortPasses * 256 : 1];
   if constexpr (HIST) {
     for (int i = threadIdx.x; i < kMaxSortPasses * 256; i += 256) s_hist[i] = 0;
@@ -115,13 +120,13 @@ hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf 
   const int64_t threads0 = nb > n_said / 4 ? nb : n_said / 4;
   hipLaunchKernelGGL(begin_kernel, dim3((unsigned)(threads0 > 256 ? (threads0 + 255) / 256 : 1)), dim3(256), 0, s, nb,
                      b.d_offsets, g.within_bits, ss.too_long, (uint4 *)ss.said, n_said, (uint4 *)ss.said_counts, n_counts,
-                     b.cnt);
+                     ss.refused, b.cnt);
   const int64_t threads = nb * kKeygenLanes;
   if (threads > 0) {
     const int64_t blocks = (threads + 255) / 256;
     hipLaunchKernelGGL((small ? keygen_kernel<true> : keygen_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, s, tm, g.T,
                        b.batch, b.n, b.d_indices, b.d_offsets, ss.keys[0], ss.vals[0], b.bag_of_pos,
-                       b.mean ? b.inv_len : nullptr, g.within_bits, ss.too_long, digits, ss.said, b.cnt);
+                       b.mean ? b.inv_len : nullptr, g.within_bits, ss.too_long, ss.refused, digits, ss.said, b.cnt);
   }
   return hipGetLastError();
 }

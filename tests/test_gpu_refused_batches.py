@@ -1,0 +1,96 @@
+"""A batch that the device refuses (an index out of range), with more batches behind it that the caller issues before a
+synchronising call tells of the refusal: none of them does anything, the error is there however many follow, and the
+flush leaves the backing tier as the last batch in front of the refused one left it."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import Oracle
+from paper_2305_01515_amd import synth
+from parity_util import compare_backing, make_backing
+
+pytestmark = pytest.mark.gpu
+T = synth.TableCfg
+
+
+def model(seed, dtype):
+    tabs = [T(60, 16, dtype, 0.7, "poisson", 2, 0, 20, cache_slots=16), T(45, 8, dtype, None, "poisson", 1, 0, 20, cache_slots=8),
+            T(30, 8, dtype, None, "fixed", 1, cache_slots=0)]
+    return synth.WorkloadCfg("refused", tabs, batch=19, ways=4, steps=12, seed=seed, init_std=0.05, lr=0.05)
+
+
+def start(cfg, n, **kw):
+    """library, oracle and the first n batches; the last of them with an index that no table has"""
+    from paper_2305_01515_amd.tbe import TBE
+    Wn, Mn, Wp, Mp = make_backing(cfg)
+    slots = [t.cache_slots for t in cfg.tables]
+    o = Oracle(Wn, Mn, slots, cfg.ways)
+    stream = synth.BatchStream(cfg)
+    host = [stream.next() for _ in range(n)]
+    bad = host[-1][0].clone()
+    bad[bad.numel() // 2] = 60
+    dev = [(i.cuda(), f.cuda()) for i, f in host[:-1]] + [(bad.cuda(), host[-1][1].cuda())]
+    g = TBE(Wp, Mp, slots, cfg.ways, cfg.batch, max(i.numel() for i, _ in host) + 1, **kw)
+    return g, o, host, dev, (Wn, Mn, Wp, Mp)
+
+
+def train(g, o, cfg, s, host, dev, ahead=()):
+    for b in ahead:
+        g.prefetch(*b)
+    g.forward(*dev[s])
+    go = synth.grad_out(cfg, s + 1)
+    g.backward_update(go.cuda(), cfg.lr, cfg.eps)
+    o.prefetch(host[s][0].numpy(), host[s][1].numpy())
+    o.forward()
+    o.backward_update(go.numpy(), cfg.lr, cfg.eps)
+
+
+def expect_refusal(call, code=-2):
+    from paper_2305_01515_amd.tbe import TbeError
+    with pytest.raises(TbeError) as e:
+        call()
+    assert e.value.code == code
+
+
+@pytest.mark.parametrize("behind", [1, 2, 3, 4, 7])
+@pytest.mark.parametrize("ahead", [True, False], ids=["ahead", "one_by_one"])
+@pytest.mark.parametrize("dtype", [synth.FP32, synth.FP16])
+def test_nothing_behind_a_refused_batch_trains(behind, ahead, dtype):
+    """behind: good batches after the bad one, each forwarded and updated by a caller that does not know yet"""
+    cfg = model(3 + behind, dtype)
+    g, o, host, dev, (Wn, Mn, Wp, Mp) = start(cfg, 6)
+    if ahead:
+        g.prefetch(*dev[0])
+    for s in range(5):
+        train(g, o, cfg, s, host, dev, dev[s + 1:s + 2] if ahead else ())
+    assert o.stats()[0]["bypasses"] > 0
+    late = [dev[5]] + [dev[s % 5] for s in range(behind)]  # the bad batch, then rows that were bypassed just before
+    zero = torch.ones(cfg.batch, cfg.sum_dim, device="cuda")
+    for n, b in enumerate(late):
+        if ahead and n + 1 < len(late):
+            g.prefetch(*late[n + 1])
+        g.forward(*b)
+        g.backward_update(zero, cfg.lr, cfg.eps)
+    expect_refusal(g.flush)
+    expect_refusal(g.flush)
+    expect_refusal(lambda: g.prefetch(*dev[0]))
+    o.flush()
+    compare_backing(cfg, Wn, Mn, Wp, Mp, "after the refused batch")
+    g.close()
+    o.close()
+
+
+def test_the_first_refusal_is_the_one_reported():
+    """bad offsets behind an index out of range, then good batches: TBE_ERANGE, as if it had been asked for at once"""
+    cfg = model(1, synth.FP32)
+    g, o, host, dev, _ = start(cfg, 3)
+    train(g, o, cfg, 0, host, dev)
+    zero = torch.zeros(cfg.batch, cfg.sum_dim, device="cuda")
+    off = dev[1][1].clone()
+    off[0] = 1
+    for b in (dev[2], (dev[1][0], off), dev[0], dev[1], dev[0], dev[1]):
+        g.forward(*b)
+        g.backward_update(zero, cfg.lr, cfg.eps)
+    expect_refusal(g.stats, -2)
+    g.close()
+    o.close()
