@@ -1274,9 +1274,18 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
   const int per = 256 / G;  // lane groups of a workgroup
   const int blocks_per_table = (b.batch + per - 1) / per;
   const int combine = (which & kBwdCombine) && tiled ? work_blocks(most_heavy, per, 2048) : 0;
+  const int shrt = (which & kBwdShort) ? work_blocks(b.n / 2, per, 4096) : 0;
+  // A launch holds fewer than 2^32 threads: the bags of as many tables as make 2^30 at a time (16384 tables of 64 lanes,
+  // batch 4096, are 2^32), the other sections with the first of them.
+  const int tables_per_launch = blocks_per_table < (1 << 22) ? (1 << 22) / blocks_per_table : 1;
+  if ((which & kBwdSingle) && count > tables_per_launch) {
+    for (int t = tables_per_launch; t < count; t += tables_per_launch)
+      bwd_one<DT, G>(kBwdSingle, tm, tables + t, count - t < tables_per_launch ? count - t : tables_per_launch, cls, table_class, g, b,
+                     grad_out, partials, lr, eps, s);
+    count = tables_per_launch;
+  }
   // (padded, so that the workgroups behind it keep their XCDs)
   const int single = (which & kBwdSingle) ? (blocks_per_table * count + kXcds - 1) / kXcds * kXcds : 0;
-  const int shrt = (which & kBwdShort) ? work_blocks(b.n / 2, per, 4096) : 0;
   if (combine + single + shrt == 0) return;
   constexpr int kRows = kBwdSingle | kBwdShort;
   const bool rows = single + shrt > 0;
