@@ -70,7 +70,7 @@ struct DevAlloc {  // everything hipMalloc'ed, freed together
     }
     hipError_t e = hipMalloc(&v, bytes);
     if (e == hipSuccess) ptrs.push_back(v);
-    *p = (P *)v;
+    *p = e == hipSuccess ? (P *)v : nullptr;
     return e;
   }
   void release() {
@@ -246,6 +246,17 @@ int alloc_batchbuf(tbe_ctx *h, BatchBuf &b, int64_t n) {
   HIP_TRY(h, h->mem.get(&b.hperm, 4 * (N / 32 + 1)));
   HIP_TRY(h, h->mem.get(&b.hstart, 4 * (h->huge_slots + 1)));
   b.cnt = h->counters + (&b - h->buf);
+  return TBE_OK;
+}
+
+// What max pooling needs beside that: who supplied each maximum, by element and by lookup, and the lookups' positions by
+// sorted order.  Whatever of it the buffer does not have yet: the mode and the prefetch depth, which adds buffers, can be set
+// in any order and more than once, and an allocation that failed can be tried again.
+int alloc_max_records(tbe_ctx *h, BatchBuf &b) {
+  const size_t N = (size_t)std::max<int64_t>(h->max_lookups, 1);
+  if (!b.argpos) HIP_TRY(h, h->mem.get(&b.argpos, 4 * (size_t)h->max_batch * (size_t)h->g.sum_dim));
+  if (!b.wins) HIP_TRY(h, h->mem.get(&b.wins, (size_t)h->g.win_stride * N));
+  if (!b.sorted_pos) HIP_TRY(h, h->mem.get(&b.sorted_pos, 4 * N));
   return TBE_OK;
 }
 
@@ -748,11 +759,7 @@ int tbe_set_prefetch_depth(tbe_handle h, int32_t depth) {
   for (int i = h->nbuf; i < want; i++) {
     int rc = alloc_batchbuf(h, h->buf[i], h->max_lookups);
     if (rc) return rc;
-    if (h->pooling == TBE_POOL_MAX) {
-      HIP_TRY(h, h->mem.get(&h->buf[i].argpos, 4 * (size_t)h->max_batch * (size_t)h->g.sum_dim));
-      HIP_TRY(h, h->mem.get(&h->buf[i].wins, (size_t)h->g.win_stride * (size_t)std::max<int64_t>(h->max_lookups, 1)));
-      HIP_TRY(h, h->mem.get(&h->buf[i].sorted_pos, 4 * (size_t)std::max<int64_t>(h->max_lookups, 1)));
-    }
+    if (h->pooling == TBE_POOL_MAX && (rc = alloc_max_records(h, h->buf[i]))) return rc;
     HIP_TRY(h, hipEventCreateWithFlags(&h->ev_ready[i], hipEventDisableTiming));
     HIP_TRY(h, hipEventCreateWithFlags(&h->ev_trained[i], hipEventDisableTiming));
     HIP_TRY(h, hipEventCreateWithFlags(&h->ev_probed[i], hipEventDisableTiming));
@@ -1118,13 +1125,11 @@ int tbe_set_pooling(tbe_handle h, int32_t pooling) {
   if (pooling != TBE_POOL_SUM && pooling != TBE_POOL_MEAN && pooling != TBE_POOL_MAX)
     return fail(h, TBE_EINVAL, "set_pooling: unknown pooling mode");
   if (h->k != 0) return fail(h, TBE_EORDER, "set_pooling: batches have been prefetched already");
-  if (pooling == TBE_POOL_MAX && !h->buf[0].argpos) {  // who supplied each maximum, by element and by lookup, and the lookups' positions by sorted order
+  if (pooling == TBE_POOL_MAX)
     for (int i = 0; i < h->nbuf; i++) {
-      HIP_TRY(h, h->mem.get(&h->buf[i].argpos, 4 * (size_t)h->max_batch * (size_t)h->g.sum_dim));
-      HIP_TRY(h, h->mem.get(&h->buf[i].wins, (size_t)h->g.win_stride * (size_t)std::max<int64_t>(h->max_lookups, 1)));
-      HIP_TRY(h, h->mem.get(&h->buf[i].sorted_pos, 4 * (size_t)std::max<int64_t>(h->max_lookups, 1)));
+      const int rc = alloc_max_records(h, h->buf[i]);
+      if (rc) return rc;
     }
-  }
   h->pooling = pooling;
   return TBE_OK;
 }

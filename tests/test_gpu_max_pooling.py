@@ -70,3 +70,46 @@ def test_argmax_export_order_errors():
         g.argmax()  # sum pooling keeps no such record
     g.backward_update(torch.zeros(3, 8, device="cuda"), 0.1, 1e-8)
     g.close()
+
+
+@pytest.mark.parametrize("calls", [("max", "sum", 2, "max"), ("max", "mean", 3, "max"), (2, "max"), ("max", 2), ("max", 2, "sum", "max")],
+                         ids=lambda c: "-".join(map(str, c)))
+def test_mode_and_prefetch_depth_set_in_any_order(calls):
+    """the mode may be set more than once before the first batch, and the depth adds batch buffers in between: eight batches
+    go through all of them, two batches ahead"""
+    from oracle import Oracle
+    from parity_util import compare_argmax, compare_backing, compare_forward, make_backing
+    from paper_2305_01515_amd.tbe import POOLINGS, lib
+    cfg = small_cfg(synth.FP32, 8, seed=61, batch=40)
+    Wn, Mn, Wp, Mp = make_backing(cfg)
+    slots = [t.cache_slots for t in cfg.tables]
+    depth = max(c for c in calls if isinstance(c, int))
+    o = Oracle(Wn, Mn, slots, cfg.ways, pooling="max", prefetch_lock=depth)
+    stream = synth.BatchStream(cfg)
+    host = [stream.next() for _ in range(8)]
+    dev = [(i.cuda(), f.cuda()) for i, f in host]
+    g = TBE(Wp, Mp, slots, cfg.ways, cfg.batch, max(i.numel() for i, _ in host))
+    for c in calls:
+        if isinstance(c, int):
+            g.set_prefetch_depth(c)
+        else:
+            assert lib().tbe_set_pooling(g._h, POOLINGS[c]) == 0
+    for b in dev[:2]:
+        g.prefetch(*b)
+    for s in range(8):
+        if s + 2 < 8:
+            g.prefetch(*dev[s + 2])
+        out, arg = g.forward(*dev[s]), g.argmax()
+        go = synth.grad_out(cfg, s + 1)
+        g.backward_update(go.cuda(), cfg.lr, cfg.eps)
+        i, f = (x.numpy() for x in host[s])
+        o.prefetch(i, f)
+        out_o, out_g = o.forward(), out.cpu().numpy()
+        assert compare_argmax(cfg, o, i, f, arg.cpu().numpy(), out_g, f"step {s + 1}") == 0
+        compare_forward(cfg, out_o, out_g, f"step {s + 1}")
+        o.backward_update(go.numpy(), cfg.lr, cfg.eps)
+    o.flush()
+    g.flush()
+    compare_backing(cfg, Wn, Mn, Wp, Mp, "after flush")
+    g.close()
+    o.close()
