@@ -384,9 +384,17 @@ int do_prefetch_deep(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offs
   return TBE_OK;
 }
 
-int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, int32_t batch, int64_t n) {
-  if (!d_offsets || batch < 0 || n < 0 || (n > 0 && !d_indices)) return fail(h, TBE_EINVAL, "prefetch: bad argument");
+// What the host can say about a batch.  (Lookups of no bag are bad offsets like others -- one offset cannot be 0 and n -- but
+// the kernel that checks offsets does so bag by bag, so it would never see these.)
+int check_batch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, int32_t batch, int64_t n) {
+  if (!d_offsets || batch < 0 || n < 0 || (n > 0 && (!d_indices || batch == 0))) return fail(h, TBE_EINVAL, "prefetch: bad argument");
   if (batch > h->max_batch || n > h->max_lookups) return fail(h, TBE_ELIMIT, "prefetch: batch or lookups above the sizes given to tbe_create");
+  return TBE_OK;
+}
+
+int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, int32_t batch, int64_t n) {
+  int rc = check_batch(h, d_indices, d_offsets, batch, n);
+  if (rc) return rc;
   if (h->deep) return do_prefetch_deep(h, d_indices, d_offsets, batch, n);
   if (h->n_pend + (h->current >= 0 ? 1 : 0) > 1) return fail(h, TBE_EORDER, "prefetch: more than one batch would be ahead of training");
   const int bi = h->k % kBatchBufs;  // free: at most the batch before this one is still in use
@@ -737,8 +745,8 @@ int tbe_prefetch(tbe_handle h, const int64_t *d_indices, const int64_t *d_offset
   if (h->sticky) return h->sticky;
   const int ahead = h->n_pend + (h->current >= 0 ? 1 : 0) + (int)h->queued.size();
   if (h->depth > 1 && (ahead > 1 || !h->queued.empty())) {  // beyond what runs now: keep it for later
-    if (!d_offsets || batch < 0 || num_lookups < 0 || (num_lookups > 0 && !d_indices)) return fail(h, TBE_EINVAL, "prefetch: bad argument");
-    if (batch > h->max_batch || num_lookups > h->max_lookups) return fail(h, TBE_ELIMIT, "prefetch: batch or lookups above the sizes given to tbe_create");
+    const int rc = check_batch(h, d_indices, d_offsets, batch, num_lookups);
+    if (rc) return rc;
     if (ahead > h->depth) return fail(h, TBE_EORDER, "prefetch: more batches ahead of training than the queue takes");
     h->queued.push_back({d_indices, d_offsets, batch, num_lookups});
     return TBE_OK;

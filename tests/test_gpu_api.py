@@ -76,6 +76,37 @@ def test_bad_offsets_are_reported(kind):
     g.close()
 
 
+@pytest.mark.parametrize("queue", [1, 3])
+def test_lookups_without_a_bag_are_refused(queue):
+    """a batch of no samples with lookups: TBE_EINVAL at the call, by itself, ahead and into the queue; the run goes on"""
+    from paper_2305_01515_amd.tbe import lib
+    cfg = little()
+    g, _, _ = make(cfg)
+    g.set_prefetch_queue(queue)
+    idx, off = batch_of(cfg)
+    room = torch.zeros(cfg.batch, cfg.sum_dim, device="cuda")
+
+    def prefetch(n):
+        return lib().tbe_prefetch(g._h, idx.data_ptr(), off.data_ptr(), 0, n)
+
+    def forward(n):
+        return lib().tbe_forward(g._h, idx.data_ptr(), off.data_ptr(), 0, n, room.data_ptr())
+
+    assert prefetch(5) == -1 and forward(5) == -1
+    for _ in range(1 + queue):  # 1: one batch ahead; 3: two of these are queued
+        g.prefetch(idx, off)
+        if queue > 1:
+            assert prefetch(1) == -1
+    for _ in range(1 + queue):
+        out = g.forward(idx, off)
+        g.backward_update(torch.zeros_like(out), 0.1, 1e-8)
+    assert forward(0) == 0  # no lookups either: an empty batch
+    g.backward_update(room, 0.1, 1e-8)
+    assert g.stats()["batch_id"] == 2 + queue
+    g.flush()
+    g.close()
+
+
 def test_call_order_and_limits():
     from paper_2305_01515_amd.tbe import TbeError, lib
     cfg = little()
