@@ -422,11 +422,13 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
       if (h->current >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_fwd, 0));
       else if (h->last_trained >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_trained[h->last_trained], 0));
     }
-    // This buffer last served the batch three before: its backward read the buffer's arrays, and the commit of the batch
-    // after that one its bypass list and overflow copies.  At most the batch before this one is still in flight, so the
-    // batch two before has trained, behind both: what was waited for above covers them.  (Each with a wait of its own, and
-    // both of the waits above: mean pooling, ragged, four steps 687 instead of 638 us, 8 x 500k rows under max pooling 1049
-    // instead of 1028.)
+    // This buffer (k - 3's, for batch k) is read by that batch's own kernels, by the list passes of k - 2 and k - 1 (this stream),
+    // by the commit of batch k - 2 -- its bypass list, overflow copies and counters -- and, if batch k - 3 had no successor
+    // when it had trained, by its write-back on the link stream, which that commit follows.  At most the batch before this
+    // one is still in flight, so batch k - 2 has trained, behind its commit: what was waited for above covers them all.  (The
+    // write-back of copies that commit(k - 2) parked runs behind the update of k - 2 and so is not covered: it reads nothing
+    // of this buffer.)  (Each with a wait of its own, and both of the waits above: mean pooling, ragged, four steps 687
+    // instead of 638 us, 8 x 500k rows under max pooling 1049 instead of 1028.)
   }
   {
     StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
@@ -898,10 +900,9 @@ static int backward_update_with(tbe_ctx *h, const float *d_grad_out, float lr, f
   }
   {
     // no batch has been prefetched after this one, so no transfer has run since its commit: the
-    // overflow copies that commit parked (the previous batch's) go home first, then this batch's
+    // overflow copies that commit parked (the previous batch's) go home, and this batch's
     const BatchBuf &b = h->buf[bi];
-    const BatchBuf *parked_prev = (b.parks_prev && b.prev_bi >= 0) ? &h->buf[b.prev_bi] : nullptr;
-    HIP_TRY(h, launch_ovf_writeback(b, parked_prev, h->st, h->d_rb, h->d_bytes + 1, h->ls));
+    HIP_TRY(h, launch_ovf_writeback(b, b.parks_prev && b.prev_bi >= 0, h->st, h->d_rb, h->d_bytes + 1, h->ls));
     if (h->deep) {  // the buffer is free once they are home
       HIP_TRY(h, hipEventRecord(h->ev_home[bi], h->ls));
       h->home_recorded[bi] = true;
@@ -947,7 +948,7 @@ int tbe_flush(tbe_handle h) {
     // pipeline several batches deep every batch's copies go home after its own backward.)
     const int undone = h->deep ? -1 : h->current >= 0 ? h->current : (h->n_pend > 0 && h->pend[0] != h->deferred) ? h->pend[0] : -1;
     if (undone >= 0)
-      HIP_TRY(h, launch_ovf_writeback(h->buf[undone], nullptr, h->st, h->d_rb, h->d_bytes + 1, h->cs));
+      HIP_TRY(h, launch_ovf_writeback(h->buf[undone], false, h->st, h->d_rb, h->d_bytes + 1, h->cs));
     h->n_pend = 0;
     h->current = -1;
     h->deferred = -1;

@@ -383,9 +383,9 @@ struct OverflowCopies {
 hipError_t launch_fixup(const TableMeta *tm, const BatchBuf &b, const OverflowCopies &oc, const Staging &st,
                         const uint32_t *rb_of_table, unsigned long long *n_copied, hipStream_t s);
 // after the batch's backward: its bypassed rows go from their HBM copies to the backing tier
-// parked_prev: the batch whose overflow copies b's commit parked and no transfer has written yet (else null)
-hipError_t launch_ovf_writeback(const BatchBuf &b, const BatchBuf *parked_prev, const Staging &st,
-                                const uint32_t *rb_of_table, unsigned long long *bytes_d2h, hipStream_t s);
+// parked: first the overflow copies of the batch before, which b's commit parked and no transfer has written yet
+hipError_t launch_ovf_writeback(const BatchBuf &b, bool parked, const Staging &st, const uint32_t *rb_of_table,
+                                unsigned long long *bytes_d2h, hipStream_t s);
 hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const Level2 &l2,
                         unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
 // after launch_flush: the accumulators of the tables of at most max_rows rows to their host arrays

@@ -494,14 +494,16 @@ __global__ __launch_bounds__(256) void ovf_writeback_kernel(Staging st, const Ba
   if ((threadIdx.x & 63) == 0 && out_b) atomicAdd(bytes_d2h, out_b);
 }
 
-// The overflow copies that batch b's commit parked behind its victims (those of the batch before
-// it), written to the backing tier ahead of their turn: they must be home before b's own, newer
-// copies of the same rows are written.  Their slots are emptied, so the next transfer passes them by.
+// The overflow copies that batch b's commit parked behind its victims (those of the batch before it, but for the ones that b
+// took over, which are not parked), written to the backing tier ahead of their turn: b has trained with no batch prefetched
+// behind it, and a bypassed row of a batch that has trained goes home without waiting for a batch that may never come.  Their
+// slots are emptied, so the next transfer passes them by.  How many they are stands in the list's length, which only this
+// stream's kernels change; the counters of the batch before are not read, because by now its buffer may be in use again (two
+// batches prefetched before the next forward) with nothing that orders its first kernel behind this one.
 template <int L>
-__global__ __launch_bounds__(256) void parked_copies_writeback_kernel(Staging st, const BatchCounters *cnt,
-                                                                      const BatchCounters *prev_cnt, u64 *bytes_d2h) {
-  if (cnt->err || prev_cnt->err) return;
-  const int base = cnt->n_ins, n = prev_cnt->n_byp;
+__global__ __launch_bounds__(256) void parked_copies_writeback_kernel(Staging st, const BatchCounters *cnt, u64 *bytes_d2h) {
+  if (cnt->err) return;
+  const int base = cnt->n_ins, n = st.wb_n[0] - base;
   const char *out = st.out[st.wb_n[1] & 1];
   const int group = (blockIdx.x * blockDim.x + threadIdx.x) / L;
   const int lig = threadIdx.x % L;
@@ -523,11 +525,10 @@ __global__ __launch_bounds__(256) void parked_copies_writeback_kernel(Staging st
   if ((threadIdx.x & 63) == 0 && out_b) atomicAdd(bytes_d2h, out_b);
 }
 
-hipError_t launch_ovf_writeback(const BatchBuf &b, const BatchBuf *parked_prev, const Staging &st,
-                                const uint32_t *rb_of_table, u64 *bytes_d2h, hipStream_t s) {
-  if (parked_prev)
-    TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((parked_copies_writeback_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, st, b.cnt, parked_prev->cnt,
-                       bytes_d2h));
+hipError_t launch_ovf_writeback(const BatchBuf &b, bool parked, const Staging &st, const uint32_t *rb_of_table, u64 *bytes_d2h,
+                                hipStream_t s) {
+  if (parked)
+    TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((parked_copies_writeback_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, st, b.cnt, bytes_d2h));
   if (b.n == 0) return hipGetLastError();
   TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((ovf_writeback_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, st, b.cnt, b.byp_src, b.byp_tab, b.ovf,
                      rb_of_table, bytes_d2h));

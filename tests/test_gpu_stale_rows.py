@@ -3,6 +3,7 @@ while the list it points into is still alive and holds the row there.  Long runs
 rows are evicted, bypassed and wanted again over and over, so that entries many batches old point at positions that
 later batches' lists fill with other rows."""
 import pytest
+import torch
 
 from paper_2305_01515_amd import synth
 from parity_util import run_parity
@@ -27,3 +28,45 @@ def test_thirty_batches_over_the_same_rows(seed, kw):
     st = run_parity(churn(seed), steps=30, **kw)
     assert st["total"]["bypasses"] > 0 and st["total"]["inserts"] > 0
     assert st["late_fetches"] > 0
+
+
+@pytest.mark.parametrize("ready", [True, False], ids=["inputs_ready", "inputs_ordered"])
+@pytest.mark.parametrize("burst", [2, 3, 4])
+def test_bursts_that_begin_with_two_batches_prefetched(burst, ready):
+    """A loop that trains `burst` batches, the last of them with nothing behind it, and then prefetches two before the next
+    forward: the second takes the buffer of the batch whose overflow copies the burst's last commit parked, while they go
+    home.  Values, and the backing tier at the end, as trained one by one."""
+    from oracle import Oracle
+    from paper_2305_01515_amd.tbe import TBE
+    from parity_util import compare_backing, compare_forward, make_backing
+    cfg = churn(7 + burst, slots=(8, 4, 0))
+    Wn, Mn, Wp, Mp = make_backing(cfg)
+    slots = [t.cache_slots for t in cfg.tables]
+    o = Oracle(Wn, Mn, slots, cfg.ways)
+    stream = synth.BatchStream(cfg)
+    host = [stream.next() for _ in range(8 * burst)]
+    dev = [(i.cuda(), f.cuda()) for i, f in host]
+    grads = [synth.grad_out(cfg, s + 1) for s in range(len(host))]
+    dgrads = [x.cuda() for x in grads]
+    g = TBE(Wp, Mp, slots, cfg.ways, cfg.batch, max(i.numel() for i, _ in host))
+    g.set_inputs_ready(ready)
+    torch.cuda.synchronize()
+    outs = []
+    for s in range(len(host)):
+        if s % burst == 0:
+            g.prefetch(*dev[s])
+        if s % burst + 1 < burst:
+            g.prefetch(*dev[s + 1])
+        outs.append(g.forward(*dev[s]))
+        g.backward_update(dgrads[s], cfg.lr, cfg.eps)
+    g.flush()
+    for s, (i, f) in enumerate(host):
+        o.prefetch(i.numpy(), f.numpy())
+        compare_forward(cfg, o.forward(), outs[s].cpu().numpy(), f"step {s + 1}")
+        o.backward_update(grads[s].numpy(), cfg.lr, cfg.eps)
+    o.flush()
+    compare_backing(cfg, Wn, Mn, Wp, Mp, "after flush")
+    st = g.stats()
+    assert st["total"] == o.stats()[1] and st["total"]["bypasses"] > 0 and st["late_fetches"] > 0
+    g.close()
+    o.close()
