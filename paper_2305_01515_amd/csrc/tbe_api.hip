@@ -205,6 +205,18 @@ void drop_profile(tbe_ctx *h) {
 
 int next_pow2(int v) { int p = 1; while (p < v) p <<= 1; return p; }
 
+// Can a kernel write to these `bytes` of host memory at the address the host uses?  (Pinned memory: yes.  Pageable memory,
+// and memory that was registered and mapped at another address: no.)
+bool kernels_reach(const void *p, size_t bytes) {
+  for (const char *q : {(const char *)p, (const char *)p + bytes - 1}) {
+    hipPointerAttribute_t a{};
+    const hipError_t e = hipPointerGetAttributes(&a, q);
+    (void)hipGetLastError();  // (an error, for pageable memory, on some versions)
+    if (e != hipSuccess || a.type != hipMemoryTypeHost || a.devicePointer != (const void *)q) return false;
+  }
+  return true;
+}
+
 __global__ void stream_pin_kernel() {}
 
 int alloc_batchbuf(tbe_ctx *h, BatchBuf &b, int64_t n) {
@@ -622,6 +634,7 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   for (int t = 0; t < num_tables; t++) {
     h->tm[t].lines = h->lines + line_off[t];
     h->tm[t].slot_m = h->d_slot_m + h->tm[t].slot_base;
+    h->tm[t].flush_by_kernel = h->tm[t].rows <= kFlushStateRows && kernels_reach(h->tm[t].host_m, 4 * (size_t)h->tm[t].rows);
   }
   CREATE_TRY(h->mem.get(&h->d_tm, sizeof(TableMeta) * num_tables));
   CREATE_TRY(hipMemcpy(h->d_tm, h->tm.data(), sizeof(TableMeta) * num_tables, hipMemcpyHostToDevice));
@@ -960,10 +973,11 @@ int tbe_flush(tbe_handle h) {
   h->prev_buf = -1;
   HIP_TRY(h, launch_flush(h->d_tm, h->g, h->tags, h->l2, h->d_bytes, h->d_bytes + 1, h->cs));  // also slot accumulators -> dev_m
   // A copy engine takes some 18 us per table, whatever its size, and 57 GB/s; a kernel writes all small tables' accumulators
-  // in one launch (4 tables of 100 k rows: 29 instead of 72 us).
-  HIP_TRY(h, launch_flush_state(h->d_tm, h->g, kFlushStateRows, h->cs));
+  // in one launch (4 tables of 100 k rows: 29 instead of 72 us).  An array that is not pinned, which no kernel may write, is
+  // copied whatever its size.
+  HIP_TRY(h, launch_flush_state(h->d_tm, h->g, h->cs));
   for (const TableMeta &m : h->tm) {
-    if (m.rows > kFlushStateRows)
+    if (!m.flush_by_kernel)
       HIP_TRY(h, hipMemcpyAsync(m.host_m, m.dev_m, 4 * (size_t)m.rows, hipMemcpyDeviceToHost, h->cs));
     h->flush_state_bytes += 4 * m.rows;
   }

@@ -78,6 +78,7 @@ struct TableMeta {
                           // accumulator lives here, next to 6 MB of its kind, instead of among those of all rows)
   char *host_w;           // pinned host rows [rows, row_bytes]
   float *host_m;          // host accumulators [rows]: read at create, written at flush
+  bool flush_by_kernel;   // ... by launch_flush_state (else by a copy)
   float *dev_m;           // device: row-wise Adagrad accumulators of ALL rows of the table [rows]: current for
                           // the rows that are not in a cache line (commit moves them in and out with the row)
   // second-level cache (Section 5.3): sets2 = l2_factor * sets, so the second-level sets of the
@@ -388,9 +389,9 @@ hipError_t launch_ovf_writeback(const BatchBuf &b, bool parked, const Staging &s
                                 unsigned long long *bytes_d2h, hipStream_t s);
 hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const Level2 &l2,
                         unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
-// after launch_flush: the accumulators of the tables of at most max_rows rows to their host arrays
+// after launch_flush: the accumulators of the tables with flush_by_kernel (at most kFlushStateRows rows, pinned host array)
 constexpr int64_t kFlushStateRows = 262144;  // a megabyte: what the copy engine moves in the time it takes to start
-hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, int64_t max_rows, hipStream_t s);
+hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, hipStream_t s);
 hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
                                   float *out, hipStream_t s);
 // which: kBwdHeavy (tile kernel; under max pooling the workgroup-per-row kernel instead), or any of kBwdCombine (sums of the

@@ -614,17 +614,17 @@ hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *t
 }
 
 // flush: accumulators of the small tables to the host, a table per grid row (the arrays are aligned to floats only)
-__global__ __launch_bounds__(256) void flush_state_kernel(const TableMeta *__restrict__ tm, int T, int64_t max_rows) {
+__global__ __launch_bounds__(256) void flush_state_kernel(const TableMeta *__restrict__ tm, int T) {
   for (int t = blockIdx.y; t < T; t += gridDim.y) {
     const TableMeta &m = tm[t];
-    if (m.rows > max_rows) continue;
+    if (!m.flush_by_kernel) continue;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m.rows; i += (int64_t)gridDim.x * blockDim.x)
       __builtin_nontemporal_store(m.dev_m[i], m.host_m + i);
   }
 }
 
-hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, int64_t max_rows, hipStream_t s) {
-  hipLaunchKernelGGL(flush_state_kernel, dim3(32, g.T < 1024 ? g.T : 1024), dim3(256), 0, s, tm, g.T, max_rows);
+hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, hipStream_t s) {
+  hipLaunchKernelGGL(flush_state_kernel, dim3(32, g.T < 1024 ? g.T : 1024), dim3(256), 0, s, tm, g.T);
   return hipGetLastError();
 }
 

@@ -31,3 +31,48 @@ def test_many_tables_and_rows_no_batch_touched():
     t.flush()
     assert all(np.array_equal(m.numpy(), w.numpy()) for m, w in zip(M, want))
     t.close()
+
+
+def test_state_in_memory_that_kernels_cannot_write():
+    """accumulators in ordinary, not pinned memory through the C boundary: read at creation and written by every flush, beside
+    tables whose arrays lie inside one pinned block"""
+    import ctypes as C
+    from oracle import Oracle
+    from paper_2305_01515_amd.tbe import TableSpec, lib
+    from parity_util import compare_backing, make_backing
+    tabs = [T(300, 8, synth.FP32, 1.0, "fixed", 3, cache_slots=64), T(5000, 4, synth.FP32, 1.0, "fixed", 2, cache_slots=0),
+            T(77, 16, synth.FP32, None, "fixed", 2, cache_slots=32), T(1, 4, synth.FP32, None, "fixed", 1)]
+    cfg = synth.WorkloadCfg("pageable", tabs, batch=30, ways=8, steps=4, seed=8, init_std=0.05, lr=0.05)
+    Wn, _, Wp, _ = make_backing(cfg)
+    block = torch.empty(300 + 77 + 5, dtype=torch.float32, pin_memory=True)
+    Mp = [block[1:301], torch.empty(5000), block[301:378], torch.empty(1)]
+    assert [m.is_pinned() for m in Mp] == [True, False, True, False]
+    for m in Mp:
+        m.copy_(torch.rand(m.numel(), generator=torch.Generator().manual_seed(m.numel())))
+    Mn = [m.numpy().copy() for m in Mp]
+    edges = (float(block[0].fill_(-1.0)), block[378:].fill_(-2.0).tolist())
+    slots = [t.cache_slots for t in tabs]
+    o = Oracle(Wn, Mn, slots, cfg.ways)
+    specs = (TableSpec * 4)(*[TableSpec(t.rows, t.dim, 0, w.data_ptr(), m.data_ptr(), t.cache_slots) for t, w, m in zip(tabs, Wp, Mp)])
+    h = C.c_void_p()
+    assert lib().tbe_create(C.byref(h), specs, 4, cfg.ways, cfg.batch, 1024, None, None) == 0
+    for m in Mp:
+        m.zero_()  # what the flush does not write stays zero
+    stream = synth.BatchStream(cfg)
+    for s in range(4):
+        idx, off = stream.next()
+        di, df, out, go = idx.cuda(), off.cuda(), torch.empty(cfg.batch, cfg.sum_dim, device="cuda"), synth.grad_out(cfg, s + 1)
+        dg = go.cuda()
+        assert lib().tbe_forward(h, di.data_ptr(), df.data_ptr(), cfg.batch, di.numel(), out.data_ptr()) == 0
+        assert lib().tbe_backward_update(h, dg.data_ptr(), cfg.lr, cfg.eps) == 0
+        o.prefetch(idx.numpy(), off.numpy())
+        o.forward()
+        o.backward_update(go.numpy(), cfg.lr, cfg.eps)
+        if s % 2:
+            assert lib().tbe_flush(h) == 0
+            o.flush()
+            compare_backing(cfg, Wn, Mn, Wp, Mp, f"flush after step {s + 1}")
+        torch.cuda.synchronize()
+    assert (float(block[0]), block[378:].tolist()) == edges
+    assert lib().tbe_destroy(h) == 0
+    o.close()
