@@ -267,7 +267,10 @@ int alloc_batchbuf(tbe_ctx *h, BatchBuf &b, int64_t n) {
 int alloc_max_records(tbe_ctx *h, BatchBuf &b) {
   const size_t N = (size_t)std::max<int64_t>(h->max_lookups, 1);
   if (!b.argpos) HIP_TRY(h, h->mem.get(&b.argpos, 4 * (size_t)h->max_batch * (size_t)h->g.sum_dim));
-  if (!b.wins) HIP_TRY(h, h->mem.get(&b.wins, (size_t)h->g.win_stride * N));
+  // One array for all buffers: the forward writes it, the update of the same batch reads it, both on the compute stream, and no
+  // other batch is forwarded in between.  It lies in the partial sums' memory, which this mode does not use: with an array of
+  // its own in every buffer a handle took up to 192 bytes more per lookup than before there were such records.
+  b.wins = (uint8_t *)h->partials;
   if (!b.sorted_pos) HIP_TRY(h, h->mem.get(&b.sorted_pos, 4 * N));
   return TBE_OK;
 }
@@ -688,7 +691,8 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
     int widest = 0;
     for (const TableMeta &m : h->tm) widest = std::max(widest, m.lanes * (m.dtype == TBE_FP32 ? 4 : 8));
     h->g.partial_stride = widest;
-    CREATE_TRY(h->mem.get(&h->partials, 4 * (size_t)widest * h->huge_slots));
+    // (max pooling, which makes no partial sums, keeps the lookups' records there: at most as many bytes, but for 1/65 of them)
+    CREATE_TRY(h->mem.get(&h->partials, std::max(4 * (size_t)widest * h->huge_slots, (size_t)h->g.win_stride * (size_t)max_lookups)));
   }
   {
     Staging &st = h->st;

@@ -125,7 +125,8 @@ struct BatchBuf {
   int32_t *argpos;      // [batch * sum_dim] max pooling: position inside its bag of the lookup that supplied the
                         //     maximum of each pooled element (-1 for an empty bag); null unless max pooling is set
   uint8_t *wins;        // [N * win_stride] max pooling: which elements of its row a lookup supplied the maximum of, input
-                        //     order: byte l for the elements of lane l, bit e for the lane's e-th
+                        //     order: byte l for the elements of lane l, bit e for the lane's e-th; one array for all
+                        //     batches (only the batch between its forward and its update has one)
   uint32_t *sorted_pos; // [N] max pooling: position (input order) of the i-th lookup in sorted order
   uint32_t *uid_sorted; // [N] index of the distinct row of the i-th sorted lookup
   // per distinct row (ascending key)

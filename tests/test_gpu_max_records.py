@@ -2,6 +2,7 @@
 wavefront each: every number of lanes per row, rows with 65 to thousands of lookups (one chunk a chain to many, ragged
 ends)."""
 import pytest
+import torch
 
 from paper_2305_01515_amd import synth
 from parity_util import run_parity
@@ -18,3 +19,15 @@ def test_rows_of_every_width_and_length(dim, dtype):
             T(1, dim, dtype, None, "fixed", 1)]
     run_parity(synth.WorkloadCfg("rec", tabs, batch=523, ways=16, steps=3, seed=dim, init_std=0.05, lr=0.05), steps=3,
                order="early", pooling="max")
+
+
+def test_records_take_no_memory_of_their_own():
+    """a byte per lane and lookup, in memory that the handle has anyway: setting the mode allocates the positions alone"""
+    from paper_2305_01515_amd.tbe import TBE, lib, pinned_empty
+    n, batch, dim = 1 << 20, 64, 256
+    g = TBE([pinned_empty((1000, dim), torch.float32).zero_()], [pinned_empty((1000,), torch.float32).zero_()], [64], 8, batch, n)
+    free = torch.cuda.mem_get_info()[0]
+    assert lib().tbe_set_pooling(g._h, 2) == 0
+    taken = free - torch.cuda.mem_get_info()[0]
+    assert taken <= 3 * 4 * (n + batch * dim) + (16 << 20)  # three buffers; (one such record: 64 MB)
+    g.close()
