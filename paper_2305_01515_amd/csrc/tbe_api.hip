@@ -342,6 +342,14 @@ StaleRows stale_rows(const tbe_ctx *h, const BatchBuf &b, int bi) {
   return r;
 }
 
+// Pipeline several batches deep: the rows of `b` whose value was an overflow copy of a batch that had not trained when `b` was
+// fetched are copied from there.
+hipError_t fix_up(tbe_ctx *h, const BatchBuf &b) {
+  OverflowCopies oc{};
+  for (int x = 0; x < h->nbuf; x++) oc.of_buf[x] = h->buf[x].ovf;
+  return launch_fixup(h->d_tm, b, oc, h->st, h->d_rb, h->d_bytes + 6, h->cs);
+}
+
 // Pipeline several batches deep (Section 5.7): the batch is fetched into the cache as soon as it is decided on.
 // The ways of the batches that may still wait for their training are locked (ts >= k - D), so its victims and
 // the lines it fills are used by none of them and nothing waits for a backward -- except the rows whose current
@@ -850,11 +858,7 @@ int tbe_forward(tbe_handle h, const int64_t *d_indices, const int64_t *d_offsets
     // A kernel is held back by the wait, so an empty one in front of the bracket pins its beginning.
     if (h->profiling) hipLaunchKernelGGL(stream_pin_kernel, dim3(1), dim3(64), 0, h->cs);
   }
-  if (h->deep) {  // rows whose value was an overflow copy of a batch that had not trained when this one was fetched
-    OverflowCopies oc{};
-    for (int x = 0; x < h->nbuf; x++) oc.of_buf[x] = h->buf[x].ovf;
-    HIP_TRY(h, launch_fixup(h->d_tm, b, oc, h->st, h->d_rb, h->d_bytes + 6, h->cs));
-  }
+  if (h->deep) HIP_TRY(h, fix_up(h, b));
   {
     StageTimer tm_(h, TBE_STAGE_FORWARD, h->cs);
     HIP_TRY(h, launch_forward_classes(h->d_tm, h->ci, h->g, b, d_out, h->cs));
@@ -960,12 +964,17 @@ int tbe_flush(tbe_handle h) {
     // brings the backing tier up to the last batch that trained.
     (void)collect_device_errors(h);
     if (!h->sticky) return fail(h, TBE_EORDER, "flush: a batch is still in flight");
-    // The batch in front of the refused one may have been committed without training: rows it bypassed and took over
-    // from the copies of the batch before it have their value in its own copies alone, which go home here.  (In the
-    // pipeline several batches deep every batch's copies go home after its own backward.)
-    const int undone = h->deep ? -1 : h->current >= 0 ? h->current : (h->n_pend > 0 && h->pend[0] != h->deferred) ? h->pend[0] : -1;
-    if (undone >= 0)
-      HIP_TRY(h, launch_ovf_writeback(h->buf[undone], false, h->st, h->d_rb, h->d_bytes + 1, h->cs));
+    // Batches in front of the refused one may have been committed without training, and there is then a row whose value is in
+    // their own copy alone: one that such a batch bypassed and took over from a parked victim, or from a copy of the batch
+    // before it.  These copies go home here.  In the pipeline several batches deep some of their rows have yet to be copied
+    // from the copies of earlier batches, into overflow copies or cache lines, which the forward would have done: in the order
+    // of the batches, because one may take from the one before.
+    for (int i = -1; i < h->n_pend; i++) {
+      const int bi = i < 0 ? h->current : h->pend[i];
+      if (bi < 0 || bi == h->deferred) continue;
+      if (h->deep && i >= 0) HIP_TRY(h, fix_up(h, h->buf[bi]));
+      HIP_TRY(h, launch_ovf_writeback(h->buf[bi], false, h->st, h->d_rb, h->d_bytes + 1, h->cs));
+    }
     h->n_pend = 0;
     h->current = -1;
     h->deferred = -1;

@@ -94,3 +94,28 @@ def test_the_first_refusal_is_the_one_reported():
     expect_refusal(g.stats, -2)
     g.close()
     o.close()
+
+
+@pytest.mark.parametrize("seed", range(6))
+@pytest.mark.parametrize("forwarded", [True, False])
+@pytest.mark.parametrize("depth", [2, 3])
+def test_refused_batch_behind_batches_fetched_ahead(depth, forwarded, seed):
+    """In the pipeline several batches deep the batches in front of the refused one are in their cache lines already, some of
+    their rows as copies that wait for the forward, others with their value in a bypassed row's copy alone."""
+    cfg = model(20 + seed, synth.FP32)
+    steps = 6
+    g, o, host, dev, (Wn, Mn, Wp, Mp) = start(cfg, steps + depth)
+    g.set_prefetch_depth(depth)
+    for b in dev[:depth]:
+        g.prefetch(*b)
+    for s in range(steps - 1):
+        train(g, o, cfg, s, host, dev, dev[s + depth:s + depth + 1])
+    g.prefetch(*dev[-1])
+    if forwarded:
+        g.forward(*dev[steps - 1])
+    assert o.stats()[1]["bypasses"] > 0 and o.stats()[1]["evictions"] > 0
+    expect_refusal(g.flush)
+    o.flush()
+    compare_backing(cfg, Wn, Mn, Wp, Mp, "after the refused batch")
+    g.close()
+    o.close()
