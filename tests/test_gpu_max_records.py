@@ -1,6 +1,6 @@
 """Max pooling: the lookups' records of the maxima they supplied, and the kernel that gives a row's chains of lookups a
-wavefront each: every number of lanes per row, rows with 65 to thousands of lookups (one chunk a chain to many, ragged
-ends)."""
+wavefront each: every number of lanes per row, rows with 65 to about a thousand lookups (one chunk a chain to many,
+ragged ends)."""
 import pytest
 import torch
 
@@ -17,8 +17,9 @@ T = synth.TableCfg
 def test_rows_of_every_width_and_length(dim, dtype):
     tabs = [T(900, dim, dtype, 1.3, "poisson", 9, 0, 60, cache_slots=16 * 9), T(3, 16, dtype, None, "fixed", 2, cache_slots=16),
             T(1, dim, dtype, None, "fixed", 1)]
-    run_parity(synth.WorkloadCfg("rec", tabs, batch=523, ways=16, steps=3, seed=dim, init_std=0.05, lr=0.05), steps=3,
-               order="early", pooling="max")
+    st = run_parity(synth.WorkloadCfg("rec", tabs, batch=523, ways=16, steps=3, seed=dim, init_std=0.05, lr=0.05), steps=3,
+                    order="early", pooling="max")
+    assert st["last_long_rows"] > 0 and st["parted_at"] is None  # no near-tie taken differently: values compared to the end
 
 
 def test_records_take_no_memory_of_their_own():

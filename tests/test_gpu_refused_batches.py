@@ -54,23 +54,23 @@ def expect_refusal(call, code=-2):
 
 @pytest.mark.parametrize("behind", [1, 2, 3, 4, 7])
 @pytest.mark.parametrize("ahead", [True, False], ids=["ahead", "one_by_one"])
-@pytest.mark.parametrize("dtype", [synth.FP32, synth.FP16])
-def test_nothing_behind_a_refused_batch_trains(behind, ahead, dtype):
+@pytest.mark.parametrize("dtype,level2", [(synth.FP32, 0), (synth.FP16, 0), (synth.FP32, 2)])
+def test_nothing_behind_a_refused_batch_trains(behind, ahead, dtype, level2):
     """behind: good batches after the bad one, each forwarded and updated by a caller that does not know yet"""
     cfg = model(3 + behind, dtype)
-    g, o, host, dev, (Wn, Mn, Wp, Mp) = start(cfg, 6)
+    g, o, host, dev, (Wn, Mn, Wp, Mp) = start(cfg, 6, second_level_factor=level2)
     if ahead:
         g.prefetch(*dev[0])
     for s in range(5):
         train(g, o, cfg, s, host, dev, dev[s + 1:s + 2] if ahead else ())
     assert o.stats()[0]["bypasses"] > 0
     late = [dev[5]] + [dev[s % 5] for s in range(behind)]  # the bad batch, then rows that were bypassed just before
-    zero = torch.ones(cfg.batch, cfg.sum_dim, device="cuda")
+    ones = torch.ones(cfg.batch, cfg.sum_dim, device="cuda")
     for n, b in enumerate(late):
         if ahead and n + 1 < len(late):
             g.prefetch(*late[n + 1])
         g.forward(*b)
-        g.backward_update(zero, cfg.lr, cfg.eps)
+        g.backward_update(ones, cfg.lr, cfg.eps)
     expect_refusal(g.flush)
     expect_refusal(g.flush)
     expect_refusal(lambda: g.prefetch(*dev[0]))
@@ -98,13 +98,14 @@ def test_the_first_refusal_is_the_one_reported():
 
 @pytest.mark.parametrize("seed", range(6))
 @pytest.mark.parametrize("forwarded", [True, False])
-@pytest.mark.parametrize("depth", [2, 3])
-def test_refused_batch_behind_batches_fetched_ahead(depth, forwarded, seed):
-    """In the pipeline several batches deep the batches in front of the refused one are in their cache lines already, some of
-    their rows as copies that wait for the forward, others with their value in a bypassed row's copy alone."""
+@pytest.mark.parametrize("depth,level2", [(1, 0), (1, 1), (1, 2), (2, 0), (3, 0)])
+def test_refused_batch_behind_batches_fetched_ahead(depth, level2, forwarded, seed):
+    """The last batch in front of the refused one has not trained and holds rows whose value is in its copies alone.  In the
+    pipeline several batches deep several such batches are in their cache lines already, some of their rows as copies that
+    wait for the forward."""
     cfg = model(20 + seed, synth.FP32)
     steps = 6
-    g, o, host, dev, (Wn, Mn, Wp, Mp) = start(cfg, steps + depth)
+    g, o, host, dev, (Wn, Mn, Wp, Mp) = start(cfg, steps + depth, second_level_factor=level2)
     g.set_prefetch_depth(depth)
     for b in dev[:depth]:
         g.prefetch(*b)

@@ -52,8 +52,9 @@ def test_more_tables_than_constants_fit_in_lds():
 @pytest.mark.parametrize("batch", [200, 4500])
 @pytest.mark.parametrize("pooling", ["sum", "mean", "max"])
 def test_heavy_rows_of_many_lengths(batch, pooling):
-    """rows with 65 to tens of thousands of lookups, entered once or several times, over several tables"""
+    """rows with 65 to ten thousand lookups, entered once or several times, over several tables"""
     tabs = [T(40, 16, synth.FP32, 1.3, "fixed", 8, cache_slots=64), T(900, 32, synth.FP32, None, "fixed", 1, cache_slots=64),
             T(7, 16, synth.FP32, 1.0, "poisson", 4, 0, 20), T(2500, 32, synth.FP32, 1.1, "poisson", 12, 0, 90, cache_slots=320)]
-    run_parity(synth.WorkloadCfg("heavy", tabs, batch=batch, ways=16, steps=2, seed=9, init_std=0.05, lr=0.05), steps=2, order="early",
-               pooling=pooling)
+    st = run_parity(synth.WorkloadCfg("heavy", tabs, batch=batch, ways=16, steps=2, seed=9, init_std=0.05, lr=0.05), steps=2,
+                    order="early", pooling=pooling)
+    assert st["last_long_rows"] > 0 and st["parted_at"] is None  # max: no near-tie taken differently, values compared to the end
