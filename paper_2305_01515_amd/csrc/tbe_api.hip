@@ -1041,6 +1041,8 @@ int tbe_enable_second_level(tbe_handle h, int32_t factor) {
     bytes2 += (size_t)m.sets * factor * h->g.ways * m.row_bytes;
   }
   if (slots2 == 0) return fail(h, TBE_EINVAL, "enable_second_level: no table has a first-level cache");
+  if (h->lines2) (void)hipHostFree(h->lines2);  // of an earlier call that failed
+  h->lines2 = nullptr;
   HIP_TRY(h, hipHostMalloc((void **)&h->lines2, bytes2, hipHostMallocDefault));
   h->l2.lines_lo = h->lines2;
   h->l2.lines_hi = h->lines2 + bytes2;
@@ -1052,9 +1054,13 @@ int tbe_enable_second_level(tbe_handle h, int32_t factor) {
   HIP_TRY(h, hipMemset(l2.ts2, 0xFF, 4 * (size_t)slots2));
   for (int p2 = 0; p2 < 2; p2++) {
     HIP_TRY(h, h->mem.get(&l2.out2[p2], M * h->st.stride));
-    // the skip flags of the staged second-level victims follow those of the first-level ones
-    HIP_TRY(h, h->mem.get(&h->st.wb_skip[p2], 2 * M));
-    HIP_TRY(h, hipMemset(h->st.wb_skip[p2], 0, 2 * M ? 2 * M : 1));
+    // the skip flags of the staged second-level victims follow those of the first-level ones (a larger array in place of the
+    // one there is, never a smaller: if a later allocation fails the handle goes on with one level and its parked copies)
+    const size_t flags = std::max(2 * M, M + (size_t)h->st.max_parked);
+    uint8_t *skip = nullptr;
+    HIP_TRY(h, h->mem.get(&skip, flags));
+    HIP_TRY(h, hipMemset(skip, 0, flags ? flags : 1));
+    h->st.wb_skip[p2] = skip;
   }
   HIP_TRY(h, h->mem.get(&l2.wb2_dst, 8 * M));
   HIP_TRY(h, hipMemset(l2.wb2_dst, 0, 8 * M ? 8 * M : 8));
