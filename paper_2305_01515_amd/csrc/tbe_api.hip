@@ -275,7 +275,7 @@ int alloc_max_records(tbe_ctx *h, BatchBuf &b) {
   return TBE_OK;
 }
 
-int device_error_code(int e) { return e == 0 ? 0 : e == 1 ? TBE_EINVAL : TBE_ERANGE; }
+int device_error_code(int e) { return e == 0 ? 0 : (e & ~kRefusedBefore) == 1 ? TBE_EINVAL : TBE_ERANGE; }
 
 // After a synchronisation: pick up errors the device recorded.
 int collect_device_errors(tbe_ctx *h) {
@@ -285,7 +285,7 @@ int collect_device_errors(tbe_ctx *h) {
     const BatchCounters &c = all[i];
     if (c.err && !h->sticky) {
       h->sticky = device_error_code(c.err);
-      h->err = c.err == 1 ? "offsets are not a non-decreasing partition of [0, num_lookups]"
+      h->err = h->sticky == TBE_EINVAL ? "offsets are not a non-decreasing partition of [0, num_lookups]"
                           : "an index is outside its table";
     }
   }

@@ -1053,7 +1053,7 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(int n, const ui
   const bool last = blockIdx.x + 1 == gridDim.x;
   if (last && threadIdx.x == 0) {
     *too_long = 0u;  // as the next batch expects it, whatever became of this one
-    if (cnt->err && *refused == 0) *refused = cnt->err;  // (read by the first two kernels of a stage alone, long done)
+    if (cnt->err && *refused == 0) *refused = cnt->err | kRefusedBefore;  // (read by a stage's first kernel alone)
   }
   if (cnt->err) return;
   if (last) {

@@ -89,6 +89,8 @@ struct TableMeta {
   uint32_t *init_bits;    // device: deferred initialisation, one bit per row (1 = the row has a value); null = off
 };
 
+constexpr int32_t kRefusedBefore = 4;  // above any error of a batch's own
+
 // Device-side scalars of one batch (one per batch buffer).
 struct BatchCounters {
   int32_t n_uniq;     // distinct (table,row) of the batch
@@ -96,7 +98,7 @@ struct BatchCounters {
   int32_t n_ins;
   int32_t n_byp;
   int32_t n_heavy;    // entries of the heavy list (rows with more than kLongRun lookups, a hot row several times)
-  int32_t err;        // 1 = bad offsets, 2 = index out of range, 0 = none
+  int32_t err;        // 1 = bad offsets, 2 = index out of range, 0 = none; with kRefusedBefore: that of an earlier batch
   int32_t h_ranges;   // bag ranges the heavy rows' sums are split over in this batch
   int32_t n_mid;      // rows with 2..kLongRun lookups
   unsigned long long hits, evictions, hit_lookups;
@@ -192,7 +194,8 @@ struct SortScratch {
   unsigned long long *tally;  // [3 * wavefronts of a compaction pass] (evictions, lookups that hit, late rows) per wave-
   int tally_waves;            //     front of the last batch's status pass, and how many wavefronts that pass had
   uint32_t *too_long;         // a bag of the batch does not fit the packed payload (0 between batches)
-  int32_t *refused;           // error of the first batch that was refused (0: none): no batch behind it does anything
+  int32_t *refused;           // error of the first batch that was refused, with kRefusedBefore (0: none): no batch behind it
+                              //   does anything
   // small batches (small_batch): what the workgroups of a kernel tell each other
   uint32_t *ticket;           // workgroups of the running kernel that have begun (0 between kernels)
   uint32_t *said;             // [kMaxSortPasses][256] digit totals, then [kMaxSortPasses][workgroups][256] digit counts

@@ -16,6 +16,7 @@ constexpr int kKeygenLanes = 8;
 // tell each other their counts.  Behind a batch that was refused every batch starts as refused, with that one's error (the
 // host learns of it only when it synchronises, and until then issues more): every later kernel of the batch then returns at
 // once, so tags, lines and copies stay as the last good batch left them, and a batch buffer that is used again still says so.
+// (The key generation alone does not ask: a first load for every wavefront of it.  What it finds is below that error.)
 __global__ __launch_bounds__(256) void begin_kernel(int64_t nb, const int64_t *__restrict__ offsets, int within_bits,
                                                     uint32_t *too_long, uint4 *said, int n_said, uint4 *said_counts,
                                                     int n_said_counts, const int32_t *refused, BatchCounters *cnt) {
@@ -42,10 +43,8 @@ __global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict
                                                      const int64_t *__restrict__ offsets, uint32_t *__restrict__ keys,
                                                      uint32_t *__restrict__ vals, int32_t *__restrict__ bag_of_pos,
                                                      float *__restrict__ inv_len, int within_bits,
-                                                     const uint32_t *__restrict__ too_long,
-                                                     const int32_t *__restrict__ refused, DigitPlan digits,
+                                                     const uint32_t *__restrict__ too_long, DigitPlan digits,
                                                      uint32_t *digit_totals, BatchCounters *cnt) {
-  if (*refused) return;
   __shared__ uint32_t s_hist[HIST ? kMaxSortPasses * 256 : 1];
   if constexpr (HIST) {
     for (int i = threadIdx.x; i < kMaxSortPasses * 256; i += 256) s_hist[i] = 0;
@@ -126,7 +125,7 @@ hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf 
     const int64_t blocks = (threads + 255) / 256;
     hipLaunchKernelGGL((small ? keygen_kernel<true> : keygen_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, s, tm, g.T,
                        b.batch, b.n, b.d_indices, b.d_offsets, ss.keys[0], ss.vals[0], b.bag_of_pos,
-                       b.mean ? b.inv_len : nullptr, g.within_bits, ss.too_long, ss.refused, digits, ss.said, b.cnt);
+                       b.mean ? b.inv_len : nullptr, g.within_bits, ss.too_long, digits, ss.said, b.cnt);
   }
   return hipGetLastError();
 }
