@@ -495,7 +495,9 @@ __device__ inline void plan_heavy(int blk, int blocks, const TableMeta *__restri
 // by the lane that handles the row; its entries are checked against the lists of the batches whose copies are on their
 // way instead of being taken out again.  (With a pass of its own over the missed rows for the look-up and up to three
 // for entering and taking out entries, four launches more: small configuration, six steps 1276 -> 1198 us; 16 x 500k
-// resident rows, four steps 2773 -> 2731 us.)
+// resident rows, four steps 2773 -> 2731 us.  On the benchmark workload, where two thirds of the distinct rows miss, this pass
+// itself takes 66 to 92 instead of 34 us alone and 114 instead of 38 beside the other streams, as a row's entry and the list that it
+// points into are two dependent reads; the five kinds of launches that it took over were 128 us there.)
 struct StatusOp {
   static constexpr int kItems = 1;
   typedef Counts<2> V;  // lo and hi of word 0: inserts, bypasses; of word 1: rows with 2..kLongRun lookups, heavy-list entries
@@ -573,7 +575,7 @@ struct StatusOp {
       if (stale.deep) {
         const uint32_t buf = (code >> kWhereBufShift) & (kMaxBatchBufs - 1), j = code & kWhereBufIndex;
         if (!(stale.live >> buf & 1u)) return 0u;
-        const DeepBuf d = stale.deep[buf];
+        const DeepBuf d = stale.deep[buf];  // (whose copy goes home all the same, right behind its batch's own backward)
         return (int)j < d.cnt->n_byp && d.byp_key[j] == key ? code : 0u;
       }
       const int j = (int)(code & kWhereIndex);

@@ -308,11 +308,14 @@ struct ClassInfo {
 // one that scans in between, for the sort).  A workgroup takes the next ticket when it begins and waits only for the counts
 // of workgroups with earlier tickets, which have begun and say their counts before they wait for anything: every wait ends
 // whatever else runs on the GPU.  The words are cleared by the stage's first kernel.
-// The line lies where both ways cost the same on this chip: with a kernel a pass, four tables of 41 k lookups take 845
-// instead of 1054 us for six steps, 262 k lookups 1080 instead of 1113 us for five, 327 k 2660 instead of 2740; beyond half
-// a million the sums over the workgroups before one's own (128 x 256 words a pass) take as long as the launches they
-// spare.  The digit totals cost the key generation an addition to memory per digit value and workgroup of 32 bags: not
-// with more than 65536 bags.
+// The line lies where whole steps cost the same either way.  8 tables of 200 k rows of 64 bytes, 4096 bags each, the next
+// batch prefetched ahead, us a step with a kernel a pass / with two or three: every row resident 126 / 143 at 131072 lookups,
+// 149 / 156 at 262144, 169 / 170 at 393216, 191 / 188 at 524288; a fifth of the rows cached 308 / 330, 462 / 481, 570 / 588,
+// 651 / 665.  The stage's kernels alone cross over earlier, at about 200 k lookups (107 / 113, 123 / 120, 134 / 121,
+// 152 / 134 us), because every workgroup adds up the counts of all before it; up to the line the launches and the host time
+// that they spare (15 to 35 us of host time a step) make up for that.  Beyond it they do not: with twice and four times the
+// workgroups of the sort the stage takes 203 / 157 us at 1048576 lookups and 311 / 199 at 2097152.  The digit totals cost
+// the key generation an addition to memory per digit value and workgroup of 32 bags: not with more than 65536 bags.
 constexpr int64_t kSmallLookups = 524288, kSmallBags = 65536;
 constexpr int kMaxSortPasses = 4;
 constexpr int kSmallSortThreads = 512;
