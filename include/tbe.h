@@ -138,6 +138,8 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
  *               (t, b) are d_indices[d_offsets[t*batch+b] .. d_offsets[t*batch+b+1]).
  *   d_offsets : DEVICE int64[num_tables*batch + 1], non-decreasing, first 0, last
  *               num_lookups.
+ * TBE_ELIMIT, beside the sizes given to tbe_create, for a batch of 2^32 / lanes samples and more, where
+ * lanes is the widest row's bytes / 16 rounded up to a power of two (2^26 samples for rows of 1 KB).
  * Both buffers must stay valid and unchanged until the matching tbe_backward_update has
  * completed on the compute stream.  They must have been produced on (or be ordered
  * before) the compute stream at the time of this call.

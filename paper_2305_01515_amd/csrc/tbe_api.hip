@@ -412,6 +412,8 @@ int do_prefetch_deep(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offs
 int check_batch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, int32_t batch, int64_t n) {
   if (!d_offsets || batch < 0 || n < 0 || (n > 0 && (!d_indices || batch == 0))) return fail(h, TBE_EINVAL, "prefetch: bad argument");
   if (batch > h->max_batch || n > h->max_lookups) return fail(h, TBE_ELIMIT, "prefetch: batch or lookups above the sizes given to tbe_create");
+  // (a table's bags are one launch of the forward, a lane group each, and a launch holds fewer than 2^32 threads)
+  if ((int64_t)batch * h->g.win_stride > (1ll << 32) - 256) return fail(h, TBE_ELIMIT, "prefetch: batch times the widest row's lanes reaches 2^32");
   return TBE_OK;
 }
 

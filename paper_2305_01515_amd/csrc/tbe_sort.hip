@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256) void begin_kernel(int64_t nb, const int64_t *_
 
 // HIST (small batches): also counts the digits of every pass of the sort, in LDS, and adds them to the batch's totals.
 template <bool HIST>
-__global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict__ tm, int T, int B, int64_t N,
+__global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict__ tm, int T, int B, int64_t N, int64_t first_bag,
                                                      const int64_t *__restrict__ indices,
                                                      const int64_t *__restrict__ offsets, uint32_t *__restrict__ keys,
                                                      uint32_t *__restrict__ vals, int32_t *__restrict__ bag_of_pos,
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void keygen_kernel(const TableMeta *__restrict
   const bool packed = within_bits > 0 && *too_long == 0u;
   if (blockIdx.x == 0 && threadIdx.x == 0) cnt->packed = packed ? 1 : 0;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t bag = gid / kKeygenLanes;
+  const int64_t bag = first_bag + gid / kKeygenLanes;
   const int sub = (int)(gid % kKeygenLanes);
   auto keys_of_bag = [&]() {
     const int64_t lo = offsets[bag], hi = offsets[bag + 1];
@@ -120,11 +120,11 @@ hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf 
   hipLaunchKernelGGL(begin_kernel, dim3((unsigned)(threads0 > 256 ? (threads0 + 255) / 256 : 1)), dim3(256), 0, s, nb,
                      b.d_offsets, g.within_bits, ss.too_long, (uint4 *)ss.said, n_said, (uint4 *)ss.said_counts, n_counts,
                      ss.refused, b.cnt);
-  const int64_t threads = nb * kKeygenLanes;
-  if (threads > 0) {
-    const int64_t blocks = (threads + 255) / 256;
-    hipLaunchKernelGGL((small ? keygen_kernel<true> : keygen_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, s, tm, g.T,
-                       b.batch, b.n, b.d_indices, b.d_offsets, ss.keys[0], ss.vals[0], b.bag_of_pos,
+  constexpr int64_t kBags = 1ll << 27;  // a launch holds fewer than 2^32 threads
+  for (int64_t first = 0; first < nb; first += kBags) {
+    const int64_t threads = (nb - first < kBags ? nb - first : kBags) * kKeygenLanes;
+    hipLaunchKernelGGL((small ? keygen_kernel<true> : keygen_kernel<false>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
+                       tm, g.T, b.batch, b.n, first, b.d_indices, b.d_offsets, ss.keys[0], ss.vals[0], b.bag_of_pos,
                        b.mean ? b.inv_len : nullptr, g.within_bits, ss.too_long, digits, ss.said, b.cnt);
   }
   return hipGetLastError();
