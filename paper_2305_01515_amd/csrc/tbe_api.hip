@@ -271,7 +271,7 @@ int alloc_max_records(tbe_ctx *h, BatchBuf &b) {
   // other batch is forwarded in between.  It lies in the partial sums' memory, which this mode does not use: with an array of
   // its own in every buffer a handle took up to 192 bytes more per lookup than before there were such records.
   b.wins = (uint8_t *)h->partials;
-  if (!b.sorted_pos) HIP_TRY(h, h->mem.get(&b.sorted_pos, 4 * N));
+  if (!b.sorted_at) HIP_TRY(h, h->mem.get(&b.sorted_at, 4 * N));
   return TBE_OK;
 }
 
@@ -594,6 +594,7 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   h->g.total_slots = (int64_t)sets * ways;
   h->g.ovf_stride = 16;
   h->g.win_stride = 1;
+  for (const TableMeta &m : h->tm) h->g.dtypes |= m.dtype == TBE_FP32 ? 1 : 2;
   for (const TableMeta &m : h->tm) h->g.win_stride = std::max(h->g.win_stride, m.lanes);
   for (const TableMeta &m : h->tm) h->g.ovf_stride = std::max(h->g.ovf_stride, m.row_bytes);
   h->g.key_bits = 1;

@@ -277,7 +277,7 @@ static int run_compaction(Op op, const int32_t *n_ptr, int n_fixed, int n_bound,
 
 // n / d for any 32-bit n, with m = ceil(2^64 / d) (0 stands for d = 1): exact, because m d exceeds 2^64 by less than d
 __device__ inline uint32_t div_by(uint32_t n, u64 m) { return m ? (uint32_t)__umul64hi((u64)n, m) : n; }
-__device__ inline u64 div_magic(uint32_t d) { return d > 1 ? ~0ull / d + 1ull : 0ull; }
+__host__ __device__ inline u64 div_magic(uint32_t d) { return d > 1 ? ~0ull / d + 1ull : 0ull; }
 
 // ---- pass 1 over the N sorted lookups: distinct rows, run starts, and the first row of every touched set ----
 // Set heads are found here as well, from the keys of neighbouring rows (they were a count and emit pass of their own over
@@ -295,7 +295,9 @@ struct DedupOp {
   const BatchCounters *cnt;  // cnt->packed: the payload carries the bag
   int within_bits;
   const int64_t *offsets;
-  uint32_t *sorted_pos;      // max pooling only (else null): position of the lookup in input order
+  uint32_t *sorted_at;       // max pooling only (else null): position of the lookup in input order or inside its bag, by the
+  int dtypes;                //   table's storage type (see BatchBuf; Geometry::dtypes)
+  u64 bags_magic;            // of the bags per table
   uint32_t *uid_sorted;
   int32_t *sorted_bag;
   uint32_t *uniq_key;
@@ -355,7 +357,15 @@ struct DedupOp {
     const uint32_t p = pos[i];
     const int32_t bag = cnt->packed ? (int32_t)(p >> within_bits) : bag_of_pos[p];
     sorted_bag[i] = bag;
-    if (sorted_pos) sorted_pos[i] = cnt->packed ? (uint32_t)offsets[bag] + (p & ((1u << within_bits) - 1u)) : p;
+    if (sorted_at) {
+      const bool inside = dtypes == 1 || (dtypes == 3 && tm[div_by((uint32_t)bag, bags_magic)].dtype == 0);
+      if (cnt->packed) {
+        const uint32_t within = p & ((1u << within_bits) - 1u);
+        sorted_at[i] = inside ? within : (uint32_t)offsets[bag] + within;
+      } else {
+        sorted_at[i] = inside ? p - (uint32_t)offsets[bag] : p;
+      }
+    }
     if (f.lo(0)) {
       const uint32_t k = key[i];
       if (k < base || k > last) enter_table_of(k);  // (the lane's next element may lie in the next table)
@@ -1104,7 +1114,7 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
     return hipGetLastError();
   }
   DedupOp d{tm, g.T, sorted_keys, sorted_pos, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
-            b.maxp ? b.sorted_pos : nullptr, b.uid_sorted, b.sorted_bag, b.uniq_key, b.run_off,
+            b.maxp ? b.sorted_at : nullptr, g.dtypes, div_magic((uint32_t)b.batch), b.uid_sorted, b.sorted_bag, b.uniq_key, b.run_off,
             b.uniq_tab, b.touched, -1, 0u, 0u, 0u, 0ull, false, nullptr};
   const bool small = small_batch(g, n, b.batch);
   run_compaction(d, nullptr, n, n, ss, small ? 0 : -1, b.cnt, s);

@@ -182,8 +182,11 @@ __global__ __launch_bounds__(256) void forward_kernel(const TableMeta *__restric
 // Max pooling (Section 2.1.1): element d of the pooled vector is the largest element d among the
 // bag's rows; `argpos` records, per pooled element, the position inside the bag of the lookup
 // that supplied it -- the first one when several tie (lookups are visited in bag order), -1 for
-// an empty bag, whose pooled vector is zero.  The backward sends the element's gradient there, so every lookup gets a
-// record of the elements it supplied, a bit each (`wins`): a byte per lane of the row.
+// an empty bag, whose pooled vector is zero.  The backward sends the element's gradient there.  For it every lookup of a
+// binary16 row also gets a record of the elements it supplied, a bit each (`wins`): a byte per lane of the row, where the
+// positions of a lane's eight elements are 32.  Writing the records costs this kernel a fifth (491 k lookups of 5000 rows of 256
+// elements 35 -> 41 us) and saves the backward a fifth and more (163 -> 127 us).  fp32 rows, four elements to a lane, have none:
+// there it would cost more than it saves (64 elements 19 -> 24 us, backward 63 -> 67 us).
 template <int DT, int G>
 __global__ __launch_bounds__(256) void forward_max_kernel(const TableMeta *__restrict__ tm,
                                                           const int32_t *__restrict__ class_tables, int B, int sum_dim,
@@ -245,13 +248,26 @@ __global__ __launch_bounds__(256) void forward_max_kernel(const TableMeta *__res
       *(float4 *)(o + e) = make_float4(best[e], best[e + 1], best[e + 2], best[e + 3]);
       *(int4 *)(a + e) = make_int4(who[e], who[e + 1], who[e + 2], who[e + 3]);
     }
-    uint8_t *w = wins + (size_t)lo * win_stride + lig;
-    const int len = (int)(hi - lo);
-    for (int p = 0; p < len; p++) {
-      uint32_t bits = 0;
+    if constexpr (DT == 1) {
+      uint8_t *w = wins + (size_t)lo * win_stride + lig;
+      const int len = (int)(hi - lo);
+      if (len <= EPL) {
+        for (int p = 0; p < len; p++) {
+          uint32_t bits = 0;
 #pragma unroll
-      for (int e = 0; e < EPL; e++) bits |= (who[e] == p ? 1u : 0u) << e;
-      w[(size_t)p * win_stride] = (uint8_t)bits;
+          for (int e = 0; e < EPL; e++) bits |= (who[e] == p ? 1u : 0u) << e;
+          w[(size_t)p * win_stride] = (uint8_t)bits;
+        }
+      } else {  // most lookups supplied nothing of this lane's elements: all bytes to zero, then those of its winners
+        for (int p = 0; p < len; p++) w[(size_t)p * win_stride] = 0;
+#pragma unroll
+        for (int e = 0; e < EPL; e++) {
+          uint32_t bits = 0;
+#pragma unroll
+          for (int f = 0; f < EPL; f++) bits |= (who[f] == who[e] ? 1u : 0u) << f;
+          w[(size_t)who[e] * win_stride] = (uint8_t)bits;
+        }
+      }
     }
   }
 }
@@ -332,20 +348,21 @@ __device__ inline RowRef locate(const TableMeta &m, uint32_t key, int slot, char
 // lanes: the bag ids are read G at a time (coalesced) and handed round by shuffles, four
 // gradient rows are in flight per lane.  `stride_chunks` > 1 lets several groups share a
 // range chunk-wise (group `first_chunk` of `stride_chunks`).  Summation order is fixed.
-// MODE: kSum, kMean (every gradient row weighs 1 / lookups of its bag, from inv_len) or kMax (a lookup receives element d
-// of its bag's gradient only if it supplied the maximum: Wins has its record).
+// col: the lane's first column (max pooling).  MODE: kSum, kMean (every gradient row weighs 1 / lookups of its bag, from inv_len) or kMax (a lookup receives element d
+// of its bag's gradient only if it supplied the maximum: see Winners).
 constexpr int kSum = 0, kMean = 1, kMax = 2;
 
-struct Wins {
-  const uint8_t *rec;          // the lookups' records, input order
+// Max pooling: which elements of its row a lookup supplied the maximum of.
+struct Winners {
+  const uint8_t *rec;       // binary16 rows: the lookups' records, input order
   int stride;
-  const uint32_t *sorted_pos;  // position of the i-th lookup in sorted order
+  const int32_t *argpos;    // fp32 rows: per pooled element, the position inside its bag of the lookup that supplied it
+  const uint32_t *sorted_at;  // of the i-th lookup in sorted order: its position in input order (binary16), inside its bag (fp32)
 };
 
-// Max pooling: a lookup of a bag of L lookups supplies one element in L.  Its record, a byte per lane, says which, and a lane
-// reads only the 16-byte pieces of the gradient that hold one of its own.  (With who supplied each element recorded per
-// pooled element, four bytes each, a lookup read as many bytes of that as of gradients, and all of both: 1 KB instead of
-// about 160 bytes at 128 elements and 25 lookups.)
+// Max pooling: a lookup of a bag of L lookups supplies one element in L, and a lane that knows which reads only the 16-byte
+// pieces of the gradient that hold one of its own: for binary16 rows some 160 bytes a lookup instead of 1 KB, positions and
+// all of the gradient (128 elements, 25 lookups).
 template <int DT, int Q>
 struct MaxTaken {
   float4 v[Q][Elems<DT>::n / 4];
@@ -372,38 +389,59 @@ __device__ inline void max_add(float (&g)[Elems<DT>::n], const MaxTaken<DT, Q> &
     }
 }
 
-template <int DT, int G>
+template <int DT, int G, int Q>
 __device__ inline void reduce_max_grads(float (&g)[Elems<DT>::n], const float *gbase, const int32_t *sorted_bag, int bag0,
                                         int sum_dim, int i0, int i1, int first_chunk, int stride_chunks, int lig,
-                                        bool active, const Wins &wins) {
+                                        bool active, const Winners &wins, int col) {
   for (int base = i0 + first_chunk * G; base < i1; base += stride_chunks * G) {
     const int nq = (i1 - base) < G ? (i1 - base) : G;
     const int my_bag = lig < nq ? sorted_bag[base + lig] - bag0 : 0;
-    const uint32_t my_pos = lig < nq ? wins.sorted_pos[base + lig] : 0u;
-    for (int q = 0; q < nq; q += 4) {
-      uint32_t w[4];
-      const float *p[4];
+    const uint32_t my_at = lig < nq ? wins.sorted_at[base + lig] : 0u;
+    for (int q = 0; q < nq; q += Q) {
+      if constexpr (DT == 1) {
+        uint32_t w[Q];
+        const float *p[Q];
 #pragma unroll
-      for (int x = 0; x < 4; x++) {
-        const uint32_t pos = (uint32_t)__shfl((int)my_pos, (q + x) & (G - 1), G);
-        p[x] = gbase + (size_t)__shfl(my_bag, (q + x) & (G - 1), G) * sum_dim;
-        w[x] = (active && q + x < nq) ? wins.rec[(size_t)pos * wins.stride + lig] : 0u;
+        for (int x = 0; x < Q; x++) {
+          const uint32_t pos = (uint32_t)__shfl((int)my_at, (q + x) & (G - 1), G);
+          p[x] = gbase + (size_t)__shfl(my_bag, (q + x) & (G - 1), G) * sum_dim;
+          w[x] = (active && q + x < nq) ? wins.rec[(size_t)pos * wins.stride + lig] : 0u;
+        }
+        MaxTaken<DT, Q> t;
+        max_request(t, p, w);
+        max_add(g, t, w);
+      } else {  // gradients and positions are requested at the same time
+        float4 v[Q];
+        int4 who[Q];
+        int within[Q];
+#pragma unroll
+        for (int x = 0; x < Q; x++) {
+          within[x] = __shfl((int)my_at, (q + x) & (G - 1), G);
+          const size_t at = (size_t)__shfl(my_bag, (q + x) & (G - 1), G) * sum_dim;
+          const bool ok = active && q + x < nq;
+          v[x] = ok ? *(const float4 *)(gbase + at) : make_float4(0.f, 0.f, 0.f, 0.f);
+          who[x] = ok ? *(const int4 *)(wins.argpos + col + at) : make_int4(-1, -1, -1, -1);
+        }
+#pragma unroll
+        for (int x = 0; x < Q; x++) {
+          g[0] += who[x].x == within[x] ? v[x].x : 0.f;
+          g[1] += who[x].y == within[x] ? v[x].y : 0.f;
+          g[2] += who[x].z == within[x] ? v[x].z : 0.f;
+          g[3] += who[x].w == within[x] ? v[x].w : 0.f;
+        }
       }
-      MaxTaken<DT, 4> t;
-      max_request(t, p, w);
-      max_add(g, t, w);
     }
   }
 }
 
-template <int DT, int G, int MODE>
+template <int DT, int G, int MODE, int Q = 4>
 __device__ inline void reduce_grads(float (&g)[Elems<DT>::n], const float *gbase, const int32_t *sorted_bag, int bag0,
                                     int sum_dim, int i0, int i1, int first_chunk, int stride_chunks, int lig,
-                                    bool active, const float *inv_len, const Wins &wins) {
+                                    bool active, const float *inv_len, const Winners &wins, int col) {
   constexpr int EPL = Elems<DT>::n;
   constexpr bool MEAN = MODE == kMean;
   if constexpr (MODE == kMax) {
-    reduce_max_grads<DT, G>(g, gbase, sorted_bag, bag0, sum_dim, i0, i1, first_chunk, stride_chunks, lig, active, wins);
+    reduce_max_grads<DT, G, Q>(g, gbase, sorted_bag, bag0, sum_dim, i0, i1, first_chunk, stride_chunks, lig, active, wins, col);
     return;
   }
   for (int base = i0 + first_chunk * G; base < i1; base += stride_chunks * G) {
@@ -550,7 +588,7 @@ __device__ inline void update_single_rows_max(int blk, int blocks_per_table, con
                                                               const uint32_t *__restrict__ loc,
                                                               const float *__restrict__ grad_out, float lr, float eps,
                                                               char *__restrict__ ovf, uint32_t ovf_stride,
-                                                              const uint8_t *__restrict__ wins, int win_stride) {
+                                                              const Winners &wins) {
   constexpr int EPL = Elems<DT>::n;
   const int t = class_tables[blk / blocks_per_table];
   const TableMeta &m = tm[t];
@@ -569,6 +607,8 @@ __device__ inline void update_single_rows_max(int blk, int blocks_per_table, con
 #pragma unroll
   for (int e = 0; e < EPL; e++) g[e] = 0.f;
   if (active) load_grad<DT>(g, grad_out + (size_t)b * sum_dim + m.col + lig * EPL);
+  int4 who = make_int4(-1, -1, -1, -1);  // fp32: who supplied this lane's elements
+  if (DT == 0 && active) who = *(const int4 *)(wins.argpos + (size_t)b * sum_dim + m.col + lig * EPL);
   const float inv_dim = 1.0f / (float)m.dim;
   for (int64_t j0 = lo; j0 < hi; j0 += G) {
     const int nq = (int)((hi - j0) < G ? (hi - j0) : G);
@@ -597,7 +637,12 @@ __device__ inline void update_single_rows_max(int blk, int blocks_per_table, con
             mp[x] = slot_m + ((int)ix - slot_base);
           }
           m_old[x] = *mp[x];
-          win[x] = active ? wins[(size_t)(j0 + q) * win_stride + lig] : 0u;
+          if constexpr (DT == 1) {
+            win[x] = active ? wins.rec[(size_t)(j0 + q) * wins.stride + lig] : 0u;
+          } else {
+            const int within = (int)(j0 - lo) + q;
+            win[x] = (who.x == within ? 1u : 0u) | (who.y == within ? 2u : 0u) | (who.z == within ? 4u : 0u) | (who.w == within ? 8u : 0u);
+          }
           if (active) raw[x] = load_once(w[x]);
           n = x + 1;
         }
@@ -636,7 +681,7 @@ __device__ inline void update_short_rows(int blk, int blocks, const TableMeta *_
                                                              char *__restrict__ ovf, uint32_t ovf_stride,
                                                              const int32_t *__restrict__ table_class,
                                                              const float *__restrict__ inv_len,
-                                                             Wins wins, const BatchCounters *cnt) {
+                                                             const Winners &wins, const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
   const int n_mid = cnt->n_mid;
   const int lig = threadIdx.x % G;
@@ -653,40 +698,50 @@ __device__ inline void update_short_rows(int blk, int blocks, const TableMeta *_
 #pragma unroll
     for (int e = 0; e < EPL; e++) g[e] = 0.f;
     reduce_grads<DT, G, MODE>(g, grad_out + m.col + lig * EPL, sorted_bag, t * B, sum_dim, i0, i1, 0, 1, lig, active, inv_len,
-                              wins);
+                              wins, m.col + lig * EPL);
     update_row<DT, G>(m, uniq_key[u], loc_u[u], ovf, ovf_stride, g, lr, eps, lig, active);
   }
 }
 
-// Rows narrower than 4 lanes, and under max pooling narrower than 8: rows with more than kLongRun lookups, one workgroup per row, its 256/G groups take
-// chunks of G lookups round robin; the partial sums are added in group order through LDS.  (The
-// gradient a lookup receives is masked by who supplied each maximum, so the bags' gradient rows cannot
-// be shared between rows the way the tile kernel below shares them.)
-template <int DT, int G, int MODE>
-__global__ __launch_bounds__(256) void backward_long_kernel(const TableMeta *__restrict__ tm, int cls, int B,
-                                                            int sum_dim, const int32_t *__restrict__ heavy,
-                                                            const int32_t *__restrict__ heavy_sub,
-                                                            const uint32_t *__restrict__ uniq_key,
-                                                            const int32_t *__restrict__ uniq_tab,
-                                                            const int32_t *__restrict__ run_off,
-                                                            const int32_t *__restrict__ loc_u,
-                                                            const int32_t *__restrict__ sorted_bag,
-                                                            const float *__restrict__ grad_out, float lr, float eps,
-                                                            char *__restrict__ ovf, uint32_t ovf_stride,
-                                                            const int32_t *__restrict__ table_class,
-                                                            const float *__restrict__ inv_len,
-                                                            Wins wins, const BatchCounters *cnt) {
+// Rows narrower than 4 lanes, and under max pooling: rows with more than kLongRun lookups, one workgroup per row, its 256/G
+// groups take chunks of G lookups round robin; the partial sums are added in group order through LDS.  (The gradient a lookup
+// receives is masked by who supplied each maximum, so the bags' gradient rows cannot be shared between rows the way the tile
+// kernel below shares them.)
+//
+// Under max pooling a row's chains of chunks are what bounds a power-law batch: the hottest of 500 k rows has 12 k of a table's
+// 100 k lookups, 48 chunks a chain, each of them several dependent reads.  Rows of 16 lanes and more with more than hot_row
+// lookups therefore have a launch of their own: binary16 rows in the next kernel but one, fp32 rows here with 16 lookups of a
+// chunk in flight instead of 4 (which costs 171 registers instead of 85: not for the many rows with some hundred lookups).
+// Backward in us, 491 k lookups of 100 k rows, some rows with tens of thousands, rows of 16, 32, 64 lanes: fp32 301, 540, 1000
+// (419, 757, 1419 with 4 in flight for all rows; 247, 608, 1991 with records and the binary16 kernel for all long rows),
+// binary16 362, 867, 2820 (948, 1745, 3210 here; 336, 839, 2690 with all long rows in that kernel).  524 k lookups spread evenly over
+// rows of about 98: fp32 58, 88, 149 (120, 205, 340 with all long rows there), binary16 93, 126, 190 (160, 235, 585).
+// Where the lines lie, evenly spread lookups a row, us with all long rows in the rest's launch / all in the hot rows':
+// binary16, 16 lanes 50 / 79 at 256, 40 / 62 at 512, 54 / 49 at 1024, 156 / 61 at 4096; 32 lanes 69 / 83 at 512, 96 / 68 at 1024;
+// 64 lanes 121 / 137 at 512, 174 / 165 at 1024.  fp32, 16 lanes 31 / 47 at 512, 32 / 31 at 1024, 44 / 40 at 2048.
+template <int DT, int G>
+constexpr int hot_row() { return G < 16 ? 0x7FFFFFFF : DT == 1 ? 512 : 1024; }
+// Q: lookups a group has in flight (max pooling).  HOT: the rows with more than hot_row lookups, else those with up to that many.
+template <int DT, int G, int MODE, int Q, bool HOT>
+__device__ inline void update_long_rows(int blk, int blocks, const TableMeta *__restrict__ tm, int cls, int B, int sum_dim,
+                                        const int32_t *__restrict__ heavy, const int32_t *__restrict__ heavy_sub,
+                                        const uint32_t *__restrict__ uniq_key, const int32_t *__restrict__ uniq_tab,
+                                        const int32_t *__restrict__ run_off, const int32_t *__restrict__ loc_u,
+                                        const int32_t *__restrict__ sorted_bag, const float *__restrict__ grad_out, float lr,
+                                        float eps, char *__restrict__ ovf, uint32_t ovf_stride,
+                                        const int32_t *__restrict__ table_class, const float *__restrict__ inv_len,
+                                        const Winners &wins, const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
   constexpr int NG = 256 / G;
   __shared__ float part[NG][G * EPL + 1];
-  if (cnt->err) return;
   const int n_heavy = cnt->n_heavy;
   const int lig = threadIdx.x % G, grp = threadIdx.x / G;
   int first, end, step;
-  xcd_span(n_heavy, 1, first, end, step);  // the list is in table order
+  xcd_span_of(blk, blocks, n_heavy, 1, first, end, step);  // the list is in table order
   for (int it = first; it < end; it += step) {
     if (heavy_sub[it] & 0xFFFF) continue;  // a hot row has several entries: it is taken whole at its first
     const int u = heavy[it];
+    if (MODE == kMax && (run_off[u + 1] - run_off[u] > hot_row<DT, G>()) != HOT) continue;
     const int t = uniq_tab[u];
     if (table_class[t] != cls) continue;  // uniform over the block
     const TableMeta &m = tm[t];
@@ -694,8 +749,8 @@ __global__ __launch_bounds__(256) void backward_long_kernel(const TableMeta *__r
     float g[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; e++) g[e] = 0.f;
-    reduce_grads<DT, G, MODE>(g, grad_out + m.col + lig * EPL, sorted_bag, t * B, sum_dim, run_off[u], run_off[u + 1], grp,
-                              NG, lig, active, inv_len, wins);
+    reduce_grads<DT, G, MODE, Q>(g, grad_out + m.col + lig * EPL, sorted_bag, t * B, sum_dim, run_off[u], run_off[u + 1], grp,
+                                 NG, lig, active, inv_len, wins, m.col + lig * EPL);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < EPL; e++) part[grp][lig * EPL + e] = g[e];
@@ -712,15 +767,35 @@ __global__ __launch_bounds__(256) void backward_long_kernel(const TableMeta *__r
   }
 }
 
-// Max pooling, rows with more than kLongRun lookups, rows of at least 8 lanes: one workgroup of 1024 threads per row.  The
-// sum is made of the same 256 / G chains as above, chain c adding the chunks c, c + 256 / G, ... of G lookups in lookup
-// order (so its rounding is that of the kernel above, bit for bit), but a chain has a wavefront instead of a lane group:
-// its 64 / G groups request Q lookups each at the same time, the records a step ahead, and the running sum is handed from
-// group to group.  A chain's length is what bounds this kernel: the hottest of 500 k rows has 12 k of a table's 100 k
-// lookups, 48 chunks a chain, each of which took a lane group four rounds of dependent reads.  8 tables of 500 k rows of
-// 128 elements, 818 k lookups: 0.28 -> 0.13 ms (0.29 ms with the row's elements spread over all 64 lanes: three times as many load instructions).
-template <int DT, int G>
-__global__ __launch_bounds__(1024) void backward_long_max_kernel(const TableMeta *__restrict__ tm, int cls, int B, int sum_dim,
+// Under max pooling the long rows of 16 lanes and more share the launch of the rest of the backward, the hot ones have their own
+// in front of it (so a batch has as many launches as with one for all long rows, and the few hot rows' chains are all that the
+// rest has to wait for).
+template <int G>
+constexpr bool kLongInRest = G >= 16;
+
+template <int DT, int G, int MODE>
+__global__ __launch_bounds__(256) void backward_long_kernel(const TableMeta *__restrict__ tm, int cls, int B, int sum_dim,
+                                                            BatchBuf b, const float *__restrict__ grad_out, float lr, float eps,
+                                                            uint32_t ovf_stride, const int32_t *__restrict__ table_class,
+                                                            int win_stride) {
+  if (b.cnt->err) return;
+  constexpr bool kHot = MODE == kMax && kLongInRest<G>;
+  update_long_rows<DT, G, MODE, kHot ? 16 : 4, kHot>(
+      blockIdx.x, gridDim.x, tm, cls, B, sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off, b.loc_u, b.sorted_bag,
+      grad_out, lr, eps, b.ovf, ovf_stride, table_class, MODE == kMean ? b.inv_len : nullptr,
+      Winners{b.wins, win_stride, b.argpos, b.sorted_at}, b.cnt);
+}
+
+// Max pooling of binary16 rows of at least 16 lanes: rows with more than hot_row lookups, one workgroup per row.
+// The sum is made of the same 256 / G chains as above, chain c adding the chunks c, c + 256 / G, ... of G lookups in lookup
+// order (so its rounding is that of the kernel above, bit for bit), but a chain has a wavefront instead of a lane group, and the
+// workgroup as many wavefronts as the row has chains: a wavefront's 64 / G groups request Q lookups each at the same time, the
+// records a step ahead, and the running sum is handed from group to group.  (With 1024 threads whatever G, 512 rows of 1024
+// lookups of 64 lanes took 265 instead of 165 us: a CU holds one such workgroup, and 4 of its 16 wavefronts had a chain.)
+template <int G>
+constexpr int kHotThreads = kWave * (256 / G);
+template <int G>
+__global__ __launch_bounds__(kHotThreads<G>) void backward_long_max_kernel(const TableMeta *__restrict__ tm, int cls, int B, int sum_dim,
                                                                  const int32_t *__restrict__ heavy,
                                                                  const int32_t *__restrict__ heavy_sub,
                                                                  const uint32_t *__restrict__ uniq_key,
@@ -730,96 +805,109 @@ __global__ __launch_bounds__(1024) void backward_long_max_kernel(const TableMeta
                                                                  const int32_t *__restrict__ sorted_bag,
                                                                  const float *__restrict__ grad_out, float lr, float eps,
                                                                  char *__restrict__ ovf, uint32_t ovf_stride,
-                                                                 const int32_t *__restrict__ table_class, Wins wins,
+                                                                 const int32_t *__restrict__ table_class, Winners wins,
                                                                  const BatchCounters *cnt) {
-  static_assert(G >= 8, "a chunk of G lookups has at least a lookup for each of a wavefront's groups");
+  static_assert(G >= 16, "a chunk of G lookups has several for each of a wavefront's groups, and the chains fit a workgroup");
+  constexpr int DT = 1;
   constexpr int EPL = Elems<DT>::n;
   constexpr int NG = 256 / G;                         // chains
   constexpr int GU = kWave / G;                       // groups of a wavefront
   constexpr int Q = G / GU < 4 ? G / GU : 4;          // lookups a group requests at a time
   constexpr int STEP = GU * Q;                        // ... and the wavefront; G is a multiple of it
   __shared__ float part[NG][G * EPL + 1];
+  constexpr int kThreads = kHotThreads<G>;
+  __shared__ int s_row[kThreads], s_n;
   if (cnt->err) return;
   const int n_heavy = cnt->n_heavy;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lig = lane % G, grp = lane / G;
   int first, end, step;
   xcd_span(n_heavy, 1, first, end, step);  // the list is in table order
-  for (int it = first; it < end; it += step) {
-    if (heavy_sub[it] & 0xFFFF) continue;  // a hot row has several entries: it is taken whole at its first
-    const int u = heavy[it];
-    const int t = uniq_tab[u];
-    if (table_class[t] != cls) continue;  // uniform over the block
-    const TableMeta &m = tm[t];
-    const bool active = lig * EPL < m.dim;
-    const float *gbase = grad_out + m.col + lig * EPL;
-    const int i0 = run_off[u], i1 = run_off[u + 1];
-    const int bag0 = t * B;
-    __syncthreads();  // the row before is no longer read
-    for (int c = wave; c < NG; c += 16) {
-      float g[EPL];
-#pragma unroll
-      for (int e = 0; e < EPL; e++) g[e] = 0.f;
-      // The wavefront's steps are numbered: step s covers the lookups of chunk c + s / (G / STEP) * NG from (s % (G / STEP))
-      // * STEP on; this lane's group has Q of them.
-      auto first_of = [&](int s) { return i0 + (c + s / (G / STEP) * NG) * G + s % (G / STEP) * STEP + grp * Q; };
-      // (a chunk's lookups end where the next chain's begin, so a step never reaches past its own chunk)
-      auto places = [&](int s, int (&bag)[Q], uint32_t (&pos)[Q]) {
-        const int at = first_of(s);
-#pragma unroll
-        for (int x = 0; x < Q; x++) {
-          bag[x] = at + x < i1 ? sorted_bag[at + x] - bag0 : -1;
-          pos[x] = at + x < i1 ? wins.sorted_pos[at + x] : 0u;
-        }
-      };
-      auto records = [&](const int (&bag)[Q], const uint32_t (&pos)[Q], uint32_t (&w)[Q]) {
-#pragma unroll
-        for (int x = 0; x < Q; x++) w[x] = (bag[x] >= 0 && active) ? wins.rec[(size_t)pos[x] * wins.stride + lig] : 0u;
-      };
-      const int chunks = (i1 - i0 + G - 1) / G;
-      const int n_steps = chunks > c ? ((chunks - c + NG - 1) / NG) * (G / STEP) : 0;
-      // in flight: the gradients of step s, the records of step s + 1, the places of step s + 2 (past the last step: past
-      // the row's end or, for the chain's neighbours, looked at and never added)
-      uint32_t w[Q], w1[Q], pos1[Q], pos2[Q];
-      int bag[Q], bag1[Q], bag2[Q];
-      if (n_steps > 0) {
-        places(0, bag, pos1);
-        records(bag, pos1, w);
-        places(1, bag1, pos1);
-      }
-      for (int s = 0; s < n_steps; s++) {
-        const float *p[Q];
-#pragma unroll
-        for (int x = 0; x < Q; x++) p[x] = gbase + (size_t)(bag[x] < 0 ? 0 : bag[x]) * sum_dim;
-        MaxTaken<DT, Q> taken;
-        max_request(taken, p, w);
-        records(bag1, pos1, w1);
-        places(s + 2, bag2, pos2);
-        for (int j = 0; j < GU; j++) {  // every group adds its own lookups, the sum of group j is the one that counts
-          float sum[EPL];
-#pragma unroll
-          for (int e = 0; e < EPL; e++) sum[e] = g[e];
-          max_add(sum, taken, w);
-#pragma unroll
-          for (int e = 0; e < EPL; e++) g[e] = __shfl(sum[e], j * G + lig, kWave);
-        }
-#pragma unroll
-        for (int x = 0; x < Q; x++) { w[x] = w1[x]; bag[x] = bag1[x]; bag1[x] = bag2[x]; pos1[x] = pos2[x]; }
-      }
-      if (grp == 0)
-#pragma unroll
-        for (int e = 0; e < EPL; e++) part[c][lig * EPL + e] = g[e];
+  for (; first < end; first += step * kThreads) {  // the hot rows among a workgroup's entries, a thread looks at each
+    __syncthreads();
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const int64_t it = first + (int64_t)step * threadIdx.x;
+    if (it < end && !(heavy_sub[it] & 0xFFFF)) {  // a hot row has several entries: it is taken whole at its first
+      const int u = heavy[it];
+      if (run_off[u + 1] - run_off[u] > hot_row<DT, G>() && table_class[uniq_tab[u]] == cls) s_row[atomicAdd(&s_n, 1)] = u;
     }
     __syncthreads();
-    if (threadIdx.x < G) {
-      float g[EPL];
+    for (int r = 0; r < s_n; r++) {
+      const int u = s_row[r];
+      const int t = uniq_tab[u];
+      const TableMeta &m = tm[t];
+      const bool active = lig * EPL < m.dim;
+      const float *gbase = grad_out + m.col + lig * EPL;
+      const int i0 = run_off[u], i1 = run_off[u + 1];
+      const int bag0 = t * B;
+      __syncthreads();  // the row before is no longer read
+      {
+        const int c = wave;
+        float g[EPL];
 #pragma unroll
-      for (int e = 0; e < EPL; e++) {
-        float sum = 0.f;
-        for (int q = 0; q < NG; q++) sum += part[q][lig * EPL + e];
-        g[e] = sum;
+        for (int e = 0; e < EPL; e++) g[e] = 0.f;
+        // The wavefront's steps are numbered: step s covers the lookups of chunk c + s / (G / STEP) * NG from (s % (G / STEP))
+        // * STEP on; this lane's group has Q of them.
+        auto first_of = [&](int s) { return i0 + (c + s / (G / STEP) * NG) * G + s % (G / STEP) * STEP + grp * Q; };
+        // (a chunk's lookups end where the next chain's begin, so a step never reaches past its own chunk)
+        auto places = [&](int s, int (&bag)[Q], uint32_t (&pos)[Q]) {
+          const int at = first_of(s);
+#pragma unroll
+          for (int x = 0; x < Q; x++) {
+            bag[x] = at + x < i1 ? sorted_bag[at + x] - bag0 : -1;
+            pos[x] = at + x < i1 ? wins.sorted_at[at + x] : 0u;
+          }
+        };
+        auto records = [&](const int (&bag)[Q], const uint32_t (&pos)[Q], uint32_t (&w)[Q]) {
+#pragma unroll
+          for (int x = 0; x < Q; x++) w[x] = (bag[x] >= 0 && active) ? wins.rec[(size_t)pos[x] * wins.stride + lig] : 0u;
+        };
+        const int chunks = (i1 - i0 + G - 1) / G;
+        const int n_steps = chunks > c ? ((chunks - c + NG - 1) / NG) * (G / STEP) : 0;
+        // in flight: the gradients of step s, the records of step s + 1, the places of step s + 2 (past the last step: past
+        // the row's end or, for the chain's neighbours, looked at and never added)
+        uint32_t w[Q], w1[Q], pos1[Q], pos2[Q];
+        int bag[Q], bag1[Q], bag2[Q];
+        if (n_steps > 0) {
+          places(0, bag, pos1);
+          records(bag, pos1, w);
+          places(1, bag1, pos1);
+        }
+        for (int s = 0; s < n_steps; s++) {
+          const float *p[Q];
+#pragma unroll
+          for (int x = 0; x < Q; x++) p[x] = gbase + (size_t)(bag[x] < 0 ? 0 : bag[x]) * sum_dim;
+          MaxTaken<DT, Q> taken;
+          max_request(taken, p, w);
+          records(bag1, pos1, w1);
+          places(s + 2, bag2, pos2);
+          for (int j = 0; j < GU; j++) {  // every group adds its own lookups, the sum of group j is the one that counts
+            float sum[EPL];
+#pragma unroll
+            for (int e = 0; e < EPL; e++) sum[e] = g[e];
+            max_add(sum, taken, w);
+#pragma unroll
+            for (int e = 0; e < EPL; e++) g[e] = __shfl(sum[e], j * G + lig, kWave);
+          }
+#pragma unroll
+          for (int x = 0; x < Q; x++) { w[x] = w1[x]; bag[x] = bag1[x]; bag1[x] = bag2[x]; pos1[x] = pos2[x]; }
+        }
+        if (grp == 0)
+#pragma unroll
+          for (int e = 0; e < EPL; e++) part[c][lig * EPL + e] = g[e];
       }
-      update_row<DT, G>(m, uniq_key[u], loc_u[u], ovf, ovf_stride, g, lr, eps, lig, active);
+      __syncthreads();
+      if (threadIdx.x < G) {
+        float g[EPL];
+#pragma unroll
+        for (int e = 0; e < EPL; e++) {
+          float sum = 0.f;
+          for (int q = 0; q < NG; q++) sum += part[q][lig * EPL + e];
+          g[e] = sum;
+        }
+        update_row<DT, G>(m, uniq_key[u], loc_u[u], ovf, ovf_stride, g, lr, eps, lig, active);
+      }
     }
   }
 }
@@ -1195,16 +1283,21 @@ __global__ __launch_bounds__(256) void backward_rest_kernel(int combine, int sin
     if constexpr (MODE != kMax && (SECT & kBwdCombine))
       combine_heavy_rows<DT, G, SECT == kBwdCombine ? 8 : 4>(blk, combine, tm, cls, b.heavy, b.heavy_sub, b.harrive, b.uniq_key, b.uniq_tab, b.loc_u, partials,
                                 pstride, lr, eps, b.ovf, ovf_stride, table_class, b.cnt);
+    if constexpr (MODE == kMax && kLongInRest<G>)
+      update_long_rows<DT, G, MODE, 4, false>(blk, combine, tm, cls, B, sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off,
+                                       b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf, ovf_stride, table_class, nullptr,
+                                       Winners{b.wins, win_stride, b.argpos, b.sorted_at}, b.cnt);
     return;
   }
   if constexpr ((SECT & kBwdSingle) != 0) {
     blk -= combine;
     if (blk < single && blk >= blocks_per_table * n_tables) return;  // padding
     const float *inv_len = MODE == kMean ? b.inv_len : nullptr;
+    const Winners wins{b.wins, win_stride, b.argpos, b.sorted_at};
     if (blk < single) {
       if constexpr (MODE == kMax)
         update_single_rows_max<DT, G>(blk, blocks_per_table, tm, class_tables, B, sum_dim, b.byp_key, b.d_offsets, b.loc, grad_out,
-                                      lr, eps, b.ovf, ovf_stride, b.wins, win_stride);
+                                      lr, eps, b.ovf, ovf_stride, wins);
       else
         update_single_rows<DT, G>(blk, blocks_per_table, tm, class_tables, B, sum_dim, b.byp_key, b.d_offsets, b.loc, grad_out, lr,
                                   eps, b.ovf, ovf_stride, inv_len);
@@ -1213,7 +1306,7 @@ __global__ __launch_bounds__(256) void backward_rest_kernel(int combine, int sin
     blk -= single;
     update_short_rows<DT, G, MODE>(blk, (int)gridDim.x - combine - single, tm, cls, B, sum_dim, b.mid_idx, b.uniq_key, b.uniq_tab,
                                    b.run_off, b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf, ovf_stride, table_class, inv_len,
-                                   Wins{b.wins, win_stride, b.sorted_pos}, b.cnt);
+                                   wins, b.cnt);
   }
 }
 
@@ -1249,7 +1342,7 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
   constexpr bool kTiled = G >= 4;
   const bool tiled = kTiled && !b.maxp;
   const int64_t most_heavy = b.n / (kLongRun + 1) + b.n / kHeavySplit;  // entries of the heavy list
-  const Wins wins{b.wins, g.win_stride, b.sorted_pos};
+  const Winners wins{b.wins, g.win_stride, b.argpos, b.sorted_at};
   if (which & kBwdHeavy) {
     if (most_heavy == 0) return;
     if (tiled) {
@@ -1257,23 +1350,25 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
         hipLaunchKernelGGL((backward_heavy_kernel<DT, G>), dim3(b.n <= kSmallLookups ? 256 : 1024), dim3(kHeavyThreads), 0, s, tm,
                            cls, b.batch, g.sum_dim, b.hchunks, b.heavy, b.heavy_sub, b.hperm, b.hstart, b.run_off, b.sorted_bag,
                            grad_out, partials, g.partial_stride, table_class, b.mean ? b.inv_len : nullptr, b.cnt);
-    } else if (b.maxp && G >= 8) {
-      if constexpr (G >= 8)
-        hipLaunchKernelGGL((backward_long_max_kernel<DT, G>), dim3(work_blocks(most_heavy, 1, 4096)), dim3(1024), 0, s, tm, cls,
+    } else if (b.maxp && kLongInRest<G> && b.n <= hot_row<DT, G>()) {
+      return;
+    } else if (b.maxp && kLongInRest<G> && DT == 1) {
+      if constexpr (kLongInRest<G> && DT == 1)
+        hipLaunchKernelGGL((backward_long_max_kernel<G>), dim3(work_blocks(most_heavy, 1, 1024)), dim3(kHotThreads<G>), 0, s, tm, cls,
                            b.batch, g.sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off, b.loc_u, b.sorted_bag,
                            grad_out, lr, eps, b.ovf, g.ovf_stride, table_class, wins, b.cnt);
     } else {
       auto kern = b.maxp ? backward_long_kernel<DT, G, kMax>
                   : b.mean ? backward_long_kernel<DT, G, kMean> : backward_long_kernel<DT, G, kSum>;
-      hipLaunchKernelGGL(kern, dim3(work_blocks(most_heavy, 1, 8192)), dim3(256), 0, s, tm, cls, b.batch, g.sum_dim, b.heavy,
-                         b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off, b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf,
-                         g.ovf_stride, table_class, b.mean ? b.inv_len : nullptr, wins, b.cnt);
+      hipLaunchKernelGGL(kern, dim3(work_blocks(most_heavy, 1, b.maxp ? 4096 : 8192)), dim3(256), 0, s, tm, cls, b.batch, g.sum_dim,
+                         b, grad_out, lr, eps, g.ovf_stride, table_class, g.win_stride);
     }
     return;
   }
   const int per = 256 / G;  // lane groups of a workgroup
   const int blocks_per_table = (b.batch + per - 1) / per;
-  const int combine = (which & kBwdCombine) && tiled ? work_blocks(most_heavy, per, 2048) : 0;
+  const int combine = (which & kBwdCombine) && tiled ? work_blocks(most_heavy, per, 2048)
+                      : (which & kBwdShort) && b.maxp && kLongInRest<G> ? work_blocks(most_heavy, 1, 4096) : 0;
   const int shrt = (which & kBwdShort) ? work_blocks(b.n / 2, per, 4096) : 0;
   // A launch holds fewer than 2^32 threads: the bags of as many tables as make 2^30 at a time (16384 tables of 64 lanes,
   // batch 4096, are 2^32), the other sections with the first of them.

@@ -126,10 +126,11 @@ struct BatchBuf {
   bool maxp;            // max pooling: forward records who supplied each maximum, backward sends the gradient there
   int32_t *argpos;      // [batch * sum_dim] max pooling: position inside its bag of the lookup that supplied the
                         //     maximum of each pooled element (-1 for an empty bag); null unless max pooling is set
-  uint8_t *wins;        // [N * win_stride] max pooling: which elements of its row a lookup supplied the maximum of, input
-                        //     order: byte l for the elements of lane l, bit e for the lane's e-th; one array for all
+  uint8_t *wins;        // [N * win_stride] max pooling: which elements of its (binary16) row a lookup supplied the maximum of,
+                        //     input order: byte l for the elements of lane l, bit e for the lane's e-th; one array for all
                         //     batches (only the batch between its forward and its update has one)
-  uint32_t *sorted_pos; // [N] max pooling: position (input order) of the i-th lookup in sorted order
+  uint32_t *sorted_at;  // [N] max pooling, of the i-th lookup in sorted order: its position in input order (rows of a binary16
+                        //     table) or inside its bag (fp32)
   uint32_t *uid_sorted; // [N] index of the distinct row of the i-th sorted lookup
   // per distinct row (ascending key)
   uint32_t *uniq_key;   // [N]
@@ -285,6 +286,7 @@ struct Geometry {
   int64_t partial_slots;   // slots of the partial-sum buffer (heavy rows x bag ranges of a batch fit in)
   int32_t probe_min_windows = 4096;  // the probe does not group touched sets while that leaves fewer windows than this
   int32_t heavy_target;    // (chunk, bag range) work items the heavy rows' tile kernel should have: the CUs free for it
+  int32_t dtypes;          // storage types among the tables: 1 fp32, 2 binary16
   int32_t win_stride;      // max pooling: bytes of a lookup's record of the maxima it supplied (lanes of the widest row)
   uint32_t ovf_stride;     // bytes per overflow / staging slot (widest row)
   uint32_t total_sets;

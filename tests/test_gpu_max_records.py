@@ -1,5 +1,5 @@
-"""Max pooling: the lookups' records of the maxima they supplied, and the kernel that gives a row's chains of lookups a
-wavefront each: every number of lanes per row, rows with 65 to about a thousand lookups (one chunk a chain to many,
+"""Max pooling: who supplied the maxima, as the backward takes it (records of the lookups of binary16 rows, positions for
+fp32 rows), and the kernel that gives the chains of lookups of a hot row a wavefront each: every number of lanes per row, rows with 65 to about a thousand lookups (one chunk a chain to many,
 ragged ends)."""
 import pytest
 import torch
@@ -16,7 +16,7 @@ T = synth.TableCfg
                                        (128, synth.FP16), (200, synth.FP16), (512, synth.FP16)])
 def test_rows_of_every_width_and_length(dim, dtype):
     tabs = [T(900, dim, dtype, 1.3, "poisson", 9, 0, 60, cache_slots=16 * 9), T(3, 16, dtype, None, "fixed", 2, cache_slots=16),
-            T(1, dim, dtype, None, "fixed", 1)]
+            T(1, dim, dtype, None, "fixed", 1), T(70, 24, synth.FP16 if dtype == synth.FP32 else synth.FP32, 1.1, "poisson", 4, 0, 20)]
     st = run_parity(synth.WorkloadCfg("rec", tabs, batch=523, ways=16, steps=3, seed=dim, init_std=0.05, lr=0.05), steps=3,
                     order="early", pooling="max")
     assert st["last_long_rows"] > 0 and st["parted_at"] is None  # no near-tie taken differently: values compared to the end
@@ -32,3 +32,28 @@ def test_records_take_no_memory_of_their_own():
     taken = free - torch.cuda.mem_get_info()[0]
     assert taken <= 3 * 4 * (n + batch * dim) + (16 << 20)  # three buffers; (one such record: 64 MB)
     g.close()
+
+
+@pytest.mark.parametrize("batch", [512, 513, 1024, 1025, 6000])
+@pytest.mark.parametrize("dim", [64, 128, 200, 512])
+def test_rows_around_the_line_of_the_hot_ones(dim, batch):
+    """rows with exactly 512, 513, 1024 and 1025 lookups, binary16 rows of 8, 16, 32 and 64 lanes and fp32 rows of 16, 32 and 64
+    beside each other, and several with many more"""
+    half, full = synth.FP16, synth.FP32
+    tabs = [T(1, dim, half, None, "fixed", 1, cache_slots=8), T(40, 20, full, 1.2, "fixed", 3, cache_slots=16),
+            T(7, dim, half, 1.0, "poisson", 5, 0, 30, cache_slots=8), T(1, min(dim, 256), full, None, "fixed", 1),
+            T(300, dim, half, 1.3, "poisson", 6, 0, 40, cache_slots=80), T(90, min(dim, 256), full, 1.3, "poisson", 5, 0, 40, cache_slots=40)]
+    st = run_parity(synth.WorkloadCfg("hot", tabs, batch=batch, ways=8, steps=2, seed=dim + batch, init_std=0.05, lr=0.05), steps=2,
+                    order="early", pooling="max")
+    assert st["last_long_rows"] > 0 and st["parted_at"] is None
+
+
+@pytest.mark.parametrize("dtype", [synth.FP32, synth.FP16])
+def test_unpacked_payload_with_both_storage_types(dtype):
+    """bags too long for the packed payload: positions come from the offsets, inside the bag for fp32 rows, in input order for
+    binary16 rows"""
+    other = synth.FP16 if dtype == synth.FP32 else synth.FP32
+    tabs = [T(900, 64, dtype, 1.1, "poisson", 60, 0, 150, cache_slots=56), T(70, 24, other, 1.1, "poisson", 40, 0, 120)]
+    st = run_parity(synth.WorkloadCfg("unpacked", tabs, batch=64, ways=8, steps=3, seed=94, init_std=0.05, lr=0.05), steps=3,
+                    order="ahead", pooling="max", max_batch=1 << 26)
+    assert st["last_long_rows"] > 0 and st["parted_at"] is None
