@@ -821,8 +821,13 @@ __global__ __launch_bounds__(kHotThreads<G>) void backward_long_max_kernel(const
   const int n_heavy = cnt->n_heavy;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lig = lane % G, grp = lane / G;
+  // The first half of the workgroups takes the hottest rows, the second the others: a CU holds one workgroup or two, and a
+  // chain of 50 chunks should not begin when those of three have ended (8 tables of 500 k rows of 128 elements, three steps
+  // 1007 instead of 1044 us).
+  const int half = gridDim.x / 2;
+  const bool hottest = (int)blockIdx.x < half;
   int first, end, step;
-  xcd_span(n_heavy, 1, first, end, step);  // the list is in table order
+  xcd_span_of(blockIdx.x % half, half, n_heavy, 1, first, end, step);  // the list is in table order
   for (; first < end; first += step * kThreads) {  // the hot rows among a workgroup's entries, a thread looks at each
     __syncthreads();
     if (threadIdx.x == 0) s_n = 0;
@@ -830,7 +835,9 @@ __global__ __launch_bounds__(kHotThreads<G>) void backward_long_max_kernel(const
     const int64_t it = first + (int64_t)step * threadIdx.x;
     if (it < end && !(heavy_sub[it] & 0xFFFF)) {  // a hot row has several entries: it is taken whole at its first
       const int u = heavy[it];
-      if (run_off[u + 1] - run_off[u] > hot_row<DT, G>() && table_class[uniq_tab[u]] == cls) s_row[atomicAdd(&s_n, 1)] = u;
+      const int len = run_off[u + 1] - run_off[u];
+      if (len > hot_row<DT, G>() && (len > 4 * hot_row<DT, G>()) == hottest && table_class[uniq_tab[u]] == cls)
+        s_row[atomicAdd(&s_n, 1)] = u;
     }
     __syncthreads();
     for (int r = 0; r < s_n; r++) {
@@ -1354,7 +1361,7 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
       return;
     } else if (b.maxp && kLongInRest<G> && DT == 1) {
       if constexpr (kLongInRest<G> && DT == 1)
-        hipLaunchKernelGGL((backward_long_max_kernel<G>), dim3(work_blocks(most_heavy, 1, 1024)), dim3(kHotThreads<G>), 0, s, tm, cls,
+        hipLaunchKernelGGL((backward_long_max_kernel<G>), dim3(2 * work_blocks(most_heavy, 1, 1024)), dim3(kHotThreads<G>), 0, s, tm, cls,
                            b.batch, g.sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off, b.loc_u, b.sorted_bag,
                            grad_out, lr, eps, b.ovf, g.ovf_stride, table_class, wins, b.cnt);
     } else {
