@@ -405,11 +405,13 @@ int tbe_get_stats(tbe_handle h, tbe_stats *out);
 #define TBE_STAGE_FILL 1           /* host link: write-back of parked victims + fetch-ahead of missed rows (aux) */
 #define TBE_STAGE_FORWARD 2        /* pooled lookup (compute stream)                              */
 #define TBE_STAGE_BACKWARD_COMBINE 3 /* heavy rows: sum of the partial sums + update (compute stream) */
-#define TBE_STAGE_BACKWARD_SHORT 4 /* backward of rows with 2..64 lookups (compute stream)          */
+#define TBE_STAGE_BACKWARD_SHORT 4 /* backward of rows with 2..64 lookups (max pooling, rows of 16 lanes and more: also of those
+                                      with up to 512, fp32 1024 lookups) (compute stream)          */
 #define TBE_STAGE_COMMIT 5         /* victims -> staging, fetched rows -> cache lines (aux stream)  */
 #define TBE_STAGE_BACKWARD_SINGLE 6 /* backward of rows with one lookup, bag by bag (compute stream) */
 #define TBE_STAGE_BACKWARD_HEAVY 7 /* rows with more than 64 lookups: partial sums per bag range from gradient tiles in LDS
-                                      (max pooling: one workgroup per row, update included) (compute stream) */
+                                      (max pooling: one workgroup per row, update included, but for the rows in bracket 4)
+                                      (compute stream) */
 #define TBE_STAGE_BACKWARD 8       /* the whole backward: from before its first kernel to after its last (compute stream);
                                       brackets 7, 3, 6, 4 lie inside it, one behind the other */
 #define TBE_NUM_STAGES 9

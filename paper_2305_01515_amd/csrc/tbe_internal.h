@@ -403,9 +403,10 @@ constexpr int64_t kFlushStateRows = 262144;  // a megabyte: what the copy engine
 hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, hipStream_t s);
 hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
                                   float *out, hipStream_t s);
-// which: kBwdHeavy (tile kernel; under max pooling the workgroup-per-row kernel instead), or any of kBwdCombine (sums of the
-// tile kernel's partial sums + update; nothing under max pooling), kBwdSingle (rows with one lookup), kBwdShort (rows with
-// 2..kLongRun lookups) in one launch
+// which: kBwdHeavy (tile kernel; under max pooling the hot rows, a workgroup each, and for rows narrower than 16 lanes all with
+// more than kLongRun lookups), or any of kBwdCombine (sums of the tile kernel's partial sums + update; nothing under max
+// pooling), kBwdSingle (rows with one lookup), kBwdShort (rows with 2..kLongRun lookups, under max pooling also the other long
+// rows) in one launch
 constexpr int kBwdHeavy = 1, kBwdCombine = 2, kBwdSingle = 4, kBwdShort = 8;
 hipError_t launch_backward_classes(int which, const TableMeta *tm, const ClassInfo &ci, const Geometry &g,
                                    const BatchBuf &b, const float *grad_out, float *partials, float lr, float eps,
