@@ -22,7 +22,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtbe.so")
-SOURCES = ["tbe_api.hip", "tbe_sort.hip", "tbe_cache.hip", "tbe_move.hip", "tbe_embed.hip", "tbe_place.hip"]
+SOURCES = ["tbe_api.hip", "tbe_sort.hip", "tbe_cache.hip", "tbe_one.hip", "tbe_move.hip", "tbe_embed.hip", "tbe_place.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
 REMARKS = ["-Rpass-analysis=kernel-resource-usage"]

@@ -342,6 +342,21 @@ StaleRows stale_rows(const tbe_ctx *h, const BatchBuf &b, int bi) {
   return r;
 }
 
+// The prefetch stage of batch `b` (buffer bi).
+hipError_t launch_stage(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
+  const bool lfu = h->policy == TBE_POLICY_LFU;
+  const StaleRows stale = stale_rows(h, b, bi);
+  const Totals totals{h->d_total, h->d_bytes + 2, h->l2.on ? h->d_l2tot : nullptr};
+  if (one_kernel_batch(h->g, b.n, b.batch))
+    return launch_one_kernel_stage(h->d_tm, h->g, b, h->ss, h->tags, h->ts, h->freq, lfu, h->l2, h->deep, stale, totals, s);
+  hipError_t e = launch_keygen(h->d_tm, h->g, b, h->ss, s);
+  int res = 0;
+  if (e == hipSuccess) e = launch_sort(h->g, b, h->ss, &res, s);
+  if (e != hipSuccess) return e;
+  return launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq, lfu, h->l2,
+                            h->deep, stale, totals, s);
+}
+
 // Pipeline several batches deep: the rows of `b` whose value was an overflow copy of a batch that had not trained when `b` was
 // fetched are copied from there.
 hipError_t fix_up(tbe_ctx *h, const BatchBuf &b) {
@@ -379,12 +394,7 @@ int do_prefetch_deep(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offs
   }
   {
     StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
-    HIP_TRY(h, launch_keygen(h->d_tm, h->g, b, h->ss, h->as));
-    int res = 0;
-    HIP_TRY(h, launch_sort(h->g, b, h->ss, &res, h->as));
-    HIP_TRY(h, launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq,
-                                  h->policy == TBE_POLICY_LFU, h->l2, h->deep, stale_rows(h, b, bi),
-                                  Totals{h->d_total, h->d_bytes + 2, nullptr}, h->as));
+    HIP_TRY(h, launch_stage(h, b, bi, h->as));
   }
   if (h->ls != h->as) {
     HIP_TRY(h, hipEventRecord(h->ev_probed[bi], h->as));
@@ -457,12 +467,7 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
   }
   {
     StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
-    HIP_TRY(h, launch_keygen(h->d_tm, h->g, b, h->ss, h->as));
-    int res = 0;
-    HIP_TRY(h, launch_sort(h->g, b, h->ss, &res, h->as));
-    HIP_TRY(h, launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq,
-                                  h->policy == TBE_POLICY_LFU, h->l2, 0, stale_rows(h, b, bi),
-                                  Totals{h->d_total, h->d_bytes + 2, h->l2.on ? h->d_l2tot : nullptr}, h->as));
+    HIP_TRY(h, launch_stage(h, b, bi, h->as));
   }
   if (h->ls != h->as) {
     HIP_TRY(h, hipEventRecord(h->ev_probed[bi], h->as));
@@ -562,6 +567,8 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
     m.col = (int32_t)col;
     m.sets = (uint32_t)std::min<int64_t>(s.cache_slots / ways, (1ll << 31) / ways);
     m.rows_per_set = m.sets ? (uint32_t)((s.rows + m.sets - 1) / m.sets) : 0;
+    m.rps_magic = div_magic(m.rows_per_set);
+    m.sets_magic = div_magic(m.sets);
     m.key_base = (uint32_t)key;
     m.set_base = (uint32_t)sets;
     m.slot_base = (int32_t)(sets * ways);
@@ -749,6 +756,8 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
     CREATE_TRY(h->mem.get(&h->ss.said, 4 * 256 * kMaxSortPasses * (size_t)(1 + most)));
   }
   CREATE_TRY(h->mem.get(&h->ss.said_counts, 8 * 4 * (size_t)kSmallScanBlocks));
+  CREATE_TRY(h->mem.get(&h->ss.one, sizeof(OneCtl)));
+  CREATE_TRY(hipMemset(h->ss.one, 0, sizeof(OneCtl)));
   CREATE_TRY(h->mem.get(&h->d_total, sizeof(BatchCounters)));
   CREATE_TRY(hipMemset(h->d_total, 0, sizeof(BatchCounters)));
   CREATE_TRY(h->mem.get(&h->d_bytes, 8 * 8));

@@ -73,6 +73,7 @@ struct TableMeta {
   int32_t col;            // first output column
   int32_t lanes;          // lanes per row: 16 bytes of the row per lane
   uint32_t row_bytes;
+  unsigned long long rps_magic, sets_magic;  // of the divisions by rows_per_set and sets (div_by)
   char *lines;            // device: cache lines of this table [sets*ways, row_bytes]
   float *slot_m;          // device: accumulators of the rows in those lines [sets*ways] (while a row is cached its
                           // accumulator lives here, next to 6 MB of its kind, instead of among those of all rows)
@@ -193,7 +194,7 @@ struct SortScratch {
   uint32_t *hist;          // [256 * max sort blocks] block histograms, then [256] digit totals
   unsigned long long *blk; // [2 * (5 * scan blocks + 1)] sums per workgroup and per wavefront of the compaction passes
   unsigned long long *tally;  // [3 * wavefronts of a compaction pass] (evictions, lookups that hit, late rows) per wave-
-  int tally_waves;            //     front of the last batch's status pass, and how many wavefronts that pass had
+                              //     front of the last batch's status pass
   uint32_t *too_long;         // a bag of the batch does not fit the packed payload (0 between batches)
   int32_t *refused;           // error of the first batch that was refused, with kRefusedBefore (0: none): no batch behind it
                               //   does anything
@@ -201,6 +202,7 @@ struct SortScratch {
   uint32_t *ticket;           // workgroups of the running kernel that have begun (0 between kernels)
   uint32_t *said;             // [kMaxSortPasses][256] digit totals, then [kMaxSortPasses][workgroups][256] digit counts
   unsigned long long *said_counts;  // [2 passes][2 words][kSmallScanBlocks] counts of the compaction passes
+  struct OneCtl *one;         // batches that one kernel takes through the stage (one_kernel_batch)
 };
 
 // Staging between the cache and the host link (one instance; the prefetch stage is serial).
@@ -333,6 +335,28 @@ inline int small_sort_blocks(int64_t n) {
   return (int)((n + tile - 1) / tile);
 }
 
+// Batches of very few lookups: one kernel takes them through the whole prefetch stage (tbe_one.hip).  The line is what one
+// workgroup sorts in its LDS: with several tiles, passes of the sort as phases of the same kernel, one XCD's 32 CUs are no
+// longer enough for the probe (4 tables of 100 k rows, 40960 lookups: 150 us a step instead of 127; 11 to 15 k lookups 1.04 to
+// 1.26 times as long, 5 k equal).  Its one workgroup reads 512 bags at a time: 3853 lookups in 3380 bags took 238 instead of
+// 217 us in two steps, a few hundred bags are faster.
+constexpr int64_t kOneLookups = 4096, kOneBags = 2048;
+constexpr int kOnePhases = 4;  // sorted lookups and distinct rows, probe, lists, end
+constexpr int kOneItems = 4;   // items of the phase that writes the lists, at most
+inline bool one_kernel_batch(const Geometry &g, int64_t n, int32_t batch) {
+  return n > 0 && n <= kOneLookups && (int64_t)g.T * batch <= kOneBags;
+}
+// What the workgroups of that kernel share; all zero between launches.  A line for each word that many of them change.
+struct OneCtl {
+  struct alignas(128) Word { uint32_t n; };
+  alignas(128) uint32_t chosen;  // 1 + the XCD that the stage runs on
+  alignas(128) uint32_t left;    // workgroups that have ended
+  alignas(128) uint32_t next;    // the next ticket
+  alignas(128) uint32_t err;     // 1 = bad offsets, 2 = index out of range
+  Word done[kOnePhases];         // items of every phase that are done
+  unsigned long long said[2 * kOneItems];  // [2 words][kOneItems] counts of the pass that writes lists
+};
+
 // Digits of the radix sort: pass p sorts by (key >> shift[p]) & mask[p].
 struct DigitPlan {
   int passes;
@@ -361,6 +385,10 @@ hipError_t launch_sort(const Geometry &g, const BatchBuf &b, SortScratch &ss, in
 hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const BatchBuf &b, SortScratch &ss,
                               const uint32_t *sorted_keys, const uint32_t *sorted_pos, int32_t *tags, int32_t *ts,
                               int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale,
+                              const Totals &totals, hipStream_t s);
+// the whole stage of a batch for which one_kernel_batch holds
+hipError_t launch_one_kernel_stage(const TableMeta *tm, const Geometry &g, const BatchBuf &b, const SortScratch &ss, int32_t *tags,
+                              int32_t *ts, int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale,
                               const Totals &totals, hipStream_t s);
 // write back the staged victims and (b != null) fetch ahead the rows b's batch inserts
 // Deferred initialisation on read (Section 5.4.2): a row of the backing tier has no value until it is
@@ -506,6 +534,10 @@ __device__ inline int take_ticket(uint32_t *ticket) {
   __syncthreads();
   return s_ticket;
 }
+
+// n / d for any 32-bit n, with m = ceil(2^64 / d) (0 stands for d = 1): exact, because m d exceeds 2^64 by less than d
+__device__ inline uint32_t div_by(uint32_t n, unsigned long long m) { return m ? (uint32_t)__umul64hi((unsigned long long)n, m) : n; }
+__host__ __device__ inline unsigned long long div_magic(uint32_t d) { return d > 1 ? ~0ull / d + 1ull : 0ull; }
 
 // table that owns sort key `key`: last t with key_base[t] <= key
 __device__ inline int find_table(const TableMeta *tm, int T, uint32_t key) {

@@ -1,0 +1,28 @@
+"""The prefetch stage of very small batches, which is one kernel: lookups and bags on either side of the lines up to which it is
+taken, one workgroup and many, every replacement policy and level, and such batches in turn with larger ones."""
+import pytest
+
+from paper_2305_01515_amd import synth
+from parity_util import run_parity
+
+pytestmark = pytest.mark.gpu
+T = synth.TableCfg
+
+
+@pytest.mark.parametrize("policy,level2", [("lru", 0), ("lfu", 0), ("lru", 1), ("lfu", 2)])
+@pytest.mark.parametrize("batch,pool", [(1, 7), (16, 4), (255, 16), (256, 16), (257, 16), (1023, 4), (1024, 4), (1025, 3)])
+def test_lookups_and_bags_around_the_lines(batch, pool, policy, level2):
+    """4080, 4096 and 4112 lookups; 2046, 2048 and 2050 bags; sets by the thousand (many workgroups) and a handful (one)"""
+    for rows, slots in ((9001, 4 * 700), (90, 4 * 3)):
+        tabs = [T(rows, 8, synth.FP32, 0.9, "fixed", pool - pool // 2, cache_slots=slots),
+                T(rows // 2, 16, synth.FP32, None, "fixed", pool // 2, cache_slots=slots // 2)]
+        run_parity(synth.WorkloadCfg("one", tabs, batch=batch, ways=4, steps=4, seed=batch, init_std=0.05, lr=0.05), steps=4,
+                   order="early", policy=policy, second_level_factor=level2)
+
+
+@pytest.mark.parametrize("overlap", [True, False])
+def test_in_turn_with_larger_batches(overlap):
+    """Poisson bags: batches of one model fall on both sides of the line"""
+    tabs = [T(3000, 16, synth.FP16, 1.0, "poisson", 20.3, 0, 60, cache_slots=256), T(500, 8, synth.FP32, None, "poisson", 4, 0, 20)]
+    run_parity(synth.WorkloadCfg("turn", tabs, batch=168, ways=16, steps=12, seed=1, init_std=0.05, lr=0.05), steps=12,
+               order="early", overlap=overlap)
