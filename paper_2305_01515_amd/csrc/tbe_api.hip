@@ -129,9 +129,12 @@ struct tbe_ctx {
   hipStream_t ls = nullptr;                // host-link stream: transfer and commit (own, unless cs == as)
   bool own_ls = false;
 
-  hipEvent_t ev_fwd = nullptr;  // the last forward launched
-  bool fwd_recorded = false;
-  int last_trained = -1;        // buffer of the batch whose backward was launched last
+  hipEvent_t ev_fwd = nullptr;  // the last forward launched ...
+  int fwd_of = -1;              //   ... that recorded it: the batch's buffer
+  int last_trained = -1;        // buffer of the batch whose backward recorded its event last
+  bool unmarked = false;        // the compute stream has been given work of a batch since that left no event
+  hipStream_t link_s = nullptr; // the stream that the last transfer went to, and what of the link comes behind it
+  bool never_bypasses = true;   // every table has a way for each of its rows
   hipEvent_t ev_inputs = nullptr, ev_ready[kMaxBatchBufs] = {}, ev_trained[kMaxBatchBufs] = {}, ev_probed[kMaxBatchBufs] = {};
   int64_t flush_state_bytes = 0;
   bool inputs_ready = false;  // caller guarantees index / offset buffers are complete when tbe_prefetch is called
@@ -299,17 +302,40 @@ int sync_all(tbe_ctx *h) {
   return TBE_OK;
 }
 
+// Stream `to` goes on behind what `from` has been given so far.
+int order_after(tbe_ctx *h, hipStream_t from, hipStream_t to) {
+  HIP_TRY(h, hipEventRecord(h->ev_inputs, from));
+  HIP_TRY(h, hipStreamWaitEvent(to, h->ev_inputs, 0));
+  return TBE_OK;
+}
+
+// The transfer of batch `b`, whose stage stream `s` has been given, on b.link.  Write-back of the previous batch's victims and
+// fetch-ahead of this batch's rows share the host link; neither touches a cache line, so a batch in flight is not disturbed.
+int enqueue_transfer(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
+  if (b.link != s) {  // (covers the transfers that `s` has had)
+    HIP_TRY(h, hipEventRecord(h->ev_probed[bi], s));
+    HIP_TRY(h, hipStreamWaitEvent(b.link, h->ev_probed[bi], 0));
+  } else if (s == h->as && h->link_s == h->ls && h->ls != s) {
+    const int rc = order_after(h, h->ls, s);
+    if (rc) return rc;
+  }
+  h->link_s = b.link;
+  StageTimer tm_(h, TBE_STAGE_FILL, b.link);
+  HIP_TRY(h, launch_transfer(&b, h->st, h->l2, h->di, h->throttle, b.k, h->d_rb, h->d_bytes, h->d_bytes + 1, b.link));
+  return TBE_OK;
+}
+
 // Victims of batch `bi` to the staging area, its new rows into the cache lines; then the
 // batch is ready for forward.  Must follow the update of the batch before it.
 int enqueue_commit(tbe_ctx *h, int bi, bool wb_prev) {
   BatchBuf &b = h->buf[bi];
   {
-    StageTimer tm_(h, TBE_STAGE_COMMIT, h->ls);
+    StageTimer tm_(h, TBE_STAGE_COMMIT, b.link);
     const int prev_mode = !wb_prev ? kPrevKeep : b.parks_prev ? kPrevPark : kPrevWrite;
     HIP_TRY(h, launch_commit(h->d_tm, b, b.prev_bi >= 0 ? &h->buf[b.prev_bi] : nullptr, prev_mode, h->st, h->l2, h->d_rb,
-                             h->d_bytes + 1, false, h->ls));
+                             h->d_bytes + 1, false, b.link));
   }
-  HIP_TRY(h, hipEventRecord(h->ev_ready[bi], h->ls));
+  if (b.link != h->cs) HIP_TRY(h, hipEventRecord(h->ev_ready[bi], b.link));
   return TBE_OK;
 }
 
@@ -365,6 +391,33 @@ hipError_t fix_up(tbe_ctx *h, const BatchBuf &b) {
   return launch_fixup(h->d_tm, b, oc, h->st, h->d_rb, h->d_bytes + 6, h->cs);
 }
 
+// The stream for the transfer and the commit of a batch.  The link's own lets them run beside the next batch's stage.  Batches
+// that one kernel takes through the stage move a few hundred rows, and what bounds them is host time, of which a record on one
+// stream and a wait for it on another take 10 us: theirs follow the stage on its stream.
+hipStream_t link_stream(const tbe_ctx *h, int32_t batch, int64_t n) {
+  return h->as != h->cs && one_kernel_batch(h->g, n, batch) ? h->as : h->ls;
+}
+
+// The prefetch stream behind training.  The prefetch stage only decides on tags and timestamps, which training never reads;
+// it follows all the same what the compute stream has been given so far, because the index buffers may have been produced
+// there, or, if they are complete, the last forward or update.
+// Training launched so far goes first: its kernels and this stage are all bound by HBM and slow each
+// other down when they overlap, the model waits for training, and this stage has the whole transfer of
+// the batch before it to finish in.  (Benchmark workload, this stage behind the last forward only, i.e.
+// beside the backward: forward 0.27 ms, backward 0.78 ms, this stage 1.5 ms per step; behind both: see
+// the design notes.  The step is bound by the host link either way.)
+// The last of them on the compute stream is the forward of the batch in training, or the last update.
+int prefetch_behind_training(tbe_ctx *h) {
+  const bool marked = h->current >= 0 ? h->fwd_of == h->current : !h->unmarked;
+  if (!h->inputs_ready || !marked) {
+    h->unmarked = false;
+    return order_after(h, h->cs, h->as);
+  }
+  if (h->current >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_fwd, 0));
+  else if (h->last_trained >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_trained[h->last_trained], 0));
+  return TBE_OK;
+}
+
 // Pipeline several batches deep (Section 5.7): the batch is fetched into the cache as soon as it is decided on.
 // The ways of the batches that may still wait for their training are locked (ts >= k - D), so its victims and
 // the lines it fills are used by none of them and nothing waits for a backward -- except the rows whose current
@@ -380,40 +433,30 @@ int do_prefetch_deep(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offs
   b.parks_prev = false;
   h->total_lookups += n;
   h->last_buf = bi;
+  b.link = link_stream(h, batch, n);
   if (h->as != h->cs) {
-    if (!h->inputs_ready) {
-      HIP_TRY(h, hipEventRecord(h->ev_inputs, h->cs));
-      HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_inputs, 0));
-    } else {
-      if (h->fwd_recorded) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_fwd, 0));
-    }
     // the buffer last served batch k - (2 D + 1): every batch that read its overflow copies (up to k - D - 1) has
     // trained, and its bypassed rows have been written back
-    if (h->last_trained >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_trained[h->last_trained], 0));
+    int rc = prefetch_behind_training(h);
+    if (rc) return rc;
     if (h->home_recorded[bi]) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_home[bi], 0));
   }
   {
     StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
     HIP_TRY(h, launch_stage(h, b, bi, h->as));
   }
-  if (h->ls != h->as) {
-    HIP_TRY(h, hipEventRecord(h->ev_probed[bi], h->as));
-    HIP_TRY(h, hipStreamWaitEvent(h->ls, h->ev_probed[bi], 0));
-  }
-  {
-    StageTimer tm_(h, TBE_STAGE_FILL, h->ls);
-    HIP_TRY(h, launch_transfer(&b, h->st, h->l2, h->di, h->throttle, b.k, h->d_rb, h->d_bytes, h->d_bytes + 1, h->ls));
-  }
+  int rc = enqueue_transfer(h, b, bi, h->as);
+  if (rc) return rc;
   b.prev_bi = h->prev_buf;
   h->prev_buf = bi;
   h->pend[h->n_pend++] = bi;
   {
-    // the link stream waits for every backward launched so far (tbe_backward_update sees to that), which covers the
+    // the prefetch stream has waited for every backward launched so far, and the link stream for it, which covers the
     // batches whose lines this commit may overwrite: they were stamped before k - D
-    StageTimer tm_(h, TBE_STAGE_COMMIT, h->ls);
-    HIP_TRY(h, launch_commit(h->d_tm, b, nullptr, kPrevKeep, h->st, h->l2, h->d_rb, h->d_bytes + 1, true, h->ls));
+    StageTimer tm_(h, TBE_STAGE_COMMIT, b.link);
+    HIP_TRY(h, launch_commit(h->d_tm, b, nullptr, kPrevKeep, h->st, h->l2, h->d_rb, h->d_bytes + 1, true, b.link));
   }
-  HIP_TRY(h, hipEventRecord(h->ev_ready[bi], h->ls));
+  if (b.link != h->cs) HIP_TRY(h, hipEventRecord(h->ev_ready[bi], b.link));
   return TBE_OK;
 }
 
@@ -427,7 +470,11 @@ int check_batch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
   return TBE_OK;
 }
 
-int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, int32_t batch, int64_t n) {
+// own: a forward prefetches its batch itself, with no other in flight.  Nothing runs beside such a prefetch, and up to
+// kOwnLookups lookups (beyond, the write-back of a batch's bypassed rows is worth running beside the next stage) it goes to
+// the compute stream like the forward: no events.  (2 tables x 2000 rows, 16 bags, two steps: 190 us with events, 102 without.)
+constexpr int64_t kOwnLookups = 65536;
+int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, int32_t batch, int64_t n, bool own = false) {
   int rc = check_batch(h, d_indices, d_offsets, batch, n);
   if (rc) return rc;
   if (h->deep) return do_prefetch_deep(h, d_indices, d_offsets, batch, n);
@@ -443,20 +490,16 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
   b.parks_prev = in_flight && h->prev_buf >= 0 && h->st.max_parked > 0 && !h->l2.on;
   h->total_lookups += n;
   h->last_buf = bi;
-  if (h->as != h->cs) {
-    if (!h->inputs_ready) {  // inputs produced on the compute stream so far come first
-      HIP_TRY(h, hipEventRecord(h->ev_inputs, h->cs));
-      HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_inputs, 0));
-    } else {
-      // Training launched so far goes first: its kernels and this stage are all bound by HBM and slow each
-      // other down when they overlap, the model waits for training, and this stage has the whole transfer of
-      // the batch before it to finish in.  (Benchmark workload, this stage behind the last forward only, i.e.
-      // beside the backward: forward 0.27 ms, backward 0.78 ms, this stage 1.5 ms per step; behind both: see
-      // the design notes.  The step is bound by the host link either way.)
-      // The last of them on the compute stream is the forward of the batch in training, or the last update.
-      if (h->current >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_fwd, 0));
-      else if (h->last_trained >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_trained[h->last_trained], 0));
-    }
+  own = own && !in_flight && n <= kOwnLookups;
+  hipStream_t stage_s = own ? h->cs : h->as;
+  b.link = own ? h->cs : link_stream(h, batch, n);
+  if (own && h->link_s != h->cs) {  // (all but the write-back behind the last update the forwards have waited for)
+    rc = order_after(h, h->link_s, h->cs);
+    if (rc) return rc;
+  }
+  if (stage_s != h->cs) {
+    rc = prefetch_behind_training(h);
+    if (rc) return rc;
     // This buffer (k - 3's, for batch k) is read by that batch's own kernels, by the list passes of k - 2 and k - 1 (this stream),
     // by the commit of batch k - 2 -- its bypass list, overflow copies and counters -- and, if batch k - 3 had no successor
     // when it had trained, by its write-back on the link stream, which that commit follows.  At most the batch before this
@@ -466,20 +509,11 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
     // instead of 638 us, 8 x 500k rows under max pooling 1049 instead of 1028.)
   }
   {
-    StageTimer tm_(h, TBE_STAGE_PREFETCH, h->as);
-    HIP_TRY(h, launch_stage(h, b, bi, h->as));
+    StageTimer tm_(h, TBE_STAGE_PREFETCH, stage_s);
+    HIP_TRY(h, launch_stage(h, b, bi, stage_s));
   }
-  if (h->ls != h->as) {
-    HIP_TRY(h, hipEventRecord(h->ev_probed[bi], h->as));
-    HIP_TRY(h, hipStreamWaitEvent(h->ls, h->ev_probed[bi], 0));
-  }
-  {
-    // write-back of the previous batch's victims and fetch-ahead of this batch's rows share
-    // the host link; neither touches a cache line, so a batch in flight is not disturbed,
-    // and the link stream lets the next batch's sort and probe run meanwhile
-    StageTimer tm_(h, TBE_STAGE_FILL, h->ls);
-    HIP_TRY(h, launch_transfer(&b, h->st, h->l2, h->di, h->throttle, b.k, h->d_rb, h->d_bytes, h->d_bytes + 1, h->ls));
-  }
+  rc = enqueue_transfer(h, b, bi, stage_s);
+  if (rc) return rc;
   b.prev_bi = h->prev_buf;
   h->prev_buf = bi;
   h->pend[h->n_pend++] = bi;
@@ -540,6 +574,7 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   h->cs = (hipStream_t)compute_stream;
   h->as = (hipStream_t)aux_stream;
   h->ls = h->cs;
+  h->link_s = h->cs;
   h->max_batch = max_batch;
   h->max_lookups = max_lookups;
   h->g.T = num_tables;
@@ -579,6 +614,7 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
     col += s.dim;
     line_off[t] = line_bytes;
     line_bytes += ((size_t)m.sets * ways * m.row_bytes + 255) & ~(size_t)255;
+    if (m.sets == 0 || m.rows_per_set > (uint32_t)ways) h->never_bypasses = false;
     if (key > (1ull << 32) || sets * ways >= (1ull << 30) || col >= (1ll << 30)) {
       delete h;
       return fail(nullptr, TBE_ELIMIT, "create: key space, slot count or output width too large");
@@ -853,7 +889,7 @@ int tbe_forward(tbe_handle h, const int64_t *d_indices, const int64_t *d_offsets
     if (rc) return rc;
   }
   if (h->n_pend == 0) {
-    int rc = do_prefetch(h, d_indices, d_offsets, batch, num_lookups);
+    int rc = do_prefetch(h, d_indices, d_offsets, batch, num_lookups, true);
     if (rc) return rc;
   }
   const int bi = h->pend[0];
@@ -863,7 +899,7 @@ int tbe_forward(tbe_handle h, const int64_t *d_indices, const int64_t *d_offsets
   if (h->deferred == bi) return fail(h, TBE_EORDER, "forward: the batch before this one has not been updated");
   for (int i = 1; i < h->n_pend; i++) h->pend[i - 1] = h->pend[i];
   h->n_pend--;
-  if (h->as != h->cs) {
+  if (b.link != h->cs) {
     HIP_TRY(h, hipStreamWaitEvent(h->cs, h->ev_ready[bi], 0));
     // A timing event recorded right after a wait for another stream is stamped before that wait is
     // over (measured: the forward's bracket began 0.15 ms before the commit it waits for had ended).
@@ -875,9 +911,13 @@ int tbe_forward(tbe_handle h, const int64_t *d_indices, const int64_t *d_offsets
     StageTimer tm_(h, TBE_STAGE_FORWARD, h->cs);
     HIP_TRY(h, launch_forward_classes(h->d_tm, h->ci, h->g, b, d_out, h->cs));
   }
-  if (h->as != h->cs) {
+  // An event that the next prefetch waits for if it comes before the update: not when one has come already and the pipeline
+  // takes no more, nor when that prefetch has to wait for all of the stream.
+  if (b.link != h->cs && h->inputs_ready && (h->deep || h->n_pend == 0)) {
     HIP_TRY(h, hipEventRecord(h->ev_fwd, h->cs));
-    h->fwd_recorded = true;
+    h->fwd_of = bi;
+  } else {
+    h->fwd_of = -1;
   }
   h->current = bi;
   return pump_queue(h);  // the next queued batch is prefetched while this one trains
@@ -916,12 +956,21 @@ static int backward_update_with(tbe_ctx *h, const float *d_grad_out, float lr, f
     if (rc) return rc;
   }
   h->current = -1;
-  if (h->as != h->cs) {
+  const BatchBuf &b = h->buf[bi];
+  // What moves this batch's bypassed rows next waits for the update: the commit of the next batch, which also overwrites lines
+  // that this batch used, if one is waiting, or a write-back of their own.  Either goes to the stream of the last transfer, so
+  // that a later transfer finds all of them in front of it.  (The prefetch stream only decides on tags and timestamps, which
+  // training never reads, so it does not wait here; a later prefetch does, for this event if the inputs are ready.)
+  const bool write_back = h->deferred < 0 && !h->never_bypasses;
+  const bool waited_for = h->deferred >= 0 || write_back || h->deep;
+  hipStream_t next = h->link_s;
+  if (next != h->cs && (waited_for || h->inputs_ready)) {
     HIP_TRY(h, hipEventRecord(h->ev_trained[bi], h->cs));
     h->last_trained = bi;
-    // later commits overwrite lines this batch used (the prefetch stream only decides on
-    // tags and timestamps, which training never reads, so it does not wait here)
-    HIP_TRY(h, hipStreamWaitEvent(h->ls, h->ev_trained[bi], 0));
+    h->unmarked = false;
+    if (waited_for) HIP_TRY(h, hipStreamWaitEvent(next, h->ev_trained[bi], 0));
+  } else {
+    h->unmarked = true;
   }
   // the rows this batch bypassed were trained on in HBM copies: back to the backing tier,
   // together with the commit of the next batch when that one is waiting
@@ -931,13 +980,12 @@ static int backward_update_with(tbe_ctx *h, const float *d_grad_out, float lr, f
     int rc = enqueue_commit(h, d, true);
     return rc ? rc : pump_queue(h);
   }
-  {
+  if (write_back) {
     // no batch has been prefetched after this one, so no transfer has run since its commit: the
     // overflow copies that commit parked (the previous batch's) go home, and this batch's
-    const BatchBuf &b = h->buf[bi];
-    HIP_TRY(h, launch_ovf_writeback(b, b.parks_prev && b.prev_bi >= 0, h->st, h->d_rb, h->d_bytes + 1, h->ls));
-    if (h->deep) {  // the buffer is free once they are home
-      HIP_TRY(h, hipEventRecord(h->ev_home[bi], h->ls));
+    HIP_TRY(h, launch_ovf_writeback(b, b.parks_prev && b.prev_bi >= 0, h->st, h->d_rb, h->d_bytes + 1, next));
+    if (h->deep && next != h->cs) {  // the buffer is free once they are home
+      HIP_TRY(h, hipEventRecord(h->ev_home[bi], next));
       h->home_recorded[bi] = true;
     }
   }

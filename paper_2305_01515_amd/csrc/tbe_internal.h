@@ -184,6 +184,7 @@ struct BatchBuf {
   int64_t n;
   int32_t k;
   int32_t prev_bi;      // buffer of the batch prefetched before this one, -1 = none
+  hipStream_t link;     // the stream that its transfer, commit and write-back go to
   bool parks_prev;      // this batch's commit parks the overflow copies of the batch before it among its victims
 };
 
