@@ -134,6 +134,7 @@ struct tbe_ctx {
   int last_trained = -1;        // buffer of the batch whose backward recorded its event last
   bool unmarked = false;        // the compute stream has been given work of a batch since that left no event
   hipStream_t link_s = nullptr; // the stream that the last transfer went to, and what of the link comes behind it
+  int64_t parked = 0;           // slots that the last commit parked for write-back, at most
   bool never_bypasses = true;   // every table has a way for each of its rows
   hipEvent_t ev_inputs = nullptr, ev_ready[kMaxBatchBufs] = {}, ev_trained[kMaxBatchBufs] = {}, ev_probed[kMaxBatchBufs] = {};
   int64_t flush_state_bytes = 0;
@@ -321,7 +322,7 @@ int enqueue_transfer(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
   }
   h->link_s = b.link;
   StageTimer tm_(h, TBE_STAGE_FILL, b.link);
-  HIP_TRY(h, launch_transfer(&b, h->st, h->l2, h->di, h->throttle, b.k, h->d_rb, h->d_bytes, h->d_bytes + 1, b.link));
+  HIP_TRY(h, launch_transfer(&b, h->parked, h->st, h->l2, h->di, h->throttle, b.k, h->d_rb, h->d_bytes, h->d_bytes + 1, b.link));
   return TBE_OK;
 }
 
@@ -329,12 +330,14 @@ int enqueue_transfer(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
 // batch is ready for forward.  Must follow the update of the batch before it.
 int enqueue_commit(tbe_ctx *h, int bi, bool wb_prev) {
   BatchBuf &b = h->buf[bi];
+  const int64_t prev_n = b.prev_bi >= 0 ? h->buf[b.prev_bi].n : 0;
   {
     StageTimer tm_(h, TBE_STAGE_COMMIT, b.link);
     const int prev_mode = !wb_prev ? kPrevKeep : b.parks_prev ? kPrevPark : kPrevWrite;
     HIP_TRY(h, launch_commit(h->d_tm, b, b.prev_bi >= 0 ? &h->buf[b.prev_bi] : nullptr, prev_mode, h->st, h->l2, h->d_rb,
                              h->d_bytes + 1, false, b.link));
   }
+  h->parked = b.n + (prev_n > 0 ? prev_n : 0);
   if (b.link != h->cs) HIP_TRY(h, hipEventRecord(h->ev_ready[bi], b.link));
   return TBE_OK;
 }
@@ -456,6 +459,7 @@ int do_prefetch_deep(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offs
     StageTimer tm_(h, TBE_STAGE_COMMIT, b.link);
     HIP_TRY(h, launch_commit(h->d_tm, b, nullptr, kPrevKeep, h->st, h->l2, h->d_rb, h->d_bytes + 1, true, b.link));
   }
+  h->parked = b.n;
   if (b.link != h->cs) HIP_TRY(h, hipEventRecord(h->ev_ready[bi], b.link));
   return TBE_OK;
 }
@@ -983,7 +987,7 @@ static int backward_update_with(tbe_ctx *h, const float *d_grad_out, float lr, f
   if (write_back) {
     // no batch has been prefetched after this one, so no transfer has run since its commit: the
     // overflow copies that commit parked (the previous batch's) go home, and this batch's
-    HIP_TRY(h, launch_ovf_writeback(b, b.parks_prev && b.prev_bi >= 0, h->st, h->d_rb, h->d_bytes + 1, next));
+    HIP_TRY(h, launch_ovf_writeback(b, b.parks_prev && b.prev_bi >= 0 ? h->parked : 0, h->st, h->d_rb, h->d_bytes + 1, next));
     if (h->deep && next != h->cs) {  // the buffer is free once they are home
       HIP_TRY(h, hipEventRecord(h->ev_home[bi], next));
       h->home_recorded[bi] = true;
@@ -1033,14 +1037,14 @@ int tbe_flush(tbe_handle h) {
       const int bi = i < 0 ? h->current : h->pend[i];
       if (bi < 0 || bi == h->deferred) continue;
       if (h->deep && i >= 0) HIP_TRY(h, fix_up(h, h->buf[bi]));
-      HIP_TRY(h, launch_ovf_writeback(h->buf[bi], false, h->st, h->d_rb, h->d_bytes + 1, h->cs));
+      HIP_TRY(h, launch_ovf_writeback(h->buf[bi], 0, h->st, h->d_rb, h->d_bytes + 1, h->cs));
     }
     h->n_pend = 0;
     h->current = -1;
     h->deferred = -1;
     h->queued.clear();
   }
-  HIP_TRY(h, launch_transfer(nullptr, h->st, h->l2, h->di, h->throttle, 0, h->d_rb, h->d_bytes, h->d_bytes + 1, h->cs));  // parked victims first
+  HIP_TRY(h, launch_transfer(nullptr, h->parked, h->st, h->l2, h->di, h->throttle, 0, h->d_rb, h->d_bytes, h->d_bytes + 1, h->cs));  // parked victims first
   // Every copy in the backing tier is current now: the next batch must not take any row for one on its way (it would
   // make the transfer skip a write-back that has already happened, and the request would hit a later batch's victim).
   h->prev_buf = -1;

@@ -262,8 +262,9 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
                      : (lfu ? probe_kernel<true, false> : probe_kernel<false, false>);
   hipLaunchKernelGGL(probe, dim3(probe_blocks), dim3(kWave), 0, s, probe_of(tm, g, b, tags, ts, freq, l2, lock), b.cnt);
   const int tally_waves = run_compaction(StatusOp{status_of(tm, g, b, l2, stale, ss.tally)}, &b.cnt->n_uniq, 0, n, ss, small ? 1 : -1, b.cnt, s) * kScanWavesPerBlock;
-  // (max pooling takes heavy rows a workgroup each and needs no plan; 64 or 256 workgroups look for the ranges' starts)
-  const int plan = b.maxp ? 0 : (g.T + (small ? 64 : 256) + kXcds - 1) / kXcds * kXcds;
+  // (max pooling takes heavy rows a workgroup each and needs no plan, nor do batches that do the same; 64 or 256 workgroups
+  // look for the ranges' starts)
+  const int plan = b.maxp || long_rows_in_rest(n, g.win_stride) ? 0 : (g.T + (small ? 64 : 256) + kXcds - 1) / kXcds * kXcds;
   // a multiple of the XCDs, no more than have a pass to do, and the one that ends the stage
   int final_blocks = (n + 4 * kFinalThreads - 1) / (4 * kFinalThreads);
   final_blocks = final_blocks > TBE_FINALIZE_BLOCKS ? TBE_FINALIZE_BLOCKS : (final_blocks + kXcds - 1) / kXcds * kXcds;

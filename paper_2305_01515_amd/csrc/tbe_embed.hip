@@ -723,7 +723,7 @@ template <int DT, int G>
 constexpr int hot_row() { return G < 16 ? 0x7FFFFFFF : DT == 1 ? 512 : 1024; }
 // Q: lookups a group has in flight (max pooling).  HOT: the rows with more than hot_row lookups, else those with up to that many.
 template <int DT, int G, int MODE, int Q, bool HOT>
-__device__ inline void update_long_rows(int blk, int blocks, const TableMeta *__restrict__ tm, int cls, int B, int sum_dim,
+__device__ __forceinline__ void update_long_rows(int blk, int blocks, const TableMeta *__restrict__ tm, int cls, int B, int sum_dim,
                                         const int32_t *__restrict__ heavy, const int32_t *__restrict__ heavy_sub,
                                         const uint32_t *__restrict__ uniq_key, const int32_t *__restrict__ uniq_tab,
                                         const int32_t *__restrict__ run_off, const int32_t *__restrict__ loc_u,
@@ -749,7 +749,7 @@ __device__ inline void update_long_rows(int blk, int blocks, const TableMeta *__
     float g[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; e++) g[e] = 0.f;
-    reduce_grads<DT, G, MODE, Q>(g, grad_out + m.col + lig * EPL, sorted_bag, t * B, sum_dim, run_off[u], run_off[u + 1], grp,
+    [[clang::always_inline]] reduce_grads<DT, G, MODE, Q>(g, grad_out + m.col + lig * EPL, sorted_bag, t * B, sum_dim, run_off[u], run_off[u + 1], grp,
                                  NG, lig, active, inv_len, wins, m.col + lig * EPL);
     __syncthreads();
 #pragma unroll
@@ -1287,6 +1287,10 @@ __global__ __launch_bounds__(256) void backward_rest_kernel(int combine, int sin
   if (b.cnt->err) return;
   int blk = blockIdx.x;
   if (blk < combine) {
+    if constexpr (MODE != kMax && (SECT & kBwdLong))
+      update_long_rows<DT, G, MODE, 4, false>(blk, combine, tm, cls, B, sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off,
+                                              b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf, ovf_stride, table_class,
+                                              MODE == kMean ? b.inv_len : nullptr, Winners{}, b.cnt);
     if constexpr (MODE != kMax && (SECT & kBwdCombine))
       combine_heavy_rows<DT, G, SECT == kBwdCombine ? 8 : 4>(blk, combine, tm, cls, b.heavy, b.heavy_sub, b.harrive, b.uniq_key, b.uniq_tab, b.loc_u, partials,
                                 pstride, lr, eps, b.ovf, ovf_stride, table_class, b.cnt);
@@ -1350,8 +1354,9 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
   const bool tiled = kTiled && !b.maxp;
   const int64_t most_heavy = b.n / (kLongRun + 1) + b.n / kHeavySplit;  // entries of the heavy list
   const Winners wins{b.wins, g.win_stride, b.argpos, b.sorted_at};
+  const bool long_rows = !b.maxp && long_rows_in_rest(b.n, G);
   if (which & kBwdHeavy) {
-    if (most_heavy == 0) return;
+    if (most_heavy == 0 || long_rows) return;
     if (tiled) {
       if constexpr (kTiled)
         hipLaunchKernelGGL((backward_heavy_kernel<DT, G>), dim3(b.n <= kSmallLookups ? 256 : 1024), dim3(kHeavyThreads), 0, s, tm,
@@ -1374,7 +1379,8 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
   }
   const int per = 256 / G;  // lane groups of a workgroup
   const int blocks_per_table = (b.batch + per - 1) / per;
-  const int combine = (which & kBwdCombine) && tiled ? work_blocks(most_heavy, per, 2048)
+  const int combine = (which & kBwdCombine) && long_rows ? work_blocks(most_heavy, 1, 4096)
+                      : (which & kBwdCombine) && tiled ? work_blocks(most_heavy, per, 2048)
                       : (which & kBwdShort) && b.maxp && kLongInRest<G> ? work_blocks(most_heavy, 1, 4096) : 0;
   const int shrt = (which & kBwdShort) ? work_blocks(b.n / 2, per, 4096) : 0;
   // A launch holds fewer than 2^32 threads: the bags of as many tables as make 2^30 at a time (16384 tables of 64 lanes,
@@ -1391,7 +1397,10 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
   if (combine + single + shrt == 0) return;
   constexpr int kRows = kBwdSingle | kBwdShort;
   const bool rows = single + shrt > 0;
-  auto kern = !rows ? (b.mean ? backward_rest_kernel<DT, G, kMean, kBwdCombine> : backward_rest_kernel<DT, G, kSum, kBwdCombine>)
+  auto kern = long_rows && combine
+                  ? (!rows ? (b.mean ? backward_rest_kernel<DT, G, kMean, kBwdLong> : backward_rest_kernel<DT, G, kSum, kBwdLong>)
+                           : (b.mean ? backward_rest_kernel<DT, G, kMean, kRows | kBwdLong> : backward_rest_kernel<DT, G, kSum, kRows | kBwdLong>))
+              : !rows ? (b.mean ? backward_rest_kernel<DT, G, kMean, kBwdCombine> : backward_rest_kernel<DT, G, kSum, kBwdCombine>)
               : b.maxp ? backward_rest_kernel<DT, G, kMax, kRows>
               : combine ? (b.mean ? backward_rest_kernel<DT, G, kMean, kRows | kBwdCombine> : backward_rest_kernel<DT, G, kSum, kRows | kBwdCombine>)
                         : (b.mean ? backward_rest_kernel<DT, G, kMean, kRows> : backward_rest_kernel<DT, G, kSum, kRows>);

@@ -358,6 +358,12 @@ struct OneCtl {
   unsigned long long said[2 * kOneItems];  // [2 words][kOneItems] counts of the pass that writes lists
 };
 
+// Sum and mean pooling, heavy rows of small batches: a workgroup each, in the launch of the rest of the backward, instead of
+// the tile kernel's launch in front of it.  A row with all n lookups of the batch is then n x lanes / 1024 reads one after the
+// other (lanes: 4 at least), some 0.7 us each; up to 64 of them that is what the tile kernel's launch costs in all (4 us of host
+// time, 2 to 12 us and the gaps before and behind it on the GPU), and rows like that are rare.
+inline bool long_rows_in_rest(int64_t n, int lanes) { return n * (lanes < 4 ? 4 : lanes) <= 65536; }
+
 // Digits of the radix sort: pass p sorts by (key >> shift[p]) & mask[p].
 struct DigitPlan {
   int passes;
@@ -400,7 +406,8 @@ struct DeferredInit {
   float std = 0.f;
 };
 
-hipError_t launch_transfer(const BatchBuf *b, const Staging &st, const Level2 &l2, const DeferredInit &di,
+// parked: slots parked for write-back, at most
+hipError_t launch_transfer(const BatchBuf *b, int64_t parked, const Staging &st, const Level2 &l2, const DeferredInit &di,
                            const Throttle &th, int k, const uint32_t *rb_of_table,
                            unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
 // prev_mode: what becomes of prev's overflow copies: kPrevKeep (nothing), kPrevWrite (to the backing tier now),
@@ -422,8 +429,8 @@ struct OverflowCopies {
 hipError_t launch_fixup(const TableMeta *tm, const BatchBuf &b, const OverflowCopies &oc, const Staging &st,
                         const uint32_t *rb_of_table, unsigned long long *n_copied, hipStream_t s);
 // after the batch's backward: its bypassed rows go from their HBM copies to the backing tier
-// parked: first the overflow copies of the batch before, which b's commit parked and no transfer has written yet
-hipError_t launch_ovf_writeback(const BatchBuf &b, bool parked, const Staging &st, const uint32_t *rb_of_table,
+// parked: how many overflow copies of the batch before, at most, b's commit parked and no transfer has written yet: they go first
+hipError_t launch_ovf_writeback(const BatchBuf &b, int64_t parked, const Staging &st, const uint32_t *rb_of_table,
                                 unsigned long long *bytes_d2h, hipStream_t s);
 hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const Level2 &l2,
                         unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
@@ -437,6 +444,7 @@ hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, cons
 // pooling), kBwdSingle (rows with one lookup), kBwdShort (rows with 2..kLongRun lookups, under max pooling also the other long
 // rows) in one launch
 constexpr int kBwdHeavy = 1, kBwdCombine = 2, kBwdSingle = 4, kBwdShort = 8;
+constexpr int kBwdLong = 16;  // (of the kernel, see long_rows_in_rest: the heavy rows, a workgroup each, in the combine's place)
 hipError_t launch_backward_classes(int which, const TableMeta *tm, const ClassInfo &ci, const Geometry &g,
                                    const BatchBuf &b, const float *grad_out, float *partials, float lr, float eps,
                                    hipStream_t s);

@@ -38,6 +38,12 @@ typedef unsigned long long u64;
   } while (0)
 constexpr int kLinkBlocks = 192;   // workgroups of the smaller kernels that write to the host link
 constexpr int kLinkThreads = 1024;
+// Workgroups of `threads` for `rows` rows of `lanes` lanes, a row to each lane group, but no more than `most`: those of a small
+// batch that find nothing to do cost it time to be dealt out (the commit of 119 lookups as 4096 workgroups 4.8 us, as two 3).
+static int row_blocks(int64_t rows, int lanes, int threads, int most) {
+  const int64_t want = (rows * lanes + threads - 1) / threads;
+  return want < 1 ? 1 : want < most ? (int)want : most;
+}
 
 // ---- deferred initialisation: counter-based normal numbers of (seed, table, row, element) ----
 // z = centred sum of twelve 16-bit uniforms (three 64-bit hashes per element, the finaliser of
@@ -271,7 +277,7 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
   if (threadIdx.x == 0 && atomicInc((unsigned int *)&st.wb_n[2], gridDim.x - 1) == gridDim.x - 1) st.wb_n[0] = 0;
 }
 
-hipError_t launch_transfer(const BatchBuf *b, const Staging &st, const Level2 &l2, const DeferredInit &di,
+hipError_t launch_transfer(const BatchBuf *b, int64_t parked, const Staging &st, const Level2 &l2, const DeferredInit &di,
                            const Throttle &th, int k, const uint32_t *rb_of_table, u64 *bytes_h2d, u64 *bytes_d2h,
                            hipStream_t s) {
   // How many waves wait on the host link, and where, decides how the link and the HBM-bound kernels
@@ -287,7 +293,8 @@ hipError_t launch_transfer(const BatchBuf *b, const Staging &st, const Level2 &l
   // (with the overflow copies riding along, later: 40 CUs 5.81 ms per step, 48: 5.67, 56: 5.70, 64: 5.93, 72: 6.03)
   // The link needs about 750 waves; given CUs of their own (48 of 256) they leave the other
   // streams' kernels at 1.3 to 2 times their stand-alone time instead of 2.5 to 5 times.
-  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((transfer_kernel<L>), dim3(kLinkCus), dim3(kLinkThreads), 0, s, st, b ? b->cnt : nullptr,
+  const int64_t passes = b && b->n > (parked + 1) / 2 ? b->n : (parked + 1) / 2;
+  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((transfer_kernel<L>), dim3(row_blocks(passes, L, kLinkThreads, kLinkCus)), dim3(kLinkThreads), 0, s, st, b ? b->cnt : nullptr,
                      b ? b->ins_src : nullptr, b ? b->ins_tab : nullptr, rb_of_table,
                      b ? b->ins_where : nullptr, b ? b->byp_src : nullptr, b ? b->byp_tab : nullptr,
                      b ? b->byp_where : nullptr, b ? b->ovf : nullptr, (b && l2.on) ? b->l2v_src : nullptr,
@@ -338,7 +345,7 @@ __global__ __launch_bounds__(256) void fixup_kernel(const TableMeta *__restrict_
 hipError_t launch_fixup(const TableMeta *tm, const BatchBuf &b, const OverflowCopies &oc, const Staging &st,
                         const uint32_t *rb_of_table, u64 *n_copied, hipStream_t s) {
   if (b.n == 0) return hipSuccess;
-  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((fixup_kernel<L>), dim3(1024), dim3(256), 0, s, tm, b.cnt, b.ins_tab, b.ins_where, b.ins_slot, b.ins_key,
+  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((fixup_kernel<L>), dim3(row_blocks(b.n, L, 256, 1024)), dim3(256), 0, s, tm, b.cnt, b.ins_tab, b.ins_where, b.ins_slot, b.ins_key,
                      b.byp_tab, b.byp_where, b.ovf, oc, st.stride, rb_of_table, n_copied));
   return hipGetLastError();
 }
@@ -525,19 +532,20 @@ __global__ __launch_bounds__(256) void parked_copies_writeback_kernel(Staging st
   if ((threadIdx.x & 63) == 0 && out_b) atomicAdd(bytes_d2h, out_b);
 }
 
-hipError_t launch_ovf_writeback(const BatchBuf &b, bool parked, const Staging &st, const uint32_t *rb_of_table, u64 *bytes_d2h,
+hipError_t launch_ovf_writeback(const BatchBuf &b, int64_t parked, const Staging &st, const uint32_t *rb_of_table, u64 *bytes_d2h,
                                 hipStream_t s) {
   if (parked)
-    TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((parked_copies_writeback_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, st, b.cnt, bytes_d2h));
+    TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((parked_copies_writeback_kernel<L>), dim3(row_blocks(parked, L, 256, kLinkBlocks)), dim3(256), 0, s, st, b.cnt, bytes_d2h));
   if (b.n == 0) return hipGetLastError();
-  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((ovf_writeback_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, st, b.cnt, b.byp_src, b.byp_tab, b.ovf,
+  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((ovf_writeback_kernel<L>), dim3(row_blocks(b.n, L, 256, kLinkBlocks)), dim3(256), 0, s, st, b.cnt, b.byp_src, b.byp_tab, b.ovf,
                      rb_of_table, bytes_d2h));
   return hipGetLastError();
 }
 
 hipError_t launch_commit(const TableMeta *tm, const BatchBuf &b, const BatchBuf *prev, int prev_mode, const Staging &st,
                          const Level2 &l2, const uint32_t *rb_of_table, u64 *bytes_d2h, bool deep, hipStream_t s) {
-  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((deep ? commit_kernel<true, L> : commit_kernel<false, L>), dim3(4096), dim3(256), 0, s, tm, st, b.cnt, b.ins_tab, b.ins_where, b.ins_slot,
+  const int64_t rows = prev && prev->n > b.n ? prev->n : b.n;
+  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((deep ? commit_kernel<true, L> : commit_kernel<false, L>), dim3(row_blocks(rows, L, 256, 4096)), dim3(256), 0, s, tm, st, b.cnt, b.ins_tab, b.ins_where, b.ins_slot,
                      b.ins_old, b.byp_tab, b.byp_where, b.ovf, prev ? prev->cnt : nullptr,
                      prev ? prev->byp_src : nullptr, prev ? prev->byp_tab : nullptr,
                      prev ? prev->byp_taken : nullptr, prev ? prev->ovf : nullptr,
