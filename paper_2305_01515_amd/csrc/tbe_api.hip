@@ -410,13 +410,19 @@ hipStream_t link_stream(const tbe_ctx *h, int32_t batch, int64_t n) {
 // beside the backward: forward 0.27 ms, backward 0.78 ms, this stage 1.5 ms per step; behind both: see
 // the design notes.  The step is bound by the host link either way.)
 // The last of them on the compute stream is the forward of the batch in training, or the last update.
-int prefetch_behind_training(tbe_ctx *h) {
+// A small batch's stage takes next to nothing of the memory system and its time is not hidden by a transfer: beside training it
+// follows only what it needs, the commit of the batch in training or of the one that trained last.  That covers the readers of
+// the buffer that it is about to put to use (three batches old, see do_prefetch) and the transfer that looked last at the skip
+// flags it sets (those of the victims of two batches before it).
+int prefetch_behind_training(tbe_ctx *h, bool small) {
   const bool marked = h->current >= 0 ? h->fwd_of == h->current : !h->unmarked;
   if (!h->inputs_ready || !marked) {
     h->unmarked = false;
     return order_after(h, h->cs, h->as);
   }
-  if (h->current >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_fwd, 0));
+  const int beside = h->current >= 0 ? h->current : h->n_pend > 0 ? h->last_trained : -1;
+  if (small && beside >= 0 && h->buf[beside].link != h->cs) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_ready[beside], 0));
+  else if (h->current >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_fwd, 0));
   else if (h->last_trained >= 0) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_trained[h->last_trained], 0));
   return TBE_OK;
 }
@@ -440,7 +446,7 @@ int do_prefetch_deep(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offs
   if (h->as != h->cs) {
     // the buffer last served batch k - (2 D + 1): every batch that read its overflow copies (up to k - D - 1) has
     // trained, and its bypassed rows have been written back
-    int rc = prefetch_behind_training(h);
+    int rc = prefetch_behind_training(h, false);
     if (rc) return rc;
     if (h->home_recorded[bi]) HIP_TRY(h, hipStreamWaitEvent(h->as, h->ev_home[bi], 0));
   }
@@ -502,7 +508,7 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
     if (rc) return rc;
   }
   if (stage_s != h->cs) {
-    rc = prefetch_behind_training(h);
+    rc = prefetch_behind_training(h, small_batch(h->g, n, batch));
     if (rc) return rc;
     // This buffer (k - 3's, for batch k) is read by that batch's own kernels, by the list passes of k - 2 and k - 1 (this stream),
     // by the commit of batch k - 2 -- its bypass list, overflow copies and counters -- and, if batch k - 3 had no successor
