@@ -434,9 +434,10 @@ hipError_t launch_ovf_writeback(const BatchBuf &b, int64_t parked, const Staging
                                 unsigned long long *bytes_d2h, hipStream_t s);
 hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const Level2 &l2,
                         unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
-// after launch_flush: the accumulators of the tables with flush_by_kernel (at most kFlushStateRows rows, pinned host array)
+// after launch_flush: the counters of `buffers` batch buffers to pinned host memory, and the accumulators of the tables with flush_by_kernel (at most kFlushStateRows rows, pinned host array)
 constexpr int64_t kFlushStateRows = 262144;  // a megabyte: what the copy engine moves in the time it takes to start
-hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, hipStream_t s);
+hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, const BatchCounters *counters, BatchCounters *host_counters,
+                              int buffers, hipStream_t s);
 hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, const Geometry &g, const BatchBuf &b,
                                   float *out, hipStream_t s);
 // which: kBwdHeavy (tile kernel; under max pooling the hot rows, a workgroup each, and for rows narrower than 16 lanes all with

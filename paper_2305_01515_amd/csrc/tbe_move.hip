@@ -621,8 +621,12 @@ hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *t
   return hipGetLastError();
 }
 
-// flush: accumulators of the small tables to the host, a table per grid row (the arrays are aligned to floats only)
-__global__ __launch_bounds__(256) void flush_state_kernel(const TableMeta *__restrict__ tm, int T) {
+// flush: accumulators of the small tables to the host, a table per grid row (the arrays are aligned to floats only), and the
+// batch buffers' counters, in which the host looks for errors once it has waited for the flush
+__global__ __launch_bounds__(256) void flush_state_kernel(const TableMeta *__restrict__ tm, int T, const uint32_t *counters,
+                                                          uint32_t *host_counters, int counter_words) {
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int i = threadIdx.x; i < counter_words; i += blockDim.x) __builtin_nontemporal_store(counters[i], host_counters + i);
   for (int t = blockIdx.y; t < T; t += gridDim.y) {
     const TableMeta &m = tm[t];
     if (!m.flush_by_kernel) continue;
@@ -631,8 +635,11 @@ __global__ __launch_bounds__(256) void flush_state_kernel(const TableMeta *__res
   }
 }
 
-hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, hipStream_t s) {
-  hipLaunchKernelGGL(flush_state_kernel, dim3(32, g.T < 1024 ? g.T : 1024), dim3(256), 0, s, tm, g.T);
+hipError_t launch_flush_state(const TableMeta *tm, const Geometry &g, const BatchCounters *counters, BatchCounters *host_counters,
+                              int buffers, hipStream_t s) {
+  static_assert(sizeof(BatchCounters) % 4 == 0, "copied word by word");
+  hipLaunchKernelGGL(flush_state_kernel, dim3(32, g.T < 1024 ? g.T : 1024), dim3(256), 0, s, tm, g.T,
+                     (const uint32_t *)counters, (uint32_t *)host_counters, (int)(buffers * sizeof(BatchCounters) / 4));
   return hipGetLastError();
 }
 
