@@ -120,7 +120,8 @@ typedef struct {
  *   max_batch         : largest `batch` (samples) of any later call.
  *   max_lookups       : largest `num_lookups` of any later call (at most 2^30).
  *   compute_stream    : hipStream_t on which forward / backward run (NULL = default stream).
- *   aux_stream        : hipStream_t on which prefetch work runs; may equal compute_stream
+ *   aux_stream        : hipStream_t on which prefetch work runs (that of a small batch which
+ *                       tbe_forward prefetches itself: on compute_stream); may equal compute_stream
  *                       (then nothing overlaps).  Both must have the default priority.
  * The sum over tables of the key spans (about the row counts, rounded up to whole sets)
  * must stay below 2^32 (TBE_ELIMIT).  All device memory is allocated here (TBE_ENOMEM): the cache
