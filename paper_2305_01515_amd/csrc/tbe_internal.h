@@ -347,6 +347,26 @@ constexpr int kOneItems = 4;   // items of the phase that writes the lists, at m
 inline bool one_kernel_batch(const Geometry &g, int64_t n, int32_t batch) {
   return n > 0 && n <= kOneLookups && (int64_t)g.T * batch <= kOneBags;
 }
+// Sets that a batch can touch, at most (all rows of a table without a cache count as one set).
+inline int64_t sets_touched(const Geometry &g, int64_t n) {
+  const int64_t sets = (int64_t)g.total_sets + g.T;
+  return sets < n ? sets : n;
+}
+// Workgroups of that kernel: a wavefront for every set that the batch can touch and a thread for every lookup (the passes over
+// lists), as far as 16 workgroups go, or 32 where a second level has many rows of a set to place.  Alone on one stream, us a
+// step with 16 sets a workgroup / with 48 and none for the lists / with a kernel a pass: one table without a cache, 2000, 3000
+// and 4096 lookups 72, 84, 97 / 79, 101, 123 / 81, 97, 102; a cache of 32 sets 86, 106 / 99, 144 / 94, 113 (2000, 4096);
+// 313 sets with a second level, 500, 1000, 2000 lookups 50, 81, 96 / 52, 90, 153 / 67, 87, 98 (with 16 of them 115); sets by the
+// thousand, 128 to 4096 lookups, equal (32 workgroups 2 to 4 % slower).  A batch of some dozen is soonest done by one workgroup,
+// which hands over to itself: 48 lookups 40 / 42, 96 and 128 lookups in sets of 64 ways 54 / 47 and 58 / 46 with one / several.
+constexpr int kOneThreads = 1024;
+inline int one_stage_workgroups(const Geometry &g, bool l2, int64_t n) {
+  const int64_t touched = sets_touched(g, n), waves = kOneThreads / kWave;
+  if (n <= 4 * waves) return 1;
+  const int64_t probe = (touched + waves - 1) / waves, lists = (n + kOneThreads - 1) / kOneThreads;
+  const int64_t wgs = probe > lists ? probe : lists, most = l2 && n >= 4 * touched ? 32 : 16;
+  return (int)(wgs < most ? wgs : most);
+}
 // What the workgroups of that kernel share; all zero between launches.  A line for each word that many of them change.
 struct OneCtl {
   struct alignas(128) Word { uint32_t n; };

@@ -22,7 +22,6 @@
 
 namespace tbe {
 
-constexpr int kOneThreads = 1024;
 constexpr int kOneWaves = kOneThreads / kWave;
 constexpr int kOneProbeSets = 4;  // of a wavefront's window: 16 wavefronts' worth of ways fit 64 KB
 constexpr int kKeygenLanes = 8;   // lanes per bag: 64-byte reads of the bag's indices
@@ -505,18 +504,10 @@ hipError_t launch_one_kernel_stage(const TableMeta *tm, const Geometry &g, const
   a.run_off = b.run_off;
   a.loc = b.loc;
   a.cnt = b.cnt;
-  // A wavefront for every three sets that the batch can touch, as far as 16 workgroups go.  (3662 lookups in 1506 sets of 64
-  // ways, one and a half windows a wavefront then: the probe 29 us with 12 workgroups, a pass of two steps 256 / 252 / 253 us
-  // with 10 / 16 / 24, the small batches' kernels 255; 1: 569 instead of 260 us with 3028 lookups in as many sets.)  A batch of
-  // some hundred is soonest done by one workgroup, which hands over to itself: 119 lookups, two steps 94 -> 88 us; 2584 lookups
-  // in 134 sets 206 -> 232.
-  const int64_t touched = (int64_t)g.total_sets + g.T < n ? (int64_t)g.total_sets + g.T : n;
-  auto parts = [](int64_t x, int64_t per) { return (int)((x + per - 1) / per); };
-  int wgs = parts(touched, 3 * kOneWaves);
-  wgs = n <= 8 * kOneWaves ? 1 : wgs > 16 ? 16 : wgs;
+  const int wgs = one_stage_workgroups(g, l2.on, n);
   a.probe_items = wgs;
   if (a.probe.min_windows > wgs * kOneWaves) a.probe.min_windows = wgs * kOneWaves;
-  a.list_items = parts(n, kOneThreads);
+  a.list_items = (n + kOneThreads - 1) / kOneThreads;
   a.plan_items = b.maxp || n <= kLongRun || long_rows_in_rest(n, g.win_stride) ? 0 : wgs < 8 ? 2 : 8;  // (see finalize_kernel)
   a.loc_items = a.list_items;
   const int items[kOnePhases] = {1, a.probe_items, a.list_items, 1 + a.plan_items + a.loc_items};

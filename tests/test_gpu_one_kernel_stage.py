@@ -26,3 +26,11 @@ def test_in_turn_with_larger_batches(overlap):
     tabs = [T(3000, 16, synth.FP16, 1.0, "poisson", 20.3, 0, 60, cache_slots=256), T(500, 8, synth.FP32, None, "poisson", 4, 0, 20)]
     run_parity(synth.WorkloadCfg("turn", tabs, batch=168, ways=16, steps=12, seed=1, init_std=0.05, lr=0.05), steps=12,
                order="early", overlap=overlap)
+
+
+@pytest.mark.parametrize("policy,level2", [("lru", 1), ("lfu", 2), ("lru", 0)])
+def test_many_rows_of_few_sets(policy, level2):
+    """400 sets and 2048 lookups: with a second level 26 workgroups, without one 16; a table without a cache beside them"""
+    tabs = [T(20000, 8, synth.FP32, None, "fixed", 3, cache_slots=400 * 4), T(3000, 16, synth.FP32, 0.8, "fixed", 1, cache_slots=0)]
+    run_parity(synth.WorkloadCfg("few", tabs, batch=512, ways=4, steps=5, seed=8, init_std=0.05, lr=0.05), steps=5,
+               order="early", policy=policy, second_level_factor=level2)

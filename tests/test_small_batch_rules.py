@@ -1,0 +1,55 @@
+"""The rules by which small batches take their ways through the library -- how many workgroups the one-kernel stage has, which
+batches it takes -- on either side of their lines.  They are host functions of the sizes: compiled here from the header that
+holds them, no GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+MAIN = r"""
+#include <cstdio>
+#include <cstring>
+#include "tbe_internal.h"
+using namespace tbe;
+int main() {
+  char what[64];
+  long long T, sets, stride, n, batch, l2;
+  while (scanf("%63s %lld %lld %lld %lld %lld %lld", what, &T, &sets, &stride, &n, &batch, &l2) == 7) {
+    Geometry g{};
+    g.T = (int)T;
+    g.total_sets = (uint32_t)sets;
+    g.ovf_stride = (uint32_t)stride;
+    long long r = -1;
+    if (!strcmp(what, "workgroups")) r = one_stage_workgroups(g, l2 != 0, n);
+    printf("%lld\n", r);
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    if not shutil.which(HIPCC):
+        pytest.skip("no hipcc")
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.hip").write_text(MAIN)
+    subprocess.check_call([HIPCC, "--offload-host-only", "-std=c++17", "-O0", "-w", "-I", os.path.join(ROOT, "paper_2305_01515_amd", "csrc"),
+                           "-I", os.path.join(ROOT, "include"), str(d / "rules.hip"), "-o", str(d / "rules")])
+
+    def ask(what, T=1, sets=0, row_bytes=64, n=1, batch=1, level2=0):
+        line = f"{what} {T} {sets} {row_bytes} {n} {batch} {level2}\n"
+        return int(subprocess.run([str(d / "rules")], input=line, capture_output=True, text=True, check=True).stdout)
+    return ask
+
+
+def test_workgroups_for_sets_and_for_lists(rule):
+    """a thread per lookup even where a batch touches a handful of sets; a wavefront per set; one for some dozen lookups"""
+    for n, want in ((1, 1), (64, 1), (65, 1), (1024, 1), (1025, 2), (2049, 3), (4096, 4)):
+        assert rule("workgroups", sets=0, n=n) == want
+    for sets, n, want in ((31, 4096, 4), (79, 4096, 5), (313, 4096, 16), (9999, 96, 6), (9999, 128, 8), (9999, 4096, 16), (9999, 64, 1)):
+        assert rule("workgroups", sets=sets, n=n) == want
+    for sets, n, want in ((313, 2048, 20), (511, 2048, 32), (512, 2048, 16), (31, 2048, 2)):  # (the table itself counts as a set)
+        assert rule("workgroups", sets=sets, n=n, level2=1) == want
