@@ -381,7 +381,7 @@ hipError_t launch_stage(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
   const bool lfu = h->policy == TBE_POLICY_LFU;
   const StaleRows stale = stale_rows(h, b, bi);
   const Totals totals{h->d_total, h->d_bytes + 2, h->l2.on ? h->d_l2tot : nullptr};
-  if (one_kernel_batch(h->g, b.n, b.batch))
+  if (one_kernel_batch(h->g, h->l2.on, s != h->cs, b.n, b.batch))
     return launch_one_kernel_stage(h->d_tm, h->g, b, h->ss, h->tags, h->ts, h->freq, lfu, h->l2, h->deep, stale, totals, s);
   hipError_t e = launch_keygen(h->d_tm, h->g, b, h->ss, s);
   int res = 0;
@@ -403,7 +403,7 @@ hipError_t fix_up(tbe_ctx *h, const BatchBuf &b) {
 // that one kernel takes through the stage move a few hundred rows, and what bounds them is host time, of which a record on one
 // stream and a wait for it on another take 10 us: theirs follow the stage on its stream.
 hipStream_t link_stream(const tbe_ctx *h, int32_t batch, int64_t n) {
-  return h->as != h->cs && one_kernel_batch(h->g, n, batch) ? h->as : h->ls;
+  return h->as != h->cs && one_kernel_batch(h->g, h->l2.on, true, n, batch) ? h->as : h->ls;
 }
 
 // The prefetch stream behind training.  The prefetch stage only decides on tags and timestamps, which training never reads;

@@ -336,16 +336,28 @@ inline int small_sort_blocks(int64_t n) {
   return (int)((n + tile - 1) / tile);
 }
 
-// Batches of very few lookups: one kernel takes them through the whole prefetch stage (tbe_one.hip).  The line is what one
-// workgroup sorts in its LDS: with several tiles, passes of the sort as phases of the same kernel, one XCD's 32 CUs are no
-// longer enough for the probe (4 tables of 100 k rows, 40960 lookups: 150 us a step instead of 127; 11 to 15 k lookups 1.04 to
-// 1.26 times as long, 5 k equal).  Its one workgroup reads 512 bags at a time: 3853 lookups in 3380 bags took 238 instead of
-// 217 us in two steps, a few hundred bags are faster.
+// Batches of very few lookups: one kernel takes them through the whole prefetch stage (tbe_one.hip), which spares eight
+// launches (30 us of host time).  4096 lookups are what one workgroup sorts in its LDS: with several tiles, passes of the sort as
+// phases of the same kernel, one XCD's 32 CUs are no longer enough for the probe (4 tables of 100 k rows, 40960 lookups: 150 us
+// a step instead of 127; 11 to 15 k lookups 1.04 to 1.26 times as long, 5 k equal).  Its one workgroup reads 512 bags at a time:
+// 3853 lookups in 3380 bags took 238 instead of 217 us in two steps, a few hundred bags are faster.  The host time counts beside
+// training, where the launches of the next batch's stage come on top of those of the step: us a step with one kernel / with a
+// kernel a pass, a third of the rows cached, 500, 2000 and 4096 lookups 53, 66, 77 / 83, 83, 86.  A stage on the compute stream,
+// which nothing runs beside, is bound by the kernels: 500, 1000, 2000 and 4096 lookups 52, 55, 64, 77 / 57, 59, 61, 71 (sets of
+// one way 65, 78, 102 / 69, 73, 87 from 1000 on).
+// With a second level one XCD is short of wavefronts where the sets are few: 625 sets, 2000, 3000 and 4096 lookups beside
+// training 80, 109, 118 / 82, 95, 107.  With more tables than the passes keep constants of in LDS its few workgroups look every
+// lookup's table up in memory: beside training 500 and 1000 lookups 71, 79 / 88, 88, 3600 lookups 99 / 97, alone 150, 500 and 1000
+// lookups 64, 66, 75 / 67, 63, 66.
 constexpr int64_t kOneLookups = 4096, kOneBags = 2048;
+constexpr int kLutTables = 512;  // models with more tables read the descriptions from memory in the passes of the stage
 constexpr int kOnePhases = 4;  // sorted lookups and distinct rows, probe, lists, end
 constexpr int kOneItems = 4;   // items of the phase that writes the lists, at most
-inline bool one_kernel_batch(const Geometry &g, int64_t n, int32_t batch) {
-  return n > 0 && n <= kOneLookups && (int64_t)g.T * batch <= kOneBags;
+// beside: on another stream than the compute stream
+inline bool one_kernel_batch(const Geometry &g, bool l2, bool beside, int64_t n, int32_t batch) {
+  const int64_t most = g.T > kLutTables ? (beside ? kOneLookups / 4 : kOneLookups / 8)
+                       : !beside ? kOneLookups / 4 : l2 ? kOneLookups / 2 : kOneLookups;
+  return n > 0 && n <= most && (int64_t)g.T * batch <= kOneBags;
 }
 // Sets that a batch can touch, at most (all rows of a table without a cache count as one set).
 inline int64_t sets_touched(const Geometry &g, int64_t n) {

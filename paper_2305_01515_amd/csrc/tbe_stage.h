@@ -63,7 +63,6 @@ __device__ inline int scan_chunk(int n, int waves, int step) {
 
 // Per-table constants the passes need for every flagged element, copied to LDS by the workgroup (a look-up in the table
 // descriptions in memory is a chain of dependent loads per element otherwise).
-constexpr int kLutTables = 512;  // models with more tables read the descriptions from memory
 struct KeyLut {
   u64 rps_magic[kLutTables];
   uint32_t key_base[kLutTables], sets[kLutTables], set_base[kLutTables];

@@ -12,12 +12,22 @@ T = synth.TableCfg
 @pytest.mark.parametrize("policy,level2", [("lru", 0), ("lfu", 0), ("lru", 1), ("lfu", 2)])
 @pytest.mark.parametrize("batch,pool", [(1, 7), (16, 4), (255, 16), (256, 16), (257, 16), (1023, 4), (1024, 4), (1025, 3)])
 def test_lookups_and_bags_around_the_lines(batch, pool, policy, level2):
-    """4080, 4096 and 4112 lookups; 2046, 2048 and 2050 bags; sets by the thousand (many workgroups) and a handful (one)"""
+    """4080, 4096 and 4112 lookups; 2046, 2048 and 2050 bags; sets by the thousand (many workgroups) and a handful (few).  (With a
+    second level the line is at 2048 lookups, see below.)"""
     for rows, slots in ((9001, 4 * 700), (90, 4 * 3)):
         tabs = [T(rows, 8, synth.FP32, 0.9, "fixed", pool - pool // 2, cache_slots=slots),
                 T(rows // 2, 16, synth.FP32, None, "fixed", pool // 2, cache_slots=slots // 2)]
         run_parity(synth.WorkloadCfg("one", tabs, batch=batch, ways=4, steps=4, seed=batch, init_std=0.05, lr=0.05), steps=4,
                    order="early", policy=policy, second_level_factor=level2)
+
+
+@pytest.mark.parametrize("batch,pool,order,level2", [(127, 16, "early", 2), (128, 16, "early", 2), (129, 16, "early", 2),
+                                                     (63, 16, "inline", 0), (64, 16, "inline", 1), (65, 16, "inline", 0)])
+def test_lookups_around_the_other_lines(batch, pool, order, level2):
+    """2048 lookups with a second level, 1024 in a stage on the compute stream"""
+    tabs = [T(9001, 8, synth.FP32, 0.9, "fixed", pool - 3, cache_slots=4 * 300), T(700, 16, synth.FP32, None, "fixed", 3, cache_slots=64)]
+    run_parity(synth.WorkloadCfg("other", tabs, batch=batch, ways=4, steps=4, seed=batch, init_std=0.05, lr=0.05), steps=4,
+               order=order, second_level_factor=level2)
 
 
 @pytest.mark.parametrize("overlap", [True, False])
@@ -34,3 +44,10 @@ def test_many_rows_of_few_sets(policy, level2):
     tabs = [T(20000, 8, synth.FP32, None, "fixed", 3, cache_slots=400 * 4), T(3000, 16, synth.FP32, 0.8, "fixed", 1, cache_slots=0)]
     run_parity(synth.WorkloadCfg("few", tabs, batch=512, ways=4, steps=5, seed=8, init_std=0.05, lr=0.05), steps=5,
                order="early", policy=policy, second_level_factor=level2)
+
+
+@pytest.mark.parametrize("tables", [512, 513, 900])
+def test_many_tables(tables):
+    """up to 512 tables the constants are in LDS; more are looked up in memory"""
+    tabs = [T(5 + t % 13, 4, synth.FP32, None, "fixed", t % 4 == 1, cache_slots=4 * (t % 3)) for t in range(tables)]
+    run_parity(synth.WorkloadCfg("many", tabs, batch=2, ways=4, steps=3, seed=5, init_std=0.05, lr=0.05), steps=3, order="early")

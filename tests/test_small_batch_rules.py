@@ -24,6 +24,8 @@ int main() {
     g.ovf_stride = (uint32_t)stride;
     long long r = -1;
     if (!strcmp(what, "workgroups")) r = one_stage_workgroups(g, l2 != 0, n);
+    if (!strcmp(what, "one_kernel_beside")) r = one_kernel_batch(g, l2 != 0, true, n, (int)batch);
+    if (!strcmp(what, "one_kernel_alone")) r = one_kernel_batch(g, l2 != 0, false, n, (int)batch);
     printf("%lld\n", r);
   }
 }
@@ -53,3 +55,13 @@ def test_workgroups_for_sets_and_for_lists(rule):
         assert rule("workgroups", sets=sets, n=n) == want
     for sets, n, want in ((313, 2048, 20), (511, 2048, 32), (512, 2048, 16), (31, 2048, 2)):  # (the table itself counts as a set)
         assert rule("workgroups", sets=sets, n=n, level2=1) == want
+
+
+def test_batches_that_one_kernel_takes(rule):
+    """beside training and on the compute stream"""
+    for T, level2, beside, alone in ((1, 0, 4096, 1024), (512, 0, 4096, 1024), (513, 0, 1024, 512), (1, 1, 2048, 1024), (513, 1, 1024, 512)):
+        for what, most in (("one_kernel_beside", beside), ("one_kernel_alone", alone)):
+            assert rule(what, T=T, n=most, level2=level2) and not rule(what, T=T, n=most + 1, level2=level2)
+    assert not rule("one_kernel_beside", n=0)
+    for T, batch in ((1, 2048), (2, 1024), (512, 4)):
+        assert rule("one_kernel_alone", T=T, batch=batch, n=500) and not rule("one_kernel_alone", T=T, batch=batch + 1, n=500)
