@@ -399,11 +399,10 @@ hipError_t fix_up(tbe_ctx *h, const BatchBuf &b) {
   return launch_fixup(h->d_tm, b, oc, h->st, h->d_rb, h->d_bytes + 6, h->cs);
 }
 
-// The stream for the transfer and the commit of a batch.  The link's own lets them run beside the next batch's stage.  Batches
-// that one kernel takes through the stage move a few hundred rows, and what bounds them is host time, of which a record on one
-// stream and a wait for it on another take 10 us: theirs follow the stage on its stream.
+// The stream for the transfer and the commit of a batch that is prefetched beside training.  The link's own lets them run beside
+// the next batch's stage; a few rows follow the stage on its stream.
 hipStream_t link_stream(const tbe_ctx *h, int32_t batch, int64_t n) {
-  return h->as != h->cs && one_kernel_batch(h->g, h->l2.on, true, n, batch) ? h->as : h->ls;
+  return h->as != h->cs && link_with_stage(h->g, h->l2.on, n, batch) ? h->as : h->ls;
 }
 
 // The prefetch stream behind training.  The prefetch stage only decides on tags and timestamps, which training never reads;

@@ -359,6 +359,19 @@ inline bool one_kernel_batch(const Geometry &g, bool l2, bool beside, int64_t n,
                        : !beside ? kOneLookups / 4 : l2 ? kOneLookups / 2 : kOneLookups;
   return n > 0 && n <= most && (int64_t)g.T * batch <= kOneBags;
 }
+// Bytes of rows that the host link moves in about the time that a record on one stream and a wait for it on another cost a step.
+constexpr int64_t kFewBytes = 512 << 10;
+// Do transfer and commit follow the stage on its stream?  A stream of their own costs a record and a wait, 10 us of host time,
+// of a step whose stage is one launch; on the stage's stream they hold the next batch's stage back, for as long as their rows
+// take.  Us a step beside training, on the stage's stream / on their own / with a kernel a pass (which varies with the host): a
+// third of the rows cached, 1000, 2000 and 4096 lookups 54, 65, 77 / 66, 67, 70 / 95, 88, 96, whatever the rows' width, and with a
+// model of 24 small kernels on either side 554 / 583 / 600 (2000 lookups); no row cached, 2000, 3000 and 4096 rows of 256 bytes
+// 83, 97, 115 / 73, 75, 80 / 107, 93, 102, 500, 1000, 2000 and 4096 rows of 1 KB 69, 90, 126, 188 / 67, 74, 92, 150 / 102, 110,
+// 115, 173.  A second level's stage takes its time as well: 500, 1000 and 2000 lookups in 32 sets 89, 103, 118 / 68, 79, 92 / 95,
+// 96, 97, in 313 sets 52, 83, 97 / 62, 72, 81 / 93, 97, 98.
+inline bool link_with_stage(const Geometry &g, bool l2, int64_t n, int32_t batch) {
+  return one_kernel_batch(g, l2, true, n, batch) && n * g.ovf_stride <= kFewBytes && (!l2 || n <= 512);
+}
 // Sets that a batch can touch, at most (all rows of a table without a cache count as one set).
 inline int64_t sets_touched(const Geometry &g, int64_t n) {
   const int64_t sets = (int64_t)g.total_sets + g.T;

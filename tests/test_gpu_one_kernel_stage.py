@@ -51,3 +51,13 @@ def test_many_tables(tables):
     """up to 512 tables the constants are in LDS; more are looked up in memory"""
     tabs = [T(5 + t % 13, 4, synth.FP32, None, "fixed", t % 4 == 1, cache_slots=4 * (t % 3)) for t in range(tables)]
     run_parity(synth.WorkloadCfg("many", tabs, batch=2, ways=4, steps=3, seed=5, init_std=0.05, lr=0.05), steps=3, order="early")
+
+
+@pytest.mark.parametrize("order,level2", [("early", 0), ("ahead", 0), ("pipe2", 0), ("early", 2)])
+def test_rows_around_half_a_megabyte(order, level2):
+    """batches of about 512 rows of 1 KB, half of them bypassed: the rows of some are moved on the stage's stream, those of others
+    on the link's, in turn"""
+    tabs = [T(3000, 256, synth.FP32, None, "poisson", 5, 0, 40, cache_slots=100 * 4), T(800, 256, synth.FP32, 0.9, "poisson", 3, 0, 20, cache_slots=0)]
+    st = run_parity(synth.WorkloadCfg("wide", tabs, batch=64, ways=4, steps=12, seed=6, init_std=0.05, lr=0.05), steps=12,
+                    order=order, second_level_factor=level2)
+    assert st["total"]["bypasses"] > 0 and st["total"]["evictions"] > 0

@@ -26,6 +26,7 @@ int main() {
     if (!strcmp(what, "workgroups")) r = one_stage_workgroups(g, l2 != 0, n);
     if (!strcmp(what, "one_kernel_beside")) r = one_kernel_batch(g, l2 != 0, true, n, (int)batch);
     if (!strcmp(what, "one_kernel_alone")) r = one_kernel_batch(g, l2 != 0, false, n, (int)batch);
+    if (!strcmp(what, "link_with_stage")) r = link_with_stage(g, l2 != 0, n, (int)batch);
     printf("%lld\n", r);
   }
 }
@@ -65,3 +66,11 @@ def test_batches_that_one_kernel_takes(rule):
     assert not rule("one_kernel_beside", n=0)
     for T, batch in ((1, 2048), (2, 1024), (512, 4)):
         assert rule("one_kernel_alone", T=T, batch=batch, n=500) and not rule("one_kernel_alone", T=T, batch=batch + 1, n=500)
+
+
+def test_rows_of_half_a_megabyte_at_most_are_moved_on_the_stage_s_stream(rule):
+    """as far as the one kernel goes; with a second level 512 of them"""
+    for row_bytes, level2, most in ((16, 0, 4096), (128, 0, 4096), (256, 0, 2048), (1024, 0, 512), (16, 1, 512), (1024, 1, 512)):
+        assert rule("link_with_stage", row_bytes=row_bytes, n=most, level2=level2)
+        assert not rule("link_with_stage", row_bytes=row_bytes, n=most + 1, level2=level2)
+    assert not rule("link_with_stage", T=2, batch=1025, n=500)  # more bags than the one kernel takes
