@@ -484,10 +484,7 @@ int check_batch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
   return TBE_OK;
 }
 
-// own: a forward prefetches its batch itself, with no other in flight.  Nothing runs beside such a prefetch, and up to
-// kOwnLookups lookups (beyond, the write-back of a batch's bypassed rows is worth running beside the next stage) it goes to
-// the compute stream like the forward: no events.  (2 tables x 2000 rows, 16 bags, two steps: 190 us with events, 102 without.)
-constexpr int64_t kOwnLookups = 65536;
+// own: a forward prefetches its batch itself.  With no other batch in flight nothing of the library's runs beside such a prefetch.
 int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, int32_t batch, int64_t n, bool own = false) {
   int rc = check_batch(h, d_indices, d_offsets, batch, n);
   if (rc) return rc;
@@ -504,7 +501,7 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
   b.parks_prev = in_flight && h->prev_buf >= 0 && h->st.max_parked > 0 && !h->l2.on;
   h->total_lookups += n;
   h->last_buf = bi;
-  own = own && !in_flight && n <= kOwnLookups;
+  own = own && !in_flight && on_compute_stream(h->g, h->inputs_ready, h->never_bypasses, n);
   hipStream_t stage_s = own ? h->cs : h->as;
   b.link = own ? h->cs : link_stream(h, batch, n);
   if (own && h->link_s != h->cs) {  // (all but the write-back behind the last update the forwards have waited for)

@@ -372,6 +372,20 @@ constexpr int64_t kFewBytes = 512 << 10;
 inline bool link_with_stage(const Geometry &g, bool l2, int64_t n, int32_t batch) {
   return one_kernel_batch(g, l2, true, n, batch) && n * g.ovf_stride <= kFewBytes && (!l2 || n <= 512);
 }
+// Does a batch that a forward prefetches itself go to the compute stream, stage, transfer and commit, like the forward?  That
+// spares the events (2 tables x 2000 rows, 16 bags, two steps: 190 us with them, 102 without).  But with the inputs ready such a
+// stage need not wait for what the caller has given the compute stream between the last update and the forward, nor the
+// transfer: on streams of their own they run beside it, which is worth the events once the transfer is long (never, when all rows
+// are in a cache that holds them all).  Us a step, on the compute stream / on their own, with a copy of 256 MB before and after
+// each update: no row cached, 16000 rows of 64 bytes 376 / 348, 16000, 32000 and 64000 of 256 bytes 455, 620, 862 / 421, 562, 787,
+// 16000 of 1 KB 887 / 818, a third cached 330, 411, 1028 / 317, 404, 1018 (64 bytes 16000, 64000, 1 KB 64000); with four products of
+// 4096 x 4096 x 4096 instead, no row cached, 1069, 1226, 1479 / 1080, 1215, 1376 (256 bytes, 16000, 32000, 64000), 1 KB 16000 and
+// 64000 1544, 2836 / 1518, 2660, a third cached, 64 bytes 16000, 64000 991, 1071 / 1012, 1091; with nothing, a third cached,
+// 16000 of 64 bytes, 16000 and 64000 of 1 KB 120, 353, 811 / 169, 408, 863.
+constexpr int64_t kOwnLookups = 65536, kOwnBytes = 4 << 20;
+inline bool on_compute_stream(const Geometry &g, bool inputs_ready, bool never_bypasses, int64_t n) {
+  return n <= kOwnLookups && (!inputs_ready || never_bypasses || n * g.ovf_stride <= kOwnBytes);
+}
 // Sets that a batch can touch, at most (all rows of a table without a cache count as one set).
 inline int64_t sets_touched(const Geometry &g, int64_t n) {
   const int64_t sets = (int64_t)g.total_sets + g.T;

@@ -27,6 +27,8 @@ int main() {
     if (!strcmp(what, "one_kernel_beside")) r = one_kernel_batch(g, l2 != 0, true, n, (int)batch);
     if (!strcmp(what, "one_kernel_alone")) r = one_kernel_batch(g, l2 != 0, false, n, (int)batch);
     if (!strcmp(what, "link_with_stage")) r = link_with_stage(g, l2 != 0, n, (int)batch);
+    if (!strcmp(what, "compute_stream_ordered")) r = on_compute_stream(g, false, l2 != 0, n);  // (l2: never_bypasses)
+    if (!strcmp(what, "compute_stream_ready")) r = on_compute_stream(g, true, l2 != 0, n);
     printf("%lld\n", r);
   }
 }
@@ -74,3 +76,13 @@ def test_rows_of_half_a_megabyte_at_most_are_moved_on_the_stage_s_stream(rule):
         assert rule("link_with_stage", row_bytes=row_bytes, n=most, level2=level2)
         assert not rule("link_with_stage", row_bytes=row_bytes, n=most + 1, level2=level2)
     assert not rule("link_with_stage", T=2, batch=1025, n=500)  # more bags than the one kernel takes
+
+
+def test_batches_that_go_to_the_compute_stream(rule):
+    """prefetched by the forward itself: 65536 lookups; with the inputs ready 4 MB of rows, unless every row has its place in the
+    cache"""
+    for what, never_bypasses, row_bytes, most in (("compute_stream_ordered", 0, 1024, 65536), ("compute_stream_ordered", 1, 16, 65536),
+                                                  ("compute_stream_ready", 0, 1024, 4096), ("compute_stream_ready", 0, 256, 16384),
+                                                  ("compute_stream_ready", 0, 16, 65536), ("compute_stream_ready", 1, 1024, 65536)):
+        assert rule(what, row_bytes=row_bytes, n=most, level2=never_bypasses)
+        assert not rule(what, row_bytes=row_bytes, n=most + 1, level2=never_bypasses)
