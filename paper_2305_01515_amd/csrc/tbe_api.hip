@@ -977,6 +977,7 @@ static int backward_update_with(tbe_ctx *h, const float *d_grad_out, float lr, f
   const bool write_back = h->deferred < 0 && !h->never_bypasses;
   const bool waited_for = h->deferred >= 0 || write_back || h->deep;
   hipStream_t next = h->link_s;
+  if (write_back && next == h->cs && h->own_ls && write_back_beside(h->g, b.n)) next = h->link_s = h->ls;
   if (next != h->cs && (waited_for || h->inputs_ready)) {
     HIP_TRY(h, hipEventRecord(h->ev_trained[bi], h->cs));
     h->last_trained = bi;

@@ -386,6 +386,13 @@ constexpr int64_t kOwnLookups = 65536, kOwnBytes = 4 << 20;
 inline bool on_compute_stream(const Geometry &g, bool inputs_ready, bool never_bypasses, int64_t n) {
   return n <= kOwnLookups && (!inputs_ready || never_bypasses || n * g.ovf_stride <= kOwnBytes);
 }
+// Does the write-back of the rows that such a batch bypassed go to the link stream all the same, beside what the caller gives the
+// compute stream behind the update?  (The next batch waits for it.)  From where it would hold that up for more than half a
+// millisecond, and not below, where the events cost more.  Inputs ordered, us a step, on the compute stream / on the link's: no
+// row cached, with a copy of 256 MB before and after each update, 8, 16 and 64 MB of rows 606, 886, 2208 / 593, 856, 2130, with
+// four products of 4096 x 4096 x 4096 1193, 1479, 2809 / 1208, 1493, 2829; a third cached, 16 MB 564, 1148 / 583, 1173.
+constexpr int64_t kWriteBackBytes = 32 << 20;
+inline bool write_back_beside(const Geometry &g, int64_t n) { return n * g.ovf_stride >= kWriteBackBytes; }
 // Sets that a batch can touch, at most (all rows of a table without a cache count as one set).
 inline int64_t sets_touched(const Geometry &g, int64_t n) {
   const int64_t sets = (int64_t)g.total_sets + g.T;

@@ -29,6 +29,7 @@ int main() {
     if (!strcmp(what, "link_with_stage")) r = link_with_stage(g, l2 != 0, n, (int)batch);
     if (!strcmp(what, "compute_stream_ordered")) r = on_compute_stream(g, false, l2 != 0, n);  // (l2: never_bypasses)
     if (!strcmp(what, "compute_stream_ready")) r = on_compute_stream(g, true, l2 != 0, n);
+    if (!strcmp(what, "write_back_beside")) r = write_back_beside(g, n);
     printf("%lld\n", r);
   }
 }
@@ -86,3 +87,9 @@ def test_batches_that_go_to_the_compute_stream(rule):
                                                   ("compute_stream_ready", 0, 16, 65536), ("compute_stream_ready", 1, 1024, 65536)):
         assert rule(what, row_bytes=row_bytes, n=most, level2=never_bypasses)
         assert not rule(what, row_bytes=row_bytes, n=most + 1, level2=never_bypasses)
+
+
+def test_long_write_backs_leave_the_compute_stream(rule):
+    """32 MB of rows that may have been bypassed"""
+    for row_bytes, least in ((1024, 32768), (512, 65536)):
+        assert rule("write_back_beside", row_bytes=row_bytes, n=least) and not rule("write_back_beside", row_bytes=row_bytes, n=least - 1)
