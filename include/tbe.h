@@ -310,7 +310,8 @@ int tbe_set_backing_throttle(tbe_handle h, int64_t ns_per_row);
 /*
  * Tuning of the probe of Section 5.5.1 (results never depend on it): a wavefront of the probe kernel
  * takes several consecutive touched sets at a time when a batch leaves only a few distinct rows per
- * set, but not while that would leave fewer than min_windows wavefronts' worth of work.  Default 4096;
+ * set, but not while that would leave fewer than min_windows wavefronts' worth of work.  Until called: 4096, or, for a
+ * batch of at most 4096 lookups that one kernel takes through the whole stage, the wavefronts of that kernel.
  * 1 groups whenever the rows per set allow it (how the tests reach the grouped path with small
  * models), a huge value never groups.  Any time between batches; TBE_EINVAL outside 1 .. 2^30.
  */

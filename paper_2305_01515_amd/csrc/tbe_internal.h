@@ -287,7 +287,7 @@ struct Geometry {
   int32_t within_bits;  // bits left for the position inside the bag in a packed sort payload (0 = never packed)
   int32_t partial_stride;  // floats per partial-sum slot (widest row, padded to whole lanes)
   int64_t partial_slots;   // slots of the partial-sum buffer (heavy rows x bag ranges of a batch fit in)
-  int32_t probe_min_windows = 4096;  // the probe does not group touched sets while that leaves fewer windows than this
+  int32_t probe_min_windows = 0;  // the probe does not group touched sets while that leaves fewer windows than this (0: not set)
   int32_t heavy_target;    // (chunk, bag range) work items the heavy rows' tile kernel should have: the CUs free for it
   int32_t dtypes;          // storage types among the tables: 1 fp32, 2 binary16
   int32_t win_stride;      // max pooling: bytes of a lookup's record of the maxima it supplied (lanes of the widest row)
@@ -358,6 +358,11 @@ inline bool one_kernel_batch(const Geometry &g, bool l2, bool beside, int64_t n,
   const int64_t most = g.T > kLutTables ? (beside ? kOneLookups / 4 : kOneLookups / 8)
                        : !beside ? kOneLookups / 4 : l2 ? kOneLookups / 2 : kOneLookups;
   return n > 0 && n <= most && (int64_t)g.T * batch <= kOneBags;
+}
+// Windows below which the probe groups no sets: what the caller has set, or the wavefronts that keep the chip busy -- of the
+// one-kernel stage, those that it has (0: the kernel of its own, which has as many as there are windows).
+inline int32_t probe_min_windows(const Geometry &g, int one_kernel_waves) {
+  return g.probe_min_windows ? g.probe_min_windows : one_kernel_waves ? one_kernel_waves : 4096;
 }
 // Bytes of rows that the host link moves in about the time that a record on one stream and a wait for it on another cost a step.
 constexpr int64_t kFewBytes = 512 << 10;

@@ -506,7 +506,7 @@ hipError_t launch_one_kernel_stage(const TableMeta *tm, const Geometry &g, const
   a.cnt = b.cnt;
   const int wgs = one_stage_workgroups(g, l2.on, n);
   a.probe_items = wgs;
-  if (a.probe.min_windows > wgs * kOneWaves) a.probe.min_windows = wgs * kOneWaves;
+  a.probe.min_windows = probe_min_windows(g, wgs * kOneWaves);
   a.list_items = (n + kOneThreads - 1) / kOneThreads;
   a.plan_items = b.maxp || n <= kLongRun || long_rows_in_rest(n, g.win_stride) ? 0 : wgs < 8 ? 2 : 8;  // (see finalize_kernel)
   a.loc_items = a.list_items;

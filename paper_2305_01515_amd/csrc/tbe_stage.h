@@ -938,7 +938,7 @@ inline DedupArgs dedup_of(const TableMeta *tm, const Geometry &g, const BatchBuf
 }
 inline ProbeArgs probe_of(const TableMeta *tm, const Geometry &g, const BatchBuf &b, int32_t *tags, int32_t *ts, int32_t *freq,
                           const Level2 &l2, int lock) {
-  return ProbeArgs{tm, g.T, g.ways, b.k, b.k - lock > 1 ? b.k - lock : 1, g.probe_min_windows, b.uniq_key, b.uniq_tab, b.touched,
+  return ProbeArgs{tm, g.T, g.ways, b.k, b.k - lock > 1 ? b.k - lock : 1, probe_min_windows(g, 0), b.uniq_key, b.uniq_tab, b.touched,
                    tags, ts, freq, b.run_off, b.loc_u, b.status, b.old_tag, l2.tags2, l2.ts2, l2.factor,
                    l2.on ? b.src2 : nullptr, l2.on ? b.dst2 : nullptr, l2.on ? b.evict2 : nullptr};
 }

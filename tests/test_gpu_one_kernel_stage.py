@@ -61,3 +61,10 @@ def test_rows_around_half_a_megabyte(order, level2):
     st = run_parity(synth.WorkloadCfg("wide", tabs, batch=64, ways=4, steps=12, seed=6, init_std=0.05, lr=0.05), steps=12,
                     order=order, second_level_factor=level2)
     assert st["total"]["bypasses"] > 0 and st["total"]["evictions"] > 0
+
+
+@pytest.mark.parametrize("min_windows", [1, 100, 1 << 30])
+def test_probe_grouping_that_the_caller_sets(min_windows):
+    tabs = [T(20000, 8, synth.FP32, None, "fixed", 3, cache_slots=400 * 4), T(3000, 16, synth.FP32, 0.8, "fixed", 1, cache_slots=60)]
+    run_parity(synth.WorkloadCfg("group", tabs, batch=500, ways=4, steps=4, seed=8, init_std=0.05, lr=0.05), steps=4, order="early",
+               probe_min_windows=min_windows)

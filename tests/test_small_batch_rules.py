@@ -30,6 +30,8 @@ int main() {
     if (!strcmp(what, "compute_stream_ordered")) r = on_compute_stream(g, false, l2 != 0, n);  // (l2: never_bypasses)
     if (!strcmp(what, "compute_stream_ready")) r = on_compute_stream(g, true, l2 != 0, n);
     if (!strcmp(what, "write_back_beside")) r = write_back_beside(g, n);
+    g.probe_min_windows = (int)sets;
+    if (!strcmp(what, "probe_min_windows")) r = probe_min_windows(g, (int)n);
     printf("%lld\n", r);
   }
 }
@@ -93,3 +95,11 @@ def test_long_write_backs_leave_the_compute_stream(rule):
     """32 MB of rows that may have been bypassed"""
     for row_bytes, least in ((1024, 32768), (512, 65536)):
         assert rule("write_back_beside", row_bytes=row_bytes, n=least) and not rule("write_back_beside", row_bytes=row_bytes, n=least - 1)
+
+
+def test_what_the_caller_sets_of_the_probe_s_grouping_holds_for_every_batch(rule):
+    """sets: what tbe_set_probe_grouping was given (0: not called); n: wavefronts of the one-kernel stage (0: another batch)"""
+    for given in (1, 300, 4096, 1 << 30):
+        for waves in (0, 16, 256):
+            assert rule("probe_min_windows", sets=given, n=waves) == given
+    assert rule("probe_min_windows", n=0) == 4096 and rule("probe_min_windows", n=16) == 16
