@@ -120,9 +120,15 @@ typedef struct {
  *   max_batch         : largest `batch` (samples) of any later call.
  *   max_lookups       : largest `num_lookups` of any later call (at most 2^30).
  *   compute_stream    : hipStream_t on which forward / backward run (NULL = default stream).
- *   aux_stream        : hipStream_t on which prefetch work runs (that of a small batch which
- *                       tbe_forward prefetches itself: on compute_stream); may equal compute_stream
- *                       (then nothing overlaps).  Both must have the default priority.
+ *   aux_stream        : hipStream_t on which prefetch work runs; may equal compute_stream (then nothing
+ *                       overlaps).  Both must have the default priority.  The rows of larger batches
+ *                       move on a stream of the library's own.  Unless the prefetch depth is above one,
+ *                       a batch that tbe_forward prefetches itself has all of this on compute_stream,
+ *                       the way home of the rows that it bypassed included, which the caller's next
+ *                       work there then follows: up to 65536 lookups; once the inputs are declared
+ *                       ready (tbe_set_inputs_ready) up to 4 MB of rows (num_lookups times the widest),
+ *                       unless every table has a slot for each of its rows; and but for the way home
+ *                       of 32 MB of rows and more.
  * The sum over tables of the key spans (about the row counts, rounded up to whole sets)
  * must stay below 2^32 (TBE_ELIMIT).  All device memory is allocated here (TBE_ENOMEM): the cache
  * lines and, sized for the worst case of max_lookups distinct rows that all miss, about
@@ -323,8 +329,10 @@ int tbe_set_probe_grouping(tbe_handle h, int32_t min_windows);
  * caller guarantees instead that the buffers passed to tbe_prefetch are complete in device
  * memory when the call is made (e.g. a data loader finished them earlier); the prefetch
  * stage of the next batch can then start while the current batch is still training
- * (Section 5.7: the stages of different batches run simultaneously); it is ordered only
- * behind the last tbe_forward launched, whose output the model is waiting for.
+ * (Section 5.7: the stages of different batches run simultaneously).  It is then ordered only
+ * behind the last tbe_forward or tbe_backward_update launched, and for a batch of at most 524288
+ * lookups and 65536 bags in all that follows another one still to train only behind the fetch of
+ * the batch in training, or that trained last.
  */
 int tbe_set_inputs_ready(tbe_handle h, int32_t ready);
 
@@ -403,13 +411,13 @@ int tbe_get_stats(tbe_handle h, tbe_stats *out);
  * and lengthen it by their own events.  Both calls synchronise; tbe_set_profiling discards earlier records.
  * With h_ms NULL, tbe_get_stage_times returns the number of records.
  */
-#define TBE_STAGE_PREFETCH 0       /* key generation, sort, dedup, probe, compaction (aux stream) */
-#define TBE_STAGE_FILL 1           /* host link: write-back of parked victims + fetch-ahead of missed rows (aux) */
+#define TBE_STAGE_PREFETCH 0       /* key generation, sort, dedup, probe, compaction (aux stream; compute stream: see tbe_create) */
+#define TBE_STAGE_FILL 1           /* host link: write-back of parked victims + fetch-ahead of missed rows (the library's stream, or as bracket 0) */
 #define TBE_STAGE_FORWARD 2        /* pooled lookup (compute stream)                              */
 #define TBE_STAGE_BACKWARD_COMBINE 3 /* heavy rows: sum of the partial sums + update (compute stream) */
 #define TBE_STAGE_BACKWARD_SHORT 4 /* backward of rows with 2..64 lookups (max pooling, rows of 16 lanes and more: also of those
                                       with up to 512, fp32 1024 lookups) (compute stream)          */
-#define TBE_STAGE_COMMIT 5         /* victims -> staging, fetched rows -> cache lines (aux stream)  */
+#define TBE_STAGE_COMMIT 5         /* victims -> staging, fetched rows -> cache lines (as bracket 1) */
 #define TBE_STAGE_BACKWARD_SINGLE 6 /* backward of rows with one lookup, bag by bag (compute stream) */
 #define TBE_STAGE_BACKWARD_HEAVY 7 /* rows with more than 64 lookups: partial sums per bag range from gradient tiles in LDS
                                       (max pooling: one workgroup per row, update included, but for the rows in bracket 4)

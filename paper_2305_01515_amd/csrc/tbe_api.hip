@@ -1,4 +1,4 @@
-// C ABI of libtbe: handle life cycle, the three-stream batch pipeline (compute, prefetch,
+// C ABI of libtbe: handle life cycle, the batch pipeline over up to three streams (compute, prefetch,
 // host link), observation calls.
 // Declarations and the contract of every call are in include/tbe.h.
 #include <algorithm>

@@ -290,7 +290,7 @@ struct Geometry {
   int32_t probe_min_windows = 0;  // the probe does not group touched sets while that leaves fewer windows than this (0: not set)
   int32_t heavy_target;    // (chunk, bag range) work items the heavy rows' tile kernel should have: the CUs free for it
   int32_t dtypes;          // storage types among the tables: 1 fp32, 2 binary16
-  int32_t win_stride;      // max pooling: bytes of a lookup's record of the maxima it supplied (lanes of the widest row)
+  int32_t win_stride;      // lanes of the widest row; under max pooling the bytes of a lookup's record of the maxima it supplied
   uint32_t ovf_stride;     // bytes per overflow / staging slot (widest row)
   uint32_t total_sets;
   int64_t total_slots;
@@ -319,8 +319,10 @@ struct ClassInfo {
 // 651 / 665.  The stage's kernels alone cross over earlier, at about 200 k lookups (107 / 113, 123 / 120, 134 / 121,
 // 152 / 134 us), because every workgroup adds up the counts of all before it; up to the line the launches and the host time
 // that they spare (15 to 35 us of host time a step) make up for that.  Beyond it they do not: with twice and four times the
-// workgroups of the sort the stage takes 203 / 157 us at 1048576 lookups and 311 / 199 at 2097152.  The digit totals cost
-// the key generation an addition to memory per digit value and workgroup of 32 bags: not with more than 65536 bags.
+// workgroups of the sort the stage takes 203 / 157 us at 1048576 lookups and 311 / 199 at 2097152.  The key generation has 256
+// workgroups at most, because each adds its digit counts to the totals in memory, and walks the bags with them: with few
+// lookups a bag that takes longer than a workgroup for every 32 bags.  One lookup a bag, alone on one stream, with a kernel a
+// pass / with two or three: 65536 bags 103 / 130, 131072 bags 127 / 141, 262144 bags 176 / 163, 524288 bags 259 / 202.
 constexpr int64_t kSmallLookups = 524288, kSmallBags = 65536;
 constexpr int kMaxSortPasses = 4;
 constexpr int kSmallSortThreads = 512;
@@ -430,9 +432,13 @@ struct OneCtl {
 };
 
 // Sum and mean pooling, heavy rows of small batches: a workgroup each, in the launch of the rest of the backward, instead of
-// the tile kernel's launch in front of it.  A row with all n lookups of the batch is then n x lanes / 1024 reads one after the
-// other (lanes: 4 at least), some 0.7 us each; up to 64 of them that is what the tile kernel's launch costs in all (4 us of host
-// time, 2 to 12 us and the gaps before and behind it on the GPU), and rows like that are rare.
+// the tile kernel's launch in front of it (which reads the gradient rows of a bag range once for all heavy rows, in tiles, and
+// takes 28 us with the launch behind it however few they are).  A workgroup reads its row's gradients one after the other, n x
+// lanes / 1024 deep (lanes: 4 at least) for a row with all n lookups of the batch.  The backward in us, here / with the tile kernel,
+// n x lanes = 65536, rows of 4, 16, 64 lanes of fp32: the lookups spread over five rows 15, 12, 11 / 40, 28, 28, over sixteen 10, 9,
+// 11 / 30, 28, 29, by a power law 16, 12, 11 / 49, 28, 28; all in one row 41, 29, 26 / 32, 37, 27 (16 and 64 lanes of binary16
+// 36, 34 / 42, 29).  At 131072 five rows 22, 17, 17 / 32, 28, 28 and one row 74, 52, 46 / 34, 29, 27.  (The line is where a table
+// of one row loses 9 us at most.)
 inline bool long_rows_in_rest(int64_t n, int lanes) { return n * (lanes < 4 ? 4 : lanes) <= 65536; }
 
 // Digits of the radix sort: pass p sorts by (key >> shift[p]) & mask[p].

@@ -12,7 +12,8 @@
 //              or among the victims batch k parked (k evicted it).)
 //   transfer : victims of batch k, parked in the staging area when k was committed, go to
 //              the backing tier; at the same time the rows batch k+1 inserts or bypasses
-//              are fetched into HBM, except the late ones.  Runs on the link stream.
+//              are fetched into HBM, except the late ones.  Runs on the link stream, that of a
+//              small batch on its stage's stream or the compute stream.
 //   commit   : after batch k has trained: victims of k+1 move from their cache lines to
 //              the staging area, the new rows move in; late rows are copied HBM to HBM from
 //              where the map pointed.  Also writes batch k's overflow copies back.
@@ -504,8 +505,8 @@ __global__ __launch_bounds__(256) void ovf_writeback_kernel(Staging st, const Ba
 // The overflow copies that batch b's commit parked behind its victims (those of the batch before it, but for the ones that b
 // took over, which are not parked), written to the backing tier ahead of their turn: b has trained with no batch prefetched
 // behind it, and a bypassed row of a batch that has trained goes home without waiting for a batch that may never come.  Their
-// slots are emptied, so the next transfer passes them by.  How many they are stands in the list's length, which only this
-// stream's kernels change; the counters of the batch before are not read, because by now its buffer may be in use again (two
+// slots are emptied, so the next transfer passes them by.  How many they are stands in the list's length, which only
+// transfers and commits change, each behind the one before and this kernel between them, whatever their streams; the counters of the batch before are not read, because by now its buffer may be in use again (two
 // batches prefetched before the next forward) with nothing that orders its first kernel behind this one.
 template <int L>
 __global__ __launch_bounds__(256) void parked_copies_writeback_kernel(Staging st, const BatchCounters *cnt, u64 *bytes_d2h) {
