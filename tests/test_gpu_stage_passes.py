@@ -1,6 +1,7 @@
 """The passes of the prefetch stage at the sizes where they can go wrong: lookups and distinct rows around the widths of a
 wavefront's step, tables whose rows, sets or heavy rows begin and end anywhere in a step, tables without a cache side by
 side, tables without a lookup, more tables than the passes keep constants of in LDS, and rows entered several times."""
+import numpy as np
 import pytest
 
 from paper_2305_01515_amd import synth
@@ -17,6 +18,23 @@ def test_lookups_around_the_steps(n):
             T(2 * n + 5, 4, synth.FP32, 1.2, "fixed", n, cache_slots=0)]
     for t in (tabs[:1], tabs):
         run_parity(synth.WorkloadCfg("edge", t, batch=1, ways=8, steps=3, seed=n, init_std=0.05, lr=0.05), steps=3, order="early")
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 1023, 1025, 2047, 2048, 2049])
+def test_lookups_around_the_steps_with_a_kernel_a_pass(n):
+    """as many lookups in 2050 bags, all but one or two of them empty: more bags than the one kernel takes"""
+    from test_gpu_mixed_calls import run
+    tabs = [T(3 * n + 1, 8, synth.FP32, None, "fixed", 1, cache_slots=8 * (1 + n // 11)), T(2 * n + 5, 4, synth.FP32, None, "fixed", 1, cache_slots=0)]
+    rng = np.random.RandomState(n)
+    for t in (tabs[:1], tabs):
+        batch, host = 2050 // len(t), []
+        for _ in range(3):
+            lens = np.zeros((len(t), batch), dtype=np.int64)
+            lens[np.arange(len(t)), rng.randint(0, batch, len(t))] = n
+            off = np.concatenate([[0], np.cumsum(lens.ravel())]).astype(np.int64)
+            host.append((np.concatenate([rng.randint(0, c.rows, n) for c in t]).astype(np.int64), off,
+                         rng.randn(batch, sum(c.dim for c in t)).astype(np.float32)))
+        run(synth.WorkloadCfg("edge", t, batch=batch, ways=8, steps=3, seed=n, init_std=0.05, lr=0.05), host, rng, False)
 
 
 @pytest.mark.parametrize("batch,pool", [(64, 64), (65, 63), (241, 17), (2047, 64), (2048, 64), (2049, 64), (4099, 63), (8191, 64),

@@ -11,12 +11,15 @@ from parity_util import run_parity
 pytestmark = pytest.mark.gpu
 
 
-def churn(seed, slots=(16, 8, 0)):
+def churn(seed, slots=(16, 8, 0), wide=False):
+    """wide: eight times the rows and lookups, of 1 KB: their transfers and commits have the link's stream to themselves, those of
+    the others follow the stage on its own"""
     T = synth.TableCfg
-    tabs = [T(60, 16, synth.FP32, 0.7, "poisson", 2, 0, 20, cache_slots=slots[0]),
-            T(45, 8, synth.FP32, None, "poisson", 1, 0, 20, cache_slots=slots[1]),
-            T(30, 4, synth.FP32, None, "fixed", 1, cache_slots=slots[2])]
-    return synth.WorkloadCfg("churn", tabs, batch=19, ways=4, steps=30, seed=seed, init_std=0.05, lr=0.05)
+    f, d = (8, 16) if wide else (1, 1)
+    tabs = [T(60 * f, 16 * d, synth.FP32, 0.7, "poisson", 2, 0, 20, cache_slots=slots[0] * f),
+            T(45 * f, 8 * d, synth.FP32, None, "poisson", 1, 0, 20, cache_slots=slots[1] * f),
+            T(30 * f, 4 * d, synth.FP32, None, "fixed", 1, cache_slots=slots[2] * f)]
+    return synth.WorkloadCfg("churn", tabs, batch=19 * f, ways=4, steps=30, seed=seed, init_std=0.05, lr=0.05)
 
 
 @pytest.mark.parametrize("kw", [dict(order="early"), dict(order="ahead", vary_batch=3), dict(order="serial", flush_every=4),
@@ -30,16 +33,28 @@ def test_thirty_batches_over_the_same_rows(seed, kw):
     assert st["late_fetches"] > 0
 
 
+@pytest.mark.parametrize("kw", [dict(order="early"), dict(order="ahead", vary_batch=3), dict(order="serial", flush_every=4),
+                                dict(order="early", second_level_factor=1), dict(order="pipe2"), dict(order="pipe3", vary_batch=2),
+                                dict(order="deep3", vary_batch=5)],
+                         ids=["early", "ahead", "flush", "two_level", "pipe2", "pipe3", "queue"])
+def test_thirty_batches_of_wide_rows(kw):
+    """vary_batch: batches on both sides of the line in turn"""
+    st = run_parity(churn(1, wide=True), steps=30, **kw)
+    assert st["total"]["bypasses"] > 0 and st["total"]["inserts"] > 0
+    assert st["late_fetches"] > 0
+
+
+@pytest.mark.parametrize("wide", [False, True], ids=["narrow", "wide"])
 @pytest.mark.parametrize("ready", [True, False], ids=["inputs_ready", "inputs_ordered"])
 @pytest.mark.parametrize("burst", [2, 3, 4])
-def test_bursts_that_begin_with_two_batches_prefetched(burst, ready):
+def test_bursts_that_begin_with_two_batches_prefetched(burst, ready, wide):
     """A loop that trains `burst` batches, the last of them with nothing behind it, and then prefetches two before the next
     forward: the second takes the buffer of the batch whose overflow copies the burst's last commit parked, while they go
     home.  Values, and the backing tier at the end, as trained one by one."""
     from oracle import Oracle
     from paper_2305_01515_amd.tbe import TBE
     from parity_util import compare_backing, compare_forward, make_backing
-    cfg = churn(7 + burst, slots=(8, 4, 0))
+    cfg = churn(7 + burst, slots=(8, 4, 0), wide=wide)
     Wn, Mn, Wp, Mp = make_backing(cfg)
     slots = [t.cache_slots for t in cfg.tables]
     o = Oracle(Wn, Mn, slots, cfg.ways)
