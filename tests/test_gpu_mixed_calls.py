@@ -110,3 +110,20 @@ def test_wide_rows_in_turn(seed, depth, ready):
     cfg = synth.WorkloadCfg("wide", tabs, batch=17500, ways=4, steps=len(sizes), seed=seed, init_std=0.05, lr=0.05)
     st = run(cfg, host, rng, ready, depth, own=(3, 4, 5, 7, 8, 9, 11), ahead_of=(2, 6, 10))
     assert st["total"]["bypasses"] > 0 and st["total"]["evictions"] > 0
+
+
+@pytest.mark.parametrize("ready", [False, True], ids=["inputs_ordered", "inputs_ready"])
+@pytest.mark.parametrize("depth", [1, 2, 3])
+@pytest.mark.parametrize("seed", range(2))
+def test_models_that_never_bypass(seed, depth, ready):
+    """every table has a way for each of its rows: no update is followed by a write-back, and what follows it on the other streams
+    goes by the marks that other batches left; flushes in mid-stream, with batches before and behind them"""
+    rng = np.random.RandomState(500 + 10 * depth + seed)
+    tabs = [T(4001, 16, synth.FP32, None, "poisson", 1.0, cache_slots=4001 + 4), T(900, 256, synth.FP32, None, "poisson", 1.0, cache_slots=900 + 4),
+            T(50, 32, synth.FP32, None, "poisson", 1.0, cache_slots=50 + 4)]
+    sizes = [(int(rng.choice([1, 3, 40, 300, 500, 1400, 3000])), 1.0) for _ in range(24)]
+    sizes[6], sizes[13] = (9000, 2.9), (9000, 2.9)
+    host = drawn(rng, tabs, sizes)
+    cfg = synth.WorkloadCfg("resident", tabs, batch=9000, ways=4, steps=24, seed=seed, init_std=0.05, lr=0.05)
+    st = run(cfg, host, rng, ready, depth, own=(3, 6, 16, 17), ahead_of=(7, 10, 11, 13, 14), flush_behind=(8, 15))
+    assert st["total"]["bypasses"] == 0 and st["total"]["evictions"] == 0 and st["total"]["hits"] > 0
