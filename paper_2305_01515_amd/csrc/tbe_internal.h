@@ -622,6 +622,17 @@ __device__ inline int take_ticket(uint32_t *ticket) {
   return s_ticket;
 }
 
+// The batch's counters as its stage finds them; err: of a batch before it that was refused.
+__device__ inline void begin_counters(BatchCounters *c, int32_t err) {
+  c->n_uniq = c->n_touched = c->n_ins = c->n_byp = c->n_heavy = 0;
+  c->err = err;
+  c->n_mid = c->n_hchunks = 0;
+  c->h_ranges = 1;
+  c->hits = c->evictions = c->hit_lookups = 0;
+  c->l2_hits = c->l2_demotions = c->l2_evictions = c->l2_bypasses = 0;
+  c->packed = 0;
+}
+
 // n / d for any 32-bit n, with m = ceil(2^64 / d) (0 stands for d = 1): exact, because m d exceeds 2^64 by less than d
 __device__ inline uint32_t div_by(uint32_t n, unsigned long long m) { return m ? (uint32_t)__umul64hi((unsigned long long)n, m) : n; }
 __host__ __device__ inline unsigned long long div_magic(uint32_t d) { return d > 1 ? ~0ull / d + 1ull : 0ull; }

@@ -103,16 +103,6 @@ union OneLds {
 __device__ inline uint32_t word_of(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline uint32_t add_to(uint32_t *p, uint32_t v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-__device__ inline void begin_counters(BatchCounters *c) {
-  c->n_uniq = c->n_touched = c->n_ins = c->n_byp = c->n_heavy = 0;
-  c->err = 0;
-  c->n_mid = c->n_hchunks = 0;
-  c->h_ranges = 1;
-  c->hits = c->evictions = c->hit_lookups = 0;
-  c->l2_hits = c->l2_demotions = c->l2_evictions = c->l2_bypasses = 0;
-  c->packed = 0;
-}
-
 // The batch's bags, 8 lanes each: put(position, sort key, bag) for every lookup, refuse(code) for what makes the batch one to
 // refuse.  Four bags of a lane group are under way at a time: each is a chain of three reads (offsets, table, indices).
 template <class Refuse, class Put>
@@ -260,7 +250,7 @@ __device__ __forceinline__ void tile_phase(const OneStage &a, TileLds &s) {
   const int tid = my_thread(), lane = tid & 63, wave = tid >> 6;
   const int n = a.n;
   if (tid == 0) {
-    begin_counters(a.cnt);
+    begin_counters(a.cnt, 0);
     s.err = 0;
     s.refused = word_of((const uint32_t *)a.refused);
   }

@@ -24,14 +24,7 @@ __global__ __launch_bounds__(256) void begin_kernel(int64_t nb, const int64_t *_
   for (int64_t i = gid; i < n_said + n_said_counts; i += (int64_t)gridDim.x * blockDim.x)
     (i < n_said ? said + i : said_counts + (i - n_said))[0] = make_uint4(0u, 0u, 0u, 0u);
   const int64_t bag = gid;
-  if (bag == 0) {
-    cnt->n_uniq = cnt->n_touched = cnt->n_ins = cnt->n_byp = cnt->n_heavy = 0;
-    cnt->err = *refused;
-    cnt->n_mid = cnt->n_hchunks = 0;
-    cnt->h_ranges = 1;
-    cnt->hits = cnt->evictions = cnt->hit_lookups = 0;
-    cnt->l2_hits = cnt->l2_demotions = cnt->l2_evictions = cnt->l2_bypasses = 0;
-  }
+  if (bag == 0) begin_counters(cnt, *refused);
   const bool is = within_bits > 0 && bag < nb && offsets[bag + 1] - offsets[bag] > (1ll << within_bits);
   if (__ballot(is) && (threadIdx.x & 63) == 0) atomicOr(too_long, 1u);
 }
