@@ -381,7 +381,7 @@ hipError_t launch_stage(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
   const bool lfu = h->policy == TBE_POLICY_LFU;
   const StaleRows stale = stale_rows(h, b, bi);
   const Totals totals{h->d_total, h->d_bytes + 2, h->l2.on ? h->d_l2tot : nullptr};
-  if (one_kernel_batch(h->g, h->l2.on, s != h->cs, b.n, b.batch))
+  if (one_kernel_batch(h->g, h->l2.on, h->as == h->cs, b.n, b.batch))
     return launch_one_kernel_stage(h->d_tm, h->g, b, h->ss, h->tags, h->ts, h->freq, lfu, h->l2, h->deep, stale, totals, s);
   hipError_t e = launch_keygen(h->d_tm, h->g, b, h->ss, s);
   int res = 0;

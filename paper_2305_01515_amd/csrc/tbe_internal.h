@@ -342,23 +342,29 @@ inline int small_sort_blocks(int64_t n) {
 // launches (30 us of host time).  4096 lookups are what one workgroup sorts in its LDS: with several tiles, passes of the sort as
 // phases of the same kernel, one XCD's 32 CUs are no longer enough for the probe (4 tables of 100 k rows, 40960 lookups: 150 us
 // a step instead of 127; 11 to 15 k lookups 1.04 to 1.26 times as long, 5 k equal).  Its one workgroup reads 512 bags at a time:
-// 3853 lookups in 3380 bags took 238 instead of 217 us in two steps, a few hundred bags are faster.  The host time counts beside
-// training, where the launches of the next batch's stage come on top of those of the step: us a step with one kernel / with a
-// kernel a pass, a third of the rows cached, 500, 2000 and 4096 lookups 53, 66, 77 / 83, 83, 86.  A stage on the compute stream,
-// which nothing runs beside, is bound by the kernels: 500, 1000, 2000 and 4096 lookups 52, 55, 64, 77 / 57, 59, 61, 71 (sets of
-// one way 65, 78, 102 / 69, 73, 87 from 1000 on).
-// With a second level one XCD is short of wavefronts where the sets are few: 625 sets, 2000, 3000 and 4096 lookups beside
-// training 80, 109, 118 / 82, 95, 107.  With more tables than the passes keep constants of in LDS its few workgroups look every
-// lookup's table up in memory: beside training 500 and 1000 lookups 71, 79 / 88, 88, 3600 lookups 99 / 97, alone 150, 500 and 1000
-// lookups 64, 66, 75 / 67, 63, 66.
+// 3853 lookups in 3380 bags took 238 instead of 217 us in two steps, a few hundred bags are faster.  Us a step with one kernel /
+// with a kernel a pass, a third of the rows cached: beside training 500, 2000 and 4096 lookups 53, 66, 77 / 83, 83, 86; in a batch
+// that the forward prefetches, between a model of 24 small kernels on either side, 2000 and 4096 lookups 590, 595 / 616, 632, and
+// with no model, where the host is idle, 64, 77 / 61, 71.  On one stream for everything the kernels are all that counts: 1000, 2000
+// and 4096 lookups 54, 62, 74 / 59, 60, 72 (sets of one way 65, 76, 102 / 69, 73, 89).
+// With a second level one XCD is short of wavefronts where the sets are few: 4096 lookups beside training in 625, 1250 and 1876
+// sets 118, 107, 71 / 101, 97, 99, 3000 in 1250 sets 81 / 95, 2000 in 625 sets 80 / 82.  With more tables than the passes keep
+// constants of in LDS its few workgroups look every lookup's table up in memory: beside training 500, 1000, 1200, 2000 and 3600
+// lookups 71, 79, 69, 96, 99 / 88, 88, 94, 70, 97, on one stream 150, 500 and 1000 lookups 64, 66, 75 / 67, 63, 66.
 constexpr int64_t kOneLookups = 4096, kOneBags = 2048;
 constexpr int kLutTables = 512;  // models with more tables read the descriptions from memory in the passes of the stage
 constexpr int kOnePhases = 4;  // sorted lookups and distinct rows, probe, lists, end
 constexpr int kOneItems = 4;   // items of the phase that writes the lists, at most
-// beside: on another stream than the compute stream
-inline bool one_kernel_batch(const Geometry &g, bool l2, bool beside, int64_t n, int32_t batch) {
-  const int64_t most = g.T > kLutTables ? (beside ? kOneLookups / 4 : kOneLookups / 8)
-                       : !beside ? kOneLookups / 4 : l2 ? kOneLookups / 2 : kOneLookups;
+// Sets that a batch can touch, at most (all rows of a table without a cache count as one set).
+inline int64_t sets_touched(const Geometry &g, int64_t n) {
+  const int64_t sets = (int64_t)g.total_sets + g.T;
+  return sets < n ? sets : n;
+}
+inline bool many_rows_a_set(const Geometry &g, int64_t n) { return 2 * n > 5 * sets_touched(g, n); }
+// one_stream: the prefetch stream is the compute stream
+inline bool one_kernel_batch(const Geometry &g, bool l2, bool one_stream, int64_t n, int32_t batch) {
+  const int64_t most = g.T > kLutTables ? (one_stream ? 512 : 1536)
+                       : one_stream ? 1024 : l2 && many_rows_a_set(g, n) ? 2048 : kOneLookups;
   return n > 0 && n <= most && (int64_t)g.T * batch <= kOneBags;
 }
 // Windows below which the probe groups no sets: what the caller has set, or the wavefronts that keep the chip busy -- of the
@@ -366,18 +372,17 @@ inline bool one_kernel_batch(const Geometry &g, bool l2, bool beside, int64_t n,
 inline int32_t probe_min_windows(const Geometry &g, int one_kernel_waves) {
   return g.probe_min_windows ? g.probe_min_windows : one_kernel_waves ? one_kernel_waves : 4096;
 }
-// Bytes of rows that the host link moves in about the time that a record on one stream and a wait for it on another cost a step.
-constexpr int64_t kFewBytes = 512 << 10;
 // Do transfer and commit follow the stage on its stream?  A stream of their own costs a record and a wait, 10 us of host time,
 // of a step whose stage is one launch; on the stage's stream they hold the next batch's stage back, for as long as their rows
 // take.  Us a step beside training, on the stage's stream / on their own / with a kernel a pass (which varies with the host): a
 // third of the rows cached, 1000, 2000 and 4096 lookups 54, 65, 77 / 66, 67, 70 / 95, 88, 96, whatever the rows' width, and with a
 // model of 24 small kernels on either side 554 / 583 / 600 (2000 lookups); no row cached, 2000, 3000 and 4096 rows of 256 bytes
 // 83, 97, 115 / 73, 75, 80 / 107, 93, 102, 500, 1000, 2000 and 4096 rows of 1 KB 69, 90, 126, 188 / 67, 74, 92, 150 / 102, 110,
-// 115, 173.  A second level's stage takes its time as well: 500, 1000 and 2000 lookups in 32 sets 89, 103, 118 / 68, 79, 92 / 95,
-// 96, 97, in 313 sets 52, 83, 97 / 62, 72, 81 / 93, 97, 98.
+// 115, 173.  The probe of a second level with many rows a set takes its time as well: 500, 1000 and 2000 lookups in 32 sets 89, 103,
+// 118 / 68, 79, 92 / 95, 96, 97, 1000 and 2000 in 313 sets 83, 97 / 72, 81 / 97, 98, 500 52 / 62 / 93, 1000 in 625 and 1876 sets
+// 56, 57 / 64, 66 / 96, 98.
 inline bool link_with_stage(const Geometry &g, bool l2, int64_t n, int32_t batch) {
-  return one_kernel_batch(g, l2, true, n, batch) && n * g.ovf_stride <= kFewBytes && (!l2 || n <= 512);
+  return one_kernel_batch(g, l2, false, n, batch) && (n <= 1024 || n * g.ovf_stride <= 512 << 10) && !(l2 && many_rows_a_set(g, n));
 }
 // Does a batch that a forward prefetches itself go to the compute stream, stage, transfer and commit, like the forward?  That
 // spares the events (2 tables x 2000 rows, 16 bags, two steps: 190 us with them, 102 without).  But with the inputs ready such a
@@ -400,11 +405,6 @@ inline bool on_compute_stream(const Geometry &g, bool inputs_ready, bool never_b
 // four products of 4096 x 4096 x 4096 1193, 1479, 2809 / 1208, 1493, 2829; a third cached, 16 MB 564, 1148 / 583, 1173.
 constexpr int64_t kWriteBackBytes = 32 << 20;
 inline bool write_back_beside(const Geometry &g, int64_t n) { return n * g.ovf_stride >= kWriteBackBytes; }
-// Sets that a batch can touch, at most (all rows of a table without a cache count as one set).
-inline int64_t sets_touched(const Geometry &g, int64_t n) {
-  const int64_t sets = (int64_t)g.total_sets + g.T;
-  return sets < n ? sets : n;
-}
 // Workgroups of that kernel: a wavefront for every set that the batch can touch and a thread for every lookup (the passes over
 // lists), as far as 16 workgroups go, or 32 where a second level has many rows of a set to place.  Alone on one stream, us a
 // step with 16 sets a workgroup / with 48 and none for the lists / with a kernel a pass: one table without a cache, 2000, 3000

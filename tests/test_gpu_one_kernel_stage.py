@@ -21,13 +21,13 @@ def test_lookups_and_bags_around_the_lines(batch, pool, policy, level2):
                    order="early", policy=policy, second_level_factor=level2)
 
 
-@pytest.mark.parametrize("batch,pool,order,level2", [(127, 16, "early", 2), (128, 16, "early", 2), (129, 16, "early", 2),
-                                                     (63, 16, "inline", 0), (64, 16, "inline", 1), (65, 16, "inline", 0)])
-def test_lookups_around_the_other_lines(batch, pool, order, level2):
-    """2048 lookups with a second level, 1024 in a stage on the compute stream"""
+@pytest.mark.parametrize("batch,pool,order,level2,overlap", [(127, 16, "early", 2, True), (128, 16, "early", 2, True), (129, 16, "early", 2, True),
+                                                             (63, 16, "early", 0, False), (64, 16, "inline", 1, False), (65, 16, "early", 0, False)])
+def test_lookups_around_the_other_lines(batch, pool, order, level2, overlap):
+    """2048 lookups with a second level of few sets, 1024 on one stream"""
     tabs = [T(9001, 8, synth.FP32, 0.9, "fixed", pool - 3, cache_slots=4 * 300), T(700, 16, synth.FP32, None, "fixed", 3, cache_slots=64)]
     run_parity(synth.WorkloadCfg("other", tabs, batch=batch, ways=4, steps=4, seed=batch, init_std=0.05, lr=0.05), steps=4,
-               order=order, second_level_factor=level2)
+               order=order, second_level_factor=level2, overlap=overlap)
 
 
 @pytest.mark.parametrize("overlap,batch", [(True, 168), (False, 42)])
@@ -54,11 +54,11 @@ def test_many_tables(tables):
 
 
 @pytest.mark.parametrize("order,level2", [("early", 0), ("ahead", 0), ("pipe2", 0), ("early", 2)])
-def test_rows_around_half_a_megabyte(order, level2):
-    """batches of about 512 rows of 1 KB, half of them bypassed: the rows of some are moved on the stage's stream, those of others
+def test_rows_of_some_batches_on_the_stage_s_stream(order, level2):
+    """batches of about 1024 rows of 1 KB, half of them bypassed: the rows of some are moved on the stage's stream, those of others
     on the link's, in turn"""
-    tabs = [T(3000, 256, synth.FP32, None, "poisson", 5, 0, 40, cache_slots=100 * 4), T(800, 256, synth.FP32, 0.9, "poisson", 3, 0, 20, cache_slots=0)]
-    st = run_parity(synth.WorkloadCfg("wide", tabs, batch=64, ways=4, steps=12, seed=6, init_std=0.05, lr=0.05), steps=12,
+    tabs = [T(3000, 256, synth.FP32, None, "poisson", 5, 0, 40, cache_slots=(405 if level2 else 100) * 4), T(800, 256, synth.FP32, 0.9, "poisson", 3, 0, 20, cache_slots=0)]
+    st = run_parity(synth.WorkloadCfg("wide", tabs, batch=128, ways=4, steps=12, seed=6, init_std=0.05, lr=0.05), steps=12,
                     order=order, second_level_factor=level2)
     assert st["total"]["bypasses"] > 0 and st["total"]["evictions"] > 0
 

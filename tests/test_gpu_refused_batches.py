@@ -16,11 +16,11 @@ pytestmark = pytest.mark.gpu
 T = synth.TableCfg
 
 
-LOOKUPS = {"one_workgroup": 12,    # <= 64 lookups: one kernel of one workgroup
-           "one_kernel": 19,       # <= 1024: one kernel of several
-           "one_or_many": 500,     # <= 4096: one kernel beside training, a kernel a pass on the compute stream
-           "kernel_a_pass": 1500,  # <= 524288
-           "large": 21846}         # > 65536 bags: two or three kernels a pass
+LOOKUPS = {"one_workgroup": 12,     # one kernel of one workgroup
+           "few_workgroups": 150,   # ... of 3
+           "many_workgroups": 500,  # ... of 10, several of them with lists
+           "kernel_a_pass": 1500,   # 4097 to 524288 lookups
+           "large": 21846}          # > 65536 bags: two or three kernels a pass
 
 
 def model(seed, dtype, batch=19):
@@ -103,16 +103,16 @@ def test_nothing_behind_a_refused_batch_trains(behind, ahead, dtype, level2):
     refuse_and_go_on(model(3 + behind, dtype), behind, ahead, level2)
 
 
-@pytest.mark.parametrize("size", ["one_workgroup", "one_or_many", "kernel_a_pass", "large"])
+@pytest.mark.parametrize("size", ["one_workgroup", "many_workgroups", "kernel_a_pass", "large"])
 @pytest.mark.parametrize("behind,ahead,level2,bad_offsets", [(1, True, 0, False), (4, True, 0, True), (4, False, 0, False), (2, False, 0, True),
                                                              (4, True, 2, False), (3, False, 2, False)])
 def test_every_form_of_the_stage_refuses(size, behind, ahead, level2, bad_offsets):
     refuse_and_go_on(model(11 + behind, synth.FP32, LOOKUPS[size]), behind, ahead, level2, good=3, bad_offsets=bad_offsets)
 
 
-@pytest.mark.parametrize("refused,later", [("one_workgroup", "kernel_a_pass"), ("one_kernel", "one_or_many"), ("one_or_many", "kernel_a_pass"),
-                                           ("one_or_many", "one_workgroup"), ("kernel_a_pass", "one_kernel"), ("kernel_a_pass", "one_or_many"),
-                                           ("large", "one_kernel"), ("one_or_many", "large")])
+@pytest.mark.parametrize("refused,later", [("one_workgroup", "kernel_a_pass"), ("few_workgroups", "many_workgroups"), ("many_workgroups", "kernel_a_pass"),
+                                           ("many_workgroups", "one_workgroup"), ("kernel_a_pass", "few_workgroups"), ("kernel_a_pass", "many_workgroups"),
+                                           ("large", "few_workgroups"), ("many_workgroups", "large")])
 @pytest.mark.parametrize("ahead", [True, False], ids=["ahead", "one_by_one"])
 def test_one_form_hears_of_the_refusal_of_another(refused, later, ahead):
     """the good batches, in front of the refused one and behind it, go through another form of the stage"""
@@ -146,7 +146,7 @@ def test_refused_batch_behind_batches_fetched_ahead(depth, level2, forwarded, se
     refuse_behind_fetched(model(20 + seed, synth.FP32), depth, level2, forwarded)
 
 
-@pytest.mark.parametrize("size", ["one_or_many", "kernel_a_pass"])
+@pytest.mark.parametrize("size", ["many_workgroups", "kernel_a_pass"])
 @pytest.mark.parametrize("forwarded", [True, False])
 @pytest.mark.parametrize("depth,level2", [(1, 0), (1, 2), (2, 0), (3, 0)])
 def test_every_form_refuses_behind_batches_fetched_ahead(depth, level2, forwarded, size):

@@ -12,10 +12,10 @@ pytestmark = pytest.mark.gpu
 
 
 def churn(seed, slots=(16, 8, 0), wide=False):
-    """wide: eight times the rows and lookups, of 1 KB: their transfers and commits have the link's stream to themselves, those of
+    """wide: sixteen times the rows and lookups, of 1 KB: their transfers and commits have the link's stream to themselves, those of
     the others follow the stage on its own"""
     T = synth.TableCfg
-    f, d = (8, 16) if wide else (1, 1)
+    f, d = (16, 16) if wide else (1, 1)
     tabs = [T(60 * f, 16 * d, synth.FP32, 0.7, "poisson", 2, 0, 20, cache_slots=slots[0] * f),
             T(45 * f, 8 * d, synth.FP32, None, "poisson", 1, 0, 20, cache_slots=slots[1] * f),
             T(30 * f, 4 * d, synth.FP32, None, "fixed", 1, cache_slots=slots[2] * f)]

@@ -24,8 +24,8 @@ int main() {
     g.ovf_stride = (uint32_t)stride;
     long long r = -1;
     if (!strcmp(what, "workgroups")) r = one_stage_workgroups(g, l2 != 0, n);
-    if (!strcmp(what, "one_kernel_beside")) r = one_kernel_batch(g, l2 != 0, true, n, (int)batch);
-    if (!strcmp(what, "one_kernel_alone")) r = one_kernel_batch(g, l2 != 0, false, n, (int)batch);
+    if (!strcmp(what, "one_kernel")) r = one_kernel_batch(g, l2 != 0, false, n, (int)batch);
+    if (!strcmp(what, "one_kernel_one_stream")) r = one_kernel_batch(g, l2 != 0, true, n, (int)batch);
     if (!strcmp(what, "link_with_stage")) r = link_with_stage(g, l2 != 0, n, (int)batch);
     if (!strcmp(what, "compute_stream_ordered")) r = on_compute_stream(g, false, l2 != 0, n);  // (l2: never_bypasses)
     if (!strcmp(what, "compute_stream_ready")) r = on_compute_stream(g, true, l2 != 0, n);
@@ -64,20 +64,22 @@ def test_workgroups_for_sets_and_for_lists(rule):
 
 
 def test_batches_that_one_kernel_takes(rule):
-    """beside training and on the compute stream"""
-    for T, level2, beside, alone in ((1, 0, 4096, 1024), (512, 0, 4096, 1024), (513, 0, 1024, 512), (1, 1, 2048, 1024), (513, 1, 1024, 512)):
-        for what, most in (("one_kernel_beside", beside), ("one_kernel_alone", alone)):
-            assert rule(what, T=T, n=most, level2=level2) and not rule(what, T=T, n=most + 1, level2=level2)
-    assert not rule("one_kernel_beside", n=0)
+    """with a prefetch stream and without; with a second level fewer where there are more than two and a half rows a set"""
+    for T, sets, level2, most, one_stream in ((1, 0, 0, 4096, 1024), (512, 0, 0, 4096, 1024), (513, 0, 0, 1536, 512), (1, 900, 1, 2252, 1024),
+                                              (1, 9999, 1, 4096, 1024), (1, 500, 1, 2048, 1024), (1, 0, 1, 2048, 1024), (513, 0, 1, 1536, 512)):
+        for what, m in (("one_kernel", most), ("one_kernel_one_stream", one_stream)):
+            assert rule(what, T=T, sets=sets, n=m, level2=level2) and not rule(what, T=T, sets=sets, n=m + 1, level2=level2)
+    assert not rule("one_kernel", n=0)
     for T, batch in ((1, 2048), (2, 1024), (512, 4)):
-        assert rule("one_kernel_alone", T=T, batch=batch, n=500) and not rule("one_kernel_alone", T=T, batch=batch + 1, n=500)
+        assert rule("one_kernel", T=T, batch=batch, n=500) and not rule("one_kernel", T=T, batch=batch + 1, n=500)
 
 
-def test_rows_of_half_a_megabyte_at_most_are_moved_on_the_stage_s_stream(rule):
-    """as far as the one kernel goes; with a second level 512 of them"""
-    for row_bytes, level2, most in ((16, 0, 4096), (128, 0, 4096), (256, 0, 2048), (1024, 0, 512), (16, 1, 512), (1024, 1, 512)):
-        assert rule("link_with_stage", row_bytes=row_bytes, n=most, level2=level2)
-        assert not rule("link_with_stage", row_bytes=row_bytes, n=most + 1, level2=level2)
+def test_few_rows_are_moved_on_the_stage_s_stream(rule):
+    """1024 rows, or half a megabyte of them, as far as the one kernel goes; with a second level two and a half a set"""
+    for row_bytes, sets, level2, most in ((16, 0, 0, 4096), (128, 0, 0, 4096), (256, 0, 0, 2048), (512, 0, 0, 1024), (1024, 0, 0, 1024),
+                                          (16, 199, 1, 500), (1024, 9999, 1, 1024), (16, 9999, 1, 4096)):
+        assert rule("link_with_stage", row_bytes=row_bytes, sets=sets, n=most, level2=level2)
+        assert not rule("link_with_stage", row_bytes=row_bytes, sets=sets, n=most + 1, level2=level2)
     assert not rule("link_with_stage", T=2, batch=1025, n=500)  # more bags than the one kernel takes
 
 
