@@ -355,6 +355,7 @@ constexpr int64_t kOneLookups = 4096, kOneBags = 2048;
 constexpr int kLutTables = 512;  // models with more tables read the descriptions from memory in the passes of the stage
 constexpr int kOnePhases = 4;  // sorted lookups and distinct rows, probe, lists, end
 constexpr int kOneItems = 4;   // items of the phase that writes the lists, at most
+
 // Sets that a batch can touch, at most (all rows of a table without a cache count as one set).
 inline int64_t sets_touched(const Geometry &g, int64_t n) {
   const int64_t sets = (int64_t)g.total_sets + g.T;
@@ -367,11 +368,13 @@ inline bool one_kernel_batch(const Geometry &g, bool l2, bool one_stream, int64_
                        : one_stream ? 1024 : l2 && many_rows_a_set(g, n) ? 2048 : kOneLookups;
   return n > 0 && n <= most && (int64_t)g.T * batch <= kOneBags;
 }
+
 // Windows below which the probe groups no sets: what the caller has set, or the wavefronts that keep the chip busy -- of the
 // one-kernel stage, those that it has (0: the kernel of its own, which has as many as there are windows).
 inline int32_t probe_min_windows(const Geometry &g, int one_kernel_waves) {
   return g.probe_min_windows ? g.probe_min_windows : one_kernel_waves ? one_kernel_waves : 4096;
 }
+
 // Do transfer and commit follow the stage on its stream?  A stream of their own costs a record and a wait, 10 us of host time,
 // of a step whose stage is one launch; on the stage's stream they hold the next batch's stage back, for as long as their rows
 // take.  Us a step beside training, on the stage's stream / on their own / with a kernel a pass (which varies with the host): a
@@ -384,6 +387,7 @@ inline int32_t probe_min_windows(const Geometry &g, int one_kernel_waves) {
 inline bool link_with_stage(const Geometry &g, bool l2, int64_t n, int32_t batch) {
   return one_kernel_batch(g, l2, false, n, batch) && (n <= 1024 || n * g.ovf_stride <= 512 << 10) && !(l2 && many_rows_a_set(g, n));
 }
+
 // Does a batch that a forward prefetches itself go to the compute stream, stage, transfer and commit, like the forward?  That
 // spares the events (2 tables x 2000 rows, 16 bags, two steps: 190 us with them, 102 without).  But with the inputs ready such a
 // stage need not wait for what the caller has given the compute stream between the last update and the forward, nor the
@@ -398,6 +402,7 @@ constexpr int64_t kOwnLookups = 65536, kOwnBytes = 4 << 20;
 inline bool on_compute_stream(const Geometry &g, bool inputs_ready, bool never_bypasses, int64_t n) {
   return n <= kOwnLookups && (!inputs_ready || never_bypasses || n * g.ovf_stride <= kOwnBytes);
 }
+
 // Does the write-back of the rows that such a batch bypassed go to the link stream all the same, beside what the caller gives the
 // compute stream behind the update?  (The next batch waits for it.)  From where it would hold that up for more than half a
 // millisecond, and not below, where the events cost more.  Inputs ordered, us a step, on the compute stream / on the link's: no
@@ -405,7 +410,8 @@ inline bool on_compute_stream(const Geometry &g, bool inputs_ready, bool never_b
 // four products of 4096 x 4096 x 4096 1193, 1479, 2809 / 1208, 1493, 2829; a third cached, 16 MB 564, 1148 / 583, 1173.
 constexpr int64_t kWriteBackBytes = 32 << 20;
 inline bool write_back_beside(const Geometry &g, int64_t n) { return n * g.ovf_stride >= kWriteBackBytes; }
-// Workgroups of that kernel: a wavefront for every set that the batch can touch and a thread for every lookup (the passes over
+
+// Workgroups of the one-kernel stage: a wavefront for every set that the batch can touch and a thread for every lookup (the passes over
 // lists), as far as 16 workgroups go, or 32 where a second level has many rows of a set to place.  Alone on one stream, us a
 // step with 16 sets a workgroup / with 48 and none for the lists / with a kernel a pass: one table without a cache, 2000, 3000
 // and 4096 lookups 72, 84, 97 / 79, 101, 123 / 81, 97, 102; a cache of 32 sets 86, 106 / 99, 144 / 94, 113 (2000, 4096);
@@ -420,7 +426,8 @@ inline int one_stage_workgroups(const Geometry &g, bool l2, int64_t n) {
   const int64_t wgs = probe > lists ? probe : lists, most = l2 && n >= 4 * touched ? 32 : 16;
   return (int)(wgs < most ? wgs : most);
 }
-// What the workgroups of that kernel share; all zero between launches.  A line for each word that many of them change.
+
+// What they share; all zero between launches.  A line for each word that many of them change.
 struct OneCtl {
   struct alignas(128) Word { uint32_t n; };
   alignas(128) uint32_t chosen;  // 1 + the XCD that the stage runs on
