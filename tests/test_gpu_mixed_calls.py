@@ -101,11 +101,11 @@ def test_sizes_and_orders_in_turn(seed, ready, depth, level2):
 @pytest.mark.parametrize("depth", [1, 2])
 @pytest.mark.parametrize("seed", range(2))
 def test_wide_rows_in_turn(seed, depth, ready):
-    """rows of 1 KB, most of them bypassed: batches of 40 to 35000 lookups, around half a megabyte of rows, 4 MB and 32 MB, prefetched
-    by the forward and ahead"""
+    """rows of 1 KB, most of them bypassed: batches of 40 to 35000 lookups, around 1024 rows, 4 MB and 32 MB of them, prefetched by the
+    forward and ahead"""
     rng = np.random.RandomState(77 + seed)
     tabs = [T(9000, 256, synth.FP32, None, "poisson", 1.0, cache_slots=4 * 50), T(9000, 256, synth.FP32, None, "poisson", 1.0, cache_slots=0)]
-    sizes = [(b, 1.0) for b in (20, 240, 270, 1900, 17500, 20, 2200, 15000, 500, 17500, 17500, 2200, 250, 260)]
+    sizes = [(b, 1.0) for b in (20, 490, 530, 1900, 17500, 20, 2200, 15000, 500, 17500, 17500, 2200, 540, 480)]
     host = drawn(rng, tabs, sizes)
     cfg = synth.WorkloadCfg("wide", tabs, batch=17500, ways=4, steps=len(sizes), seed=seed, init_std=0.05, lr=0.05)
     st = run(cfg, host, rng, ready, depth, own=(3, 4, 5, 7, 8, 9, 11), ahead_of=(2, 6, 10))
