@@ -385,9 +385,9 @@ hipError_t launch_stage(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
     return launch_one_kernel_stage(h->d_tm, h->g, b, h->ss, h->tags, h->ts, h->freq, lfu, h->l2, h->deep, stale, totals, s);
   hipError_t e = launch_keygen(h->d_tm, h->g, b, h->ss, s);
   int res = 0;
-  if (e == hipSuccess) e = launch_sort(h->g, b, h->ss, &res, s);
+  if (e == hipSuccess) e = launch_sort(h->d_tm, h->g, b, h->ss, &res, s);
   if (e != hipSuccess) return e;
-  return launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.keys[res], h->ss.vals[res], h->tags, h->ts, h->freq, lfu, h->l2,
+  return launch_dedup_probe(h->d_tm, h->g, b, h->ss, h->ss.pairs[res], h->tags, h->ts, h->freq, lfu, h->l2,
                             h->deep, stale, totals, s);
 }
 
@@ -652,7 +652,11 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   for (const TableMeta &m : h->tm) h->g.dtypes |= m.dtype == TBE_FP32 ? 1 : 2;
   for (const TableMeta &m : h->tm) h->g.win_stride = std::max(h->g.win_stride, m.lanes);
   for (const TableMeta &m : h->tm) h->g.ovf_stride = std::max(h->g.ovf_stride, m.row_bytes);
-  h->g.key_bits = 1;
+  h->g.key_bits = h->g.seg_bits = 1;
+  for (const TableMeta &m : h->tm) {
+    const uint64_t span = m.sets ? (uint64_t)m.sets * m.rows_per_set : (uint64_t)m.rows;
+    while (h->g.seg_bits < 32 && (1ull << h->g.seg_bits) < span) h->g.seg_bits++;
+  }
   while (h->g.key_bits < 32 && (1ull << h->g.key_bits) < key) h->g.key_bits++;
   {  // sort payload (bag, position inside the bag) when both fit 32 bits
     int bag_bits = 0;
@@ -751,8 +755,7 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
   CREATE_TRY(hipEventCreateWithFlags(&h->ev_fwd, hipEventDisableTiming));
   const size_t N = (size_t)max_lookups;
   for (int i = 0; i < 2; i++) {
-    CREATE_TRY(h->mem.get(&h->ss.keys[i], 4 * N));
-    CREATE_TRY(h->mem.get(&h->ss.vals[i], 4 * N));
+    CREATE_TRY(h->mem.get(&h->ss.pairs[i], 8 * N));
   }
   {
     int widest = 0;
@@ -792,19 +795,21 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
     CREATE_TRY(static_scratch_of_current_device(&p, &h->device));
     h->static_partials = (float *)p;
   }
-  CREATE_TRY(h->mem.get(&h->ss.hist, 4 * (512 * 1024 + 512)));  // sort: counts per digit value (<= 512) and block (<= 1024), digit totals
-  CREATE_TRY(h->mem.get(&h->ss.blk, 16 * (8192 + 1)));
-  CREATE_TRY(h->mem.get(&h->ss.tally, 8 * 3 * 8192));
+  {
+    const SortNeeds need = sort_needs(h->g, max_lookups, max_batch);
+    CREATE_TRY(h->mem.get(&h->ss.slots, 4 * (size_t)need.slots));
+    CREATE_TRY(h->mem.get(&h->ss.tiles, 16 * (size_t)need.tiles));
+    CREATE_TRY(h->mem.get(&h->ss.said, 4 * (size_t)need.said));
+    CREATE_TRY(h->mem.get(&h->ss.flags, 8 * (size_t)need.tiles));
+    CREATE_TRY(hipMemset(h->ss.flags, 0, 8 * (size_t)need.tiles));
+  }
+  CREATE_TRY(h->mem.get(&h->ss.said_counts, 8 * 2 * 4 * (size_t)kScanBlocks));
+  CREATE_TRY(hipMemset(h->ss.said_counts, 0, 8 * 2 * 4 * (size_t)kScanBlocks));
+  CREATE_TRY(h->mem.get(&h->ss.tally, 8 * 3 * 4 * (size_t)kScanBlocks));
   CREATE_TRY(h->mem.get(&h->ss.too_long, 16));
   CREATE_TRY(hipMemset(h->ss.too_long, 0, 16));
-  h->ss.ticket = h->ss.too_long + 1;
   h->ss.refused = (int32_t *)h->ss.too_long + 2;
-  {  // (the larger tiles begin at 131073 lookups, so the batch with the most workgroups need not be the largest)
-    const int most = std::max(small_sort_blocks(std::min<int64_t>(max_lookups, 131072)),
-                              small_sort_blocks(std::min<int64_t>(max_lookups, kSmallLookups)));
-    CREATE_TRY(h->mem.get(&h->ss.said, 4 * 256 * kMaxSortPasses * (size_t)(1 + most)));
-  }
-  CREATE_TRY(h->mem.get(&h->ss.said_counts, 8 * 4 * (size_t)kSmallScanBlocks));
+  h->ss.stage_err = h->ss.too_long + 3;
   CREATE_TRY(h->mem.get(&h->ss.one, sizeof(OneCtl)));
   CREATE_TRY(hipMemset(h->ss.one, 0, sizeof(OneCtl)));
   CREATE_TRY(h->mem.get(&h->d_total, sizeof(BatchCounters)));

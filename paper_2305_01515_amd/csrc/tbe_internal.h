@@ -190,19 +190,18 @@ struct BatchBuf {
 
 // Scratch shared by all batches (only used inside the prefetch stage, which is serial).
 struct SortScratch {
-  uint32_t *keys[2];
-  uint32_t *vals[2];
-  uint32_t *hist;          // [256 * max sort blocks] block histograms, then [256] digit totals
-  unsigned long long *blk; // [2 * (5 * scan blocks + 1)] sums per workgroup and per wavefront of the compaction passes
+  uint2 *pairs[2];         // (sort key, payload) of every lookup
+  uint32_t *slots;         // digit counts of the key generation's workgroups, then their sums (see SortShape)
+  uint4 *tiles;            // the sort's tiles
+  uint32_t *said;          // what its tiles say of each digit value
+  unsigned long long *flags; //   and that they have said it
+  unsigned long long *said_counts;  // [2 passes][4 words][kScanBlocks] counts of the compaction passes
   unsigned long long *tally;  // [3 * wavefronts of a compaction pass] (evictions, lookups that hit, late rows) per wave-
                               //     front of the last batch's status pass
   uint32_t *too_long;         // a bag of the batch does not fit the packed payload (0 between batches)
+  uint32_t *stage_err;        // what the key generation finds wrong with the batch (0 between batches)
   int32_t *refused;           // error of the first batch that was refused, with kRefusedBefore (0: none): no batch behind it
                               //   does anything
-  // small batches (small_batch): what the workgroups of a kernel tell each other
-  uint32_t *ticket;           // workgroups of the running kernel that have begun (0 between kernels)
-  uint32_t *said;             // [kMaxSortPasses][256] digit totals, then [kMaxSortPasses][workgroups][256] digit counts
-  unsigned long long *said_counts;  // [2 passes][2 words][kSmallScanBlocks] counts of the compaction passes
   struct OneCtl *one;         // batches that one kernel takes through the stage (one_kernel_batch)
 };
 
@@ -284,6 +283,7 @@ struct Geometry {
   int32_t T, ways;
   int32_t sum_dim;
   int32_t key_bits;     // bits of the largest sort key
+  int32_t seg_bits;     // bits of the widest table's keys
   int32_t within_bits;  // bits left for the position inside the bag in a packed sort payload (0 = never packed)
   int32_t partial_stride;  // floats per partial-sum slot (widest row, padded to whole lanes)
   int64_t partial_slots;   // slots of the partial-sum buffer (heavy rows x bag ranges of a batch fit in)
@@ -308,34 +308,96 @@ struct ClassInfo {
   const int32_t *table_class;              // device: class of every table
 };
 
-// Batches of few lookups are bound by launches, not by bytes: every pass of the prefetch stage over them is one kernel,
-// whose workgroups tell each other their counts through memory, instead of a kernel that counts and one that writes (and
-// one that scans in between, for the sort).  A workgroup takes the next ticket when it begins and waits only for the counts
-// of workgroups with earlier tickets, which have begun and say their counts before they wait for anything: every wait ends
-// whatever else runs on the GPU.  The words are cleared by the stage's first kernel.
-// The line lies where whole steps cost the same either way.  8 tables of 200 k rows of 64 bytes, 4096 bags each, the next
-// batch prefetched ahead, us a step with a kernel a pass / with two or three: every row resident 126 / 143 at 131072 lookups,
-// 149 / 156 at 262144, 169 / 170 at 393216, 191 / 188 at 524288; a fifth of the rows cached 308 / 330, 462 / 481, 570 / 588,
-// 651 / 665.  The stage's kernels alone cross over earlier, at about 200 k lookups (107 / 113, 123 / 120, 134 / 121,
-// 152 / 134 us), because every workgroup adds up the counts of all before it; up to the line the launches and the host time
-// that they spare (15 to 35 us of host time a step) make up for that.  Beyond it they do not: with twice and four times the
-// workgroups of the sort the stage takes 203 / 157 us at 1048576 lookups and 311 / 199 at 2097152.  The key generation has 256
-// workgroups at most, because each adds its digit counts to the totals in memory, and walks the bags with them: with few
-// lookups a bag that takes longer than a workgroup for every 32 bags.  One lookup a bag, alone on one stream, with a kernel a
-// pass / with two or three: 65536 bags 103 / 130, 131072 bags 127 / 141, 262144 bags 176 / 163, 524288 bags 259 / 202.
+// Batches of few lookups, which are bound by launches and by the latency of dependent kernels, not by bytes: their stage runs
+// beside training behind the last commit (prefetch_behind_training), the plan of the heavy rows has fewer workgroups, and the
+// backward is the tile kernel and one launch for everything else.
 constexpr int64_t kSmallLookups = 524288, kSmallBags = 65536;
 constexpr int kMaxSortPasses = 4;
-constexpr int kSmallSortThreads = 512;
-constexpr int kSmallSortBlocks = 128;  // a workgroup's tile is 4 or 8 keys per thread
-constexpr int kSmallScanBlocks = 256;
-static_assert(kSmallLookups <= kSmallSortBlocks * kSmallSortThreads * 8, "the sort's workgroups must hold the batch");
+constexpr int kScanBlocks = 2048;  // workgroups of a compaction pass, at most
 inline bool small_batch(const Geometry &g, int64_t n, int32_t batch) {
   return n > 0 && n <= kSmallLookups && (int64_t)g.T * batch <= kSmallBags;
 }
-inline int small_sort_items(int64_t n) { return n <= 131072 ? 4 : 8; }
-inline int small_sort_blocks(int64_t n) {
-  const int tile = kSmallSortThreads * small_sort_items(n);
-  return (int)((n + tile - 1) / tile);
+
+// Digits of the radix sort: pass p sorts by (key >> shift[p]) & mask[p].
+struct DigitPlan {
+  int passes;
+  int shift[kMaxSortPasses];
+  uint32_t mask[kMaxSortPasses];
+};
+inline DigitPlan digit_plan(int key_bits, int passes) {
+  DigitPlan d{};
+  d.passes = passes;
+  int shift = 0;
+  for (int p = 0; p < passes; p++) {
+    const int w = (key_bits - shift + (passes - p) - 1) / (passes - p);  // balanced digit widths, the wider ones first
+    d.shift[p] = shift;
+    d.mask[p] = (1u << w) - 1u;
+    shift += w;
+  }
+  return d;
+}
+
+// ---- the sort of a batch that goes through the stage a kernel a pass ----
+// Bags are table-major, so a batch's keys arrive sorted by table.  Where the tables have enough lookups to fill tiles of their
+// own, every table is a segment that is sorted by itself, by the bits of the widest table's keys: 32 tables of a million rows
+// are two passes by 10 bits instead of three by 9, 8 and 8.  A pass is one kernel; what bounds it is the number of its tiles
+// (latency of a tile's chain: keys, ranks, counts said and heard, output), so a tile has as many keys as leave enough of them to
+// fill the chip.  Us a pass, tiles of 1024 / 2048 / 4096 / 8192 keys: 41 k lookups 7.8 / 8.8 / 9.7 / -, 90 k 10.5 / 11.7 / 13.5 / -,
+// 262 k - / 15.0 / 16.2 / -, 818 k - / - / 18.6 / 22.3, 3.9 M - / - / 39.7 / 32.2, 7.9 M - / - / 70 / 55.6.
+// Digits of 11 bits spare keys of 21 and 22 bits a pass, which pays where a pass is latency; 10.5 M lookups take two passes of
+// 120 us so and three by 8 bits 64 us each.
+// (Digits of 8 bits with a kernel that counts, one that scans and one that writes to a pass: 3.9 M lookups of 23 bits 115 us, now
+// 64; 7.9 M of 25 bits 207, now 111; 818 k 69, now 37.)
+constexpr int kLutTables = 512;  // models with more tables read the descriptions from memory in the passes of the stage
+constexpr int kSortThreads = 512;
+constexpr int64_t kTiles1k = 131072, kTiles2k = 524288, kTiles4k = 2097152;  // lookups up to which tiles have 1024, 2048, 4096 keys
+constexpr int64_t kWideDigits = 1048576;                                     // ... and digits 11 bits
+constexpr int64_t kSegmentLookups = 2048;                                    // lookups a table, on average, from which tables are segments
+constexpr int kSlotsHeard = 32;  // slots of a segment that the workgroups of the sort add up themselves
+constexpr uint32_t kLastTile = 0x80000000u;
+struct SortShape {
+  DigitPlan digits;
+  int rb;          // bits of the widest digit (8 at least)
+  int segs, bags;  // segments, and the bags of one
+  int items;       // keys of a thread
+  int slots;       // workgroups of the key generation for a segment, each with a slot for its counts of all digit values
+  bool add_slots;  // they are added up by a kernel of their own
+  int tiles;       // at most
+  __host__ __device__ int tile() const { return kSortThreads * items; }
+};
+inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch) {
+  SortShape s{};
+  s.segs = g.T > 1 && g.T <= kLutTables && n >= kSegmentLookups * g.T ? g.T : 1;
+  s.bags = (int)((int64_t)g.T * batch / s.segs);
+  const int bits = s.segs > 1 ? g.seg_bits : g.key_bits, widest = n <= kWideDigits ? 11 : 10;
+  const int passes = (bits + widest - 1) / widest;
+  s.digits = digit_plan(bits, passes);
+  s.rb = (bits + passes - 1) / passes;
+  if (s.rb < 8) s.rb = 8;
+  s.items = n <= kTiles1k ? 2 : n <= kTiles2k ? 4 : n <= kTiles4k ? 8 : 16;
+  // A workgroup of the key generation takes 64 bags at a time.  Up to two rounds of them are left to kSlotsHeard workgroups, whose
+  // counts the sort can add up by itself; many more lookups are worth the addition's launch, 5 us.
+  const int64_t rounds = (s.bags + 63) / 64, most = 1024 / s.segs > kSlotsHeard ? 1024 / s.segs : kSlotsHeard;
+  s.slots = (int)(rounds < 1 ? 1 : rounds < 4 * kSlotsHeard && rounds > kSlotsHeard ? kSlotsHeard : rounds > most ? most : rounds);
+  s.add_slots = s.slots > kSlotsHeard || (s.slots > 4 && n > 1000000);
+  s.tiles = (int)((n + s.tile() - 1) / s.tile() + s.segs);
+  return s;
+}
+// What the sort of any batch of at most `n` lookups in `batch` bags a table needs.
+struct SortNeeds { int64_t said, tiles, slots; };  // words of tiles' counts, tiles, words of slots
+inline SortNeeds sort_needs(const Geometry &g, int64_t n, int32_t batch) {
+  SortNeeds r{1, 1, 1};
+  // (a batch of fewer lookups can have more tiles, wider digits or, as one segment, more workgroups)
+  const int64_t steps[] = {n, kTiles1k, kTiles2k, kTiles4k, kWideDigits, kSegmentLookups * g.T - 1};
+  for (int64_t m : steps) {
+    if (m > n || m < 1) continue;
+    const SortShape s = sort_shape(g, m, batch);
+    const int64_t said = 2 * (int64_t)s.tiles << s.rb, slots = (int64_t)(s.slots + 1) * s.segs * (s.digits.passes << s.rb);
+    if (said > r.said) r.said = said;
+    if (s.tiles > r.tiles) r.tiles = s.tiles;
+    if (slots > r.slots) r.slots = slots;
+  }
+  return r;
 }
 
 // Batches of very few lookups: one kernel takes them through the whole prefetch stage (tbe_one.hip), which spares eight
@@ -352,7 +414,6 @@ inline int small_sort_blocks(int64_t n) {
 // constants of in LDS its few workgroups look every lookup's table up in memory: beside training 500, 1000, 1200, 2000 and 3600
 // lookups 71, 79, 69, 96, 99 / 88, 88, 94, 70, 97, on one stream 150, 500 and 1000 lookups 64, 66, 75 / 67, 63, 66.
 constexpr int64_t kOneLookups = 4096, kOneBags = 2048;
-constexpr int kLutTables = 512;  // models with more tables read the descriptions from memory in the passes of the stage
 constexpr int kOnePhases = 4;  // sorted lookups and distinct rows, probe, lists, end
 constexpr int kOneItems = 4;   // items of the phase that writes the lists, at most
 
@@ -448,34 +509,14 @@ struct OneCtl {
 // of one row loses 9 us at most.)
 inline bool long_rows_in_rest(int64_t n, int lanes) { return n * (lanes < 4 ? 4 : lanes) <= 65536; }
 
-// Digits of the radix sort: pass p sorts by (key >> shift[p]) & mask[p].
-struct DigitPlan {
-  int passes;
-  int shift[kMaxSortPasses];
-  uint32_t mask[kMaxSortPasses];
-};
-inline DigitPlan digit_plan(int key_bits, int passes) {
-  DigitPlan d{};
-  d.passes = passes;
-  int shift = 0;
-  for (int p = 0; p < passes; p++) {
-    const int w = (key_bits - shift + (passes - p) - 1) / (passes - p);  // balanced digit widths, the wider ones first
-    d.shift[p] = shift;
-    d.mask[p] = (1u << w) - 1u;
-    shift += w;
-  }
-  return d;
-}
-
 // ---- launchers (each enqueues on `s` and returns the HIP status of the launch) ----
 
-// counters of the batch to zero, sort keys and payloads of its lookups into ss.keys[0] / ss.vals[0]
+// counters of the batch to zero, sort keys and payloads of its lookups into ss.pairs[0]
 hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf &b, const SortScratch &ss, hipStream_t s);
-hipError_t launch_sort(const Geometry &g, const BatchBuf &b, SortScratch &ss, int *result_buf, hipStream_t s);
+hipError_t launch_sort(const TableMeta *tm, const Geometry &g, const BatchBuf &b, const SortScratch &ss, int *result_buf, hipStream_t s);
 // lock: batches before the current one whose ways are locked like the current batch's own (0 in the one-deep pipeline)
 hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const BatchBuf &b, SortScratch &ss,
-                              const uint32_t *sorted_keys, const uint32_t *sorted_pos, int32_t *tags, int32_t *ts,
-                              int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale,
+                              const uint2 *sorted, int32_t *tags, int32_t *ts, int32_t *freq, bool lfu, const Level2 &l2, int lock, const StaleRows &stale,
                               const Totals &totals, hipStream_t s);
 // the whole stage of a batch for which one_kernel_batch holds
 hipError_t launch_one_kernel_stage(const TableMeta *tm, const Geometry &g, const BatchBuf &b, const SortScratch &ss, int32_t *tags,
@@ -621,13 +662,11 @@ __device__ inline W hear(const W *p, W v) {  // v: what a first look found
   }
   return v & ~kSaid;
 }
-// The workgroup's number by the order in which workgroups began; the counter is back at zero when all have.
-__device__ inline int take_ticket(uint32_t *ticket) {
-  __shared__ int s_ticket;
-  if (threadIdx.x == 0) s_ticket = gridDim.x == 1 ? 0 : (int)atomicInc(ticket, gridDim.x - 1);
-  __syncthreads();
-  return s_ticket;
-}
+// How often a workgroup looks at what another one has yet to say before it counts that one's part itself: some 60 us.
+#ifndef TBE_POLLS
+#define TBE_POLLS 64
+#endif
+constexpr int kPolls = TBE_POLLS;
 
 // The batch's counters as its stage finds them; err: of a batch before it that was refused.
 __device__ inline void begin_counters(BatchCounters *c, int32_t err) {

@@ -482,13 +482,13 @@ hipError_t launch_one_kernel_stage(const TableMeta *tm, const Geometry &g, const
   a.digits = digit_plan(g.key_bits, (g.key_bits + 7) / 8);
   a.ctl = ss.one;
   a.refused = ss.refused;
-  a.dedup = dedup_of(tm, g, b, nullptr, nullptr);
+  a.dedup = dedup_of(tm, g, b);
   a.probe = probe_of(tm, g, b, tags, ts, freq, l2, lock);
   a.status = status_of(tm, g, b, l2, stale, ss.tally);
   a.plan = plan_of(tm, g, b);
   a.totals = totals;
   a.tally = ss.tally;
-  a.sorted_pos = ss.vals[0];
+  a.sorted_pos = (uint32_t *)ss.pairs[0];
   a.uid_sorted = b.uid_sorted;
   a.loc_u = b.loc_u;
   a.run_off = b.run_off;

@@ -125,8 +125,6 @@ __device__ __forceinline__ void write_chunk(const Op &op, int base, int end, int
 struct DedupArgs {
   const TableMeta *tm;
   int T;
-  const uint32_t *key;      // sorted
-  const uint32_t *pos;      // lookup position of each sorted element
   const int32_t *bag_of_pos;
   const BatchCounters *cnt;
   int within_bits;
@@ -150,7 +148,7 @@ struct DedupArgs {
   uint2 *touched;
 };
 // Args: DedupArgs, or a reference to it (what a method needs of it is then loaded there)
-template <class Args, int ITEMS = 2>
+template <class Args, int ITEMS = 1>
 struct DedupPass {
   static constexpr int kItems = ITEMS;
   typedef Counts<1> V;  // lo: distinct rows, hi: touched sets
@@ -169,7 +167,6 @@ struct DedupPass {
     last = 0;
     return lut != nullptr;
   }
-  __device__ bool prepare_count(KeyLut &l) const { return prepare(l); }
   __device__ void enter_table(uint32_t k) const {  // last table with key_base <= k
     int lo = t < 0 ? 0 : t, hi = a.T - 1;
     uint32_t sets;
@@ -191,16 +188,28 @@ struct DedupPass {
     t = lo;
     cached = sets != 0;
   }
+  // Is the lookup with key k, behind one with key `before`, the first of its row (bit 0), the row the first of its set (bit 1)?
+  __device__ uint32_t head(bool first, uint32_t k, uint32_t before) const {
+    if (!first && k == before) return 0u;
+    if (t < 0 || k > last) enter_table(k);
+    // rows of a table without a cache are one set
+    return first || before < base || (cached && div_by(k - base, magic) != div_by(before - base, magic)) ? 3u : 1u;
+  }
   __device__ V flag(int i, int) const {
-    V f{};
-    const uint32_t k = a.key[i], before = i ? a.key[i - 1] : 0u;
-    if (i == 0 || k != before) {
-      if (t < 0 || k > last) enter_table(k);
-      // rows of a table without a cache are one set
-      const bool head = i == 0 || before < base || (cached && div_by(k - base, magic) != div_by(before - base, magic));
-      f.w[0] = head ? (1ull | 1ull << 32) : 1ull;
-    }
-    return f;
+    const uint32_t f = head(i == 0, a.key[i], i ? a.key[i - 1] : 0u);
+    return V{{(f & 1u) | (u64)(f >> 1) << 32}};
+  }
+  __device__ uint32_t sorted_at(uint32_t p, int32_t bag) const {
+    const bool inside = a.dtypes == 1 || (a.dtypes == 3 && a.tm[div_by((uint32_t)bag, a.bags_magic)].dtype == 0);
+    return inside ? a.within(p, bag) : a.position(p, bag);
+  }
+  // distinct row u, whose first lookup is the i-th; set_head: the first of the v-th touched set
+  __device__ void write_row(uint32_t k, int i, uint32_t u, bool set_head, uint32_t v) const {
+    if (t < 0 || k < base || k > last) enter_table_of(k);  // (the lane's next element may lie in the next table)
+    a.uniq_key[u] = k;
+    a.run_off[u] = i;
+    a.uniq_tab[u] = t;
+    if (set_head) a.touched[v] = make_uint2(cached ? set_base + div_by(k - base, magic) : kNoSet, u);
   }
   __device__ void emit(int i, int, const V &pre, const V &f) const {
     const uint32_t u = pre.lo(0) + f.lo(0) - 1u;
@@ -208,18 +217,8 @@ struct DedupPass {
     const uint32_t p = a.pos[i];
     const int32_t bag = a.bag_of(p);
     a.sorted_bag[i] = bag;
-    if (a.sorted_at) {
-      const bool inside = a.dtypes == 1 || (a.dtypes == 3 && a.tm[div_by((uint32_t)bag, a.bags_magic)].dtype == 0);
-      a.sorted_at[i] = inside ? a.within(p, bag) : a.position(p, bag);
-    }
-    if (f.lo(0)) {
-      const uint32_t k = a.key[i];
-      if (k < base || k > last) enter_table_of(k);  // (the lane's next element may lie in the next table)
-      a.uniq_key[u] = k;
-      a.run_off[u] = i;
-      a.uniq_tab[u] = t;
-      if (f.hi(0)) a.touched[pre.hi(0)] = make_uint2(cached ? set_base + div_by(k - base, magic) : kNoSet, u);
-    }
+    if (a.sorted_at) a.sorted_at[i] = sorted_at(p, bag);
+    if (f.lo(0)) write_row(a.key[i], i, u, f.hi(0) != 0, pre.hi(0));
   }
   __device__ void enter_table_of(uint32_t k) const {
     t = -1;
@@ -233,7 +232,6 @@ struct DedupPass {
     a.run_off[total.lo(0)] = n;
   }
 };
-typedef DedupPass<DedupArgs> DedupOp;
 
 // The plan of the tile kernel, from the heavy list (in table order; first_of_table[t] = position of table t's first entry,
 // first_of_table[T] = their number), by workgroups of the stage's last kernel:
@@ -412,7 +410,6 @@ struct StatusPass {
   mutable unsigned int evs, late;
   mutable u64 hit_lookups;
   mutable const TableLut *lut;  // null: the model has too many tables for it
-  __device__ bool prepare_count(TableLut &) const { return false; }
   __device__ bool prepare(TableLut &l) const {
     lut = a.T <= kLutTables ? &l : nullptr;
     if (lut) fill_lut(l, a.tm, a.T);
@@ -931,8 +928,8 @@ __device__ __forceinline__ void add_totals(BatchCounters *c, const Totals &t, co
 }
 
 // What the passes of the stage work on, of one batch.
-inline DedupArgs dedup_of(const TableMeta *tm, const Geometry &g, const BatchBuf &b, const uint32_t *sorted_keys, const uint32_t *sorted_pos) {
-  return DedupArgs{tm, g.T, sorted_keys, sorted_pos, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
+inline DedupArgs dedup_of(const TableMeta *tm, const Geometry &g, const BatchBuf &b) {
+  return DedupArgs{tm, g.T, b.bag_of_pos, b.cnt, g.within_bits, b.d_offsets,
                  b.maxp ? b.sorted_at : nullptr, g.dtypes, div_magic((uint32_t)b.batch), b.uid_sorted, b.sorted_bag, b.uniq_key, b.run_off,
                  b.uniq_tab, b.touched};
 }

@@ -1,0 +1,46 @@
+"""The sort of a kernel a pass at the sizes where it can go wrong: segments that begin and end anywhere in a tile or have no
+lookup, digits of every width, tiles of every size, slots that the sort adds up itself or has added up, and more lookups than
+the pass behind it has workgroups for.  Cache state and lists bit for bit against the oracle, values on its bars."""
+import pytest
+
+from paper_2305_01515_amd import synth
+from parity_util import run_parity
+
+pytestmark = pytest.mark.gpu
+T = synth.TableCfg
+
+
+def parity(tabs, batch, seed, steps=2):
+    run_parity(synth.WorkloadCfg("segments", tabs, batch=batch, ways=8, steps=steps, seed=seed, init_std=0.05, lr=0.05), steps=steps, order="early")
+
+
+@pytest.mark.parametrize("bits", [3, 8, 9, 10, 11, 12, 16, 20, 21, 22, 23])
+def test_digits_of_every_width(bits):
+    """one table whose keys have so many bits, then three side by side (a segment each: more than 2048 lookups a table)"""
+    one = [T((1 << bits) - 1, 4, synth.FP32, 0.9, "fixed", 3, cache_slots=8 * (1 << min(bits, 9)))]
+    parity(one, 2100, bits)
+    parity(one + [T(5, 4, synth.FP32, None, "fixed", 3, cache_slots=8), T(777, 4, synth.FP32, None, "fixed", 3)], 2100, bits)
+
+
+@pytest.mark.parametrize("batch", [1023, 1024, 1025, 2047, 2048, 2049, 4097])
+def test_segments_around_the_tiles(batch):
+    """tables of one, of two and of no lookup a bag; on average 2048 lookups a table from a batch of 2048 on"""
+    tabs = [T(3000, 4, synth.FP32, None, "fixed", 1, cache_slots=160), T(50, 4, synth.FP32, None, "fixed", 0, cache_slots=8),
+            T(900, 4, synth.FP32, 1.2, "fixed", 2, cache_slots=80), T(40, 4, synth.FP32, 1.0, "poisson", 1.0, 0, 9),
+            T(7, 4, synth.FP32, None, "fixed", 1, cache_slots=8)]
+    parity(tabs, batch, batch)
+
+
+@pytest.mark.parametrize("batch,pool", [(9000, 1), (9000, 3), (70000, 1)])
+def test_more_slots_than_the_sort_adds_up_itself(batch, pool):
+    parity([T(20011, 4, synth.FP32, 1.0, "fixed", pool, cache_slots=8 * 400)], batch, batch)
+
+
+@pytest.mark.parametrize("batch", [16384, 16385, 65536, 65537])
+def test_tiles_of_every_size(batch):
+    """32 lookups a bag: either side of 524288 and of 2097152 lookups, in two segments of unlike size"""
+    parity([T(60013, 4, synth.FP32, 1.1, "fixed", 30, cache_slots=8 * 2000), T(3001, 4, synth.FP32, None, "fixed", 2)], batch, batch, steps=1)
+
+
+def test_more_lookups_than_the_distinct_rows_pass_has_workgroups_for():
+    parity([T(900001, 4, synth.FP32, 0.8, "fixed", 128, cache_slots=8 * 20000)], 66000, 5, steps=1)
