@@ -76,3 +76,37 @@ def test_state_in_memory_that_kernels_cannot_write():
     assert (float(block[0]), block[378:].tolist()) == edges
     assert lib().tbe_destroy(h) == 0
     o.close()
+
+
+@pytest.mark.parametrize("second_level", [0, 2])
+def test_a_flush_writes_what_has_changed_since_the_last_one(second_level):
+    """rows looked up again between two flushes and rows that were not, all of them cached: the tables are current after every
+    flush, and only the rows of the batches in between have crossed the link"""
+    from oracle import Oracle
+    from paper_2305_01515_amd.tbe import TBE
+    from parity_util import compare_backing, make_backing
+    tabs = [T(400, 16, synth.FP32, None, "fixed", 4, cache_slots=480)]
+    cfg = synth.WorkloadCfg("dirty", tabs, batch=64, ways=8, steps=4, seed=2, init_std=0.05, lr=0.05)
+    Wn, Mn, Wp, Mp = make_backing(cfg)
+    o = Oracle(Wn, Mn, [480], 8, second_level_slots=[480 * second_level] if second_level else None)
+    g = TBE(Wp, Mp, [480], 8, 64, 256, second_level_factor=second_level)
+    off = torch.arange(0, 257, 4, dtype=torch.int64)
+    seen = 0
+    for step, rows in enumerate(([0, 400], [40, 90], None, [390, 400], [0, 400])):
+        if rows:
+            idx = torch.arange(256, dtype=torch.int64) % (rows[1] - rows[0]) + rows[0]
+            go = synth.grad_out(cfg, step + 1)
+            di, df, dg = idx.cuda(), off.cuda(), go.cuda()
+            g.forward(di, df)
+            g.backward_update(dg, cfg.lr, cfg.eps)
+            o.prefetch(idx.numpy(), off.numpy())
+            o.forward()
+            o.backward_update(go.numpy(), cfg.lr, cfg.eps)
+        o.flush()
+        g.flush()
+        compare_backing(cfg, Wn, Mn, Wp, Mp, f"flush {step}")
+        now = g.stats()["d2h_bytes"] - seen - 4 * 400 * (step + 1)
+        assert now == (64 * len(set(idx.tolist())) if rows else 0), step
+        seen += now
+    g.close()
+    o.close()
