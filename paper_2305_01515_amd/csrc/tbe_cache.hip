@@ -328,8 +328,8 @@ __global__ __launch_bounds__(kWave) void probe_kernel(ProbeArgs a, BatchCounters
 // dealt round robin over the XCDs wrote every line from eight L2s, in eight partial pieces: 260 MB of write
 // traffic for 31 MB of words.)
 //
-// The first workgroups plan the heavy rows (plan_heavy; `plan` of them, a multiple of the XCDs), which needs the same lists
-// and nothing of the location words.  One workgroup more (the last) ends the stage (add_totals).
+// The first workgroup ends the stage (add_totals), the next plan the heavy rows for the tile kernel (plan_heavy; `plan` of them, a
+// multiple of the XCDs), which needs the same lists and nothing of the location words.
 #ifndef TBE_FINALIZE_BLOCKS
 #define TBE_FINALIZE_BLOCKS 512  // a multiple of 8
 #endif
@@ -342,31 +342,33 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(int n, const u6
                                                                  const int64_t *__restrict__ offsets, int within_bits,
                                                                  Totals totals, const u64 *__restrict__ tally,
                                                                  int tally_waves, uint32_t *too_long, uint32_t *stage_err,
-                                                                 int32_t *refused, int plan,
+                                                                 int32_t *refused, int split, int plan,
                                                                  PlanArgs pa, BatchCounters *cnt) {
-  const bool last = blockIdx.x + 1 == gridDim.x;
-  if (last && threadIdx.x == 0) {
+  const bool totals_here = blockIdx.x == 0;  // (the next seven are there so that those behind them keep their XCDs)
+  const int id = (int)blockIdx.x - kXcds;
+  if (totals_here && threadIdx.x == 0) {
     *too_long = 0u;  // as the next batch expects them, whatever became of this one
     if (n == 0 && (int)*stage_err > cnt->err) cnt->err = (int)*stage_err;  // (no pass of the sort has; there is one workgroup)
     *stage_err = 0u;
     if (cnt->err && *refused == 0) *refused = cnt->err | kRefusedBefore;  // (read by a stage's first kernel alone)
   }
   if (cnt->err) return;
-  if (last) {
+  if (totals_here) {
     __shared__ TotalsLds<kFinalThreads> s;
-    add_totals(cnt, totals, tally, tally_waves, s);
+    add_totals(cnt, totals, tally, tally_waves, pa.heavy_sub, split, s);
     return;
   }
-  if ((int)blockIdx.x < plan) {
+  if (id < 0) return;
+  if (id < plan) {
     __shared__ PlanLds<kFinalThreads> s;
-    plan_heavy(blockIdx.x, plan, pa, s, cnt);
+    plan_heavy(id, plan, pa, s, cnt);
     return;
   }
   const bool packed = cnt->packed != 0;
   const uint32_t within_mask = (1u << within_bits) - 1u;
   constexpr int K = 4;  // lookups per thread and pass, a workgroup's width apart: their loads are in flight together
   int first, end, step;
-  xcd_span_of(blockIdx.x - plan, gridDim.x - 1 - plan, n, kFinalThreads * K, first, end, step);
+  xcd_span_of(id - plan, (int)gridDim.x - kXcds - plan, n, kFinalThreads * K, first, end, step);
   for (int i0 = first + threadIdx.x; i0 < end; i0 += step) {
     uint32_t u[K], p[K], w[K], at[K];
 #pragma unroll
@@ -394,10 +396,9 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
   const int n = (int)b.n;
   if (n == 0) {  // nothing but the end of the stage
     hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kFinalThreads), 0, s, 0, (const u64 *)sorted, b.uid_sorted, b.loc_u, b.run_off,
-                       b.loc, b.d_offsets, g.within_bits, totals, ss.tally, 0, ss.too_long, ss.stage_err, ss.refused, 0, PlanArgs{}, b.cnt);
+                       b.loc, b.d_offsets, g.within_bits, totals, ss.tally, 0, ss.too_long, ss.stage_err, ss.refused, kHeavySplit, 0, PlanArgs{}, b.cnt);
     return hipGetLastError();
   }
-  const bool small = small_batch(g, n, b.batch);
   auto dedup = n <= 131072 ? launch_dedup<2, true> : n <= 2097152 ? launch_dedup<4, true>
                : n <= kScanBlocks * kScanThreads * 16 ? launch_dedup<8, true> : launch_dedup<4, false>;
   dedup(dedup_of(tm, g, b), sorted, n, ss, b.k, b.cnt, s);
@@ -408,14 +409,13 @@ hipError_t launch_dedup_probe(const TableMeta *tm, const Geometry &g, const Batc
                      : (lfu ? probe_kernel<true, false> : probe_kernel<false, false>);
   hipLaunchKernelGGL(probe, dim3(probe_blocks), dim3(kWave), 0, s, probe_of(tm, g, b, tags, ts, freq, l2, lock), b.cnt);
   const int tally_waves = run_compaction(StatusOp{status_of(tm, g, b, l2, stale, ss.tally)}, &b.cnt->n_uniq, 0, n, ss, 1, b.k, b.cnt, s) * kScanWavesPerBlock;
-  // (max pooling takes heavy rows a workgroup each and needs no plan, nor do batches that do the same; 64 or 256 workgroups
-  // look for the ranges' starts)
-  const int plan = b.maxp || long_rows_in_rest(n, g.win_stride) ? 0 : (g.T + (small ? 64 : 256) + kXcds - 1) / kXcds * kXcds;
-  // a multiple of the XCDs, no more than have a pass to do, and the one that ends the stage
+  // (only the tile kernel needs a plan; 256 workgroups look for the ranges' starts)
+  const int plan = b.maxp || long_rows_in_rest(n) ? 0 : (g.T + 256 + kXcds - 1) / kXcds * kXcds;
+  // a multiple of the XCDs, no more than have a pass to do
   int final_blocks = (n + 4 * kFinalThreads - 1) / (4 * kFinalThreads);
   final_blocks = final_blocks > TBE_FINALIZE_BLOCKS ? TBE_FINALIZE_BLOCKS : (final_blocks + kXcds - 1) / kXcds * kXcds;
-  hipLaunchKernelGGL(finalize_kernel, dim3(plan + final_blocks + 1), dim3(kFinalThreads), 0, s, n, (const u64 *)sorted, b.uid_sorted, b.loc_u,
-                     b.run_off, b.loc, b.d_offsets, g.within_bits, totals, ss.tally, tally_waves, ss.too_long, ss.stage_err, ss.refused, plan,
+  hipLaunchKernelGGL(finalize_kernel, dim3(kXcds + plan + final_blocks), dim3(kFinalThreads), 0, s, n, (const u64 *)sorted, b.uid_sorted, b.loc_u,
+                     b.run_off, b.loc, b.d_offsets, g.within_bits, totals, ss.tally, tally_waves, ss.too_long, ss.stage_err, ss.refused, heavy_split(n, b.maxp), plan,
                      plan_of(tm, g, b), b.cnt);
   return hipGetLastError();
 }

@@ -11,6 +11,7 @@ namespace tbe {
 
 template <int DT> struct Elems { static constexpr int n = DT == 0 ? 4 : 8; };
 
+typedef unsigned long long u64;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // 16 bytes of a row that the backward reads once and writes once: non-temporal accesses, so that
@@ -767,6 +768,88 @@ __device__ __forceinline__ void update_long_rows(int blk, int blocks, const Tabl
   }
 }
 
+// Sum and mean pooling, small batches: a workgroup per entry of the heavy list, in the launch of the rest of the backward.  A row's
+// entries (heavy_parts) take a stretch of its lookups each: a row with one entry is updated by its workgroup, of one with several
+// every workgroup leaves its sum in the entry's slot of `partials` and counts itself in, and the one that finds all the others in
+// adds them up in the order of the groups and updates the row.  (The sums pass the L2s by, both ways, instead of fences, which write an
+// XCD's whole L2 back.)
+template <int DT, int G, int MODE>
+__device__ __forceinline__ void update_long_parts(int blk, int blocks, const TableMeta *__restrict__ tm, int cls, int B, int sum_dim,
+                                                  const int32_t *__restrict__ heavy, const int32_t *__restrict__ heavy_sub, int32_t *harrive,
+                                                  const uint32_t *__restrict__ uniq_key, const int32_t *__restrict__ uniq_tab,
+                                                  const int32_t *__restrict__ run_off, const int32_t *__restrict__ loc_u,
+                                                  const int32_t *__restrict__ sorted_bag, const float *__restrict__ grad_out,
+                                                  float *partials, int pstride, float lr, float eps, char *__restrict__ ovf,
+                                                  uint32_t ovf_stride, const int32_t *__restrict__ table_class,
+                                                  const float *__restrict__ inv_len, const BatchCounters *cnt) {
+  constexpr int EPL = Elems<DT>::n;
+  constexpr int NG = 256 / G;
+  __shared__ float part[NG][G * EPL + 1];
+  __shared__ int s_last;
+  const int n_heavy = cnt->n_heavy;
+  const int lig = threadIdx.x % G, grp = threadIdx.x / G;
+  auto add_groups = [&](float (&g)[EPL]) {  // the groups' sums, in the first group
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EPL; e++) part[grp][lig * EPL + e] = g[e];
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int e = 0; e < EPL; e++) {
+        float sum = 0.f;
+        for (int q = 0; q < NG; q++) sum += part[q][lig * EPL + e];
+        g[e] = sum;
+      }
+    }
+  };
+  int first, end, step;
+  xcd_span_of(blk, blocks, n_heavy, 1, first, end, step);  // the list is in table order
+  for (int it = first; it < end; it += step) {
+    const int u = heavy[it], t = uniq_tab[u];
+    if (table_class[t] != cls) continue;  // uniform over the block
+    const int sub = heavy_sub[it], p = sub & 0xFFFF, parts = sub >> 16;
+    const TableMeta &m = tm[t];
+    const bool active = lig * EPL < m.dim;
+    const int i0 = run_off[u], i1 = run_off[u + 1], chunks = (i1 - i0 + G - 1) / G;
+    const int from = i0 + (int)((int64_t)chunks * p / parts) * G, to = min(i1, i0 + (int)((int64_t)chunks * (p + 1) / parts) * G);
+    float g[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; e++) g[e] = 0.f;
+    [[clang::always_inline]] reduce_grads<DT, G, MODE>(g, grad_out + m.col + lig * EPL, sorted_bag, t * B, sum_dim, from, to, grp, NG, lig,
+                                                       active, inv_len, Winners{}, 0);
+    add_groups(g);
+    if (parts > 1) {
+      u64 *slots = (u64 *)(partials + (size_t)(it - p) * pstride) + lig * EPL / 2;  // of the row's first entry
+      if (grp == 0) {
+#pragma unroll
+        for (int e = 0; e < EPL; e += 2)
+          __hip_atomic_store(slots + (size_t)p * pstride / 2 + e / 2, __float_as_uint(g[e]) | (u64)__float_as_uint(g[e + 1]) << 32,
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the sum is out before this entry is counted in
+        if (lig == 0) s_last = __hip_atomic_fetch_add(harrive + (it - p), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+      }
+      __syncthreads();
+      if (!s_last) continue;
+      if (threadIdx.x == 0) harrive[it - p] = 0;  // as the next batch expects it
+#pragma unroll
+      for (int e = 0; e < EPL; e++) g[e] = 0.f;
+      for (int q0 = grp; q0 < parts; q0 += 4 * NG) {
+        u64 v[4][EPL / 2];
+#pragma unroll
+        for (int x = 0; x < 4; x++)
+#pragma unroll
+          for (int e = 0; e < EPL / 2; e++) v[x][e] = q0 + x * NG < parts ? look(slots + (size_t)(q0 + x * NG) * pstride / 2 + e) : 0ull;
+#pragma unroll
+        for (int x = 0; x < 4; x++)
+#pragma unroll
+          for (int e = 0; e < EPL; e++) g[e] += __uint_as_float((uint32_t)(v[x][e / 2] >> (e & 1) * 32));
+      }
+      add_groups(g);
+    }
+    if (grp == 0) update_row<DT, G>(m, uniq_key[u], loc_u[u], ovf, ovf_stride, g, lr, eps, lig, active);
+  }
+}
+
 // Under max pooling the long rows of 16 lanes and more share the launch of the rest of the backward, the hot ones have their own
 // in front of it (so a batch has as many launches as with one for all long rows, and the few hot rows' chains are all that the
 // rest has to wait for).
@@ -1187,7 +1270,7 @@ __global__ __launch_bounds__(kHeavyThreads) void backward_heavy_kernel(const Tab
 // sums of one row from which its parts are added up side by side (128: the hot rows of a heterogeneous model pay
 // for the fences beside the other streams, its backward 4.6 -> 5.0 ms; 2048: a chain of 2047 sums takes 0.2 ms)
 constexpr int kCombineChain = 512;
-template <int DT, int G, int kCombineLoads>
+template <int DT, int G>
 __device__ inline void combine_heavy_rows(int blk, int blocks, const TableMeta *__restrict__ tm, int cls,
                                                                const int32_t *__restrict__ heavy,
                                                                const int32_t *__restrict__ heavy_sub,
@@ -1202,6 +1285,7 @@ __device__ inline void combine_heavy_rows(int blk, int blocks, const TableMeta *
                                                                const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
   constexpr int NG = 256 / G;
+  constexpr int kCombineLoads = 8;
   const int n_heavy = cnt->n_heavy;
   const int R = cnt->h_ranges;
   const int lig = threadIdx.x % G, grp = threadIdx.x / G;
@@ -1269,13 +1353,12 @@ __device__ inline void combine_heavy_rows(int blk, int blocks, const TableMeta *
   }
 }
 
-// The rest of the backward: workgroups [0, combine) add up the heavy rows' partial sums, the next `single` take the bags'
-// single-lookup rows, the last the rows with 2..kLongRun lookups.  The three touch disjoint rows, so any of SECT can share a
-// launch: a small batch's backward, bound by launches, is the heavy rows' kernel and this one, where it was four; with more
-// lookups the combine, whose partial sums in flight cost the others two of seven wavefronts per SIMD, keeps a launch of its
-// own (with eight sums in flight instead of four: a chain of 500 sums 0.049 instead of 0.059 ms).  Small
-// configuration: combine, single-lookup and short rows 7 + 9 + 11 -> 11 us a step; 16 x 500k resident rows: single-lookup
-// and short rows 242 -> 235 us.
+// The rest of the backward: workgroups [0, combine) take the heavy rows -- add up the tile kernel's partial sums, or (kBwdLong) a
+// workgroup for every entry -- the next `single` take the bags' single-lookup rows, the last the rows with 2..kLongRun lookups.
+// The three touch disjoint rows, so any of SECT can share a launch: a small batch's backward, bound by launches, is this one
+// (four, then two: 4 tables of 100 k rows 27, 24, now 12 us); with more lookups the heavy rows, whose registers cost the others one or
+// two of seven wavefronts per SIMD, keep a launch of their own (the combine with eight sums in flight instead of four: a chain of
+// 500 sums 0.049 instead of 0.059 ms).  16 x 500k resident rows: single-lookup and short rows 242 -> 235 us in one launch.
 template <int DT, int G, int MODE, int SECT>
 __global__ __launch_bounds__(256) void backward_rest_kernel(int combine, int single, int blocks_per_table, int n_tables,
                                                             const TableMeta *__restrict__ tm,
@@ -1288,11 +1371,11 @@ __global__ __launch_bounds__(256) void backward_rest_kernel(int combine, int sin
   int blk = blockIdx.x;
   if (blk < combine) {
     if constexpr (MODE != kMax && (SECT & kBwdLong))
-      update_long_rows<DT, G, MODE, 4, false>(blk, combine, tm, cls, B, sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off,
-                                              b.loc_u, b.sorted_bag, grad_out, lr, eps, b.ovf, ovf_stride, table_class,
-                                              MODE == kMean ? b.inv_len : nullptr, Winners{}, b.cnt);
+      update_long_parts<DT, G, MODE>(blk, combine, tm, cls, B, sum_dim, b.heavy, b.heavy_sub, b.harrive, b.uniq_key, b.uniq_tab, b.run_off,
+                                     b.loc_u, b.sorted_bag, grad_out, partials, pstride, lr, eps, b.ovf, ovf_stride, table_class,
+                                     MODE == kMean ? b.inv_len : nullptr, b.cnt);
     if constexpr (MODE != kMax && (SECT & kBwdCombine))
-      combine_heavy_rows<DT, G, SECT == kBwdCombine ? 8 : 4>(blk, combine, tm, cls, b.heavy, b.heavy_sub, b.harrive, b.uniq_key, b.uniq_tab, b.loc_u, partials,
+      combine_heavy_rows<DT, G>(blk, combine, tm, cls, b.heavy, b.heavy_sub, b.harrive, b.uniq_key, b.uniq_tab, b.loc_u, partials,
                                 pstride, lr, eps, b.ovf, ovf_stride, table_class, b.cnt);
     if constexpr (MODE == kMax && kLongInRest<G>)
       update_long_rows<DT, G, MODE, 4, false>(blk, combine, tm, cls, B, sum_dim, b.heavy, b.heavy_sub, b.uniq_key, b.uniq_tab, b.run_off,
@@ -1352,14 +1435,14 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
   // what its bookkeeping in LDS is sized for, take the workgroup-per-row kernel, as max pooling does.
   constexpr bool kTiled = G >= 4;
   const bool tiled = kTiled && !b.maxp;
-  const int64_t most_heavy = b.n / (kLongRun + 1) + b.n / kHeavySplit;  // entries of the heavy list
+  const int64_t most_heavy = b.n / (kLongRun + 1) + b.n / heavy_split(b.n, b.maxp);  // entries of the heavy list
   const Winners wins{b.wins, g.win_stride, b.argpos, b.sorted_at};
-  const bool long_rows = !b.maxp && long_rows_in_rest(b.n, G);
+  const bool long_rows = !b.maxp && long_rows_in_rest(b.n);
   if (which & kBwdHeavy) {
     if (most_heavy == 0 || long_rows) return;
     if (tiled) {
       if constexpr (kTiled)
-        hipLaunchKernelGGL((backward_heavy_kernel<DT, G>), dim3(b.n <= kSmallLookups ? 256 : 1024), dim3(kHeavyThreads), 0, s, tm,
+        hipLaunchKernelGGL((backward_heavy_kernel<DT, G>), dim3(1024), dim3(kHeavyThreads), 0, s, tm,
                            cls, b.batch, g.sum_dim, b.hchunks, b.heavy, b.heavy_sub, b.hperm, b.hstart, b.run_off, b.sorted_bag,
                            grad_out, partials, g.partial_stride, table_class, b.mean ? b.inv_len : nullptr, b.cnt);
     } else if (b.maxp && kLongInRest<G> && b.n <= hot_row<DT, G>()) {
@@ -1379,7 +1462,7 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
   }
   const int per = 256 / G;  // lane groups of a workgroup
   const int blocks_per_table = (b.batch + per - 1) / per;
-  const int combine = (which & kBwdCombine) && long_rows ? work_blocks(most_heavy, 1, 4096)
+  const int combine = (which & kBwdCombine) && long_rows ? work_blocks(most_heavy, 1, 1024)
                       : (which & kBwdCombine) && tiled ? work_blocks(most_heavy, per, 2048)
                       : (which & kBwdShort) && b.maxp && kLongInRest<G> ? work_blocks(most_heavy, 1, 4096) : 0;
   const int shrt = (which & kBwdShort) ? work_blocks(b.n / 2, per, 4096) : 0;
@@ -1402,8 +1485,7 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
                            : (b.mean ? backward_rest_kernel<DT, G, kMean, kRows | kBwdLong> : backward_rest_kernel<DT, G, kSum, kRows | kBwdLong>))
               : !rows ? (b.mean ? backward_rest_kernel<DT, G, kMean, kBwdCombine> : backward_rest_kernel<DT, G, kSum, kBwdCombine>)
               : b.maxp ? backward_rest_kernel<DT, G, kMax, kRows>
-              : combine ? (b.mean ? backward_rest_kernel<DT, G, kMean, kRows | kBwdCombine> : backward_rest_kernel<DT, G, kSum, kRows | kBwdCombine>)
-                        : (b.mean ? backward_rest_kernel<DT, G, kMean, kRows> : backward_rest_kernel<DT, G, kSum, kRows>);
+                       : (b.mean ? backward_rest_kernel<DT, G, kMean, kRows> : backward_rest_kernel<DT, G, kSum, kRows>);
   hipLaunchKernelGGL(kern, dim3(combine + single + shrt), dim3(256), 0, s, combine, single, blocks_per_table, count, tm, tables, cls,
                      b.batch, g.sum_dim, b, grad_out, partials, g.partial_stride, lr, eps, g.ovf_stride, table_class,
                      g.win_stride);

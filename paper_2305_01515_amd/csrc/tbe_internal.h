@@ -10,7 +10,8 @@ constexpr uint32_t kNoSet = 0xFFFFFFFFu;  // global set id of rows of a table wi
 // Backward work classes by the number of lookups a distinct row has in the batch:
 //   1            : updated bag by bag (the gradient is the bag's), flagged in the location word
 //   2..kLongRun  : one lane group per row, gradient rows gathered per lookup
-//   above        : "heavy" rows.  The table's gradient slice is streamed through LDS tile by tile, once per
+//   above        : "heavy" rows.  In all but the largest batches a workgroup for each entry of a row in the heavy list, gradient
+//                  rows gathered per lookup (long_rows_in_rest); else the table's gradient slice is streamed through LDS, once per
 //                  (chunk of up to heavy_chunk_rows of the table's heavy rows, bag range),
 //                  and every lane group adds up, from LDS, the lookups of its rows that fall into the tile;
 //                  the partial sums of a row, one per bag range, are added up by the combine kernel.
@@ -111,6 +112,7 @@ struct BatchCounters {
   // the gather of the bag ids after the sort; 0 = a bag is too long for that, the payload is the
   // lookup's position and the bag comes from bag_of_pos
   int32_t packed;
+  int32_t n_long;     // rows with more than kLongRun lookups, one with several times kHeavySplit counted as often (what the caller is told)
 };
 
 // Arrays of one batch; three of these rotate: batch k+1 is prepared while batch k trains, and
@@ -309,8 +311,7 @@ struct ClassInfo {
 };
 
 // Batches of few lookups, which are bound by launches and by the latency of dependent kernels, not by bytes: their stage runs
-// beside training behind the last commit (prefetch_behind_training), the plan of the heavy rows has fewer workgroups, and the
-// backward is the tile kernel and one launch for everything else.
+// beside training behind the last commit (prefetch_behind_training), and the backward is one launch.
 constexpr int64_t kSmallLookups = 524288, kSmallBags = 65536;
 constexpr int kMaxSortPasses = 4;
 constexpr int kScanBlocks = 2048;  // workgroups of a compaction pass, at most
@@ -499,15 +500,25 @@ struct OneCtl {
   unsigned long long said[2 * kOneItems];  // [2 words][kOneItems] counts of the pass that writes lists
 };
 
-// Sum and mean pooling, heavy rows of small batches: a workgroup each, in the launch of the rest of the backward, instead of
-// the tile kernel's launch in front of it (which reads the gradient rows of a bag range once for all heavy rows, in tiles, and
-// takes 28 us with the launch behind it however few they are).  A workgroup reads its row's gradients one after the other, n x
-// lanes / 1024 deep (lanes: 4 at least) for a row with all n lookups of the batch.  The backward in us, here / with the tile kernel,
-// n x lanes = 65536, rows of 4, 16, 64 lanes of fp32: the lookups spread over five rows 15, 12, 11 / 40, 28, 28, over sixteen 10, 9,
-// 11 / 30, 28, 29, by a power law 16, 12, 11 / 49, 28, 28; all in one row 41, 29, 26 / 32, 37, 27 (16 and 64 lanes of binary16
-// 36, 34 / 42, 29).  At 131072 five rows 22, 17, 17 / 32, 28, 28 and one row 74, 52, 46 / 34, 29, 27.  (The line is where a table
-// of one row loses 9 us at most.)
-inline bool long_rows_in_rest(int64_t n, int lanes) { return n * (lanes < 4 ? 4 : lanes) <= 65536; }
+// Sum and mean pooling, heavy rows of batches that are not among the largest: a workgroup for each of their entries in the heavy
+// list, in the launch of the rest of the backward (up to kSmallLookups) or one behind it, instead of the tile kernel's launch, which
+// reads the gradient rows of a bag range once for all heavy rows, in tiles, and the one that adds up its sums.  A tile is read
+// whatever few heavy rows look at it, and a workgroup that reads a lookup's gradient row from L2 has no other to wait for.
+// The backward alone, us, tile kernel / entries, one table of 50 k rows of 64 fp32, 32 lookups a bag, lookups by a power law, on a
+// hundred rows, evenly on all: 65536 lookups 52, 31, 17 / 14, 11, 14; 524288 83, 67, 26 / 31, 21, 22; 2097152 159, 76, 97 / 97, 64, 97;
+// rows of 256 fp32, 262144 103, 60, 50 / 43, 37, 44, 2097152 1197, 291, 367 / 398, 266, 367; rows of 8 fp32, all lookups on five rows
+// 524288 279 / 18.  Eight tables, 2097152 lookups, 128 binary16: 156, 75, 120 / 119, 81, 120.  Behind the line the lookups' gradient rows
+// at L2 cost more than the tiles: 7.9 M lookups on 32 x 1M rows of 128 binary16, whole backward, 463 / 536, 3.9 M on 16 x 500k 246 / 250.
+// (Slower below it only where all lookups are on a hundred rows a table: 8 tables, 1 M, 8 fp32 23 / 37, one table, 2 M, 128 binary16 105 / 135.)
+constexpr int64_t kLongLookups = 2097152;
+inline bool long_rows_in_rest(int64_t n) { return n <= kLongLookups; }
+// Lookups of a heavy row from which it has one entry more: a workgroup's share, or what would hold up a lane group of the tile
+// kernel.  Entries of 256 / 512 / 1024 lookups, 256 fp32, us: 8192 lookups on one row 14 / 19 / 28, 65536 on five 16 / 20 / 30, 524288 on
+// one 106 / 69 / 55 (the sums of a row's entries are one workgroup's to add up).
+inline int heavy_split(int64_t n, bool maxp) {
+  return maxp || !long_rows_in_rest(n) ? kHeavySplit : n <= 32768 ? 256 : n <= 262144 ? 512 : 1024;
+}
+
 
 // ---- launchers (each enqueues on `s` and returns the HIP status of the launch) ----
 
@@ -571,7 +582,7 @@ hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, cons
 // pooling), kBwdSingle (rows with one lookup), kBwdShort (rows with 2..kLongRun lookups, under max pooling also the other long
 // rows) in one launch
 constexpr int kBwdHeavy = 1, kBwdCombine = 2, kBwdSingle = 4, kBwdShort = 8;
-constexpr int kBwdLong = 16;  // (of the kernel, see long_rows_in_rest: the heavy rows, a workgroup each, in the combine's place)
+constexpr int kBwdLong = 16;  // (of the kernel, see long_rows_in_rest: the heavy rows, a workgroup for each entry, in the combine's place)
 hipError_t launch_backward_classes(int which, const TableMeta *tm, const ClassInfo &ci, const Geometry &g,
                                    const BatchBuf &b, const float *grad_out, float *partials, float lr, float eps,
                                    hipStream_t s);
@@ -598,9 +609,9 @@ __host__ __device__ inline int heavy_ranges(int n_hchunks, int n_heavy, long lon
 // `lanes` lanes of 16 bytes (4 fp32 or 8 fp16 elements each).
 __host__ __device__ inline int heavy_chunk_rows(int lanes, int dtype) { return kHeavyThreads / lanes * heavy_rows_per_group(dtype); }
 // parts a heavy row of `len` lookups is split into
-__host__ __device__ inline int heavy_parts(int len) {
-  const int p = (len + kHeavySplit - 1) / kHeavySplit;
-  return p < 1 ? 1 : (p > kHeavyMaxParts ? kHeavyMaxParts : p);
+__host__ __device__ inline int heavy_parts(int len, int split) {
+  const int p = (len + split - 1) / split, most = split < kHeavySplit ? 0x7FFF : kHeavyMaxParts;
+  return p < 1 ? 1 : (p > most ? most : p);
 }
 // first bag of bag range `range` of R over a batch of B bags per table (the ranges are equal to within one bag, so
 // that the workgroups of the tile kernel, one per (chunk, range), have equal shares of the lookups)
@@ -671,7 +682,7 @@ constexpr int kPolls = TBE_POLLS;
 
 // The batch's counters as its stage finds them; err: of a batch before it that was refused.
 __device__ inline void begin_counters(BatchCounters *c, int32_t err) {
-  c->n_uniq = c->n_touched = c->n_ins = c->n_byp = c->n_heavy = 0;
+  c->n_uniq = c->n_touched = c->n_ins = c->n_byp = c->n_heavy = c->n_long = 0;
   c->err = err;
   c->n_mid = c->n_hchunks = 0;
   c->h_ranges = 1;

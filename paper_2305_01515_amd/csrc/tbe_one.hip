@@ -44,14 +44,13 @@ struct OneStage {
   DedupArgs dedup;            // (its keys and payloads are not used)
   ProbeArgs probe;
   StatusArgs status;
-  PlanArgs plan;
   Totals totals;
   const u64 *tally;
   const uint32_t *uid_sorted;
   const int32_t *loc_u, *run_off;
   uint32_t *loc;
   BatchCounters *cnt;
-  int probe_items, list_items, plan_items, loc_items;
+  int probe_items, list_items, loc_items;
   int first[kOnePhases + 1];  // first ticket of every phase; behind the last one their number
 };
 
@@ -96,7 +95,6 @@ union OneLds {
   TileLds tile;
   ListLds<OneStatus> status;
   ProbeLds<L2, kOneProbeSets> probe[kOneWaves];
-  PlanLds<kOneThreads> plan;
   TotalsLds<kOneThreads> totals;
 };
 
@@ -332,33 +330,20 @@ __device__ __forceinline__ void locations(const OneStage &a, int item, int items
   }
 }
 
-// The end of the stage: the totals by its first item, the plan of the heavy rows, the location words.
+// The end of the stage: the totals by its first item, the location words.  (Heavy rows need no plan, see long_rows_in_rest.)
 template <bool L2>
 __device__ __forceinline__ void end_phase(const OneStage &a, OneLds<L2> &s, int item, uint32_t err) {
   const int tid = my_thread();
   if (item == 0) {
     if (tid < 2 * kOneItems) a.ctl->said[tid] = 0ull;
     if (err == 0) {
-      add_totals(a.cnt, a.totals, a.tally, a.list_items * kOneWaves, s.totals);
+      add_totals(a.cnt, a.totals, a.tally, a.list_items * kOneWaves, a.status.heavy_sub, a.status.heavy_split, s.totals);
     } else if (tid == 0) {  // (what this batch's own fault is stays below that of a batch before it)
       a.cnt->err = (int32_t)err;
       if (*a.refused == 0) *a.refused = (int32_t)err | kRefusedBefore;  // (later items of this launch know of it from ctl->err)
     }
-  } else if (item <= a.plan_items) {
-    if (err == 0 && a.cnt->n_heavy) {
-      const int tables = min(a.T, max(1, a.plan_items / 2));  // items that order tables' entries; the others look for the ranges' starts
-      const int other = a.plan_items - tables;
-      if (item <= tables) {
-        for (int t = item - 1; t < a.T; t += tables) {
-          plan_heavy(t, a.T + other, a.plan, s.plan, a.cnt);
-          __syncthreads();
-        }
-      } else {
-        plan_heavy(a.T + item - 1 - tables, a.T + other, a.plan, s.plan, a.cnt);
-      }
-    }
   } else {
-    if (err == 0) locations(a, item - 1 - a.plan_items, a.loc_items);
+    if (err == 0) locations(a, item - 1, a.loc_items);
   }
 }
 
@@ -485,7 +470,6 @@ hipError_t launch_one_kernel_stage(const TableMeta *tm, const Geometry &g, const
   a.dedup = dedup_of(tm, g, b);
   a.probe = probe_of(tm, g, b, tags, ts, freq, l2, lock);
   a.status = status_of(tm, g, b, l2, stale, ss.tally);
-  a.plan = plan_of(tm, g, b);
   a.totals = totals;
   a.tally = ss.tally;
   a.sorted_pos = (uint32_t *)ss.pairs[0];
@@ -498,9 +482,9 @@ hipError_t launch_one_kernel_stage(const TableMeta *tm, const Geometry &g, const
   a.probe_items = wgs;
   a.probe.min_windows = probe_min_windows(g, wgs * kOneWaves);
   a.list_items = (n + kOneThreads - 1) / kOneThreads;
-  a.plan_items = b.maxp || n <= kLongRun || long_rows_in_rest(n, g.win_stride) ? 0 : wgs < 8 ? 2 : 8;  // (see finalize_kernel)
   a.loc_items = a.list_items;
-  const int items[kOnePhases] = {1, a.probe_items, a.list_items, 1 + a.plan_items + a.loc_items};
+  static_assert(kOneLookups <= kLongLookups, "no plan of the heavy rows");
+  const int items[kOnePhases] = {1, a.probe_items, a.list_items, 1 + a.loc_items};
   for (int p = 0; p < kOnePhases; p++) a.first[p + 1] = a.first[p] + items[p];
   auto kern = l2.on ? (lfu ? one_stage_kernel<true, true> : one_stage_kernel<false, true>)
                     : (lfu ? one_stage_kernel<true, false> : one_stage_kernel<false, false>);

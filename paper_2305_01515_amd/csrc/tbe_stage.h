@@ -397,6 +397,7 @@ struct StatusArgs {
   char **ins_dst, **l2v_src, **l2v_dst;
   uint32_t *l2v_key;
   u64 *tally;
+  int heavy_split;
 };
 template <class Args>
 struct StatusPass {
@@ -480,7 +481,7 @@ struct StatusPass {
     const uint8_t s = a.status[u];
     const int len = a.run_off[u + 1] - a.run_off[u];
     f.w[0] = s == ST_INSERT ? 1ull : s == ST_BYPASS ? (1ull << 32) : 0ull;
-    f.w[1] = len > kLongRun ? (u64)heavy_parts(len) << 32 : len >= 2 ? 1ull : 0ull;
+    f.w[1] = len > kLongRun ? (u64)heavy_parts(len, a.heavy_split) << 32 : len >= 2 ? 1ull : 0ull;
     return f;
   }
   __device__ void emit(int u, int, const V &pre, const V &f) const {
@@ -893,22 +894,44 @@ __device__ __forceinline__ void probe_windows(const ProbeArgs &a, ProbeLds<L2, S
 
 // Completes the batch's counters -- evictions, lookups that hit and late rows from the per-wavefront sums of the status pass,
 // hits as what is left of the distinct rows -- and adds them to the running totals.  By one workgroup.
+// heavy_sub, split: the heavy list's parts and what makes one; a row counts as often as it would be entered by kHeavySplit.
 template <int THREADS>
 struct TotalsLds {
   u64 e[THREADS / kWave], l[THREADS / kWave], t[THREADS / kWave];
+  int longs;
 };
 template <int THREADS>
-__device__ __forceinline__ void add_totals(BatchCounters *c, const Totals &t, const u64 *tally, int tally_waves, TotalsLds<THREADS> &s) {
+__device__ __forceinline__ void add_totals(BatchCounters *c, const Totals &t, const u64 *tally, int tally_waves, const int32_t *heavy_sub,
+                                           int split, TotalsLds<THREADS> &s) {
   constexpr int kFinalThreads = THREADS;
   auto &s_e = s.e; auto &s_l = s.l; auto &s_t = s.t;
+  const int n_heavy = c->n_heavy, per = kHeavySplit / split;
+  if (threadIdx.x == 0) s.longs = 0;
   u64 e = 0, l = 0, late = 0;
+#pragma unroll 4
   for (int w = threadIdx.x; w < tally_waves; w += kFinalThreads) { e += tally[3 * w]; l += tally[3 * w + 1]; late += tally[3 * w + 2]; }
   for (int d = 32; d >= 1; d >>= 1) { e += __shfl_xor(e, d); l += __shfl_xor(l, d); late += __shfl_xor(late, d); }
   if ((threadIdx.x & 63) == 0) { s_e[threadIdx.x >> 6] = e; s_l[threadIdx.x >> 6] = l; s_t[threadIdx.x >> 6] = late; }
   __syncthreads();
+  if (per > 1 && n_heavy) {
+    int longs = 0;
+    for (int h0 = threadIdx.x; h0 < n_heavy; h0 += 8 * kFinalThreads) {
+      int sub[8];
+#pragma unroll
+      for (int q = 0; q < 8; q++) sub[q] = h0 + q * kFinalThreads < n_heavy ? heavy_sub[h0 + q * kFinalThreads] : 1;
+#pragma unroll
+      for (int q = 0; q < 8; q++) {
+        const int parts = ((sub[q] >> 16) + per - 1) / per;
+        if (!(sub[q] & 0xFFFF)) longs += parts < kHeavyMaxParts ? parts : kHeavyMaxParts;
+      }
+    }
+    if (longs) atomicAdd(&s.longs, longs);
+    __syncthreads();
+  }
   if (threadIdx.x != 0) return;
   e = l = late = 0;
   for (int w = 0; w < kFinalThreads / 64; w++) { e += s_e[w]; l += s_l[w]; late += s_t[w]; }
+  c->n_long = per > 1 ? s.longs : n_heavy;
   c->hits = (u64)(c->n_uniq - c->n_ins - c->n_byp);
   c->evictions = e;
   c->hit_lookups = l;
@@ -945,7 +968,7 @@ inline StatusArgs status_of(const TableMeta *tm, const Geometry &g, const BatchB
                   b.byp_idx, b.byp_tab, b.byp_key, b.byp_src, b.byp_where, b.byp_taken, stale, b.loc_u, b.mid_idx, b.heavy, b.heavy_sub, b.hfirst,
                   l2.on ? b.src2 : nullptr, l2.on ? b.dst2 : nullptr, l2.on ? b.evict2 : nullptr,
                   l2.on ? b.ins_dst : nullptr, l2.on ? b.l2v_src : nullptr, l2.on ? b.l2v_dst : nullptr,
-                  l2.on ? b.l2v_key : nullptr, tally};
+                  l2.on ? b.l2v_key : nullptr, tally, heavy_split(b.n, b.maxp)};
 }
 inline PlanArgs plan_of(const TableMeta *tm, const Geometry &g, const BatchBuf &b) {
   return PlanArgs{tm, g.T, b.batch, b.hfirst, b.heavy, b.heavy_sub, b.uniq_tab, b.run_off, b.sorted_bag, b.hchunks, b.hperm, b.hstart,

@@ -1,5 +1,5 @@
-"""Heavy rows (more than 64 lookups) of small batches: a workgroup each in the launch of the rest of the backward up to a number
-of lookups that depends on the rows' lanes, the tile kernel (or a launch of their own, for narrow rows) beyond."""
+"""Heavy rows (more than 64 lookups): a workgroup for each of a row's entries in the launch of the rest of the backward, or in one
+behind it, up to 2097152 lookups, the tile kernel (or a launch of their own, for narrow rows) beyond."""
 import pytest
 
 from paper_2305_01515_amd import synth
@@ -22,8 +22,27 @@ def test_either_side_of_the_line(dim, dtype, bags, pooling):
 
 
 def test_widths_on_both_sides_in_one_model():
-    """2048 lookups: rows of 64 lanes take the tile kernel, the others share the rest's launch"""
+    """rows of 64, 2 and 4 lanes side by side"""
     tabs = [T(4, 256, synth.FP32, 1.0, "fixed", 4, cache_slots=2), T(9, 8, synth.FP32, None, "fixed", 2, cache_slots=4),
             T(300, 32, synth.FP16, 1.2, "poisson", 2, 0, 9, cache_slots=64)]
     st = run_parity(synth.WorkloadCfg("widths", tabs, batch=256, ways=2, steps=4, seed=2, init_std=0.05, lr=0.05), steps=4, order="inline")
     assert st["last_long_rows"] > 0
+
+
+@pytest.mark.parametrize("pooling", ["sum", "mean"])
+@pytest.mark.parametrize("dim,dtype", [(4, synth.FP32), (20, synth.FP32), (256, synth.FP32), (128, synth.FP16)])
+@pytest.mark.parametrize("n", [255, 256, 257, 512, 2049, 32768, 32769, 60000, 262145])
+def test_rows_of_one_and_of_many_entries(n, dim, dtype, pooling):
+    """a row with all n lookups of its table (an entry for every 256, 512 or 1024 of them), beside rows with none or one entry"""
+    tabs = [T(1, dim, dtype, None, "fixed", 1, cache_slots=2), T(60, dim, dtype, 1.3, "fixed", 1, cache_slots=16)]
+    st = run_parity(synth.WorkloadCfg("entries", tabs, batch=n, ways=2, steps=2, seed=n, init_std=0.05, lr=0.05), steps=2, order="early",
+                    pooling=pooling)
+    assert st["last_long_rows"] >= min(64, (n + 2047) // 2048)
+
+
+@pytest.mark.parametrize("n", [524288, 524289, 2097152, 2097153])
+def test_either_side_of_the_larger_lines(n):
+    """the launch of their own, and the tile kernel: rows with a third of the lookups, some hundred and none"""
+    tabs = [T(3001, 32, synth.FP32, 1.4, "fixed", 1, cache_slots=2048)]
+    st = run_parity(synth.WorkloadCfg("lines", tabs, batch=n, ways=8, steps=1, seed=3, init_std=0.05, lr=0.05), steps=1, order="early")
+    assert st["last_long_rows"] > 100
