@@ -381,7 +381,7 @@ StaleRows stale_rows(const tbe_ctx *h, const BatchBuf &b, int bi) {
 hipError_t launch_stage(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
   const bool lfu = h->policy == TBE_POLICY_LFU;
   const StaleRows stale = stale_rows(h, b, bi);
-  const Totals totals{h->d_total, h->d_bytes + 2, h->l2.on ? h->d_l2tot : nullptr};
+  const Totals totals{h->d_total, h->d_bytes + 2, h->l2.on ? h->d_l2tot : nullptr, h->l2.sums};
   if (one_kernel_batch(h->g, h->l2.on, h->as == h->cs, b.n, b.batch))
     return launch_one_kernel_stage(h->d_tm, h->g, b, h->ss, h->tags, h->ts, h->freq, lfu, h->l2, h->deep, stale, totals, s);
   hipError_t e = launch_keygen(h->d_tm, h->g, b, h->ss, s);
@@ -1151,6 +1151,8 @@ int tbe_enable_second_level(tbe_handle h, int32_t factor) {
   }
   HIP_TRY(h, h->mem.get(&l2.wb2_dst, 8 * M));
   HIP_TRY(h, hipMemset(l2.wb2_dst, 0, 8 * M ? 8 * M : 8));
+  HIP_TRY(h, h->mem.get(&l2.sums, 4 * kL2Sums * kL2Line));
+  HIP_TRY(h, hipMemset(l2.sums, 0, 4 * kL2Sums * kL2Line));
   HIP_TRY(h, h->mem.get(&h->d_l2tot, 8 * 4));
   HIP_TRY(h, hipMemset(h->d_l2tot, 0, 8 * 4));
   for (int i = 0; i < h->nbuf; i++) {

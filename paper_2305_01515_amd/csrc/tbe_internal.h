@@ -234,11 +234,15 @@ struct Staging {
 // and the staging of the rows it evicts: such a row is read into `out2` by the transfer of
 // the batch that pushes it out and written to the lower tier by the next transfer, exactly
 // like a first-level victim parked in Staging::out; its map code is kWhereParked | (max_inserts + i).
+constexpr int kL2Sums = 64, kL2Line = 32;
+static_assert(kL2Sums == kWave, "a lane each adds them up");
 struct Level2 {
   bool on = false;
   int32_t factor = 0;
   int64_t total_slots2 = 0;
   int32_t *tags2 = nullptr, *ts2 = nullptr;
+  int32_t *sums = nullptr;  // [kL2Sums * kL2Line] what the probe's wavefronts add to the batch's four counters, a line each
+                            //   (0 between batches)
   char *out2[2] = {nullptr, nullptr};  // [max_inserts * stride] each, by batch parity
   char **wb2_dst = nullptr;            // [max_inserts] lower-tier row of each staged second-level victim
   const char *lines_lo = nullptr, *lines_hi = nullptr;  // address range of the second-level lines (pinned host memory)
@@ -279,6 +283,7 @@ struct StaleRows {
 struct Totals {
   BatchCounters *sum;
   unsigned long long *n, *l2;
+  int32_t *l2_sums;
 };
 
 struct Geometry {
