@@ -318,7 +318,8 @@ int order_after(tbe_ctx *h, hipStream_t from, hipStream_t to) {
 
 // The transfer of batch `b`, whose stage stream `s` has been given, on b.link.  Write-back of the previous batch's victims and
 // fetch-ahead of this batch's rows share the host link; neither touches a cache line, so a batch in flight is not disturbed.
-int enqueue_transfer(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
+// `swap`: its commit in the same launch (enqueue_commit then has nothing to launch).
+int enqueue_transfer(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s, bool swap = false) {
   if (b.link != s) {  // (covers the transfers that `s` has had)
     HIP_TRY(h, hipEventRecord(h->ev_probed[bi], s));
     HIP_TRY(h, hipStreamWaitEvent(b.link, h->ev_probed[bi], 0));
@@ -327,6 +328,11 @@ int enqueue_transfer(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
     if (rc) return rc;
   }
   h->link_s = b.link;
+  if (swap) {
+    HIP_TRY(h, launch_swap(h->d_tm, b, b.prev_bi >= 0 ? &h->buf[b.prev_bi] : nullptr, h->parked, h->st, h->l2, h->di, h->throttle,
+                           h->d_rb, h->d_bytes, h->d_bytes + 1, b.link));
+    return TBE_OK;
+  }
   StageTimer tm_(h, TBE_STAGE_FILL, b.link);
   HIP_TRY(h, launch_transfer(&b, h->parked, h->st, h->l2, h->di, h->throttle, b.k, h->d_rb, h->d_bytes, h->d_bytes + 1, b.link));
   return TBE_OK;
@@ -334,10 +340,10 @@ int enqueue_transfer(tbe_ctx *h, const BatchBuf &b, int bi, hipStream_t s) {
 
 // Victims of batch `bi` to the staging area, its new rows into the cache lines; then the
 // batch is ready for forward.  Must follow the update of the batch before it.
-int enqueue_commit(tbe_ctx *h, int bi, bool wb_prev) {
+int enqueue_commit(tbe_ctx *h, int bi, bool wb_prev, bool swapped = false) {
   BatchBuf &b = h->buf[bi];
   const int64_t prev_n = b.prev_bi >= 0 ? h->buf[b.prev_bi].n : 0;
-  {
+  if (!swapped) {
     StageTimer tm_(h, TBE_STAGE_COMMIT, b.link);
     const int prev_mode = !wb_prev ? kPrevKeep : b.parks_prev ? kPrevPark : kPrevWrite;
     HIP_TRY(h, launch_commit(h->d_tm, b, b.prev_bi >= 0 ? &h->buf[b.prev_bi] : nullptr, prev_mode, h->st, h->l2, h->d_rb,
@@ -524,16 +530,17 @@ int do_prefetch(tbe_ctx *h, const int64_t *d_indices, const int64_t *d_offsets, 
     StageTimer tm_(h, TBE_STAGE_PREFETCH, stage_s);
     HIP_TRY(h, launch_stage(h, b, bi, stage_s));
   }
-  rc = enqueue_transfer(h, b, bi, stage_s);
-  if (rc) return rc;
   b.prev_bi = h->prev_buf;
+  const bool swap = !in_flight && !h->profiling && n <= kSwapLookups;
+  rc = enqueue_transfer(h, b, bi, stage_s, swap);
+  if (rc) return rc;
   h->prev_buf = bi;
   h->pend[h->n_pend++] = bi;
   if (in_flight) {
     h->deferred = bi;  // its cache lines may still be in use: commit after that batch's update
     return TBE_OK;
   }
-  return enqueue_commit(h, bi, false);
+  return enqueue_commit(h, bi, false, swap);
 }
 
 }  // namespace

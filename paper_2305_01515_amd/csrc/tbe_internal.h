@@ -559,6 +559,15 @@ constexpr int kPrevKeep = 0, kPrevWrite = 1, kPrevPark = 2;
 hipError_t launch_commit(const TableMeta *tm, const BatchBuf &b, const BatchBuf *prev, int prev_mode, const Staging &st,
                          const Level2 &l2, const uint32_t *rb_of_table, unsigned long long *bytes_d2h, bool deep,
                          hipStream_t s);
+// Transfer and commit of a batch, with none in flight in front of it, in one launch (prev_mode: kPrevKeep)?  That spares a launch and
+// the 2 us between two kernels of a chain that the forward waits for; but the transfer kernel's own workgroups keep the link busier.
+// Us a step on the compute stream, two launches / one: no row cached, 1000 rows of 64 bytes to 1 KB 57 / 55, 4000 80..83 / 77..80,
+// 16000 of 64 bytes, 256 bytes and 1 KB 140, 182, 453 / 129, 186, 455, 64000 334, 584, 2069 / 338, 603, 2080; a third cached, 16000
+// and 64000 of 256 bytes 68, 94 / 67, 94.
+constexpr int64_t kSwapLookups = 8192;
+hipError_t launch_swap(const TableMeta *tm, const BatchBuf &b, const BatchBuf *prev, int64_t parked, const Staging &st, const Level2 &l2,
+                       const DeferredInit &di, const Throttle &th, const uint32_t *rb_of_table, unsigned long long *bytes_h2d,
+                       unsigned long long *bytes_d2h, hipStream_t s);
 // ---- pipeline several batches deep (Section 5.7) ----
 // The overflow copies of every batch buffer, by buffer number.
 struct OverflowCopies {

@@ -39,6 +39,7 @@ typedef unsigned long long u64;
   } while (0)
 constexpr int kLinkBlocks = 192;   // workgroups of the smaller kernels that write to the host link
 constexpr int kLinkThreads = 1024;
+constexpr int kSwapThreads = 256, kSwapBlocks = 192;
 // Workgroups of `threads` for `rows` rows of `lanes` lanes, a row to each lane group, but no more than `most`: those of a small
 // batch that find nothing to do cost it time to be dealt out (the commit of 119 lookups as 4096 workgroups 4.8 us, as two 3).
 static int row_blocks(int64_t rows, int lanes, int threads, int most) {
@@ -115,28 +116,18 @@ __device__ inline void copy_row(char *dst, const char *src, uint32_t bytes, int 
   for (uint32_t c = lig * 16; c < bytes; c += L * 16) *(uint4 *)(dst + c) = *(const uint4 *)(src + c);
 }
 
+// Rows between the host link and the staging areas: what transfer_kernel and swap_kernel share.
 template <int L>
-__global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, const BatchCounters *cnt,
-                                                       char *const *__restrict__ ins_src,
-                                                       const int32_t *__restrict__ ins_tab,
-                                                       const uint32_t *__restrict__ rb_of_table,
-                                                       const uint32_t *__restrict__ ins_where,
-                                                       char *const *__restrict__ byp_src,
-                                                       const int32_t *__restrict__ byp_tab,
-                                                       const uint32_t *__restrict__ byp_where, char *__restrict__ ovf,
-                                                       char *const *__restrict__ l2v_src,
-                                                       char *const *__restrict__ wb2_dst, char *out2_even,
-                                                       char *out2_odd, int k, const TableMeta *__restrict__ di_tm,
-                                                       u64 di_seed, float di_std,
-                                                       const uint32_t *__restrict__ ins_key,
-                                                       const uint32_t *__restrict__ byp_key, u64 *bytes_h2d,
-                                                       u64 *bytes_d2h, const char *l2_lo, const char *l2_hi,
-                                                       int pauses) {
-  // Waves that wait on the host link slow the memory accesses of every wave that shares their CU,
-  // so this kernel keeps its CUs to itself: a workgroup of 16 wavefronts that claims 128 vector
-  // registers per lane fills the register files of a CU's four SIMDs, and no wave of another
-  // kernel is placed beside it (the clobber makes the compiler allocate up to v127).
-  asm volatile("" ::: "v127");
+__device__ __forceinline__ void transfer_rows(const Staging &st, const BatchCounters *cnt, char *const *__restrict__ ins_src,
+                                              const int32_t *__restrict__ ins_tab, const uint32_t *__restrict__ rb_of_table,
+                                              const uint32_t *__restrict__ ins_where, char *const *__restrict__ byp_src,
+                                              const int32_t *__restrict__ byp_tab, const uint32_t *__restrict__ byp_where,
+                                              char *__restrict__ ovf, char *const *__restrict__ l2v_src,
+                                              char *const *wb2_dst, char *out2_even, char *out2_odd, int k,
+                                              const TableMeta *__restrict__ di_tm, u64 di_seed, float di_std,
+                                              const uint32_t *__restrict__ ins_key, const uint32_t *__restrict__ byp_key,
+                                              u64 *bytes_h2d, u64 *bytes_d2h, const char *l2_lo, const char *l2_hi,
+                                              int pauses) {
   const int bid = blockIdx.x, n_blocks = gridDim.x;
   const int n_wb = *st.wb_n;
   const int n_ins = (cnt && cnt->err == 0) ? cnt->n_ins : 0;
@@ -273,6 +264,33 @@ __global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, cons
     if (in_b) atomicAdd(bytes_h2d, in_b);
     if (out_b) atomicAdd(bytes_d2h, out_b);
   }
+}
+
+template <int L>
+__global__ __launch_bounds__(kLinkThreads) void transfer_kernel(Staging st, const BatchCounters *cnt,
+                                                       char *const *__restrict__ ins_src,
+                                                       const int32_t *__restrict__ ins_tab,
+                                                       const uint32_t *__restrict__ rb_of_table,
+                                                       const uint32_t *__restrict__ ins_where,
+                                                       char *const *__restrict__ byp_src,
+                                                       const int32_t *__restrict__ byp_tab,
+                                                       const uint32_t *__restrict__ byp_where, char *__restrict__ ovf,
+                                                       char *const *__restrict__ l2v_src,
+                                                       char *const *__restrict__ wb2_dst, char *out2_even,
+                                                       char *out2_odd, int k, const TableMeta *__restrict__ di_tm,
+                                                       u64 di_seed, float di_std,
+                                                       const uint32_t *__restrict__ ins_key,
+                                                       const uint32_t *__restrict__ byp_key, u64 *bytes_h2d,
+                                                       u64 *bytes_d2h, const char *l2_lo, const char *l2_hi,
+                                                       int pauses) {
+  // Waves that wait on the host link slow the memory accesses of every wave that shares their CU,
+  // so this kernel keeps its CUs to itself: a workgroup of 16 wavefronts that claims 128 vector
+  // registers per lane fills the register files of a CU's four SIMDs, and no wave of another
+  // kernel is placed beside it (the clobber makes the compiler allocate up to v127).
+  asm volatile("" ::: "v127");
+  transfer_rows<L>(st, cnt, ins_src, ins_tab, rb_of_table, ins_where, byp_src, byp_tab, byp_where, ovf, l2v_src, wb2_dst,
+                   out2_even, out2_odd, k, di_tm, di_seed, di_std, ins_key, byp_key, bytes_h2d, bytes_d2h, l2_lo, l2_hi,
+                   pauses);
   // The last workgroup through empties the list of parked victims (every other one has read its length long before).
   __syncthreads();
   if (threadIdx.x == 0 && atomicInc((unsigned int *)&st.wb_n[2], gridDim.x - 1) == gridDim.x - 1) st.wb_n[0] = 0;
@@ -357,25 +375,19 @@ hipError_t launch_fixup(const TableMeta *tm, const BatchBuf &b, const OverflowCo
 // parked behind this batch's victims for the next transfer to write them (kPrevPark): the link's
 // write direction then carries them beside that transfer's fetches, which costs the transfer a
 // hundredth of its time, instead of alone between two transfers.
-template <bool DEEP, int L>
-__global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict__ tm, Staging st,
-                                                     const BatchCounters *cnt, const int32_t *__restrict__ ins_tab,
-                                                     const uint32_t *__restrict__ ins_where,
-                                                     const int32_t *__restrict__ ins_slot,
-                                                     const int32_t *__restrict__ ins_old,
-                                                     const int32_t *__restrict__ byp_tab,
-                                                     const uint32_t *__restrict__ byp_where, char *__restrict__ ovf,
-                                                     const BatchCounters *prev_cnt,
-                                                     char *const *__restrict__ prev_byp_src,
-                                                     const int32_t *__restrict__ prev_byp_tab,
-                                                     const uint8_t *__restrict__ prev_byp_taken,
-                                                     const char *__restrict__ prev_ovf, int wb_prev, int k,
-                                                     char *const *__restrict__ ins_dst,
-                                                     char *const *__restrict__ l2v_src,
-                                                     char *const *__restrict__ l2v_dst, char **wb2_dst,
-                                                     const char *__restrict__ out2_prev,
-                                                     const uint32_t *__restrict__ rb_of_table,
-                                                     const uint32_t *__restrict__ ins_key, u64 *bytes_d2h) {
+template <bool DEEP, bool LIST, int L>
+__device__ __forceinline__ void commit_rows(const TableMeta *__restrict__ tm, const Staging &st, const BatchCounters *cnt,
+                                            const int32_t *__restrict__ ins_tab, const uint32_t *__restrict__ ins_where,
+                                            const int32_t *__restrict__ ins_slot, const int32_t *__restrict__ ins_old,
+                                            const int32_t *__restrict__ byp_tab, const uint32_t *__restrict__ byp_where,
+                                            char *__restrict__ ovf, const BatchCounters *prev_cnt,
+                                            char *const *__restrict__ prev_byp_src, const int32_t *__restrict__ prev_byp_tab,
+                                            const uint8_t *__restrict__ prev_byp_taken, const char *__restrict__ prev_ovf,
+                                            int wb_prev, int k, char *const *__restrict__ ins_dst,
+                                            char *const *__restrict__ l2v_src, char *const *__restrict__ l2v_dst,
+                                            char **wb2_dst, const char *__restrict__ out2_prev,
+                                            const uint32_t *__restrict__ rb_of_table, const uint32_t *__restrict__ ins_key,
+                                            u64 *bytes_d2h) {
   constexpr bool deep = DEEP;  // pipeline several batches deep (an instance of its own: the one-deep pipeline's commit
                                // is on the critical path of every step and keeps its code as it was)
   const uint32_t M = (uint32_t)st.max_inserts;  // map codes kWhereParked | (M + i): rows staged in out2
@@ -401,7 +413,7 @@ __global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict
   }
   const int n_ins = cnt->n_ins, n_byp = cnt->n_byp;
   const int par = k & 1, ppar = par ^ 1;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (LIST && blockIdx.x == 0 && threadIdx.x == 0) {
     st.wb_n[0] = n_ins + (wb_prev == kPrevPark ? n_prev : 0);
     st.wb_n[1] = par;
   }
@@ -481,6 +493,74 @@ __global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict
   if ((threadIdx.x & 63) == 0 && out_b) atomicAdd(bytes_d2h, out_b);
 }
 
+template <bool DEEP, int L>
+__global__ __launch_bounds__(256) void commit_kernel(const TableMeta *__restrict__ tm, Staging st,
+                                                     const BatchCounters *cnt, const int32_t *__restrict__ ins_tab,
+                                                     const uint32_t *__restrict__ ins_where,
+                                                     const int32_t *__restrict__ ins_slot,
+                                                     const int32_t *__restrict__ ins_old,
+                                                     const int32_t *__restrict__ byp_tab,
+                                                     const uint32_t *__restrict__ byp_where, char *__restrict__ ovf,
+                                                     const BatchCounters *prev_cnt,
+                                                     char *const *__restrict__ prev_byp_src,
+                                                     const int32_t *__restrict__ prev_byp_tab,
+                                                     const uint8_t *__restrict__ prev_byp_taken,
+                                                     const char *__restrict__ prev_ovf, int wb_prev, int k,
+                                                     char *const *__restrict__ ins_dst,
+                                                     char *const *__restrict__ l2v_src,
+                                                     char *const *__restrict__ l2v_dst, char **wb2_dst,
+                                                     const char *__restrict__ out2_prev,
+                                                     const uint32_t *__restrict__ rb_of_table,
+                                                     const uint32_t *__restrict__ ins_key, u64 *bytes_d2h) {
+  commit_rows<DEEP, true, L>(tm, st, cnt, ins_tab, ins_where, ins_slot, ins_old, byp_tab, byp_where, ovf, prev_cnt,
+                             prev_byp_src, prev_byp_tab, prev_byp_taken, prev_ovf, wb_prev, k, ins_dst, l2v_src, l2v_dst,
+                             wb2_dst, out2_prev, rb_of_table, ins_key, bytes_d2h);
+}
+
+// Transfer and commit in one launch, for a batch that was prefetched with none in flight: its commit need not wait for an update.
+// Small batches only, bound by the latency of one trip over the link and by launches: 92 lookups 62.5 -> 58.0 us a step, 18 and 51
+// 48.5 -> 46.2 and 47.3 -> 45.0.  A lane group handles the same items in both parts, so what it fetched (st.in), the parked victim it wrote
+// home and that victim's slot in the list are its own.  The groups need not wait for one another: the transfer part touches no cache
+// line, reads the victims of the batch before (out[par ^ 1], which the commit part only reads), the list's slots i and i + n, n >=
+// n_ins (the commit part writes slots i < n_ins, each after its group has read it), and the second level's lines, which no commit
+// touches; rows pushed out of the second level go to out2[par], late ones come from out2[par ^ 1].  No workgroup of 1024 threads
+// with a CU to itself: nothing of the library's runs beside it, and 192 of 256 threads are as many wavefronts.
+template <int L>
+__global__ __launch_bounds__(kSwapThreads) void swap_kernel(Staging st, const BatchCounters *cnt,
+                                                            char *const *__restrict__ ins_src,
+                                                            const int32_t *__restrict__ ins_tab,
+                                                            const uint32_t *__restrict__ rb_of_table,
+                                                            const uint32_t *__restrict__ ins_where,
+                                                            char *const *__restrict__ byp_src,
+                                                            const int32_t *__restrict__ byp_tab,
+                                                            const uint32_t *__restrict__ byp_where, char *__restrict__ ovf,
+                                                            char *const *__restrict__ l2v_src, char **wb2_dst,
+                                                            char *out2_even, char *out2_odd, int k,
+                                                            const TableMeta *__restrict__ di_tm, u64 di_seed, float di_std,
+                                                            const uint32_t *__restrict__ ins_key,
+                                                            const uint32_t *__restrict__ byp_key, u64 *bytes_h2d,
+                                                            u64 *bytes_d2h, const char *l2_lo, const char *l2_hi, int pauses,
+                                                            const TableMeta *__restrict__ tm,
+                                                            const int32_t *__restrict__ ins_slot,
+                                                            const int32_t *__restrict__ ins_old,
+                                                            const char *__restrict__ prev_ovf,
+                                                            char *const *__restrict__ ins_dst,
+                                                            char *const *__restrict__ l2v_dst,
+                                                            const char *__restrict__ out2_prev) {
+  transfer_rows<L>(st, cnt, ins_src, ins_tab, rb_of_table, ins_where, byp_src, byp_tab, byp_where, ovf, l2v_src, wb2_dst,
+                   out2_even, out2_odd, k, di_tm, di_seed, di_std, ins_key, byp_key, bytes_h2d, bytes_d2h, l2_lo, l2_hi,
+                   pauses);
+  commit_rows<false, false, L>(tm, st, cnt, ins_tab, ins_where, ins_slot, ins_old, byp_tab, byp_where, ovf, nullptr, nullptr,
+                               nullptr, nullptr, prev_ovf, kPrevKeep, k, ins_dst, l2v_src, l2v_dst, wb2_dst, out2_prev,
+                               rb_of_table, ins_key, bytes_d2h);
+  // The last workgroup through leaves the list of this batch's victims (every other one has read the old one's length).
+  __syncthreads();
+  if (threadIdx.x == 0 && atomicInc((unsigned int *)&st.wb_n[2], gridDim.x - 1) == gridDim.x - 1) {
+    st.wb_n[0] = cnt->err ? 0 : cnt->n_ins;
+    if (!cnt->err) st.wb_n[1] = k & 1;
+  }
+}
+
 template <int L>
 __global__ __launch_bounds__(256) void ovf_writeback_kernel(Staging st, const BatchCounters *cnt,
                                                             char *const *__restrict__ byp_src,
@@ -553,6 +633,18 @@ hipError_t launch_commit(const TableMeta *tm, const BatchBuf &b, const BatchBuf 
                      prev ? prev_mode : kPrevKeep, b.k, l2.on ? b.ins_dst : nullptr, l2.on ? b.l2v_src : nullptr,
                      l2.on ? b.l2v_dst : nullptr, l2.on ? l2.wb2_dst : nullptr, l2.out2[(b.k & 1) ^ 1], rb_of_table,
                      b.ins_key, bytes_d2h));
+  return hipGetLastError();
+}
+
+hipError_t launch_swap(const TableMeta *tm, const BatchBuf &b, const BatchBuf *prev, int64_t parked, const Staging &st, const Level2 &l2,
+                       const DeferredInit &di, const Throttle &th, const uint32_t *rb_of_table, u64 *bytes_h2d, u64 *bytes_d2h,
+                       hipStream_t s) {
+  const int64_t passes = std::max(b.n, (parked + 1) / 2);
+  TBE_BY_ROW_LANES(st.stride, hipLaunchKernelGGL((swap_kernel<L>), dim3(row_blocks(passes, L, kSwapThreads, kSwapBlocks)), dim3(kSwapThreads), 0, s, st, b.cnt, b.ins_src, b.ins_tab, rb_of_table, b.ins_where, b.byp_src, b.byp_tab, b.byp_where, b.ovf,
+                     l2.on ? b.l2v_src : nullptr, l2.on ? l2.wb2_dst : nullptr, l2.out2[0], l2.out2[1], b.k, di.tm, di.seed,
+                     di.std, b.ins_key, b.byp_key, bytes_h2d, bytes_d2h, l2.lines_lo, l2.lines_hi, th.pauses, tm, b.ins_slot,
+                     b.ins_old, prev ? prev->ovf : nullptr, l2.on ? b.ins_dst : nullptr, l2.on ? b.l2v_dst : nullptr,
+                     l2.out2[(b.k & 1) ^ 1]));
   return hipGetLastError();
 }
 
