@@ -350,14 +350,17 @@ inline DigitPlan digit_plan(int key_bits, int passes) {
 // (latency of a tile's chain: keys, ranks, counts said and heard, output), so a tile has as many keys as leave enough of them to
 // fill the chip.  Us a pass, tiles of 1024 / 2048 / 4096 / 8192 keys: 41 k lookups 7.8 / 8.8 / 9.7 / -, 90 k 10.5 / 11.7 / 13.5 / -,
 // 262 k - / 15.0 / 16.2 / -, 818 k - / - / 18.6 / 22.3, 3.9 M - / - / 39.7 / 32.2, 7.9 M - / - / 70 / 55.6.
-// Digits of 11 bits spare keys of 21 and 22 bits a pass, which pays where a pass is latency; 10.5 M lookups take two passes of
-// 120 us so and three by 8 bits 64 us each.
+// Digits of 10 bits at most: a tile hears the counts of every digit value from the key generation's slots and from the tiles before
+// it, so a pass by 11 bits, which would spare keys of 21 and 22 bits one of three, takes more than it saves.  Us for the passes, two
+// by 11 / three by 8, lookups of ten to 32 tables as one segment, 5 k, 15 k, 30 k, 60 k 22, 38, 48, 54 / 20, 25, 29, 32; of one table 8 k,
+// 40 k, 130 k, 260 k, 520 k, 1 M 27, 50, 37, 40, 60, 67 / 24, 30, 32, 37, 48, 60; 10.5 M 240 / 192.  Two by 10 pay: 20-bit keys, 8 k, 40 k,
+// 130 k, 260 k, 520 k, 1 M 18, 26, 27, 30, 42, 49 / 24, 30, 32, 36, 48, 60.
 // (Digits of 8 bits with a kernel that counts, one that scans and one that writes to a pass: 3.9 M lookups of 23 bits 115 us, now
 // 64; 7.9 M of 25 bits 207, now 111; 818 k 69, now 37.)
 constexpr int kLutTables = 512;  // models with more tables read the descriptions from memory in the passes of the stage
 constexpr int kSortThreads = 512;
 constexpr int64_t kTiles1k = 131072, kTiles2k = 524288, kTiles4k = 2097152;  // lookups up to which tiles have 1024, 2048, 4096 keys
-constexpr int64_t kWideDigits = 1048576;                                     // ... and digits 11 bits
+constexpr int kWidestDigit = 10;
 constexpr int64_t kSegmentLookups = 2048;                                    // lookups a table, on average, from which tables are segments
 constexpr int kSlotsHeard = 32;  // slots of a segment that the workgroups of the sort add up themselves
 constexpr uint32_t kLastTile = 0x80000000u;
@@ -375,8 +378,8 @@ inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch) {
   SortShape s{};
   s.segs = g.T > 1 && g.T <= kLutTables && n >= kSegmentLookups * g.T ? g.T : 1;
   s.bags = (int)((int64_t)g.T * batch / s.segs);
-  const int bits = s.segs > 1 ? g.seg_bits : g.key_bits, widest = n <= kWideDigits ? 11 : 10;
-  const int passes = (bits + widest - 1) / widest;
+  const int bits = s.segs > 1 ? g.seg_bits : g.key_bits;
+  const int passes = (bits + kWidestDigit - 1) / kWidestDigit;
   s.digits = digit_plan(bits, passes);
   s.rb = (bits + passes - 1) / passes;
   if (s.rb < 8) s.rb = 8;
@@ -393,8 +396,8 @@ inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch) {
 struct SortNeeds { int64_t said, tiles, slots; };  // words of tiles' counts, tiles, words of slots
 inline SortNeeds sort_needs(const Geometry &g, int64_t n, int32_t batch) {
   SortNeeds r{1, 1, 1};
-  // (a batch of fewer lookups can have more tiles, wider digits or, as one segment, more workgroups)
-  const int64_t steps[] = {n, kTiles1k, kTiles2k, kTiles4k, kWideDigits, kSegmentLookups * g.T - 1};
+  // (a batch of fewer lookups can have more tiles or, as one segment, more workgroups)
+  const int64_t steps[] = {n, kTiles1k, kTiles2k, kTiles4k, kSegmentLookups * g.T - 1};
   for (int64_t m : steps) {
     if (m > n || m < 1) continue;
     const SortShape s = sort_shape(g, m, batch);

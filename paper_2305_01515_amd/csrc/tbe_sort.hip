@@ -263,8 +263,8 @@ template <int RB, int ITEMS>
 __global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortPassArgs a) {
   constexpr int R = 1 << RB, kWords = R / 2;  // counts of two digit values to a word
   constexpr int kWaves = kSortThreads / kWave, kTile = kSortThreads * ITEMS;
-  constexpr int WPT = kWords > kSortThreads ? kWords / kSortThreads : 1;  // a thread's words: consecutive digit values
-  constexpr int D = 2 * WPT;
+  constexpr int D = 2;  // a thread's digit values: a word
+  static_assert(kWords <= kSortThreads, "a word a thread");
   __shared__ union {
     uint32_t cnt[kWaves][kWords];  // per wavefront and digit value: count, later the first place of its keys in the tile
     uint2 pairs[kTile];
@@ -316,33 +316,28 @@ __global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortPassArgs a)
     place[q] = __shfl(prev, leader) + below;
   }
   __syncthreads();
-  const bool mine = tid * WPT < kWords;  // this thread has digit values
+  const bool mine = tid < kWords;  // this thread has digit values
   uint32_t count[D] = {}, total[D] = {}, before[D] = {};
   // The tile's counts, or the sums up to it, for the tiles behind it, and the flag that says that they are there.  They are
   // written through to memory and have arrived when the flag is.
   auto say_counts = [&](const uint32_t (&c)[D], size_t at, u64 state) {
     if (mine)
-#pragma unroll
-      for (int x = 0; x < WPT; x++)
-        __hip_atomic_store((u64 *)(a.said + at + (size_t)blk * R + tid * D + 2 * x), c[2 * x] | (u64)c[2 * x + 1] << 32, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store((u64 *)(a.said + at + (size_t)blk * R + tid * D), c[0] | (u64)c[1] << 32, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) __hip_atomic_store(a.flags + blk, a.epoch << 2 | state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
   if (mine) {
+    uint32_t sum = 0;
 #pragma unroll
-    for (int x = 0; x < WPT; x++) {
-      uint32_t sum = 0;
-#pragma unroll
-      for (int w = 0; w < kWaves; w++) {
-        const uint32_t c = s.cnt[w][tid * WPT + x];
-        s.cnt[w][tid * WPT + x] = sum;
-        sum += c;
-      }
-      count[2 * x] = sum & 0xFFFFu;
-      count[2 * x + 1] = sum >> 16;
+    for (int w = 0; w < kWaves; w++) {
+      const uint32_t c = s.cnt[w][tid];
+      s.cnt[w][tid] = sum;
+      sum += c;
     }
+    count[0] = sum & 0xFFFFu;
+    count[1] = sum >> 16;
   }
   if (!(tile.z & kLastTile)) say_counts(count, tile.w ? 0 : a.sums_at, tile.w ? kSaidOwn : kSaidSum);
   if (mine) {
@@ -374,16 +369,11 @@ __global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortPassArgs a)
     uint32_t at = ci - c, to = tile.x - tile.w * (uint32_t)kTile + ti - t;  // (the segment begins tile.w tiles before this one)
     for (int w = 0; w < wave; w++) { at += s_wtot[0][w]; to += s_wtot[1][w]; }
     if (mine) {
+      const uint32_t at1 = at + count[0];
 #pragma unroll
-      for (int x = 0; x < WPT; x++) {
-        const uint32_t at1 = at + count[2 * x];
-#pragma unroll
-        for (int w = 0; w < kWaves; w++) s.cnt[w][tid * WPT + x] += at | at1 << 16;
-        out[2 * x] = to - at;
-        out[2 * x + 1] = to + total[2 * x] - at1;
-        at = at1 + count[2 * x + 1];
-        to += total[2 * x] + total[2 * x + 1];
-      }
+      for (int w = 0; w < kWaves; w++) s.cnt[w][tid] += at | at1 << 16;
+      out[0] = to - at;
+      out[1] = to + total[0] - at1;
     }
   }
   __syncthreads();
@@ -428,21 +418,17 @@ __global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortPassArgs a)
     if (mine) {
       const uint32_t *p = a.said + ((size_t)blk - done - 1) * R + tid * D;
       for (int t0 = 0; t0 < take; t0 += 8) {
-        u64 v[8][WPT];
+        u64 v[8];
 #pragma unroll
-        for (int q = 0; q < 8; q++)
+        for (int q = 0; q < 8; q++) {
+          const uint32_t *from = p - (size_t)(t0 + q) * R + (how == 1 && t0 + q + 1 == take ? a.sums_at : 0);
+          v[q] = t0 + q < take ? look((const u64 *)from) : 0ull;
+        }
 #pragma unroll
-          for (int x = 0; x < WPT; x++) {
-            const uint32_t *from = p - (size_t)(t0 + q) * R + 2 * x + (how == 1 && t0 + q + 1 == take ? a.sums_at : 0);
-            v[q][x] = t0 + q < take ? look((const u64 *)from) : 0ull;
-          }
-#pragma unroll
-        for (int q = 0; q < 8; q++)
-#pragma unroll
-          for (int x = 0; x < WPT; x++) {
-            before[2 * x] += (uint32_t)v[q][x];
-            before[2 * x + 1] += (uint32_t)(v[q][x] >> 32);
-          }
+        for (int q = 0; q < 8; q++) {
+          before[0] += (uint32_t)v[q];
+          before[1] += (uint32_t)(v[q] >> 32);
+        }
       }
     }
     done = how == 1 ? (int)tile.w : done + take;
@@ -486,7 +472,7 @@ hipError_t launch_sort(const TableMeta *tm, const Geometry &g, const BatchBuf &b
   const SortShape sh = sort_shape(g, b.n, b.batch);
   const int words = sh.digits.passes << sh.rb;
   auto kern = sh.rb == 8 ? sort_kernel_of<8>(sh.items) : sh.rb == 9 ? sort_kernel_of<9>(sh.items)
-              : sh.rb == 10 ? sort_kernel_of<10>(sh.items) : sort_kernel_of<11>(sh.items);
+              : sort_kernel_of<10>(sh.items);
   SortPassArgs a{};
   a.tiles = ss.tiles;
   a.n_slots = sh.add_slots ? 1 : sh.slots;
