@@ -384,10 +384,12 @@ inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch) {
   s.rb = (bits + passes - 1) / passes;
   if (s.rb < 8) s.rb = 8;
   s.items = n <= kTiles1k ? 2 : n <= kTiles2k ? 4 : n <= kTiles4k ? 8 : 16;
-  // A workgroup of the key generation takes 64 bags at a time.  Up to two rounds of them are left to kSlotsHeard workgroups, whose
-  // counts the sort can add up by itself; many more lookups are worth the addition's launch, 5 us.
+  // A workgroup of the key generation takes 64 bags at a time.  Up to four rounds of them are left to kSlotsHeard workgroups, whose
+  // counts the sort can add up by itself; many more lookups are worth the addition's launch, 5 us.  Us for keys, addition and two
+  // passes, 32 workgroups / one a round and the addition: 40 k lookups in 8000 bags 33 / 32, 21 k in 2100 25 / 25, 84 k 33 / 32, 96 k in
+  // 2400 30 / 30, 128 k in 8000 37 / 32, 210 k in 2100 44 / 41, 242 k in 4756 44 / 38, 320 k in 8000 51 / 40.
   const int64_t rounds = (s.bags + 63) / 64, most = 1024 / s.segs > kSlotsHeard ? 1024 / s.segs : kSlotsHeard;
-  s.slots = (int)(rounds < 1 ? 1 : rounds < 4 * kSlotsHeard && rounds > kSlotsHeard ? kSlotsHeard : rounds > most ? most : rounds);
+  s.slots = (int)(rounds < 1 ? 1 : rounds > kSlotsHeard && rounds < 4 * kSlotsHeard && n <= 65536 ? kSlotsHeard : rounds > most ? most : rounds);
   s.add_slots = s.slots > kSlotsHeard || (s.slots > 4 && n > 1000000);
   s.tiles = (int)((n + s.tile() - 1) / s.tile() + s.segs);
   return s;
@@ -409,14 +411,15 @@ inline SortNeeds sort_needs(const Geometry &g, int64_t n, int32_t batch) {
   return r;
 }
 
-// Batches of very few lookups: one kernel takes them through the whole prefetch stage (tbe_one.hip), which spares eight
-// launches (30 us of host time).  4096 lookups are what one workgroup sorts in its LDS: with several tiles, passes of the sort as
+// Batches of very few lookups: one kernel takes them through the whole prefetch stage (tbe_one.hip), which spares six
+// launches (22 us of host time).  4096 lookups are what one workgroup sorts in its LDS: with several tiles, passes of the sort as
 // phases of the same kernel, one XCD's 32 CUs are no longer enough for the probe (4 tables of 100 k rows, 40960 lookups: 150 us
 // a step instead of 127; 11 to 15 k lookups 1.04 to 1.26 times as long, 5 k equal).  Its one workgroup reads 512 bags at a time:
 // 3853 lookups in 3380 bags took 238 instead of 217 us in two steps, a few hundred bags are faster.  Us a step with one kernel /
-// with a kernel a pass, a third of the rows cached: beside training 500, 2000 and 4096 lookups 53, 66, 77 / 83, 83, 86; in a batch
-// that the forward prefetches, between a model of 24 small kernels on either side, 2000 and 4096 lookups 590, 595 / 616, 632, and
-// with no model, where the host is idle, 64, 77 / 61, 71.  On one stream for everything the kernels are all that counts: 1000, 2000
+// with a kernel a pass, a third of the rows cached: beside training 500, 2000, 3000 and 4096 lookups 60, 68, 74, 90 / 94, 94, 94, 95; in a
+// batch that the forward prefetches, where the host is idle, 52, 60, 68, 73 / 51, 58, 62, 63, no row cached 1000, 2000 and 4096 73, 101,
+// 149 / 80, 102, 139.  (With a kernel a pass in nine instead of seven launches, between a model of 24 small kernels on either side, 2000
+// and 4096 lookups 590, 595 / 616, 632: the host is busy, and the launches spared count.  So are the figures from here on.)  On one stream for everything the kernels are all that counts: 1000, 2000
 // and 4096 lookups 54, 62, 74 / 59, 60, 72 (sets of one way 65, 76, 102 / 69, 73, 89).
 // With a second level one XCD is short of wavefronts where the sets are few: 4096 lookups beside training in 625, 1250 and 1876
 // sets 118, 107, 71 / 101, 97, 99, 3000 in 1250 sets 81 / 95, 2000 in 625 sets 80 / 82.  With more tables than the passes keep
