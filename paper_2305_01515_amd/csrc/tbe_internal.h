@@ -387,9 +387,10 @@ inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch) {
   // A workgroup of the key generation takes 64 bags at a time.  Up to four rounds of them are left to kSlotsHeard workgroups, whose
   // counts the sort can add up by itself; many more lookups are worth the addition's launch, 5 us.  Us for keys, addition and two
   // passes, 32 workgroups / one a round and the addition: 40 k lookups in 8000 bags 33 / 32, 21 k in 2100 25 / 25, 84 k 33 / 32, 96 k in
-  // 2400 30 / 30, 128 k in 8000 37 / 32, 210 k in 2100 44 / 41, 242 k in 4756 44 / 38, 320 k in 8000 51 / 40.
+  // 2400 30 / 30, 128 k in 8000 37 / 32, 210 k in 2100 44 / 41, 242 k in 4756 44 / 38, 320 k in 8000 51 / 40; four tables, 252 k in 2100
+  // bags of each 32 / 31, 280 k in 7000 40 / 36, less what one launch more takes the host.  So from 131072 lookups a segment on.
   const int64_t rounds = (s.bags + 63) / 64, most = 1024 / s.segs > kSlotsHeard ? 1024 / s.segs : kSlotsHeard;
-  s.slots = (int)(rounds < 1 ? 1 : rounds > kSlotsHeard && rounds < 4 * kSlotsHeard && n <= 65536 ? kSlotsHeard : rounds > most ? most : rounds);
+  s.slots = (int)(rounds < 1 ? 1 : rounds > kSlotsHeard && rounds < 4 * kSlotsHeard && n <= (int64_t)kTiles1k * s.segs ? kSlotsHeard : rounds > most ? most : rounds);
   s.add_slots = s.slots > kSlotsHeard || (s.slots > 4 && n > 1000000);
   s.tiles = (int)((n + s.tile() - 1) / s.tile() + s.segs);
   return s;
