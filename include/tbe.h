@@ -178,7 +178,7 @@ int tbe_prefetch(tbe_handle h, const int64_t *d_indices, const int64_t *d_offset
  *       among equals), stamped k; what that way held is written to the backing tier; with no
  *       such way the row goes to the backing tier directly.  Entries stamped by the current
  *       batch or the one before are never replaced (their data may still be in flight).
- * tbe_flush also writes the second-level lines to the backing tier.  Values do not
+ * tbe_flush also writes every valid second-level line to the backing tier.  Values do not
  * depend on the hierarchy.  Only before the first tbe_prefetch (TBE_EORDER afterwards or when
  * called twice); allocates (TBE_ENOMEM / TBE_EHIP if that fails); TBE_EINVAL for a factor
  * outside 1..1024 or when no table has a first-level cache; TBE_ELIMIT when 2^31 slots or
@@ -387,8 +387,6 @@ int tbe_backward_update_static(tbe_handle h, const float *d_grad_out, float lr, 
 /*
  * Write every valid cache line and its accumulator to the backing tier (Section 5.5.4,
  * write-back) and wait for both streams: afterwards the host arrays hold the current model.
- * (Rows that are cached and that no batch has looked up since the last flush are there already
- * and are not written again; host_state is written whole.)
  * Tags and timestamps stay.  TBE_EORDER while a batch is prefetched or forwarded but not
  * updated.  Also reports errors the device found earlier: once the device has refused a batch
  * (TBE_EINVAL / TBE_ERANGE, which stick), tbe_flush drops that batch and any behind it, writes

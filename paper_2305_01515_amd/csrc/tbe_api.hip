@@ -139,7 +139,6 @@ struct tbe_ctx {
   bool never_bypasses = true;   // every table has a way for each of its rows
   hipEvent_t ev_inputs = nullptr, ev_ready[kMaxBatchBufs] = {}, ev_trained[kMaxBatchBufs] = {}, ev_probed[kMaxBatchBufs] = {};
   int64_t flush_state_bytes = 0;
-  int32_t flushed = 0;          // the last batch before the last flush
   bool inputs_ready = false;  // caller guarantees index / offset buffers are complete when tbe_prefetch is called
   int32_t max_batch = 0;
   int64_t max_lookups = 0;
@@ -1075,7 +1074,7 @@ int tbe_flush(tbe_handle h) {
   // Every copy in the backing tier is current now: the next batch must not take any row for one on its way (it would
   // make the transfer skip a write-back that has already happened, and the request would hit a later batch's victim).
   h->prev_buf = -1;
-  HIP_TRY(h, launch_flush(h->d_tm, h->g, h->tags, h->ts, h->flushed, h->l2, h->d_bytes, h->d_bytes + 1, h->cs));  // also slot accumulators -> dev_m
+  HIP_TRY(h, launch_flush(h->d_tm, h->g, h->tags, h->l2, h->d_bytes, h->d_bytes + 1, h->cs));  // also slot accumulators -> dev_m
   // A copy engine takes some 18 us per table, whatever its size, and 57 GB/s; a kernel writes all small tables' accumulators
   // in one launch (4 tables of 100 k rows: 29 instead of 72 us).  An array that is not pinned, which no kernel may write, is
   // copied whatever its size.
@@ -1089,7 +1088,6 @@ int tbe_flush(tbe_handle h) {
   // kernels as well and the counters fetched by a copy of their own behind them, 485 so.)
   rc = sync_all(h);
   if (rc) return rc;
-  h->flushed = h->k;
   return take_device_errors(h, h->host_counters);
 }
 

@@ -589,8 +589,7 @@ hipError_t launch_fixup(const TableMeta *tm, const BatchBuf &b, const OverflowCo
 // parked: how many overflow copies of the batch before, at most, b's commit parked and no transfer has written yet: they go first
 hipError_t launch_ovf_writeback(const BatchBuf &b, int64_t parked, const Staging &st, const uint32_t *rb_of_table,
                                 unsigned long long *bytes_d2h, hipStream_t s);
-// since: the last batch before the last flush (0: none yet); lines stamped by it or earlier are in the backing tier since then
-hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const int32_t *ts, int32_t since, const Level2 &l2,
+hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const Level2 &l2,
                         unsigned long long *bytes_h2d, unsigned long long *bytes_d2h, hipStream_t s);
 // after launch_flush: the counters of `buffers` batch buffers to pinned host memory, and the accumulators of the tables with flush_by_kernel (at most kFlushStateRows rows, pinned host array)
 constexpr int64_t kFlushStateRows = 262144;  // a megabyte: what the copy engine moves in the time it takes to start

@@ -648,21 +648,17 @@ hipError_t launch_swap(const TableMeta *tm, const BatchBuf &b, const BatchBuf *p
   return hipGetLastError();
 }
 
-// flush: every line that a batch has looked up since the last flush goes to the backing tier, its accumulator to those of all
-// rows (which the host code copies).  A line changes only when its batch trains, and a batch stamps all its lines, so those with
-// an older stamp are in the backing tier as the last flush left them.  Bound by the host link, one way: a checkpoint of 4 tables x
-// 100 k rows after every other step, 40 k lines valid, takes 175 us with all of them written and 130 so (and the whole pass 473 and 428).
+// flush: every valid line goes to the backing tier, its accumulator to those of all rows (which the host code copies)
 template <int L>
 __global__ __launch_bounds__(256) void flush_kernel(const TableMeta *__restrict__ tm, int T, int64_t total_slots,
-                                                    const int32_t *__restrict__ tags, const int32_t *__restrict__ ts, int32_t since,
-                                                    u64 *bytes_d2h) {
+                                                    const int32_t *__restrict__ tags, u64 *bytes_d2h) {
   const int64_t group = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / L;
   const int lig = threadIdx.x % L;
   const int64_t n_groups = (int64_t)gridDim.x * blockDim.x / L;
   u64 out_b = 0;
   for (int64_t slot = group; slot < total_slots; slot += n_groups) {
-    const int32_t row = tags[slot], stamp = ts[slot];
-    if (row < 0 || stamp <= since) continue;
+    const int32_t row = tags[slot];
+    if (row < 0) continue;
     int lo = 0, hi = T - 1;  // table owning this slot: last t with slot_base <= slot
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -679,19 +675,19 @@ __global__ __launch_bounds__(256) void flush_kernel(const TableMeta *__restrict_
   if ((threadIdx.x & 63) == 0 && out_b) atomicAdd(bytes_d2h, out_b);
 }
 
-// flush of the second level: every line that has taken its row in, or was used in place, since the last flush goes to the row in
-// the lower tier (host to host through the GPU); the levels are exclusive, so no row is written twice
+// flush of the second level: every valid line goes to its row in the lower tier (host to
+// host through the GPU); the levels are exclusive, so no row is written twice
 template <int L>
 __global__ __launch_bounds__(256) void flush2_kernel(const TableMeta *__restrict__ tm, int T, int64_t total_slots2,
-                                                     const int32_t *__restrict__ tags2, const int32_t *__restrict__ ts2,
-                                                     int32_t since, u64 *bytes_h2d, u64 *bytes_d2h) {
+                                                     const int32_t *__restrict__ tags2, u64 *bytes_h2d,
+                                                     u64 *bytes_d2h) {
   const int64_t group = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / L;
   const int lig = threadIdx.x % L;
   const int64_t n_groups = (int64_t)gridDim.x * blockDim.x / L;
   u64 b = 0;
   for (int64_t slot = group; slot < total_slots2; slot += n_groups) {
-    const int32_t row = tags2[slot], stamp = ts2[slot];
-    if (row < 0 || stamp <= since) continue;
+    const int32_t row = tags2[slot];
+    if (row < 0) continue;
     int lo = 0, hi = T - 1;  // table owning this slot: last t with slot2_base <= slot
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -708,12 +704,12 @@ __global__ __launch_bounds__(256) void flush2_kernel(const TableMeta *__restrict
   }
 }
 
-hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const int32_t *ts, int32_t since, const Level2 &l2,
-                        u64 *bytes_h2d, u64 *bytes_d2h, hipStream_t s) {
+hipError_t launch_flush(const TableMeta *tm, const Geometry &g, const int32_t *tags, const Level2 &l2, u64 *bytes_h2d,
+                        u64 *bytes_d2h, hipStream_t s) {
   if (g.total_slots)
-    TBE_BY_ROW_LANES(g.ovf_stride, hipLaunchKernelGGL((flush_kernel<L>), dim3(1024), dim3(256), 0, s, tm, g.T, g.total_slots, tags, ts, since, bytes_d2h));
+    TBE_BY_ROW_LANES(g.ovf_stride, hipLaunchKernelGGL((flush_kernel<L>), dim3(1024), dim3(256), 0, s, tm, g.T, g.total_slots, tags, bytes_d2h));
   if (l2.on && l2.total_slots2)
-    TBE_BY_ROW_LANES(g.ovf_stride, hipLaunchKernelGGL((flush2_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, tm, g.T, l2.total_slots2, l2.tags2, l2.ts2, since, bytes_h2d,
+    TBE_BY_ROW_LANES(g.ovf_stride, hipLaunchKernelGGL((flush2_kernel<L>), dim3(kLinkBlocks), dim3(256), 0, s, tm, g.T, l2.total_slots2, l2.tags2, bytes_h2d,
                        bytes_d2h));
   return hipGetLastError();
 }
