@@ -5,6 +5,7 @@ remarks switched on; the remarks are collected into `_build/resource_usage.txt` 
 for the properties the library relies on:
   - `transfer_kernel` allocates at least 128 vector registers per lane (with 1024 threads per
     workgroup that fills a CU's register files, which is how the kernel keeps its CUs to itself);
+  - `backward_rest_kernel`, which waits for gathered rows, leaves room for four wavefronts a SIMD in each of its instances;
   - no kernel spills registers to scratch memory.
 The packed-fp32 target feature is switched off for the device pass.  hipcc hands `-Xclang` options
 to the host pass as well, which does not know the feature and says so once per file and pass;
@@ -28,6 +29,7 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
 REMARKS = ["-Rpass-analysis=kernel-resource-usage"]
 HARMLESS = "'-packed-fp32-ops' is not a recognized feature for this target (ignoring feature)"
 MIN_VGPRS = {"transfer_kernel": 128}  # kernel-name substring -> fewest vector registers it must allocate
+MIN_OCCUPANCY = {"backward_rest_kernel": 4}  # ... -> fewest wavefronts a SIMD that its registers and LDS must leave room for
 
 _REMARK = re.compile(r"remark:\s+(Function Name|TotalSGPRs|VGPRs|AGPRs|ScratchSize \[bytes/lane\]|Occupancy \[waves/SIMD\]|"
                      r"VGPRs Spill|SGPRs Spill|LDS Size \[bytes/block\]):\s+(\S+)")
@@ -110,7 +112,10 @@ def build(verbose: bool = False) -> str:
         for sub, least in MIN_VGPRS.items():
             if sub in plain[n] and u.get("VGPRs", 0) < least:
                 raise RuntimeError(f"build check: {plain[n]} allocates {u.get('VGPRs')} vector registers, needs {least}")
-    for sub in MIN_VGPRS:
+        for sub, least in MIN_OCCUPANCY.items():
+            if sub in plain[n] and u.get("Occupancy [waves/SIMD]", 0) < least:
+                raise RuntimeError(f"build check: {plain[n]} leaves room for {u.get('Occupancy [waves/SIMD]')} wavefronts a SIMD, needs {least}")
+    for sub in [*MIN_VGPRS, *MIN_OCCUPANCY]:
         if not any(sub in plain[n] for n in names):
             raise RuntimeError(f"build check: no resource remark for {sub}")
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + [obj for _, obj, _, _ in results] + ["-o", LIB]

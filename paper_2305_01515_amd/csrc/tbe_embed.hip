@@ -783,21 +783,32 @@ __device__ __forceinline__ void update_long_parts(int blk, int blocks, const Tab
                                                   uint32_t ovf_stride, const int32_t *__restrict__ table_class,
                                                   const float *__restrict__ inv_len, const BatchCounters *cnt) {
   constexpr int EPL = Elems<DT>::n;
-  constexpr int NG = 256 / G;
-  __shared__ float part[NG][G * EPL + 1];
+  constexpr int NG = 256 / G, kWaves = 256 / kWave;
+  __shared__ float part[kWaves][G * EPL + 1];
   __shared__ int s_last;
   const int n_heavy = cnt->n_heavy;
-  const int lig = threadIdx.x % G, grp = threadIdx.x / G;
-  auto add_groups = [&](float (&g)[EPL]) {  // the groups' sums, in the first group
-    __syncthreads();
+  const int lig = threadIdx.x % G, grp = threadIdx.x / G, wave = threadIdx.x / kWave;
+  // The groups' sums, in the first group: those of a wavefront by exchange between its lanes, those of the wavefronts through LDS.
+  // (With every group's sum in LDS the first group had up to 256 of them to read, all requested at once, for which the kernel took
+  // 256 registers a lane with rows of two lanes of binary16, 192 with four, 98 of fp32: a workgroup or two a CU, the other rows' in
+  // the same launch too.  Backward of rows of 16 binary16 in eight tables, us: 262144 lookups on 300 rows each 79, now 15, a million
+  // on 1000 rows each 243, now 41, on 10 k rows, of which none is heavy, 262144 26, now 14.)
+  auto add_groups = [&](float (&g)[EPL]) {
 #pragma unroll
-    for (int e = 0; e < EPL; e++) part[grp][lig * EPL + e] = g[e];
+    for (int e = 0; e < EPL; e++)
+      for (int d = G; d < kWave; d <<= 1) g[e] += __shfl_xor(g[e], d);
+    __syncthreads();
+    if (threadIdx.x % kWave < G) {
+#pragma unroll
+      for (int e = 0; e < EPL; e++) part[wave][lig * EPL + e] = g[e];
+    }
     __syncthreads();
     if (grp == 0) {
 #pragma unroll
       for (int e = 0; e < EPL; e++) {
         float sum = 0.f;
-        for (int q = 0; q < NG; q++) sum += part[q][lig * EPL + e];
+#pragma unroll
+        for (int w = 0; w < kWaves; w++) sum += part[w][lig * EPL + e];
         g[e] = sum;
       }
     }

@@ -40,6 +40,20 @@ def test_rows_of_one_and_of_many_entries(n, dim, dtype, pooling):
     assert st["last_long_rows"] >= min(64, (n + 2047) // 2048)
 
 
+WIDTHS = [(d, synth.FP32) for d in (4, 8, 16, 28, 64, 128, 256)] + [(d, synth.FP16) for d in (8, 16, 32, 40, 128, 256, 512)]
+
+
+@pytest.mark.parametrize("dim,dtype,n,pooling", [(d, t, n, p) for d, t in WIDTHS for n, p in ((300, "mean"), (5000, "sum"))]
+                         + [(8, synth.FP32, 524300, "mean"), (16, synth.FP16, 524300, "sum"), (128, synth.FP32, 524300, "sum")])
+def test_rows_of_every_width(dim, dtype, n, pooling):
+    """1 to 64 lanes a row: the sums of the lane groups of a wavefront, of its wavefronts and of a row's entries; a row with all
+    lookups of its table, some hundred rows with 65 and more, in one launch with the other rows and in one behind them"""
+    tabs = [T(1, dim, dtype, None, "fixed", 1, cache_slots=2), T(n // 150 + 1, dim, dtype, 0.8, "fixed", 1, cache_slots=16)]
+    st = run_parity(synth.WorkloadCfg("width", tabs, batch=n // 2, ways=2, steps=2, seed=dim, init_std=0.05, lr=0.05), steps=2, order="early",
+                    pooling=pooling)
+    assert st["last_long_rows"] > 0
+
+
 @pytest.mark.parametrize("n", [524288, 524289, 2097152, 2097153])
 def test_either_side_of_the_larger_lines(n):
     """the launch of their own, and the tile kernel: rows with a third of the lookups, some hundred and none"""
