@@ -1473,7 +1473,11 @@ static void bwd_one(int which, const TableMeta *tm, const int32_t *tables, int c
   }
   const int per = 256 / G;  // lane groups of a workgroup
   const int blocks_per_table = (b.batch + per - 1) / per;
-  const int combine = (which & kBwdCombine) && long_rows ? work_blocks(most_heavy, 1, 1024)
+  // Entries: a launch of their own has 4096 workgroups for rows of up to 64 elements, whose entries are short, so that tables with
+  // thousands of heavy rows leave no long last round.  Wider rows' gradients come from L2, where more of them at a time hold a few
+  // rows less.  Backward in us, 1024 / 4096: a million lookups on 8 x 1000 rows of 8 fp32, 16 binary16, 64 fp32 35, 41, 57 / 29, 34, 47;
+  // two million on 8 x 300 rows of 128 binary16 and of 256 fp32 140, 276 / 148, 320.
+  const int combine = (which & kBwdCombine) && long_rows ? work_blocks(most_heavy, 1, !(which & kBwdShort) && G * Elems<DT>::n <= 64 ? 4096 : 1024)
                       : (which & kBwdCombine) && tiled ? work_blocks(most_heavy, per, 2048)
                       : (which & kBwdShort) && b.maxp && kLongInRest<G> ? work_blocks(most_heavy, 1, 4096) : 0;
   const int shrt = (which & kBwdShort) ? work_blocks(b.n / 2, per, 4096) : 0;

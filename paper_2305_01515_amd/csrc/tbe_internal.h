@@ -521,7 +521,12 @@ struct OneCtl {
 // rows of 256 fp32, 262144 103, 60, 50 / 43, 37, 44, 2097152 1197, 291, 367 / 398, 266, 367; rows of 8 fp32, all lookups on five rows
 // 524288 279 / 18.  Eight tables, 2097152 lookups, 128 binary16: 156, 75, 120 / 119, 81, 120.  Behind the line the lookups' gradient rows
 // at L2 cost more than the tiles: 7.9 M lookups on 32 x 1M rows of 128 binary16, whole backward, 463 / 536, 3.9 M on 16 x 500k 246 / 250.
-// (Slower below it only where all lookups are on a hundred rows a table: 8 tables, 1 M, 8 fp32 23 / 37, one table, 2 M, 128 binary16 105 / 135.)
+// Tables of 100 to 3000 rows, which have all the lookups, one, four and sixteen of them, 8, 32 and 128 lookups a bag, 1, 1.5 and 2 M
+// lookups, rows of 32 to 512 binary16 and of 64 and 128 fp32: entries take 0.15 to 1.0 times as long in ten of eleven such models, up to
+// 1.4 times in the others, most of them with rows of 128 and 256 binary16 from 1.5 M on.  Which it is changes from table count to table
+// count and from bag length to bag length (2 M, 128 binary16, one table of 100 rows, 8, 32, 128 a bag 192, 104, 84 / 180, 137, 77; four of
+// 300 128, 77, 65 / 164, 94, 66; sixteen of 300 126, 76, 63 / 118, 68, 60), and a model with some larger tables beside the small ones is
+// faster by entries throughout (1.2 to 1.5 times): no line between them.
 constexpr int64_t kLongLookups = 2097152;
 inline bool long_rows_in_rest(int64_t n) { return n <= kLongLookups; }
 // Lookups of a heavy row from which it has one entry more: a workgroup's share, or what would hold up a lane group of the tile
