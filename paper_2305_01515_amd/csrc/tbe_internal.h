@@ -384,13 +384,20 @@ inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch) {
   s.rb = (bits + passes - 1) / passes;
   if (s.rb < 8) s.rb = 8;
   s.items = n <= kTiles1k ? 2 : n <= kTiles2k ? 4 : n <= kTiles4k ? 8 : 16;
-  // A workgroup of the key generation takes 64 bags at a time.  Up to four rounds of them are left to kSlotsHeard workgroups, whose
-  // counts the sort can add up by itself; many more lookups are worth the addition's launch, 5 us.  Us for keys, addition and two
+  // A workgroup of the key generation takes 64 bags at a time.  Up to four rounds of them are left to kSlotsHeard
+  // workgroups, whose counts the sort can add up by itself; many more lookups are worth the addition's launch, 5 us.  Us for keys, addition and two
   // passes, 32 workgroups / one a round and the addition: 40 k lookups in 8000 bags 33 / 32, 21 k in 2100 25 / 25, 84 k 33 / 32, 96 k in
   // 2400 30 / 30, 128 k in 8000 37 / 32, 210 k in 2100 44 / 41, 242 k in 4756 44 / 38, 320 k in 8000 51 / 40; four tables, 252 k in 2100
   // bags of each 32 / 31, 280 k in 7000 40 / 36, less what one launch more takes the host.  So from 131072 lookups a segment on.
-  const int64_t rounds = (s.bags + 63) / 64, most = 1024 / s.segs > kSlotsHeard ? 1024 / s.segs : kSlotsHeard;
-  s.slots = (int)(rounds < 1 ? 1 : rounds > kSlotsHeard && rounds < 4 * kSlotsHeard && n <= (int64_t)kTiles1k * s.segs ? kSlotsHeard : rounds > most ? most : rounds);
+  // 1024 workgroups in all, or as many as have 256 lookups each: a workgroup writes some thousand counters, and with 32 for each of
+  // 512 segments of 2112 lookups the counters were 134 MB for 9 MB of keys, which took 17 of 243 us.
+  const int64_t rounds = (s.bags + 63) / 64;
+  int64_t most = n / ((int64_t)s.segs * 256);
+  if (most > kSlotsHeard) most = kSlotsHeard;
+  if (most < 1024 / s.segs) most = 1024 / s.segs;
+  int64_t slots = rounds > kSlotsHeard && rounds < 4 * kSlotsHeard && n <= (int64_t)kTiles1k * s.segs ? kSlotsHeard : rounds;
+  if (slots > most) slots = most;
+  s.slots = (int)(slots < 1 ? 1 : slots);
   s.add_slots = s.slots > kSlotsHeard || (s.slots > 4 && n > 1000000);
   s.tiles = (int)((n + s.tile() - 1) / s.tile() + s.segs);
   return s;

@@ -44,3 +44,9 @@ def test_tiles_of_every_size(batch):
 
 def test_more_lookups_than_the_distinct_rows_pass_has_workgroups_for():
     parity([T(900001, 4, synth.FP32, 0.8, "fixed", 128, cache_slots=8 * 20000)], 66000, 5, steps=1)
+
+
+@pytest.mark.parametrize("tables", [511, 512, 513])
+def test_as_many_tables_as_can_be_segments_and_one_more(tables):
+    """one lookup a bag, 2049 of each table; beyond 512 tables they are one segment"""
+    parity([T(3 + 7 * (t % 9), 4, synth.FP32, None, "fixed", 1, cache_slots=8 * (t % 3)) for t in range(tables)], 2049, tables, steps=1)
