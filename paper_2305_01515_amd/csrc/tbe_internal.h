@@ -369,12 +369,14 @@ struct SortShape {
   int rb;          // bits of the widest digit (8 at least)
   int segs, bags;  // segments, and the bags of one
   int items;       // keys of a thread
+  int lanes;       // of the key generation that read a bag
   int slots;       // workgroups of the key generation for a segment, each with a slot for its counts of all digit values
   bool add_slots;  // they are added up by a kernel of their own
   int tiles;       // at most
   __host__ __device__ int tile() const { return kSortThreads * items; }
 };
-inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch) {
+// lanes: 0, or what the batch would have with other lookups a bag
+inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch, int lanes = 0) {
   SortShape s{};
   s.segs = g.T > 1 && g.T <= kLutTables && n >= kSegmentLookups * g.T ? g.T : 1;
   s.bags = (int)((int64_t)g.T * batch / s.segs);
@@ -384,14 +386,19 @@ inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch) {
   s.rb = (bits + passes - 1) / passes;
   if (s.rb < 8) s.rb = 8;
   s.items = n <= kTiles1k ? 2 : n <= kTiles2k ? 4 : n <= kTiles4k ? 8 : 16;
-  // A workgroup of the key generation takes 64 bags at a time.  Up to four rounds of them are left to kSlotsHeard
-  // workgroups, whose counts the sort can add up by itself; many more lookups are worth the addition's launch, 5 us.  Us for keys, addition and two
+  // A bag has eight lanes, or one where bags have two lookups or fewer on average: seven of eight lanes had nothing to read, and the
+  // rounds that this takes were what bounded the kernel.  The whole stage and the forward, us, with eight / one: 2.2 M bags of one lookup in
+  // one table and in eight 304, 314 / 218, 229, 400 k in one 121 / 104, 200 k of two 111 / 102, 100 k of four 106 / 103, of eight 106 / 109;
+  // 256 tables of 2112 bags of one, 512 of 8192 166, 630 / 139, 506.
+  s.lanes = lanes ? lanes : n <= 2 * (int64_t)s.segs * s.bags ? 1 : 8;
+  // A workgroup of the key generation takes 64 bags at a time (512, a lane each).  Up to four rounds of them are left to
+  // kSlotsHeard workgroups, whose counts the sort can add up by itself; many more lookups are worth the addition's launch, 5 us.  Us for keys, addition and two
   // passes, 32 workgroups / one a round and the addition: 40 k lookups in 8000 bags 33 / 32, 21 k in 2100 25 / 25, 84 k 33 / 32, 96 k in
   // 2400 30 / 30, 128 k in 8000 37 / 32, 210 k in 2100 44 / 41, 242 k in 4756 44 / 38, 320 k in 8000 51 / 40; four tables, 252 k in 2100
   // bags of each 32 / 31, 280 k in 7000 40 / 36, less what one launch more takes the host.  So from 131072 lookups a segment on.
   // 1024 workgroups in all, or as many as have 256 lookups each: a workgroup writes some thousand counters, and with 32 for each of
   // 512 segments of 2112 lookups the counters were 134 MB for 9 MB of keys, which took 17 of 243 us.
-  const int64_t rounds = (s.bags + 63) / 64;
+  const int64_t round = 2 * 256 / s.lanes, rounds = (s.bags + round - 1) / round;
   int64_t most = n / ((int64_t)s.segs * 256);
   if (most > kSlotsHeard) most = kSlotsHeard;
   if (most < 1024 / s.segs) most = 1024 / s.segs;
@@ -406,11 +413,11 @@ inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch) {
 struct SortNeeds { int64_t said, tiles, slots; };  // words of tiles' counts, tiles, words of slots
 inline SortNeeds sort_needs(const Geometry &g, int64_t n, int32_t batch) {
   SortNeeds r{1, 1, 1};
-  // (a batch of fewer lookups can have more tiles or, as one segment, more workgroups)
+  // (a batch of fewer lookups can have more tiles or, as one segment, more workgroups, one of fewer bags more lanes and so workgroups)
   const int64_t steps[] = {n, kTiles1k, kTiles2k, kTiles4k, kSegmentLookups * g.T - 1};
   for (int64_t m : steps) {
     if (m > n || m < 1) continue;
-    const SortShape s = sort_shape(g, m, batch);
+    const SortShape s = sort_shape(g, m, batch, 8);
     const int64_t said = 2 * (int64_t)s.tiles << s.rb, slots = (int64_t)(s.slots + 1) * s.segs * (s.digits.passes << s.rb);
     if (said > r.said) r.said = said;
     if (s.tiles > r.tiles) r.tiles = s.tiles;

@@ -8,9 +8,8 @@ namespace tbe {
 typedef unsigned long long u64;
 
 // --------------------------------------------------------------------------------------
-// key generation: 8 lanes per bag, 64-byte coalesced reads of the bag's indices
+// key generation: 8 lanes per bag, 64-byte coalesced reads of the bag's indices; short bags a lane each (SortShape::lanes)
 // --------------------------------------------------------------------------------------
-constexpr int kKeygenLanes = 8;
 constexpr int kKeygenThreads = 256;
 
 // First kernel of the stage where a bag may be too long for the packed payload, which only the offsets tell: it looks at every
@@ -97,6 +96,11 @@ __device__ __forceinline__ void list_tiles(const KeygenArgs &a, int *s_first, in
 // kernel of the batch then returns at once, so tags, lines and copies stay as the last good batch left them, and a batch buffer
 // that is used again still says so.  What is wrong with this batch is gathered in *stage_err, which the sort's first pass
 // adds to the counters (a workgroup that finds a fault may run before workgroup 0).
+//
+// LANES: of a bag.  With one lane a bag, what a bag has beyond kLaneLookups is left to all lanes of the wavefront together, bag after
+// bag, so that a long bag among short ones holds nobody up for longer than it does eight lanes.
+constexpr int kLaneLookups = 16;
+template <int LANES>
 __global__ __launch_bounds__(kKeygenThreads) void keygen_kernel(KeygenArgs a) {
   extern __shared__ uint32_t s_hist[];
   __shared__ int s_wave[kKeygenThreads / kWave];
@@ -115,10 +119,31 @@ __global__ __launch_bounds__(kKeygenThreads) void keygen_kernel(KeygenArgs a) {
   const int seg = blockIdx.x / a.sh.slots, part = blockIdx.x % a.sh.slots;
   const int first = seg * a.sh.bags + (int)((int64_t)a.sh.bags * part / a.sh.slots);
   const int end = seg * a.sh.bags + (int)((int64_t)a.sh.bags * (part + 1) / a.sh.slots);
-  const int sub = threadIdx.x % kKeygenLanes;
-  constexpr int kBags = kKeygenThreads / kKeygenLanes, K = 2, X = 4;  // two bags, four indices of each under way per lane
+  const int sub = threadIdx.x % LANES;
+  constexpr int kBags = kKeygenThreads / LANES, K = 2, X = 4;  // two bags, four indices of each under way per lane
   const uint32_t key0 = a.sh.segs > 1 ? a.tm[seg].key_base : 0u;
-  for (int64_t bag0 = first + (int)threadIdx.x / kKeygenLanes; bag0 < end; bag0 += K * kBags) {
+  struct Keys {  // of a table (in registers: the stores could be to the descriptions for all that the compiler knows)
+    int64_t rows;
+    uint32_t key_base, sets, rows_per_set;
+    u64 sets_magic;
+  };
+  auto keys_of = [&](int bag) __attribute__((always_inline)) {
+    const TableMeta &m = a.tm[a.sh.segs > 1 ? seg : bag / a.B];
+    return Keys{m.rows, m.key_base, m.sets, m.rows_per_set, m.sets_magic};
+  };
+  auto put = [&](const Keys m, int64_t row, int bag, int64_t bag_first, int64_t j) __attribute__((always_inline)) {
+    if (row < 0 || row >= m.rows) {
+      atomicMax(a.stage_err, 2u /* -TBE_ERANGE */);
+      row = 0;
+    }
+    const uint32_t d = div_by((uint32_t)row, m.sets_magic);
+    const uint32_t key = m.sets ? m.key_base + ((uint32_t)row - d * m.sets) * m.rows_per_set + d : m.key_base + (uint32_t)row;
+    a.pairs[j] = make_uint2(key, packed ? ((uint32_t)bag << a.within_bits) | (uint32_t)(j - bag_first) : (uint32_t)j);
+    if (!packed) a.bag_of_pos[j] = bag;
+    for (int p = 0; p < a.sh.digits.passes; p++)
+      atomicAdd(&s_hist[(p << a.sh.rb) + (((key - key0) >> a.sh.digits.shift[p]) & a.sh.digits.mask[p])], 1u);
+  };
+  for (int64_t bag0 = first + (int)threadIdx.x / LANES; bag0 < end; bag0 += K * kBags) {
     int64_t lo[K], hi[K], r[K][X];
 #pragma unroll
     for (int q = 0; q < K; q++) {
@@ -140,40 +165,40 @@ __global__ __launch_bounds__(kKeygenThreads) void keygen_kernel(KeygenArgs a) {
     for (int q = 0; q < K; q++)
 #pragma unroll
       for (int x = 0; x < X; x++) {
-        const int64_t j = lo[q] + sub + x * kKeygenLanes;
+        const int64_t j = lo[q] + sub + x * LANES;
         r[q][x] = j < hi[q] ? a.indices[j] : 0;
       }
 #pragma unroll
     for (int q = 0; q < K; q++) {
-      if (lo[q] + sub >= hi[q]) continue;
-      const int bag = (int)(bag0 + q * kBags);
-      const TableMeta &m = a.tm[a.sh.segs > 1 ? seg : bag / a.B];
-      const int64_t rows = m.rows;
-      const uint32_t key_base = m.key_base, sets = m.sets, rows_per_set = m.rows_per_set;
-      const u64 sets_magic = m.sets_magic;
-      for (int64_t j0 = lo[q] + sub;;) {
+      const int64_t mine = LANES > 1 || hi[q] - lo[q] < kLaneLookups ? hi[q] : lo[q] + kLaneLookups;
+      if (lo[q] + sub < mine) {
+        const int bag = (int)(bag0 + q * kBags);
+        const Keys m = keys_of(bag);
+        for (int64_t j0 = lo[q] + sub;;) {
 #pragma unroll
-        for (int x = 0; x < X; x++) {
-          const int64_t j = j0 + x * kKeygenLanes;
-          if (j >= hi[q]) continue;
-          int64_t row = r[q][x];
-          if (row < 0 || row >= rows) {
-            atomicMax(a.stage_err, 2u /* -TBE_ERANGE */);
-            row = 0;
+          for (int x = 0; x < X; x++) {
+            const int64_t j = j0 + x * LANES;
+            if (j < mine) put(m, r[q][x], bag, lo[q], j);
           }
-          const uint32_t d = div_by((uint32_t)row, sets_magic);
-          const uint32_t key = sets ? key_base + ((uint32_t)row - d * sets) * rows_per_set + d : key_base + (uint32_t)row;
-          a.pairs[j] = make_uint2(key, packed ? ((uint32_t)bag << a.within_bits) | (uint32_t)(j - lo[q]) : (uint32_t)j);
-          if (!packed) a.bag_of_pos[j] = bag;
-          for (int p = 0; p < a.sh.digits.passes; p++)
-            atomicAdd(&s_hist[(p << a.sh.rb) + (((key - key0) >> a.sh.digits.shift[p]) & a.sh.digits.mask[p])], 1u);
-        }
-        j0 += X * kKeygenLanes;
-        if (j0 >= hi[q]) break;
+          j0 += X * LANES;
+          if (j0 >= mine) break;
 #pragma unroll
-        for (int x = 0; x < X; x++) {
-          const int64_t j = j0 + x * kKeygenLanes;
-          r[q][x] = j < hi[q] ? a.indices[j] : 0;
+          for (int x = 0; x < X; x++) {
+            const int64_t j = j0 + x * LANES;
+            r[q][x] = j < mine ? a.indices[j] : 0;
+          }
+        }
+      }
+      if constexpr (LANES == 1) {
+        const int lane = threadIdx.x & 63;
+        const uint64_t here = __ballot(true);  // (the last round has fewer lanes)
+        const int helpers = __popcll(here), rank = __popcll(here & ((1ull << lane) - 1ull));
+        for (uint64_t todo = __ballot(mine < hi[q]); todo; todo &= todo - 1) {
+          const int src = __ffsll((unsigned long long)todo) - 1;
+          const int64_t l = __shfl(lo[q], src), h = __shfl(hi[q], src);
+          const int bag = __shfl((int)(bag0 + q * kBags), src);
+          const Keys m = keys_of(bag);
+          for (int64_t j = l + kLaneLookups + rank; j < h; j += helpers) put(m, a.indices[j], bag, l, j);
         }
       }
     }
@@ -226,7 +251,7 @@ hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf 
   }
   const int words = a.sh.digits.passes << a.sh.rb;
   const int lds = 4 * (words > kLutTables + 1 ? words : kLutTables + 1);
-  hipLaunchKernelGGL(keygen_kernel, dim3(a.sh.segs * a.sh.slots + 1), dim3(kKeygenThreads), lds, s, a);
+  hipLaunchKernelGGL(a.sh.lanes == 1 ? keygen_kernel<1> : keygen_kernel<8>, dim3(a.sh.segs * a.sh.slots + 1), dim3(kKeygenThreads), lds, s, a);
   if (a.sh.add_slots)
     hipLaunchKernelGGL(add_slots_kernel, dim3(words / 64, a.sh.segs), dim3(64 * kSlotParts), 0, s, ss.slots, a.sh.slots, words,
                        ss.slots + (size_t)a.sh.segs * a.sh.slots * words);

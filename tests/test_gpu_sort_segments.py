@@ -1,6 +1,7 @@
 """The sort of a kernel a pass at the sizes where it can go wrong: segments that begin and end anywhere in a tile or have no
 lookup, digits of every width, tiles of every size, slots that the sort adds up itself or has added up, and more lookups than
 the pass behind it has workgroups for.  Cache state and lists bit for bit against the oracle, values on its bars."""
+import numpy as np
 import pytest
 
 from paper_2305_01515_amd import synth
@@ -50,3 +51,23 @@ def test_more_lookups_than_the_distinct_rows_pass_has_workgroups_for():
 def test_as_many_tables_as_can_be_segments_and_one_more(tables):
     """one lookup a bag, 2049 of each table; beyond 512 tables they are one segment"""
     parity([T(3 + 7 * (t % 9), 4, synth.FP32, None, "fixed", 1, cache_slots=8 * (t % 3)) for t in range(tables)], 2049, tables, steps=1)
+
+
+@pytest.mark.parametrize("within", [300, 1500])
+@pytest.mark.parametrize("tables,batch", [(1, 3000), (3, 4100)])
+def test_long_bags_among_short_ones(tables, batch, within):
+    """two lookups a bag on average or fewer: a lane a bag, and all of a wavefront's lanes for what a bag has beyond 16; one segment and
+    three; with room for 2^22 bags the payload takes bags of 1024 lookups, so that the longest fits or does not"""
+    from test_gpu_mixed_calls import run
+    rng = np.random.RandomState(within + tables)
+    tabs = [T(40000 - 9000 * t, 4, synth.FP32, None, "fixed", 1, cache_slots=8 * 300) for t in range(tables)]
+    host = []
+    for step in range(3):
+        lens = rng.poisson(0.6, (tables, batch))
+        for at, n in zip(rng.choice(tables * batch, 12, False), (15, 16, 17, 18, 64, 79, 80, 81, 144, 200, within, 2)):
+            lens.ravel()[at] = n
+        lens[-1, -1] = 33 if step else 0  # the last bag, in a wavefront with few others
+        off = np.concatenate([[0], np.cumsum(lens.ravel())]).astype(np.int64)
+        host.append((np.concatenate([rng.randint(0, c.rows, l.sum()) for c, l in zip(tabs, lens)]).astype(np.int64), off,
+                     rng.randn(batch, 4 * tables).astype(np.float32)))
+    run(synth.WorkloadCfg("short", tabs, batch=(1 << 22) // tables, ways=8, steps=3, seed=1, init_std=0.05, lr=0.05), host, rng, False)

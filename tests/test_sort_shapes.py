@@ -34,10 +34,11 @@ int main() {
       const long long words = (long long)s.digits.passes << s.rb, bags = (long long)g.T * batch;
       const bool ok = (long long)(s.slots + 1) * s.segs * words <= need.slots && s.tiles <= need.tiles && (2ll * s.tiles << s.rb) <= need.said &&
                       s.slots >= 1 && (long long)s.slots * s.segs <= std::max(1024ll, n / 256) && (s.add_slots || s.slots <= kSlotsHeard) &&
-                      s.digits.passes <= kMaxSortPasses && s.rb <= 10 && (long long)s.bags * s.segs == bags && s.segs <= kLutTables;
+                      s.digits.passes <= kMaxSortPasses && s.rb <= 10 && (long long)s.bags * s.segs == bags && s.segs <= kLutTables &&
+                      s.lanes == (n <= 2 * bags ? 1 : 8);
       if (!ok) {
-        printf("T %d seg_bits %d key_bits %d max_batch %d max_n %lld batch %d n %lld: slots %d segs %d tiles %d\n", g.T, g.seg_bits,
-               g.key_bits, max_batch, max_n, batch, n, s.slots, s.segs, s.tiles);
+        printf("T %d seg_bits %d key_bits %d max_batch %d max_n %lld batch %d n %lld: slots %d segs %d lanes %d tiles %d\n", g.T, g.seg_bits,
+               g.key_bits, max_batch, max_n, batch, n, s.slots, s.segs, s.lanes, s.tiles);
         return 1;
       }
     }
