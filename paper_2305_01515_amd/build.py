@@ -7,6 +7,9 @@ for the properties the library relies on:
     workgroup that fills a CU's register files, which is how the kernel keeps its CUs to itself);
   - `backward_rest_kernel`, which waits for gathered rows, leaves room for four wavefronts a SIMD in each of its instances;
   - no kernel spills registers to scratch memory.
+Beside it, for the tests, it builds the library twice more, with workgroups that look 0 and 1 times at what another one has
+yet to say before they count that one's part themselves (64 times in libtbe.so, which a run without contention never reaches).
+
 The packed-fp32 target feature is switched off for the device pass.  hipcc hands `-Xclang` options
 to the host pass as well, which does not know the feature and says so once per file and pass;
 that one line is dropped from the output (everything else the compiler prints is shown).
@@ -26,6 +29,8 @@ LIB = os.path.join(HERE, "libtbe.so")
 SOURCES = ["tbe_api.hip", "tbe_sort.hip", "tbe_cache.hip", "tbe_one.hip", "tbe_move.hip", "tbe_embed.hip", "tbe_place.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
+IMPATIENT = {polls: os.path.join(HERE, f"libtbe_polls{polls}.so") for polls in (0, 1)}
+POLLING = ["tbe_sort.hip", "tbe_cache.hip"]  # the sources whose kernels look
 REMARKS = ["-Rpass-analysis=kernel-resource-usage"]
 HARMLESS = "'-packed-fp32-ops' is not a recognized feature for this target (ignoring feature)"
 MIN_VGPRS = {"transfer_kernel": 128}  # kernel-name substring -> fewest vector registers it must allocate
@@ -61,9 +66,9 @@ def parse_resource_usage(stderr: str):
     return usage
 
 
-def _compile(hipcc: str, src: str, verbose: bool):
-    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc] + FLAGS + REMARKS + ["-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(hipcc: str, src: str, verbose: bool, polls=None):
+    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ("" if polls is None else f"_polls{polls}") + ".o")
+    cmd = [hipcc] + FLAGS + ([] if polls is None else [f"-DTBE_POLLS={polls}"]) + REMARKS + ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     p = subprocess.run(cmd, capture_output=True, text=True)
@@ -85,16 +90,18 @@ def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(6, os.cpu_count() or 1)) as ex:
-        results = list(ex.map(lambda s: _compile(hipcc, s, verbose), SOURCES))
+        jobs = [(s, None) for s in SOURCES] + [(s, polls) for polls in IMPATIENT for s in POLLING]
+        compiled = dict(zip(jobs, ex.map(lambda j: _compile(hipcc, j[0], verbose, j[1]), jobs)))
     usage, failed = {}, False
-    for src, obj, rc, err in results:
+    for (_, polls), (src, obj, rc, err) in compiled.items():
         state = {}
         for line in err.splitlines():
             if line.strip() == HARMLESS or _is_remark_line(line, state):
                 continue
             print(line, file=sys.stderr)
         failed |= rc != 0
-        usage.update(parse_resource_usage(err))
+        if polls is None:
+            usage.update(parse_resource_usage(err))
     if failed:
         raise subprocess.CalledProcessError(1, "hipcc -c")
     names = list(usage)
@@ -118,10 +125,12 @@ def build(verbose: bool = False) -> str:
     for sub in [*MIN_VGPRS, *MIN_OCCUPANCY]:
         if not any(sub in plain[n] for n in names):
             raise RuntimeError(f"build check: no resource remark for {sub}")
-    cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + [obj for _, obj, _, _ in results] + ["-o", LIB]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+    for lib, polls in [(LIB, None)] + [(path, polls) for polls, path in IMPATIENT.items()]:
+        objs = [compiled[src, polls if src in POLLING else None][1] for src in SOURCES]
+        cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", lib]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
     return LIB
 
 
