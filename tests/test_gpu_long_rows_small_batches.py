@@ -13,7 +13,7 @@ T = synth.TableCfg
 @pytest.mark.parametrize("dim,dtype,bags", [(4, synth.FP32, 1024), (16, synth.FP32, 1024), (64, synth.FP32, 256), (256, synth.FP32, 64),
                                             (128, synth.FP16, 256), (512, synth.FP16, 64), (24, synth.FP16, 1024)])
 def test_either_side_of_the_line(dim, dtype, bags, pooling):
-    """bags x 16 lookups x lanes: 65536 lanes in all, and one bag less and more; a few rows with most of the lookups, a row with 65"""
+    """a few rows with most of the lookups, a row with 65, where bags x 16 lookups x lanes are 65536 lanes, one bag less and one more"""
     for batch in (bags - 1, bags, bags + 1):
         tabs = [T(5, dim, dtype, 1.2, "fixed", 15, cache_slots=4), T(batch // 65 + 1, dim, dtype, None, "fixed", 1, cache_slots=0)]
         st = run_parity(synth.WorkloadCfg("long", tabs, batch=batch, ways=2, steps=3, seed=batch, init_std=0.05, lr=0.05), steps=3,

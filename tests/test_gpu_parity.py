@@ -119,9 +119,9 @@ def test_sparse_sets_in_caches_as_large_as_the_tables(ways, second_level_factor)
 @pytest.mark.parametrize("pooling", ["sum", "mean"])
 def test_rows_with_a_large_share_of_all_lookups(dtype, dim, pooling):
     """Zipf 1.4 over a single table: one row takes a third of the batch's quarter of a million lookups and a dozen
-    more take thousands each.  Such rows enter the heavy rows' kernel in parts of 2048 lookups, and from 512 partial
-    sums on their parts are added up side by side, the last part in finishing the row (arrival counters, which must
-    be back at zero for the next batch: six steps); a second, ordinary table runs along."""
+    more take thousands each.  Such rows have an entry, and so a workgroup, for every 1024 lookups, the last of a row's
+    workgroups to be done finishing it (arrival counters, which must be back at zero for the next batch: six steps); a
+    second, ordinary table runs along."""
     T = synth.TableCfg
     tabs = [
         T(200_000, dim, dtype, 1.4, "fixed", 64, cache_slots=32 * 400),
@@ -156,8 +156,8 @@ def test_sort_payload_with_and_without_the_bag(max_batch):
 
 @pytest.mark.parametrize("big_rows,key_bits", [(17_000_000, 25), (40_000_000, 26), (100_000_000, 27), (9_000_000, 24)])
 def test_sort_digit_widths_on_small_ragged_batches(big_rows, key_bits):
-    """The sort key has as many bits as the keys of all tables need; 25 to 27 bits are sorted in three passes with
-    9-bit digits among them, everything else by digits of up to 8 bits.  One table of narrow rows sets the key width
+    """Tables are sorted as segments, by as many bits as the widest one's keys need: 25 to 27 in three passes with 9-bit
+    digits among them, 24 by three of 8.  One table of narrow rows sets the key width
     (its rows are spread over the whole range by uniform indices, so every digit value occurs), small ragged
     batches: tiles that are not full, workgroups without keys."""
     T = synth.TableCfg

@@ -20,7 +20,7 @@ LOOKUPS = {"one_workgroup": 12,     # one kernel of one workgroup
            "few_workgroups": 150,   # ... of 3
            "many_workgroups": 500,  # ... of 10, several of them with lists
            "kernel_a_pass": 1500,   # 4097 to 524288 lookups
-           "large": 21846}          # > 65536 bags: two or three kernels a pass
+           "large": 21846}          # > 65536 bags: no small batch, its stage behind training
 
 
 def model(seed, dtype, batch=19):

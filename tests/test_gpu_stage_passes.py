@@ -40,7 +40,7 @@ def test_lookups_around_the_steps_with_a_kernel_a_pass(n):
 @pytest.mark.parametrize("batch,pool", [(64, 64), (65, 63), (241, 17), (2047, 64), (2048, 64), (2049, 64), (4099, 63), (8191, 64),
                                         (8192, 64), (8193, 64)])
 def test_lookups_around_the_lines_of_the_small_batches(batch, pool):
-    """the sort's tiles (2048 keys, from 131073 lookups on 4096) and the last batch size with a kernel a pass (524288)"""
+    """the sort's tiles (1024 keys, from 131073 lookups on 2048) and the last small batch (524288)"""
     tabs = [T(70001, 4, synth.FP32, 0.9, "fixed", pool - pool // 3, cache_slots=32 * 300),
             T(1999, 4, synth.FP32, None, "fixed", pool // 3, cache_slots=320)]
     run_parity(synth.WorkloadCfg("lines", tabs, batch=batch, ways=32, steps=2, seed=batch, init_std=0.05, lr=0.05), steps=2, order="early")
