@@ -408,19 +408,23 @@ int tbe_get_stats(tbe_handle h, tbe_stats *out);
  * launched on; tbe_get_stage_times returns the elapsed milliseconds of every bracket
  * recorded since profiling was switched on, in call order (at most 16384 per stage).
  * enable = 2 leaves out the brackets of the backward's single kernels (3, 4, 6, 7), which lie inside bracket 8
- * and lengthen it by their own events.  Both calls synchronise; tbe_set_profiling discards earlier records.
+ * and lengthen it by their own events.  Some batches have launches of their own while it is on, so that there is something to
+ * bracket: with enable = 1 each of the backward's kernels (3, 4, 6, 7), and with 1 or 2 the transfer and the commit (1, 5) of a batch of
+ * up to 8192 lookups that is prefetched with none in flight, which are one launch otherwise.  Results do not change.
+ * Both calls synchronise; tbe_set_profiling discards earlier records.
  * With h_ms NULL, tbe_get_stage_times returns the number of records.
  */
 #define TBE_STAGE_PREFETCH 0       /* key generation, sort, dedup, probe, compaction (aux stream; compute stream: see tbe_create) */
 #define TBE_STAGE_FILL 1           /* host link: write-back of parked victims + fetch-ahead of missed rows (the library's stream, or as bracket 0) */
 #define TBE_STAGE_FORWARD 2        /* pooled lookup (compute stream)                              */
-#define TBE_STAGE_BACKWARD_COMBINE 3 /* heavy rows: sum of the partial sums + update (compute stream) */
+#define TBE_STAGE_BACKWARD_COMBINE 3 /* rows with more than 64 lookups, sum and mean pooling: all of their backward in a batch of up to 2097152
+                                      lookups, beyond that the sum of the partial sums + update (compute stream) */
 #define TBE_STAGE_BACKWARD_SHORT 4 /* backward of rows with 2..64 lookups (max pooling, rows of 16 lanes and more: also of those
                                       with up to 512, fp32 1024 lookups) (compute stream)          */
 #define TBE_STAGE_COMMIT 5         /* victims -> staging, fetched rows -> cache lines (as bracket 1) */
 #define TBE_STAGE_BACKWARD_SINGLE 6 /* backward of rows with one lookup, bag by bag (compute stream) */
-#define TBE_STAGE_BACKWARD_HEAVY 7 /* rows with more than 64 lookups: partial sums per bag range from gradient tiles in LDS
-                                      (max pooling: one workgroup per row, update included, but for the rows in bracket 4)
+#define TBE_STAGE_BACKWARD_HEAVY 7 /* rows with more than 64 lookups, batches above 2097152: partial sums per bag range from gradient tiles
+                                      in LDS (rows of fewer than 4 lanes: one workgroup per row, update included) (max pooling, any size: one workgroup per row, update included, but for the rows in bracket 4)
                                       (compute stream) */
 #define TBE_STAGE_BACKWARD 8       /* the whole backward: from before its first kernel to after its last (compute stream);
                                       brackets 7, 3, 6, 4 lie inside it, one behind the other */

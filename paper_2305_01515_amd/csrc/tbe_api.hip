@@ -254,7 +254,7 @@ int alloc_batchbuf(tbe_ctx *h, BatchBuf &b, int64_t n) {
   HIP_TRY(h, h->mem.get(&b.byp_taken, N));
   HIP_TRY(h, h->mem.get(&b.ovf, N * (size_t)h->g.ovf_stride));
   HIP_TRY(h, h->mem.get(&b.mid_idx, 4 * (N / 2 + 1)));
-  HIP_TRY(h, h->mem.get(&b.heavy, 4 * (N / 32 + 1)));  // rows: N / 65 at most; extra parts: N / kHeavySplit at most
+  HIP_TRY(h, h->mem.get(&b.heavy, 4 * (N / 32 + 1)));  // entries: N / 65 at most (a row of len > 64 has ceil(len / 256) at most, no more than len / 65)
   HIP_TRY(h, h->mem.get(&b.heavy_sub, 4 * (N / 32 + 1)));
   HIP_TRY(h, h->mem.get(&b.harrive, 4 * (N / 32 + 1)));
   HIP_TRY(h, hipMemset(b.harrive, 0, 4 * (N / 32 + 1)));
@@ -733,9 +733,8 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
       h->ci.cls_tables[c] = d_ids;
     }
   }
-  // (heavy-list entry, bag range) pairs of a batch, one partial sum each: a batch has at most N / 32 entries
-  // (N / 65 heavy rows, N / kHeavySplit more for the parts of the hot ones); the number of ranges is chosen
-  // per batch so that the pairs fit (heavy_ranges)
+  // (heavy-list entry, bag range) pairs of a batch, one partial sum each: a batch has at most N / 65 entries (see alloc_batchbuf);
+  // the number of ranges is chosen per batch so that the pairs fit (heavy_ranges)
   h->huge_slots = std::max<size_t>(4 * ((size_t)max_lookups / (kLongRun + 1) + 1), 32768);
   h->g.partial_slots = (int64_t)h->huge_slots;
   {
@@ -954,9 +953,9 @@ static int backward_update_with(tbe_ctx *h, const float *d_grad_out, float lr, f
   if (!d_grad_out) return fail(h, TBE_EINVAL, "backward_update: null gradient");
   if (h->current < 0) return fail(h, TBE_EORDER, "backward_update: no forwarded batch");
   const int bi = h->current;
-  // The sections touch disjoint rows; the combine follows the heavy rows' kernel.  Small batches: that kernel, then
-  // everything else in one launch.  With more lookups the rows with one and with 2..64 lookups first, the heavy rows' kernel
-  // and the combine last: 0.471 ms alone against 0.479 with the tile kernel first (it takes 0.124 instead of 0.134 ms when
+  // The sections touch disjoint rows; the combine follows the heavy rows' kernel.  Small batches: everything in one launch for each
+  // width of rows (under max pooling the hot rows' kernel in front of it; see long_rows_in_rest for sum and mean).  With more
+  // lookups the rows with one and with 2..64 lookups first, the heavy rows' kernel, if there is one, and the combine last: 0.471 ms alone against 0.479 with the tile kernel first (it takes 0.124 instead of 0.134 ms when
   // it does not follow the forward), 0.627 against 0.635 ms beside the other streams.  (The heavy rows on a stream of their
   // own, beside the others: the tile kernel's workgroups need a CU to themselves each and waited for the others' waves to
   // drain -- 0.28 ms instead of 0.12 alone, the whole backward 0.51 ms instead of 0.48, and 0.72 instead of 0.65 ms beside

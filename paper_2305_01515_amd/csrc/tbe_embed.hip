@@ -1539,7 +1539,7 @@ hipError_t launch_forward_classes(const TableMeta *tm, const ClassInfo &ci, cons
   return hipGetLastError();
 }
 
-// A step runs the heavy rows' kernel, then the rest; they touch disjoint rows (but for the combine, which follows it).
+// The sections of a step touch disjoint rows, but for the combine, which follows the heavy rows' kernel.
 hipError_t launch_backward_classes(int which, const TableMeta *tm, const ClassInfo &ci, const Geometry &g,
                                    const BatchBuf &b, const float *grad_out, float *partials, float lr, float eps,
                                    hipStream_t s) {

@@ -20,9 +20,11 @@ constexpr int kLongRun = 64;
 constexpr int kHeavyThreads = 1024;       // workgroup of the tile kernel: 1024 / lanes-per-row lane groups
 // rows whose sums a lane group keeps in registers (8 fp16 elements per lane need twice the registers of 4 fp32)
 __host__ __device__ constexpr int heavy_rows_per_group(int dtype) { return dtype == 0 ? 8 : 6; }
-constexpr int kHeavySplit = 2048;          // a heavy row with more lookups is entered into the heavy list in several
-constexpr int kHeavyMaxParts = 64;         // parts (at most this many), each taking every parts-th window of G lookups,
-                                           // so that no lane group has a hot row's lookups all to itself
+// A heavy row with many lookups is entered into the heavy list in several parts (heavy_split, heavy_parts).  For the tile kernel:
+// from kHeavySplit lookups on, kHeavyMaxParts at most, each taking every parts-th window of G lookups, so that no lane group has a
+// hot row's lookups all to itself.
+constexpr int kHeavySplit = 2048;
+constexpr int kHeavyMaxParts = 64;
 // Gradient tile in LDS (wide rows padded by 16 bytes against bank conflicts).  A big tile matters: the lane groups
 // of a wavefront run in lockstep, each over its own row's lookups inside the tile, and the more lookups a tile
 // holds per row the less their counts differ (benchmark workload, tile kernel: 32 KB 0.145 ms, 64 KB 0.125, 96 KB 0.110).
@@ -694,9 +696,6 @@ __device__ inline void xcd_span_of(int id, int nblocks, int n, int per_block, in
 // ---- words through which the workgroups of one kernel tell each other their counts ----
 // A word carries its own "said" bit, so that a reader needs nothing but the word: written and read by atomics at the scope
 // of the whole GPU, which pass the XCDs' own L2s by.
-__device__ inline void say(uint32_t *p, uint32_t v) {
-  __hip_atomic_store(p, v | 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ inline void say(unsigned long long *p, unsigned long long v) {
   __hip_atomic_store(p, v | 1ull << 63, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -733,22 +732,6 @@ __device__ inline void begin_counters(BatchCounters *c, int32_t err) {
 // n / d for any 32-bit n, with m = ceil(2^64 / d) (0 stands for d = 1): exact, because m d exceeds 2^64 by less than d
 __device__ inline uint32_t div_by(uint32_t n, unsigned long long m) { return m ? (uint32_t)__umul64hi((unsigned long long)n, m) : n; }
 __host__ __device__ inline unsigned long long div_magic(uint32_t d) { return d > 1 ? ~0ull / d + 1ull : 0ull; }
-
-// table that owns sort key `key`: last t with key_base[t] <= key
-__device__ inline int find_table(const TableMeta *tm, int T, uint32_t key) {
-  int lo = 0, hi = T - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (tm[mid].key_base <= key) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
-__device__ inline uint32_t key_of_row(const TableMeta &m, uint32_t row) {
-  if (m.sets == 0) return m.key_base + row;
-  uint32_t q = row / m.sets;
-  return m.key_base + (row - q * m.sets) * m.rows_per_set + q;
-}
 
 __device__ inline uint32_t row_of_key(const TableMeta &m, uint32_t key) {
   uint32_t local = key - m.key_base;

@@ -1,5 +1,5 @@
-// Device code of the prefetch stage that its two forms share: the kernels of large batches, one or more to a pass
-// (tbe_cache.hip), and the one kernel that takes a small batch through all passes (tbe_one.hip).
+// Device code of the prefetch stage that its two forms share: a kernel a pass (tbe_sort.hip, tbe_cache.hip), and the one kernel
+// that takes a batch of very few lookups through all passes (tbe_one.hip).
 #pragma once
 #include "tbe_internal.h"
 
@@ -129,8 +129,7 @@ struct DedupArgs {
   const BatchCounters *cnt;
   int within_bits;
   const int64_t *offsets;
-  // what a payload says: the lookup's bag, its position in input order and inside the bag
-  __device__ int32_t bag_of(uint32_t p) const { return cnt->packed ? (int32_t)(p >> within_bits) : bag_of_pos[p]; }
+  // what a payload says of a lookup in `bag`: its position in input order and inside the bag
   __device__ uint32_t position(uint32_t p, int32_t bag) const {
     return cnt->packed ? (uint32_t)offsets[bag] + (p & ((1u << within_bits) - 1u)) : p;
   }
