@@ -806,6 +806,7 @@ int tbe_create(tbe_handle *out, const tbe_table_spec *specs, int32_t num_tables,
     CREATE_TRY(h->mem.get(&h->ss.slots, 4 * (size_t)need.slots));
     CREATE_TRY(h->mem.get(&h->ss.tiles, 16 * (size_t)need.tiles));
     CREATE_TRY(h->mem.get(&h->ss.said, 4 * (size_t)need.said));
+    CREATE_TRY(hipMemset(h->ss.said, 0, 4 * (size_t)need.said));
     CREATE_TRY(h->mem.get(&h->ss.flags, 8 * (size_t)need.tiles));
     CREATE_TRY(hipMemset(h->ss.flags, 0, 8 * (size_t)need.tiles));
   }

@@ -352,6 +352,13 @@ inline DigitPlan digit_plan(int key_bits, int passes) {
 // (latency of a tile's chain: keys, ranks, counts said and heard, output), so a tile has as many keys as leave enough of them to
 // fill the chip.  Us a pass, tiles of 1024 / 2048 / 4096 / 8192 keys: 41 k lookups 7.8 / 8.8 / 9.7 / -, 90 k 10.5 / 11.7 / 13.5 / -,
 // 262 k - / 15.0 / 16.2 / -, 818 k - / - / 18.6 / 22.3, 3.9 M - / - / 39.7 / 32.2, 7.9 M - / - / 70 / 55.6.
+// Tiles of 1024 keys add up the counts of all the tiles before them, in one trip, the larger ones hear in two how far the sums have come
+// (sort_pass_kernel).  The first is a hand-over shorter, but its reads grow with the square of a segment's tiles, and with the digit values.  Stage and
+// training, us a step, a kernel that counts and one that writes / sums / all counts: tables that are one segment, by 8 bits, 40 tables of 2000
+// lookups 156 / 166 / 153, 60 of 2000 168 / 164 / 156, 30 of 320 70 / 72 / 68; by 10 bits, 26 of 1700 103 / 106 / 104, one of 10 k 79 / 77 /
+// 74, 40 k 94 / 96 / 93, 70 k 155 / 155 / 151, 100 k 164 / 160 / 165, 130 k 179 / 174 / 182; four and eight segments, 41 k and 120 k 103, 179 /
+// 94, 159 / 92, 155.  All counts with tiles of 2048 keys, one segment by 10 bits: 130 k, 190 k, 260 k, 520 k 175, 184, 195, 245, by sums
+// 174, 180, 187, 226.
 // Digits of 10 bits at most: a tile hears the counts of every digit value from the key generation's slots and from the tiles before
 // it, so a pass by 11 bits, which would spare keys of 21 and 22 bits one of three, takes more than it saves.  Us for the passes, two
 // by 11 / three by 8, lookups of ten to 32 tables as one segment, 5 k, 15 k, 30 k, 60 k 22, 38, 48, 54 / 20, 25, 29, 32; of one table 8 k,
@@ -362,6 +369,7 @@ inline DigitPlan digit_plan(int key_bits, int passes) {
 constexpr int kLutTables = 512;  // models with more tables read the descriptions from memory in the passes of the stage
 constexpr int kSortThreads = 512;
 constexpr int64_t kTiles1k = 131072, kTiles2k = 524288, kTiles4k = 2097152;  // lookups up to which tiles have 1024, 2048, 4096 keys
+constexpr int64_t kTiles1kSegment = 65536;  // ... and lookups a segment up to which they have 1024, with the widest digits (more with narrower ones)
 constexpr int kWidestDigit = 10;
 constexpr int64_t kSegmentLookups = 2048;                                    // lookups a table, on average, from which tables are segments
 constexpr int kSlotsHeard = 32;  // slots of a segment that the workgroups of the sort add up themselves
@@ -387,7 +395,7 @@ inline SortShape sort_shape(const Geometry &g, int64_t n, int32_t batch, int lan
   s.digits = digit_plan(bits, passes);
   s.rb = (bits + passes - 1) / passes;
   if (s.rb < 8) s.rb = 8;
-  s.items = n <= kTiles1k ? 2 : n <= kTiles2k ? 4 : n <= kTiles4k ? 8 : 16;
+  s.items = n <= kTiles1k && n << s.rb <= (kTiles1kSegment << kWidestDigit) * s.segs ? 2 : n <= kTiles2k ? 4 : n <= kTiles4k ? 8 : 16;
   // A bag has eight lanes, or one where bags have two lookups or fewer on average: seven of eight lanes had nothing to read, and the
   // rounds that this takes were what bounded the kernel.  The whole stage and the forward, us, with eight / one: 2.2 M bags of one lookup in
   // one table and in eight 304, 314 / 218, 229, 400 k in one 121 / 104, 200 k of two 111 / 102, 100 k of four 106 / 103, of eight 106 / 109;
@@ -416,7 +424,7 @@ struct SortNeeds { int64_t said, tiles, slots; };  // words of tiles' counts, ti
 inline SortNeeds sort_needs(const Geometry &g, int64_t n, int32_t batch) {
   SortNeeds r{1, 1, 1};
   // (a batch of fewer lookups can have more tiles or, as one segment, more workgroups, one of fewer bags more lanes and so workgroups)
-  const int64_t steps[] = {n, kTiles1k, kTiles2k, kTiles4k, kSegmentLookups * g.T - 1};
+  const int64_t steps[] = {n, kTiles1kSegment, kTiles1k, kTiles2k, kTiles4k, kSegmentLookups * g.T - 1};
   for (int64_t m : steps) {
     if (m > n || m < 1) continue;
     const SortShape s = sort_shape(g, m, batch, 8);

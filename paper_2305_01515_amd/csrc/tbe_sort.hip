@@ -262,9 +262,11 @@ hipError_t launch_keygen(const TableMeta *tm, const Geometry &g, const BatchBuf 
 // LSD radix sort of every segment's pairs, a kernel per pass.  A workgroup ranks its tile's keys with ballot matching (stable),
 // says its counts of the digit values, orders the tile in LDS, adds up the counts of the segment's tiles before it and writes the
 // tile out, so that neighbouring lanes hit neighbouring addresses.  The digits' totals are known from the key generation.
+// Tiles of 1024 keys say their counts in words that carry batch and pass, and add up those of all the tiles before them; larger tiles,
+// of which a segment may have many, also say the sum up to them, and hear only as far back as one that has said it (see SortShape).
 // A tile waits only for tiles before it, and where one of them has said nothing for kPolls looks (its workgroup may not have
-// begun) counts that tile itself, so every workgroup ends whatever else runs on the GPU.  One wavefront looks at the tiles' flags,
-// and the counts are read when they are there: with every thread looking at its digit values' own words until they had come,
+// begun) counts that tile itself, so every workgroup ends whatever else runs on the GPU.  Of the larger tiles one wavefront looks at
+// flags, and the counts are read when they are there: with every thread looking at its digit values' own words until they had come,
 // that traffic past the L2s was what bounded a pass (7.9 M lookups 65 us, now 56).
 // --------------------------------------------------------------------------------------
 struct SortPassArgs {
@@ -284,29 +286,35 @@ struct SortPassArgs {
   BatchCounters *cnt;
 };
 constexpr u64 kSaidOwn = 1, kSaidSum = 2;
+constexpr int kTagCount = 12;        // bits of a count in a word with batch and pass (34 bits)
+constexpr u64 kTagged = 1ull << 63;  // set in all of them, and in no pair of counts or sums that a larger batch has left there
 template <int RB, int ITEMS>
 __global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortPassArgs a) {
   constexpr int R = 1 << RB, kWords = R / 2;  // counts of two digit values to a word
   constexpr int kWaves = kSortThreads / kWave, kTile = kSortThreads * ITEMS;
   constexpr int D = 2;  // a thread's digit values: a word
   static_assert(kWords <= kSortThreads, "a word a thread");
+  constexpr bool kDirect = ITEMS == 2;  // tiles add up the counts of all tiles before them
+  static_assert(!kDirect || kTile < 1 << kTagCount, "a count has room in a tagged word");
+  constexpr int kGroups = kSortThreads / kWords;  // of threads that add up what others have counted
   __shared__ union {
     uint32_t cnt[kWaves][kWords];  // per wavefront and digit value: count, later the first place of its keys in the tile
     uint2 pairs[kTile];
   } s;
   __shared__ uint32_t s_out[R];  // per digit value: what takes a place in the tile to one in the output
   __shared__ uint32_t s_wtot[2][kWaves];
-  __shared__ int s_err, s_take;
+  __shared__ uint2 s_part[kGroups][kWords];
+  __shared__ int s_take;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) {
-    const int err = a.cnt->err, here = (int)*a.stage_err;
-    if (blockIdx.x == 0 && here > err) a.cnt->err = here;
-    s_err = err | here;
-  }
-  __syncthreads();
-  if (s_err) return;  // the keys need not be whole; the same for all workgroups
   const int blk = blockIdx.x;
-  const uint4 tile = a.tiles[blk];
+  const uint4 tile = a.tiles[blk];  // (requested together with the errors)
+  {
+    const int err = a.cnt->err, here = (int)*a.stage_err;
+    if (err | here) {  // the keys need not be whole; the same for all threads: what thread 0 adds was `here` before
+      if (blk == 0 && tid == 0 && here > err) a.cnt->err = here;
+      return;
+    }
+  }
   if (tile.x >= tile.y) return;  // behind the last one
   const uint2 *in = a.in + tile.x;
   const int n = (int)(tile.y - tile.x), seg = (int)(tile.z & ~kLastTile);
@@ -318,6 +326,23 @@ __global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortPassArgs a)
 #pragma unroll
   for (int q = 0; q < ITEMS; q++) e[q] = w0 + q * kWave < n ? in[w0 + q * kWave] : make_uint2(0u, 0u);
   for (int i = tid; i < kWaves * kWords; i += kSortThreads) (&s.cnt[0][0])[i] = 0;
+  if (tid == 0) s_take = 0;
+  const int grp = tid / kWords, word = tid % kWords;
+  {  // the segment's totals of two digit values, a share of the slots each group
+    uint2 sum = make_uint2(0u, 0u);
+    const uint32_t *p = a.slots + (size_t)seg * a.n_slots * a.words + word * D;
+    for (int g = grp; g < a.n_slots; g += 8 * kGroups) {
+      uint2 v[8];
+#pragma unroll
+      for (int q = 0; q < 8; q++) v[q] = g + q * kGroups < a.n_slots ? *(const uint2 *)(p + (size_t)(g + q * kGroups) * a.words) : make_uint2(0u, 0u);
+#pragma unroll
+      for (int q = 0; q < 8; q++) {
+        sum.x += v[q].x;
+        sum.y += v[q].y;
+      }
+    }
+    s_part[grp][word] = sum;
+  }
   __syncthreads();
   auto digit = [&](uint32_t key) { return ((key - key0) >> a.shift) & a.mask; };
 #pragma unroll
@@ -364,21 +389,19 @@ __global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortPassArgs a)
     count[0] = sum & 0xFFFFu;
     count[1] = sum >> 16;
   }
-  if (!(tile.z & kLastTile)) say_counts(count, tile.w ? 0 : a.sums_at, tile.w ? kSaidOwn : kSaidSum);
-  if (mine) {
-    const uint32_t *p = a.slots + (size_t)seg * a.n_slots * a.words + tid * D;
-    for (int g = 0; g < a.n_slots; g += 8) {
-      uint32_t v[8][D];
-#pragma unroll
-      for (int q = 0; q < 8; q++)
-#pragma unroll
-        for (int x = 0; x < D; x++) v[q][x] = g + q < a.n_slots ? p[(size_t)(g + q) * a.words + x] : 0u;
-#pragma unroll
-      for (int q = 0; q < 8; q++)
-#pragma unroll
-        for (int x = 0; x < D; x++) total[x] += v[q][x];
-    }
+  const u64 tag = kTagged | a.epoch << 2 * kTagCount;
+  if (!(tile.z & kLastTile)) {
+    if constexpr (!kDirect) say_counts(count, tile.w ? 0 : a.sums_at, tile.w ? kSaidOwn : kSaidSum);
+    else if (mine)
+      __hip_atomic_store((u64 *)(a.said + (size_t)blk * R + tid * D), tag | count[1] << kTagCount | count[0], __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
   }
+  if (mine)
+#pragma unroll
+    for (int q = 0; q < kGroups; q++) {
+      total[0] += s_part[q][tid].x;
+      total[1] += s_part[q][tid].y;
+    }
   uint32_t out[D] = {};  // first place of the segment's keys of each digit value in the output, less that in the tile
   {  // exclusive prefix over the digit values, of the tile's counts and of the segment's
     uint32_t c = 0, t = 0;
@@ -411,9 +434,59 @@ __global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortPassArgs a)
 #pragma unroll
   for (int q = 0; q < ITEMS; q++)
     if (w0 + q * kWave < n) s.pairs[place[q]] = e[q];
+  if constexpr (kDirect) {
+    // The keys of these digit values in the segment's tiles before this one, a share of the tiles each group.
+    uint2 sum = make_uint2(0u, 0u);
+    bool silent = false;
+    int polls = 0;
+    for (int t0 = grp; t0 < (int)tile.w && !silent; t0 += 8 * kGroups) {
+      for (;;) {
+        const u64 *p = (const u64 *)(a.said + (size_t)(blk - 1 - t0) * R) + word;
+        u64 v[8];
+        bool all = true;
+#pragma unroll
+        for (int q = 0; q < 8; q++) v[q] = t0 + q * kGroups < (int)tile.w ? look(p - (size_t)q * kGroups * kWords) : tag;
+#pragma unroll
+        for (int q = 0; q < 8; q++) all = all && (v[q] ^ tag) >> 2 * kTagCount == 0;
+        if (all) {
+#pragma unroll
+          for (int q = 0; q < 8; q++) {
+            sum.x += (uint32_t)v[q] & ((1u << kTagCount) - 1u);
+            sum.y += (uint32_t)(v[q] >> kTagCount) & ((1u << kTagCount) - 1u);
+          }
+          break;
+        }
+        silent = polls++ >= kPolls;
+        if (silent) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+    if (silent) s_take = 1;
+    s_part[grp][word] = sum;
+    __syncthreads();
+    if (s_take) {
+      // A tile has said nothing for long: its workgroup may not have begun, and this one waits for nobody.  All are counted here.
+      for (int i = tid; i < R; i += kSortThreads) s_out[i] = 0;
+      __syncthreads();
+      const uint2 *old = in - (size_t)tile.w * kTile;
+      for (int i = tid; i < (int)tile.w * kTile; i += kSortThreads) atomicAdd(&s_out[digit(old[i].x)], 1u);
+      __syncthreads();
+      if (mine) {
+        before[0] = s_out[tid * D];
+        before[1] = s_out[tid * D + 1];
+      }
+    } else if (mine) {
+#pragma unroll
+      for (int q = 0; q < kGroups; q++) {
+        before[0] += s_part[q][tid].x;
+        before[1] += s_part[q][tid].y;
+      }
+    }
+    __syncthreads();
+  }
   // The keys of these digit values in the segment's tiles before this one: as many as have said their own counts, as far back
   // as one that has said the sum up to it (the segment's first says that at once).
-  for (int done = 0; done < (int)tile.w;) {
+  for (int done = kDirect ? (int)tile.w : 0; done < (int)tile.w;) {
     if (wave == 0) {
       int take = 0, how = 0;
       for (int polls = 0;; polls++) {
@@ -470,7 +543,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortPassArgs a)
     }
     __syncthreads();
   }
-  if (tile.w && !(tile.z & kLastTile)) {
+  if (!kDirect && tile.w && !(tile.z & kLastTile)) {
 #pragma unroll
     for (int x = 0; x < D; x++) count[x] += before[x];
     say_counts(count, a.sums_at, kSaidSum);

@@ -41,6 +41,11 @@ def test_segments_of_unlike_size(impatient, batch, bits):
     parity(tabs, batch, bits)
 
 
+@pytest.mark.parametrize("tables,rows,pool,batch", [(1, 1000003, 32, 2048), (70, 900, 2, 936), (26, 30000, 9, 190)])
+def test_one_segment_of_tiles_of_1024_keys(impatient, tables, rows, pool, batch):
+    parity([T(rows, 4, synth.FP32, 0.7, "fixed", pool, cache_slots=8 * 100) for _ in range(tables)], batch, batch)
+
+
 def test_tiles_of_8192_keys(impatient):
     parity([T(60013, 4, synth.FP32, 1.1, "fixed", 30, cache_slots=8 * 2000), T(3001, 4, synth.FP32, None, "fixed", 2)], 66000, 1, steps=1)
 

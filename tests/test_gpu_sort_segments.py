@@ -37,6 +37,14 @@ def test_more_slots_than_the_sort_adds_up_itself(batch, pool):
     parity([T(20011, 4, synth.FP32, 1.0, "fixed", pool, cache_slots=8 * 400)], batch, batch)
 
 
+@pytest.mark.parametrize("tables,rows,pool,batch", [(1, 1000003, 32, b) for b in (2047, 2048, 2049, 4097)]
+                         + [(70, 900, 2, b) for b in (936, 937)] + [(65, 900, 17, b) for b in (118, 119)])
+def test_one_segment_of_tiles_that_hear_all_before_them(tables, rows, pool, batch):
+    """one table by 10 bits: tiles of 1024 keys up to 65536 lookups, then of 2048; many tables with few lookups each by 8 bits: up to
+    131072, the most tiles of 1024 keys that a segment can have"""
+    parity([T(rows, 4, synth.FP32, 0.7, "fixed", pool, cache_slots=8 * 100) for _ in range(tables)], batch, batch, steps=2)
+
+
 @pytest.mark.parametrize("batch", [16384, 16385, 65536, 65537])
 def test_tiles_of_every_size(batch):
     """32 lookups a bag: either side of 524288 and of 2097152 lookups, in two segments of unlike size"""

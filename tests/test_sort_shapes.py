@@ -26,8 +26,8 @@ int main() {
     const long long max_n = upto(5e7);
     const SortNeeds need = sort_needs(g, max_n, max_batch);
     for (int x = 0; x < 60; x++) {
-      const long long line[] = {kTiles1k, kTiles2k, kTiles4k, kSegmentLookups * g.T, kTiles1k * g.T, 2ll * g.T * max_batch};
-      long long n = x < 30 ? upto(max_n + 1.0) : line[x % 6] + x % 3 - 1;
+      const long long line[] = {kTiles1k, kTiles1kSegment, kTiles2k, kTiles4k, kSegmentLookups * g.T, kTiles1k * g.T, 2ll * g.T * max_batch};
+      long long n = x < 30 ? upto(max_n + 1.0) : line[x % 7] + x % 3 - 1;
       if (n > max_n || n < 0) n = max_n;
       const int batch = x % 4 ? (int)upto(max_batch + 1.0) : max_batch;
       const SortShape s = sort_shape(g, n, batch);
