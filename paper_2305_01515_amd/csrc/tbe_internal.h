@@ -350,7 +350,7 @@ inline DigitPlan digit_plan(int key_bits, int passes) {
 // own, every table is a segment that is sorted by itself, by the bits of the widest table's keys: 32 tables of a million rows
 // are two passes by 10 bits instead of three by 9, 8 and 8.  A pass is one kernel; what bounds it is the number of its tiles
 // (latency of a tile's chain: keys, ranks, counts said and heard, output), so a tile has as many keys as leave enough of them to
-// fill the chip.  Us a pass, tiles of 1024 / 2048 / 4096 / 8192 keys: 41 k lookups 7.8 / 8.8 / 9.7 / -, 90 k 10.5 / 11.7 / 13.5 / -,
+// fill the chip.  Us a pass, tiles of 1024 / 2048 / 4096 / 8192 keys: 41 k lookups 7.0 / 8.8 / 9.7 / -, 90 k 8.4 / 11.7 / 13.5 / -,
 // 262 k - / 15.0 / 16.2 / -, 818 k - / - / 18.6 / 22.3, 3.9 M - / - / 39.7 / 32.2, 7.9 M - / - / 70 / 55.6.
 // Tiles of 1024 keys add up the counts of all the tiles before them, in one trip, the larger ones hear in two how far the sums have come
 // (sort_pass_kernel).  The first is a hand-over shorter, but its reads grow with the square of a segment's tiles, and with the digit values.  Stage and
@@ -559,7 +559,6 @@ inline bool long_rows_in_rest(int64_t n) { return n <= kLongLookups; }
 inline int heavy_split(int64_t n, bool maxp) {
   return maxp || !long_rows_in_rest(n) ? kHeavySplit : n <= 32768 ? 256 : n <= 262144 ? 512 : 1024;
 }
-
 
 // ---- launchers (each enqueues on `s` and returns the HIP status of the launch) ----
 
